@@ -21,61 +21,24 @@
 //                whose inclusive prefix sum of q exceeds r; all products zero: floor(rnd * n / 2^64)
 //
 // Kernels: prepare (group-major copy of the tokens, integer weights), k-means++ (one workgroup
-// per group, K sequential picks), and per Lloyd iteration an assignment kernel (plain fp32 VALU
-// search against the group's centroids in LDS) and an update kernel (integer LDS atomics, then
-// the new centroids).
+// per group, K sequential picks), and per Lloyd iteration the matrix-core kernel of
+// cq_kmeans_mfma.hip where a group has 256 centroids of two or more channels; else an assignment
+// kernel (plain fp32 VALU search against the group's centroids in LDS) and an update kernel
+// (integer LDS atomics, then the new centroids).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 
-#include "cq_internal.hpp"
+#include "cq_kmeans_common.hpp"
+#include "cq_kmeans_mfma.hpp"
 
 namespace cq {
 namespace {
-
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kPPThreads = 1024;     // k-means++ workgroup
 constexpr int kAssignThreads = 256;
 constexpr int kAssignPoints = 2;     // tokens per thread of the assignment kernel
 constexpr int kUpdateClusters = 256; // clusters per update workgroup
-
-template <int C>
-__device__ __forceinline__ void widen(const uint16_t* p, float (&v)[C])
-{
-    if constexpr (C == 8) {
-        const uint4 a = *reinterpret_cast<const uint4*>(p);
-        const unsigned w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const half2_t h = __builtin_bit_cast(half2_t, w[i]);
-            v[2 * i] = (float)h.x;
-            v[2 * i + 1] = (float)h.y;
-        }
-    } else if constexpr (C == 4) {
-        const uint2 a = *reinterpret_cast<const uint2*>(p);
-        const half2_t h0 = __builtin_bit_cast(half2_t, a.x), h1 = __builtin_bit_cast(half2_t, a.y);
-        v[0] = (float)h0.x; v[1] = (float)h0.y; v[2] = (float)h1.x; v[3] = (float)h1.y;
-    } else if constexpr (C == 2) {
-        const half2_t h = __builtin_bit_cast(half2_t, *reinterpret_cast<const unsigned*>(p));
-        v[0] = (float)h.x; v[1] = (float)h.y;
-    } else {
-        static_assert(C == 1, "channels per group: 1, 2, 4 or 8");
-        v[0] = (float)__builtin_bit_cast(_Float16, *p);
-    }
-}
-
-template <int C>
-__device__ __forceinline__ float dist2(const float (&x)[C], const float* c)
-{
-    float acc = 0.f;
-#pragma unroll
-    for (int i = 0; i < C; ++i) {
-        const float d = x[i] - c[i];
-        acc = __builtin_fmaf(d, d, acc);
-    }
-    return acc;
-}
 
 // ------------------------------------------------------------------------------------------
 // prepare
@@ -359,9 +322,7 @@ __global__ __launch_bounds__(256) void kmeans_update_kernel(const uint16_t* xg_a
         if (k0 + k >= K) continue;
         const long long wk = (long long)wsum[k];
         if (wk == 0) continue;                      // a cluster without tokens keeps its centroid
-        const double num = (double)(long long)s_hi[e] * 1048576.0 + (double)(long long)s_lo[e];
-        const double mean = num / (double)wk;
-        cent_all[((size_t)g * K + k0) * C + e] = (float)(mean * 0x1p-24);
+        cent_all[((size_t)g * K + k0) * C + e] = kmeans_mean((long long)s_hi[e], (long long)s_lo[e], wk);
     }
 }
 
@@ -425,6 +386,22 @@ template <int C>
 cq_status run_lloyd(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
 {
     const int G = a.f.groups, K = a.f.k, n = a.n;
+    if constexpr (C >= 2) {
+        if (K == 256) {
+            // the nearest-centre distances are done with: their room holds the sums of token splits
+            KMeansLloyd l;
+            l.xg = ws.xg;
+            l.wq = a.weights ? ws.wq : nullptr;
+            l.cent = ws.cent;
+            l.assign = a.assign_out;
+            l.scratch = ws.dmin;
+            l.scratch_bytes = sizeof(float) * (size_t)G * n;
+            l.groups = G;
+            l.n = n;
+            l.n_iter = a.n_iter;
+            return launch_kmeans_lloyd(l, C, st);
+        }
+    }
     const size_t lds = sizeof(float) * (size_t)K * C;
     const dim3 agrid((n + kAssignThreads * kAssignPoints - 1) / (kAssignThreads * kAssignPoints), G);
     const dim3 ugrid(G, (K + kUpdateClusters - 1) / kUpdateClusters);
@@ -452,7 +429,7 @@ cq_status run_all(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st
     const size_t cnt = (size_t)a.f.groups * a.f.k * C;
     hipLaunchKernelGGL(kmeans_finish_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, ws.cent, cnt, a.cent16_out,
                        a.cent32_out);
-    if (a.assign_out && a.n_iter > 0) {
+    if (a.assign_out && a.n_iter > 0 && !(C >= 2 && a.f.k == 256)) {     // (the matrix-core iteration writes it itself)
         const size_t an = (size_t)a.f.groups * a.n;
         hipLaunchKernelGGL(kmeans_copy_u16_kernel, dim3((unsigned)((an + 255) / 256)), dim3(256), 0, st, ws.assign, a.assign_out, an);
     }

@@ -124,3 +124,36 @@ def test_strided_rows_and_repeatability():
     c_ = cq.cq_kmeans_fit(torch.from_numpy(x).cuda(), fmt, 2, rnd=rnd)["centroids_f32"]
     torch.cuda.synchronize()
     assert torch.equal(a, b_) and torch.equal(b_, c_)
+
+
+@pytest.mark.parametrize("c,n,weighted", [(8, 63, False), (8, 65, True), (4, 2047, False), (8, 5000, False), (4, 9217, True),
+                                          (2, 20001, False)])
+@pytest.mark.parametrize("data", ["plain", "tiny", "large", "far points", "dead groups", "duplicates"])
+def test_lloyd_on_the_matrix_cores_decides_like_the_direct_form(c, n, weighted, data):
+    """Token splits, partial tiles, and data that leaves the filter: all-zero groups, duplicated
+    points and centroids, points far longer than every centroid, the ends of fp16's range."""
+    fmt = cq.CQFormat(c, 8, 128, 1)
+    G, K = fmt.groups, 256
+    x = _data(60 + c, n, 128).astype(np.float32)
+    if data == "tiny":
+        x *= 1e-6
+    elif data == "large":
+        x *= 60000.0 / np.abs(x).max()
+    elif data == "far points":
+        x *= 1e-2
+    elif data == "dead groups":
+        x[:, :64] = 0.0
+    elif data == "duplicates":
+        x = x[np.arange(n) % min(n, 40)]
+    x = x.astype(np.float16)
+    rng = np.random.default_rng(n)
+    init = np.stack([x.reshape(n, G, c)[rng.choice(n, size=K, replace=True), g] for g in range(G)]).astype(np.float32)
+    if data == "far points":
+        x[::7] = (x[::7].astype(np.float32) * 3e4).clip(-6e4, 6e4).astype(np.float16)
+    w = _weights(n + 1, n, G) if weighted else None
+    cent, assign, _ = KO.lloyd(x, c, init, 2, w)
+    out = cq.cq_kmeans_fit(torch.from_numpy(x).cuda(), fmt, 2, init_centroids=torch.from_numpy(init).cuda(),
+                           weights=None if w is None else torch.from_numpy(w).cuda(), want_assignment=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(out["assignment"].cpu().numpy().view(np.uint16), assign)
+    assert np.array_equal(out["centroids_f32"].cpu().numpy(), cent)
