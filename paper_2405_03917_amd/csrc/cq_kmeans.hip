@@ -108,20 +108,46 @@ __global__ __launch_bounds__(256) void kmeans_prepare_kernel(const uint16_t* x, 
 // ------------------------------------------------------------------------------------------
 // k-means++
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long v, int lane)
+// 64-bit sums over a wavefront with data-parallel-primitive moves (all 64 lanes active): a few
+// cycles per step where a shuffle through LDS costs more than a hundred.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v)      // lanes without a source read 0
 {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned long long up = __shfl_up(v, o);
-        if (lane >= o) v += up;
-    }
-    return v;
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, 0xf, 0xf, true);
+    return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v, int l)
+{
+    return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), l) << 32) |
+           (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, l);
 }
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    v += dpp_u64<0xB1>(v);       // quad_perm [1,0,3,2]
+    v += dpp_u64<0x4E>(v);       // quad_perm [2,3,0,1]
+    v += dpp_u64<0x141>(v);      // row_half_mirror
+    v += dpp_u64<0x140>(v);      // row_mirror
+    return (readlane_u64(v, 0) + readlane_u64(v, 16)) + (readlane_u64(v, 32) + readlane_u64(v, 48));
+}
+__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
+{
+    auto up = [](unsigned long long a, unsigned long long b) { return b > a ? b : a; };
+    v = up(v, dpp_u64<0xB1>(v));
+    v = up(v, dpp_u64<0x4E>(v));
+    v = up(v, dpp_u64<0x141>(v));
+    v = up(v, dpp_u64<0x140>(v));
+    return up(up(readlane_u64(v, 0), readlane_u64(v, 16)), up(readlane_u64(v, 32), readlane_u64(v, 48)));
+}
+__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long v, int lane)
+{
+    v += dpp_u64<0x111>(v);      // row_shr 1, 2, 4, 8: sums within the row of 16 lanes
+    v += dpp_u64<0x112>(v);
+    v += dpp_u64<0x114>(v);
+    v += dpp_u64<0x118>(v);
+    const unsigned long long r0 = readlane_u64(v, 15), r1 = r0 + readlane_u64(v, 31), r2 = r1 + readlane_u64(v, 47);
+    const int row = lane >> 4;
+    return v + (row == 0 ? 0ull : row == 1 ? r0 : row == 2 ? r1 : r2);
 }
 
 // One workgroup per group.  Wavefront w owns the contiguous tokens [w W, (w + 1) W), W a multiple
@@ -224,11 +250,7 @@ __global__ __launch_bounds__(kPPThreads) void kmeanspp_kernel(const uint16_t* __
             }
         }
         unsigned long long pb = (unsigned long long)__double_as_longlong(pmax);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(pb, o);
-            pb = other > pb ? other : pb;
-        }
+        pb = wave_max_u64(pb);
         __syncthreads();                                     // pmax_bits was cleared; dmin is written
         if (lane == 0) atomicMax(&pmax_bits, pb);
         __syncthreads();
@@ -239,6 +261,262 @@ __global__ __launch_bounds__(kPPThreads) void kmeanspp_kernel(const uint16_t* __
             continue;
         }
         const int kq = 62 - log2n - ((int)((pm >> 52) & 0x7ffull) - 1023 + 1);
+        draw(rnd[j + 1], kq);
+    }
+}
+
+// The same picks with the distances to the nearest centre (and the weights) in registers, for up to
+// 32 rounds of 1024 tokens: the form above walks three arrays in L2 and HBM per pick, and the walk
+// of one wavefront to the chosen token is a chain of 32 reductions.  Here wavefront w still owns
+// the contiguous tokens [w W, (w + 1) W); a token's slice x is read again for every pick -- from
+// registers (the first kRegRounds rounds), from LDS (the next kLdsRounds) or from memory (the
+// rest, requested before the pick is known) -- and a pick is three barriers: the largest
+// weighted distance, the wavefronts' masses, the token.  The owner of the r-th unit of mass keeps
+// its mass in four sums of 8 rounds, so the search is 4 + 8 independent reductions and one scan.
+// 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 7.0 ms
+// (weighted, 64 more registers' worth of weights: 30.7 -> 18 ms); 1500 tokens, 256 groups of 4:
+// 1.3 -> 0.9 ms.  Bound by the vector ALU now (busy 74 %).
+constexpr int kPPRounds = 32;
+constexpr int kPPSegs = 4;
+constexpr int min_of(int a, int b) { return a < b ? a : b; }
+template <int C, bool W, int R>
+constexpr int kPPRegRounds = min_of(R, (W ? 8 : 16) / (C / 2));
+template <int C, bool W, int R>
+constexpr int kPPLdsRounds = min_of(R - kPPRegRounds<C, W, R>, 72 / C);     // at most 144 KB
+
+// floor(m 2^sh) of an integer below 2^46 (the result fits 62 bits)
+__device__ __forceinline__ unsigned long long shift_floor(unsigned long long m, int sh)
+{
+    const int l = sh > 0 ? sh : 0, r = sh < 0 ? (-sh < 63 ? -sh : 63) : 0;
+    return (m << l) >> r;
+}
+
+template <int C, bool W, int R>
+__global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const uint16_t* __restrict__ xg_all,
+                                                                      const uint32_t* __restrict__ wq_all,
+                                                                      const uint64_t* __restrict__ rnd_all,
+                                                                      int32_t* __restrict__ picks_all,
+                                                                      float* __restrict__ cent_all, int n, int K, int log2n)
+{
+    constexpr int NWAVE = kPPThreads / 64;
+    constexpr int XW = C / 2;                                // words of a token's slice
+    constexpr int kRegRounds = kPPRegRounds<C, W, R>;
+    constexpr int kLdsRounds = kPPLdsRounds<C, W, R>;
+    constexpr int kHeld = kRegRounds + kLdsRounds;
+    constexpr int kBatch = 4;                                // rounds requested together
+    extern __shared__ __attribute__((aligned(16))) unsigned xl[];       // [kLdsRounds][1024][XW], then the exchange slots
+    unsigned long long* const wave_tot = reinterpret_cast<unsigned long long*>(xl + (size_t)kLdsRounds * kPPThreads * XW);
+    unsigned long long* const wave_max = wave_tot + NWAVE;
+    int& pick_sh = *reinterpret_cast<int*>(wave_max + NWAVE);
+
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint16_t* xg = xg_all + (size_t)g * n * C;
+    const uint64_t* rnd = rnd_all + (size_t)g * K;
+    int32_t* picks = picks_all ? picks_all + (size_t)g * K : nullptr;
+    float* cent = cent_all + (size_t)g * K * C;
+    const int rounds = (n + kPPThreads - 1) / kPPThreads;    // at most R
+    const int t0 = wave * rounds * 64;
+
+    int first = t0 + lane;                                   // this lane's token of round 0
+    auto load_words = [&](int p, unsigned (&w)[XW]) {        // token of round p (clamped to the last)
+        const unsigned* src = reinterpret_cast<const unsigned*>(reinterpret_cast<const char*>(xg) +
+                                                                (unsigned)min(first + p * 64, n - 1) * (unsigned)(2 * C));
+        if constexpr (XW == 4) {
+            const uint4 v = *reinterpret_cast<const uint4*>(src);
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        } else if constexpr (XW == 2) {
+            const uint2 v = *reinterpret_cast<const uint2*>(src);
+            w[0] = v.x; w[1] = v.y;
+        } else {
+            w[0] = src[0];
+        }
+    };
+
+    unsigned dmin[R];                                        // bits of the fp32 distance (they order like it); 0 where
+                                                             // there is no token: no mass, never the largest
+    unsigned wr[W ? R : 1];
+    unsigned xr[kRegRounds][XW];
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+        const int i = t0 + p * 64 + lane;
+        const bool there = p < rounds && i < n;
+        dmin[p] = there ? 0x7f800000u : 0u;
+        if constexpr (W) wr[p] = there ? wq_all[(size_t)g * n + i] : 0u;
+        if (p < kRegRounds) {
+            load_words(p, xr[p < kRegRounds ? p : 0]);
+        } else if (p < kHeld) {
+            unsigned w[XW];
+            load_words(p, w);
+#pragma unroll
+            for (int i2 = 0; i2 < XW; ++i2) xl[((p - kRegRounds) * kPPThreads + tid) * XW + i2] = w[i2];
+        }
+    }
+
+    // mass of this lane's token of round p: the weight itself (first pick) or floor(weight dmin 2^kq)
+    auto mass_of = [&](unsigned b, unsigned w, int kq) -> unsigned long long {
+        if (W && kq < -9000) return w;
+        const unsigned ex = b >> 23, fr = b & 0x7fffffu;
+        const unsigned m = ex ? fr | 0x800000u : fr;
+        const int sh = (int)(ex ? ex : 1u) - 150 + kq;
+        return shift_floor(W ? (unsigned long long)w * m : (unsigned long long)m, sh);
+    };
+    auto draw = [&](uint64_t word, int kq) {
+        unsigned long long seg[kPPSegs];
+#pragma unroll
+        for (int s = 0; s < kPPSegs; ++s) {
+            seg[s] = 0;
+#pragma unroll
+            for (int k = 0; k < R / kPPSegs; ++k) {
+                const int p = s * (R / kPPSegs) + k;
+                seg[s] += mass_of(dmin[p], W ? wr[W ? p : 0] : 1u, kq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const unsigned long long wtot = wave_sum_u64(seg[0] + seg[1] + seg[2] + seg[3]);
+        if (lane == 0) wave_tot[wave] = wtot;
+        __syncthreads();
+        unsigned long long off = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVE; ++w) {
+            const unsigned long long t = wave_tot[w];
+            off += w < wave ? t : 0ull;
+            total += t;
+        }
+        const unsigned long long r = __umul64hi(word, total);
+        if (r >= off && r < off + wtot) {                    // exactly one wavefront
+            unsigned long long run = off;
+            int s_hit = 0;
+            {
+                unsigned long long st[kPPSegs];
+#pragma unroll
+                for (int s = 0; s < kPPSegs; ++s) st[s] = wave_sum_u64(seg[s]);
+#pragma unroll
+                for (int s = 0; s + 1 < kPPSegs; ++s)
+                    if (s_hit == s && run + st[s] <= r) { run += st[s]; s_hit = s + 1; }
+            }
+            s_hit = __builtin_amdgcn_readfirstlane(s_hit);
+            constexpr int RS = R / kPPSegs;
+            unsigned sd[RS], sw[RS];
+#pragma unroll
+            for (int s = 0; s < kPPSegs; ++s)
+                if (s_hit == s) {
+#pragma unroll
+                    for (int k = 0; k < RS; ++k) {
+                        sd[k] = dmin[s * RS + k];
+                        sw[k] = W ? wr[W ? s * RS + k : 0] : 1u;
+                    }
+                }
+            unsigned long long q[RS], qt[RS];
+#pragma unroll
+            for (int k = 0; k < RS; ++k) {
+                q[k] = mass_of(sd[k], sw[k], kq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int k = 0; k < RS; ++k) qt[k] = wave_sum_u64(q[k]);
+            int k_hit = 0;
+            unsigned long long qh = q[0];
+#pragma unroll
+            for (int k = 0; k + 1 < RS; ++k)
+                if (k_hit == k && run + qt[k] <= r) { run += qt[k]; k_hit = k + 1; qh = q[k + 1]; }
+            const unsigned long long incl = run + wave_incl_scan_u64(qh, lane);
+            const unsigned long long hit = __ballot(incl > r);
+            if (lane == 0) pick_sh = t0 + (s_hit * RS + k_hit) * 64 + __builtin_ctzll(hit);
+        }
+        __syncthreads();
+    };
+
+    if constexpr (W) {
+        draw(rnd[0], -10000);                                // first centre: proportional to the integer weights
+    } else {
+        if (tid == 0) pick_sh = (int)__umul64hi(rnd[0], (unsigned long long)n);
+        __syncthreads();
+    }
+    for (int j = 0;; ++j) {
+        // (opaque per pick: left alone, the compiler widens the held slices and forms the addresses of
+        // all rounds once, ahead of this loop, and spills them)
+        asm volatile("" : "+v"(first));
+#pragma unroll
+        for (int p = 0; p < kRegRounds; ++p)
+#pragma unroll
+            for (int i2 = 0; i2 < XW; ++i2) asm volatile("" : "+v"(xr[p][i2]));
+        // the first tokens from memory are on their way before the pick's own centre is
+        unsigned xb[kBatch][XW];
+        if constexpr (kHeld < R) {
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) load_words(kHeld + k, xb[k]);
+        }
+        const int pick = pick_sh;
+        float cj[C];
+        widen<C>(xg + (size_t)pick * C, cj);
+        if (tid == 0 && picks) picks[j] = pick;
+        if (tid == 0) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) cent[(size_t)j * C + i] = cj[i];
+        }
+        if (j + 1 == K) break;
+
+        double pmax = 0.0;
+        unsigned fmx = 0;
+        auto visit = [&](const unsigned (&w)[XW], unsigned& dm, unsigned wgt) {
+            float xi[C];
+#pragma unroll
+            for (int i = 0; i < XW; ++i) {
+                const half2_t h = __builtin_bit_cast(half2_t, w[i]);
+                xi[2 * i] = (float)h.x;
+                xi[2 * i + 1] = (float)h.y;
+            }
+            dm = min(__float_as_uint(dist2<C>(xi, cj)), dm);
+            if constexpr (W) {
+                const double pr = (double)wgt * (double)__uint_as_float(dm);
+                pmax = pr > pmax ? pr : pmax;
+            } else {
+                fmx = max(fmx, dm);
+            }
+        };
+#pragma unroll
+        for (int p = 0; p < kHeld; ++p) {
+            unsigned w[XW];
+#pragma unroll
+            for (int i2 = 0; i2 < XW; ++i2)
+                w[i2] = p < kRegRounds ? xr[p < kRegRounds ? p : 0][i2] : xl[((p - kRegRounds) * kPPThreads + tid) * XW + i2];
+            visit(w, dmin[p], W ? wr[W ? p : 0] : 1u);
+            __builtin_amdgcn_sched_barrier(0);               // (one round's widened channels live at a time)
+        }
+#pragma unroll
+        for (int p = kHeld; p < R; p += kBatch) {
+            unsigned xn[kBatch][XW];
+            if (p + kBatch < R) {
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k) load_words(p + kBatch + k, xn[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                if (p + k < R) visit(xb[k], dmin[p + k < R ? p + k : 0], W ? wr[W && p + k < R ? p + k : 0] : 1u);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (p + kBatch < R) {
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k)
+#pragma unroll
+                    for (int i2 = 0; i2 < XW; ++i2) xb[k][i2] = xn[k][i2];
+            }
+        }
+        // the largest weighted distance (non-negative doubles order like their bits)
+        unsigned long long pb = (unsigned long long)__double_as_longlong(W ? pmax : (double)__uint_as_float(fmx));
+        pb = wave_max_u64(pb);
+        if (lane == 0) wave_max[wave] = pb;
+        __syncthreads();
+        unsigned long long pm = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVE; ++w) pm = wave_max[w] > pm ? wave_max[w] : pm;
+        if (pm == 0ull) {                                    // every token sits on a centre already
+            if (tid == 0) pick_sh = (int)__umul64hi(rnd[j + 1], (unsigned long long)n);
+            __syncthreads();
+            continue;
+        }
+        const int kq = __builtin_amdgcn_readfirstlane(62 - log2n - ((int)((pm >> 52) & 0x7ffull) - 1023 + 1));
         draw(rnd[j + 1], kq);
     }
 }
@@ -374,9 +652,37 @@ cq_status run_init(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t s
     return CQ_OK;
 }
 
+template <int C, bool W, int R>
+cq_status launch_kmeanspp_resident(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
+{
+    auto kernel = kmeanspp_resident_kernel<C, W, R>;
+    constexpr size_t lds = (size_t)kPPLdsRounds<C, W, R> * kPPThreads * C * 2 + (2 * (kPPThreads / 64) + 1) * sizeof(uint64_t);
+    static LdsKernelSetup setup;
+    if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
+    hipLaunchKernelGGL(kernel, dim3(a.f.groups), dim3(kPPThreads), lds, st, ws.xg, ws.wq, a.rnd, a.picks, ws.cent, a.n, a.f.k,
+                       ceil_log2(a.n));
+    return launch_ok() ? CQ_OK : CQ_ERR_HIP;
+}
+
+// rounds of 1024 tokens: the smallest of the four unrolled forms that holds the call's tokens
+template <int C, bool W>
+cq_status launch_kmeanspp_rounds(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
+{
+    if (a.n <= kPPThreads * 4) return launch_kmeanspp_resident<C, W, 4>(a, ws, st);
+    if (a.n <= kPPThreads * 8) return launch_kmeanspp_resident<C, W, 8>(a, ws, st);
+    if (a.n <= kPPThreads * 16) return launch_kmeanspp_resident<C, W, 16>(a, ws, st);
+    return launch_kmeanspp_resident<C, W, kPPRounds>(a, ws, st);
+}
+
 template <int C>
 cq_status run_kmeanspp(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
 {
+    if constexpr (C >= 2) {
+        // the tokens' distances fit the registers of one workgroup
+        if (a.n <= kPPThreads * kPPRounds) {
+            return a.weights ? launch_kmeanspp_rounds<C, true>(a, ws, st) : launch_kmeanspp_rounds<C, false>(a, ws, st);
+        }
+    }
     hipLaunchKernelGGL((kmeanspp_kernel<C>), dim3(a.f.groups), dim3(kPPThreads), 0, st, ws.xg, ws.wq, ws.dmin, a.rnd, a.picks,
                        ws.cent, a.n, a.f.k, ceil_log2(a.n));
     return launch_ok() ? CQ_OK : CQ_ERR_HIP;

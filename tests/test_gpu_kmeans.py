@@ -126,6 +126,22 @@ def test_strided_rows_and_repeatability():
     assert torch.equal(a, b_) and torch.equal(b_, c_)
 
 
+@pytest.mark.parametrize("n", [4096, 4097, 8193, 16385, 32768, 32769])
+@pytest.mark.parametrize("c,weighted", [(8, False), (4, True)])
+def test_picks_at_the_edges_of_the_register_resident_rounds(n, c, weighted):
+    """1024 tokens per round; forms for 4, 8, 16 and 32 rounds in registers, memory beyond."""
+    fmt = cq.CQFormat(c, 4 if c == 4 else 8, 128, 1)         # (16 picks per group suffice for c = 4)
+    G, K = fmt.groups, 1 << fmt.b
+    x = _data(50 + c, n, 128)
+    rnd = _rnd(n + c, G, K)
+    w = _weights(n, n, G) if weighted else None
+    picks, _ = KO.kmeanspp(x, c, K, rnd, w)
+    out = cq.cq_kmeans_fit(torch.from_numpy(x).cuda(), fmt, 0, rnd=_dev_rnd(rnd),
+                           weights=None if w is None else torch.from_numpy(w).cuda(), want_picks=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(out["picks"].cpu().numpy(), picks)
+
+
 @pytest.mark.parametrize("c,n,weighted", [(8, 63, False), (8, 65, True), (4, 2047, False), (8, 5000, False), (4, 9217, True),
                                           (2, 20001, False)])
 @pytest.mark.parametrize("data", ["plain", "tiny", "large", "far points", "dead groups", "duplicates"])
