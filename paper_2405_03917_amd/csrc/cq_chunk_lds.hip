@@ -1,0 +1,506 @@
+// Causal attention of a few query rows per KV head over a packed CQ cache (speculative
+// verification, short prefill chunks), for gfx950: the codebooks of the KV head in LDS, every
+// wavefront on tiles of its own.  The formats whose two codebooks fit there: CQ-8c8b and CQ-4c8b
+// (2 x 64 KB of the CU's 160 KB).
+//
+// The kernel for many rows (cq_chunk.hip) expands each 64-token tile once per workgroup from
+// codebooks in L2, which costs it 2 x 64 x Gh divergent lane-gathers of the texture path per
+// tile (about 4100 clocks at CQ-4c8b) whatever the number of rows.  Here the expansion IS the
+// operand load of the matrix product:
+//   S^T = K Q^T      v_mfma_f32_16x16x32_f16, A = keys of 16 tokens: a lane's 8 channels are the
+//                    centroid(s) of its token's code(s), read by ds_read_b128 / b64 at code
+//                    times entry size; B = 16 query rows (registers)
+//   softmax          each lane owns one query column; 2^12-scaled probabilities as two fp16
+//                    numbers (22 bits) as in cq_chunk.hip
+//   O^T += V^T P^T   A = values transposed: ds_read_b64_tr_b16 takes an address per lane and
+//                    hands lane j of 16 the j-th of 16 channels of 4 tokens, so gather and
+//                    transpose are one instruction; B = the probabilities just computed
+// A tile costs a wavefront 48 (CQ-8c8b) or 64 (4c8b) LDS gathers, 48 matrix products (32 up to 8
+// rows) and about 260 / 330 vector instructions, nothing is shared between wavefronts inside the
+// loop and there is no barrier.  Bound: the LDS.  A gather of 64 random 16-byte entries takes
+// 12.3 clocks (16 lanes at a time on 16 bank groups: the fullest holds 3.1), a transposing one
+// 6.2, i.e. 394 clocks per tile and CU at CQ-8c8b; the kernel takes 535 (LDS active 73-75 %).
+// Measured: CQ-4c8b, batch 16, 32 heads, 5 tokens over 4096: 136 us token by token, 264 us in the
+// many-row kernel, 53 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 280 us.  The first form
+// waited for every gather by itself (5800 clocks per tile and wavefront, 61 us); values gathered
+// ahead of the softmax in one batch of 64 registers spilled at CQ-4c8b and gained nothing.
+//
+// A workgroup of 8 wavefronts (one per CU) serves RB blocks of 16 rows; the 8 / RB wavefronts of
+// a block take every (8 / RB)-th tile and are merged through LDS at the end.  Workgroups walk
+// several (sequence, split) items of one KV head, so the codebooks are staged once per workgroup.
+#include "cq_decode_common.hpp"
+
+namespace cq {
+namespace {
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8;
+constexpr int kRows = 16;                               // query rows of a wavefront
+constexpr unsigned kBookBytes = 64 * 1024;              // one codebook of a KV head
+constexpr unsigned kMergeBase = 2 * kBookBytes;         // (m, l) of every wavefront and row, or 64 channels of every wavefront's
+constexpr unsigned kORow = 64 * 4;                      // output rows
+constexpr unsigned kLdsBytes = kMergeBase + kWaves * kRows * kORow;
+static_assert(kLdsBytes == 160 * 1024, "all of a CU's LDS");
+constexpr float kProbScale = 4096.f;                    // 2^12
+
+__device__ __forceinline__ half8_t lds_half8(unsigned a) { return *(__attribute__((address_space(3))) half8_t*)(a); }
+__device__ __forceinline__ half4_t lds_half4(unsigned a) { return *(__attribute__((address_space(3))) half4_t*)(a); }
+// lanes 16 b .. 16 b + 15 give the addresses of 4 rows of 16 fp16 numbers (lane 4 k + j: numbers 4 j .. 4 j + 3
+// of row k); lane 16 b + j receives number j of the four rows
+__device__ __forceinline__ half4_t lds_transposed(unsigned a)
+{
+    return __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t*)(a)));
+}
+// maximum / sum over the four lanes l % 16 + 16 b
+__device__ __forceinline__ float across_max(float v)
+{
+    v = fmaxf(v, __shfl_xor(v, 16));
+    return fmaxf(v, __shfl_xor(v, 32));
+}
+__device__ __forceinline__ float across_sum(float v)
+{
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
+}
+
+// The codes of one token that a lane needs, out of the token's record (byte w of plane p is slot
+// 16 p + w, holding the code of group (slot + token) mod Gh): every STRIDE-th group from group
+// g0 on, N of them, in group order, one byte each.  All of a lane's tokens are equal mod 16, and
+// (Gh = 32) a pair of token blocks differs by 16, which is a rotation by 16 slots, i.e. the planes
+// change places.
+template <int GH, int STRIDE>
+struct CodePick {
+    static constexpr int N = GH / STRIDE;               // 4 or 8
+    static constexpr int PL = GH / 16;
+    unsigned sel0, sel1;                                // byte selectors of v_perm_b32
+    unsigned rot;                                       // elements to rotate by
+    bool swap;
+    __device__ __forceinline__ CodePick(int g0, int token)
+    {
+        const unsigned beta = (unsigned)(g0 - token) & (GH - 1);
+        if constexpr (STRIDE == 4) {
+            const unsigned p = beta & 3;                // one byte of every dword
+            sel0 = 0x0c0c0000u | p | ((4 + p) << 8);
+            sel1 = 0x00000c0cu | (p << 16) | ((4 + p) << 24);
+            rot = (beta >> 2) & 3;
+            swap = (beta >> 2) >= 4;
+        } else {
+            const unsigned p = beta & 1;                // two bytes of every dword
+            sel0 = p | ((p + 2) << 8) | ((p + 4) << 16) | ((p + 6) << 24);
+            sel1 = 0;
+            rot = (beta >> 1) & 3;
+            swap = (beta >> 1) >= 4;
+        }
+    }
+    __device__ __forceinline__ unsigned four(const u32x4& r) const
+    {
+        return __builtin_amdgcn_perm(r[1], r[0], sel0) | __builtin_amdgcn_perm(r[3], r[2], sel1);
+    }
+    // the N codes, four to a word, of a token in an even (odd = 0) or odd block of 16
+    __device__ __forceinline__ void operator()(const u32x4 (&rec)[PL], int odd, unsigned (&z)[N / 4]) const
+    {
+        if constexpr (N == 4) {
+            const unsigned x = four(rec[0]);
+            z[0] = __builtin_amdgcn_alignbyte(x, x, rot);
+        } else {
+            unsigned x0, x1;
+            if constexpr (STRIDE == 4) {
+                x0 = four(rec[odd ? PL - 1 : 0]);
+                x1 = four(rec[odd ? 0 : PL - 1]);
+            } else {
+                x0 = __builtin_amdgcn_perm(rec[0][1], rec[0][0], sel0);
+                x1 = __builtin_amdgcn_perm(rec[0][3], rec[0][2], sel0);
+            }
+            const unsigned y0 = swap ? x1 : x0, y1 = swap ? x0 : x1;
+            z[0] = __builtin_amdgcn_alignbyte(y1, y0, rot);
+            z[1] = __builtin_amdgcn_alignbyte(y0, y1, rot);
+        }
+    }
+};
+
+// LDS address of the entry of code byte k of z: code x entry size + `base`, the lane's part (codebook,
+// first group, half), in one instruction (a dot product of bytes; shift, mask and or took two or three)
+template <int C>
+__device__ __forceinline__ unsigned entry(unsigned z, int k, unsigned base)
+{
+    return __builtin_amdgcn_udot4(z, (2u * C) << (8 * k), base, false);
+}
+
+// HALF: at most 8 rows in all.  Columns q and q + 8 of the score product hold the same query, and in the
+// value product the high parts of its probabilities in one and the low parts in the other: half the
+// matrix products there, one addition at the end.
+template <int C, bool HALF>
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves * 64) void chunk_lds_kernel(ChunkArgs a, int rb_log2, int items)
+{
+    constexpr int D = 128;
+    constexpr int GH = D / C;
+    constexpr int PL = GH / 16;
+    constexpr int TILE_BYTES = kTileTokens * GH;
+    extern __shared__ float smem[];
+    (void)smem;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, blk = lane >> 4;
+
+    const int rbs = 1 << rb_log2, cs = kWaves >> rb_log2;   // row blocks, context slices of the workgroup
+    const int rb = wave >> (3 - rb_log2), slice = wave & (cs - 1);
+    const int hkv = blockIdx.x % a.f.n_kv_heads;
+    const int stride = gridDim.x / a.f.n_kv_heads;
+    const int qper = a.n_q_heads / a.f.n_kv_heads;
+    const int rows_total = a.m * qper;
+    const int row_groups = (rows_total + kRows * rbs - 1) / (kRows * rbs);
+
+    // ---- this lane's places: keys, token col of a block of 16, groups blk, blk + 4, ...; values, token
+    // 4 blk + col / 4 of a block, channels 4 (col % 4) .. of 16 (C = 8: half of group (col % 4) / 2, then
+    // every second group; C = 4: group col % 4, then every fourth)
+    const int vtok = 4 * blk + (col >> 2);
+    const CodePick<GH, 4> kpick(blk, col);
+    const CodePick<GH, C == 8 ? 2 : 4> vpick(C == 8 ? (col & 3) >> 1 : (col & 3), vtok);
+    const unsigned kbase = (unsigned)blk * (256 * 2 * C);
+    const unsigned vbase = kBookBytes + (C == 8 ? ((unsigned)(col & 3) >> 1) * 4096 + (unsigned)(col & 1) * 8 : (unsigned)(col & 3) * 2048);
+
+
+    // ---- the items of this workgroup: (sequence, split, group of row blocks), advanced without divisions
+    const float inv_qper = 1.f / (float)qper;
+    const auto row_token = [&](int row) { return (int)(((float)row + 0.5f) * inv_qper); };     // row / qper (few rows: exact)
+    int item = blockIdx.x / a.f.n_kv_heads;
+    int rg = item % row_groups, split = item / row_groups % a.n_split, n = item / row_groups / a.n_split;
+    const int d_rg = stride % row_groups, d_split = stride / row_groups % a.n_split, d_n = stride / row_groups / a.n_split;
+    struct Item {
+        int n, rg, split, pos, pos_first, tile0, tile1;
+    };
+    const float scale = fabsf(a.scale_log2e);
+    half8_t qreg[4];
+    // the records of a tile on their way from memory, and the codes of one that this lane needs
+    u32x4 rk[4][PL], rv[4][PL];                             // token 16 i + col, token 16 i + vtok
+    unsigned zk[4][GH / 16], zv[4][2];
+    auto request = [&](const Item& it, int tile) {
+        const size_t at = a.map.tile_index(it.n, hkv, max(min(tile, it.tile1 - 1), it.tile0)) * TILE_BYTES;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int p = 0; p < PL; ++p) {
+                rk[i][p] = *reinterpret_cast<const u32x4*>(a.k_codes + at + p * 1024 + (16 * i + col) * 16);
+                rv[i][p] = *reinterpret_cast<const u32x4*>(a.v_codes + at + p * 1024 + (16 * i + vtok) * 16);
+            }
+    };
+    auto unpack = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            kpick(rk[i], i & 1, zk[i]);
+            vpick(rv[i], i & 1, zv[i]);
+        }
+    };
+    // an item's places, its queries and its first tile's records (requested ahead of the codebooks or of
+    // the previous item's merge)
+    auto open_item = [&]() {
+        Item it;
+        it.n = n;
+        it.rg = rg;
+        it.split = split;
+        int t_n = a.t;
+        if (a.seq_lens) t_n = min(max(a.seq_lens[n], a.m), a.t);
+        const int pos0 = t_n - a.m;                         // position of query token 0
+        const int row0 = (rg * rbs + rb) * kRows;           // (a block beyond the last row repeats it and stores nothing)
+        const int row = min(row0 + (HALF ? col & 7 : col), rows_total - 1);
+        const int j = row_token(row);
+        it.pos = pos0 + j;
+        it.pos_first = __builtin_amdgcn_readfirstlane(pos0 + row_token(min(row0, rows_total - 1)));
+        const int last_row = min(row0 + kRows, rows_total) - 1;
+        const int last_tile = __builtin_amdgcn_readfirstlane((pos0 + row_token(last_row)) / kTileTokens);
+        it.tile0 = split * a.tiles_per_split;
+        it.tile1 = row0 < rows_total ? min(it.tile0 + a.tiles_per_split, last_tile + 1) : it.tile0;
+        const uint16_t* qrow = a.q + (((size_t)n * a.m + j) * a.n_q_heads + hkv * qper + (row - j * qper)) * D;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if constexpr (C == 8) {
+                qreg[s] = *reinterpret_cast<const half8_t*>(qrow + 32 * s + 8 * blk);
+            } else {
+                const half4_t lo = *reinterpret_cast<const half4_t*>(qrow + 32 * s + 4 * blk);
+                const half4_t hi = *reinterpret_cast<const half4_t*>(qrow + 32 * s + 16 + 4 * blk);
+                qreg[s] = half8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            }
+        }
+        request(it, it.tile0 + slice);
+        return it;
+    };
+    Item it = open_item();
+
+    // ---- both codebooks of the head to LDS as they are ([group][code] entries)
+    {
+        const u32x4* src[2] = {reinterpret_cast<const u32x4*>(a.k_centroids + (size_t)hkv * GH * 256 * C),
+                               reinterpret_cast<const u32x4*>(a.v_centroids + (size_t)hkv * GH * 256 * C)};
+        typedef __attribute__((address_space(3))) u32x4 lds_q;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            u32x4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = src[w][i * (kWaves * 64) + tid];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) *(lds_q*)(w * kBookBytes + (unsigned)(i * (kWaves * 64) + tid) * 16) = v[i];
+        }
+    }
+
+    lds_barrier();
+
+#pragma unroll 1
+    for (;;) {
+        float4_t o[8];
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
+        float m_run = -INFINITY, l_run = 0.f;
+
+        // (a negative scale goes into the queries, so that the largest product is the largest score)
+        if (a.scale_log2e < 0.f) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) qreg[s] = -qreg[s];
+        }
+        int tile = it.tile0 + slice;
+        unpack();
+        request(it, tile + cs);
+#pragma unroll 1
+        for (; tile < it.tile1; tile += cs) {
+            // The gathers are issued in batches that the products behind them work off, one batch ahead
+            // (the scheduling fences pin that order: left alone, the compiler waits for every gather by itself,
+            // 130 clocks each).
+            // ---- scores: acc[i][e] is token 16 i + 4 blk + e, query col
+            float4_t acc[4];
+            half8_t kv[4][4];
+            auto gather_keys = [&](int i) {
+                unsigned at[GH / 4];
+#pragma unroll
+                for (int k = 0; k < GH / 4; ++k) at[k] = entry<C>(zk[i][k >> 2], k & 3, kbase);
+                __builtin_amdgcn_sched_barrier(0);          // (addresses first: a gather right behind its own would wait for it)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    if constexpr (C == 8) {
+                        kv[i][s] = lds_half8(at[s] + (unsigned)s * 16384);
+                    } else {
+                        const half4_t lo = lds_half4(at[2 * s] + (unsigned)(2 * s) * 8192);
+                        const half4_t hi = lds_half4(at[2 * s + 1] + (unsigned)(2 * s + 1) * 8192);
+                        kv[i][s] = half8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    }
+                }
+            };
+            half8_t av[2][8];
+            auto gather_values = [&](int t) {
+                unsigned at[2][8];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int cb = 0; cb < 8; ++cb) at[h][cb] = entry<C>(zv[2 * t + h][cb >> 2], cb & 3, vbase);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) {
+                    const half4_t v0 = lds_transposed(at[0][cb] + (unsigned)cb * 8192), v1 = lds_transposed(at[1][cb] + (unsigned)cb * 8192);
+                    av[t][cb] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                }
+            };
+            gather_keys(0);
+            gather_keys(1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv[i][s], qreg[s], acc[i], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i < 2) gather_keys(i + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            gather_values(0);
+            __builtin_amdgcn_sched_barrier(0);
+            // ---- online softmax of the lane's query column
+            float bmax = -INFINITY, mult = scale;
+            if (tile * kTileTokens + kTileTokens - 1 > it.pos_first) {
+                mult = 1.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int tok = tile * kTileTokens + 16 * i + 4 * blk + e;
+                        acc[i][e] = tok <= it.pos ? acc[i][e] * scale : -INFINITY;
+                        bmax = fmaxf(bmax, acc[i][e]);
+                    }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, acc[i][e]);
+                bmax *= scale;
+            }
+            const float m_new = fmaxf(m_run, across_max(bmax));
+            const float m_safe = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: all weights 0
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+            m_run = m_new;
+            const float m_shift = m_safe - 12.f;
+            float psum = 0.f;
+            half8_t ph[2], pl[2];                           // p 2^12 = ph + pl to 22 bits (HALF: ph of columns q, q + 8)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    const float2_t ps = {__builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][e], mult, -m_shift)),
+                                         __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][e + 1], mult, -m_shift))};
+                    psum += ps[0];
+                    psum += ps[1];
+                    const half2_t hi = __builtin_convertvector(ps, half2_t);
+                    const float2_t rest = {__builtin_fmaf((float)hi[0], -1.f, ps[0]), __builtin_fmaf((float)hi[1], -1.f, ps[1])};
+                    const half2_t lo = __builtin_convertvector(rest, half2_t);
+                    const int at = 4 * (i & 1) + e;
+                    if constexpr (HALF) {
+                        const half2_t v = __builtin_bit_cast(half2_t, col < 8 ? __builtin_bit_cast(unsigned, hi) : __builtin_bit_cast(unsigned, lo));
+                        ph[i >> 1][at] = v[0];
+                        ph[i >> 1][at + 1] = v[1];
+                    } else {
+                        ph[i >> 1][at] = hi[0];
+                        ph[i >> 1][at + 1] = hi[1];
+                        pl[i >> 1][at] = lo[0];
+                        pl[i >> 1][at + 1] = lo[1];
+                    }
+                }
+            l_run = __builtin_fmaf(l_run, alpha, psum);
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) o[cb] *= alpha;
+            }
+            // ---- O^T += V^T P^T: contraction index (blk, 4 h + e) is token 32 t + 16 h + 4 blk + e
+            __builtin_amdgcn_sched_barrier(0);
+            gather_values(1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) {
+                    o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], ph[t], o[cb], 0, 0, 0);
+                    if constexpr (!HALF) o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], pl[t], o[cb], 0, 0, 0);
+                }
+            // the next tile's codes, and the request for the tile after it
+            unpack();
+            request(it, tile + 2 * cs);
+        }
+
+        // ---- the next item's requests go out, then the context slices of every row block are merged: (m, l),
+        // then the rows, scaled to the common maximum, 64 channels at a time
+        const Item done = it;
+        item += stride;
+        const bool more = item < items;
+        if (more) {
+            rg += d_rg;
+            const int c0 = rg >= row_groups;
+            rg -= c0 ? row_groups : 0;
+            split += d_split + c0;
+            const int c1 = split >= a.n_split;
+            split -= c1 ? a.n_split : 0;
+            n += d_n + c1;
+            it = open_item();
+        }
+        typedef __attribute__((address_space(3))) float lds_f;
+        typedef __attribute__((address_space(3))) float2_t lds_f2;
+        typedef __attribute__((address_space(3))) float4_t lds_f4;
+        const float l = across_sum(l_run);
+        if (blk == 0) *(lds_f2*)(kMergeBase + (unsigned)(wave * kRows + col) * 8) = float2_t{m_run, l};
+        lds_barrier();
+        float2_t ml[kWaves];                                // of the wavefronts that share this one's row block, this lane's row
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) ml[w] = *(lds_f2*)(kMergeBase + (unsigned)((rb * cs + (w & (cs - 1))) * kRows + col) * 8);
+        float mm = -INFINITY, ll = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, ml[w][0]);
+        const float mz = mm == -INFINITY ? 0.f : mm;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) ll += w < cs ? ml[w][1] * __builtin_amdgcn_exp2f(ml[w][0] - mz) : 0.f;
+        float weight = __builtin_amdgcn_exp2f(m_run - mz);
+        weight *= a.n_split == 1 ? 1.f / ll : 1.f / kProbScale;
+        const int row0 = (done.rg * rbs + rb) * kRows;
+        if (a.n_split > 1 && slice == 0 && blk == 0 && row0 + col < rows_total) {
+            const int j = row_token(row0 + col);
+            const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (row0 + col - j * qper);
+            float* dst = a.partials + (out_row * a.n_split + done.split) * (D + kPartialHeader);
+            dst[0] = mm;
+            dst[1] = ll * (1.f / kProbScale);
+        }
+        lds_barrier();                                      // the pairs are read: their room is the rows'
+        const int q = tid >> 5;                             // this thread's row and pair of channels
+        const unsigned osrc = kMergeBase + (unsigned)q * kORow + (((unsigned)(tid & 31) >> 1) ^ (unsigned)q) * 16 + (tid & 1) * 8;
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                float4_t v = o[4 * part + h];
+                if constexpr (HALF) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)         // (lane l + 8 mod 16 of the row)
+                        v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));
+                }
+                // (16-byte pieces of a row change places by the row's number: 16 rows, 16 different banks)
+                *(lds_f4*)(kMergeBase + (unsigned)(wave * kRows + col) * kORow + (unsigned)((4 * h + blk) ^ col) * 16) = v * weight;
+            }
+            lds_barrier();
+            float2_t sum = {0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                sum += *(lds_f2*)(osrc + (unsigned)(w * kRows) * kORow);
+                if (((w + 1) & (cs - 1)) != 0) continue;    // (the row block's last slice)
+                const int r2 = (done.rg * rbs + (w >> (3 - rb_log2))) * kRows + q;
+                if (r2 < rows_total) {
+                    const int j = row_token(r2);
+                    const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (r2 - j * qper);
+                    const int ch = part * 64 + 2 * (tid & 31);
+                    if (a.n_split == 1)
+                        *reinterpret_cast<half2_t*>(a.out + out_row * D + ch) = __builtin_convertvector(sum, half2_t);
+                    else
+                        *reinterpret_cast<float2_t*>(a.partials + (out_row * a.n_split + done.split) * (D + kPartialHeader) + kPartialHeader + ch) = sum;
+                }
+                sum = float2_t{0.f, 0.f};
+            }
+            lds_barrier();
+        }
+        if (!more) break;
+    }
+}
+
+template <int C, bool HALF>
+cq_status launch(const ChunkArgs& a, hipStream_t stream)
+{
+    auto kernel = chunk_lds_kernel<C, HALF>;
+    static LdsKernelSetup setup;
+    if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
+    const ChunkLdsPlan p = chunk_lds_plan(a.f, a.batch, a.n_q_heads, a.m);
+    const int items = a.batch * a.n_split * p.row_groups;
+    const int per_head = items < p.wgs_per_head ? items : p.wgs_per_head;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_head * a.f.n_kv_heads)), dim3(kWaves * 64), kLdsBytes, stream, a, p.rb_log2, items);
+    return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
+}
+
+}  // namespace
+
+ChunkLdsPlan chunk_lds_plan(const Derived& f, int batch, int n_q_heads, int m)
+{
+    (void)batch;
+    ChunkLdsPlan p;
+    const int blocks = (m * (n_q_heads / f.n_kv_heads) + kRows - 1) / kRows;
+    p.rb_log2 = blocks <= 1 ? 0 : (blocks <= 2 ? 1 : (blocks <= 4 ? 2 : 3));
+    p.row_groups = (blocks + (1 << p.rb_log2) - 1) >> p.rb_log2;
+    p.wgs_per_head = f.n_kv_heads < 256 ? 256 / f.n_kv_heads : 1;      // one workgroup per CU
+    return p;
+}
+
+cq_status launch_chunk_lds(const ChunkArgs& a, hipStream_t stream)
+{
+    if (a.f.b != 8 || a.f.head_dim != 128) return CQ_ERR_UNSUPPORTED;
+    // (row / qper is formed in floating point: exact for far more rows than are served here)
+    const bool half = a.m * (a.n_q_heads / a.f.n_kv_heads) <= kRows / 2;
+    if (a.f.c == 8) return half ? launch<8, true>(a, stream) : launch<8, false>(a, stream);
+    if (a.f.c == 4) return half ? launch<4, true>(a, stream) : launch<4, false>(a, stream);
+    return CQ_ERR_UNSUPPORTED;
+}
+
+}  // namespace cq

@@ -203,3 +203,40 @@ def test_chunk_attention_sweep(case):
     out = _gpu(q, codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap), ck, cv, 0.09, fmt, T, t_cap,
                seq_lens=lens, split=split)
     _check(out, ref)
+
+
+@pytest.mark.parametrize("c", [8, 4])
+@pytest.mark.parametrize("m,hq,hkv,B,T,scale", [
+    (8, 2, 2, 2, 65, 0.09),            # 8 rows: both halves of the probabilities in one product
+    (3, 6, 2, 3, 640, 0.09),           # 9 rows
+    (4, 8, 2, 2, 129, -0.09),          # one block of 16, scores falling with the product
+    (17, 2, 2, 1, 1000, 0.0),          # two blocks, all scores equal
+    (11, 12, 4, 1, 200, 0.09),         # 33 rows: four blocks, the last one empty
+    (16, 8, 2, 2, 777, 0.2),           # 64 rows
+    (65, 2, 2, 1, 300, 0.09),          # 65: the kernel for many rows
+    (3, 64, 64, 7, 130, 0.09),         # several (sequence, split) items per workgroup
+])
+def test_chunks_of_few_rows_with_codebooks_in_lds(c, m, hq, hkv, B, T, scale):
+    fmt, q, kc, vc, ck, cv = _case(300 + m + T, c, 8, hq, hkv, B, m, T)
+    t_cap = -(-T // 64) * 64
+    lens = np.random.default_rng(T).integers(m, T + 1, size=B).astype(np.int32)
+    lens[0] = T
+    ref = O.chunk_attention(q, kc, vc, ck, cv, scale, hkv, seq_lens=lens)
+    kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
+    for split in (0, 64, 192):
+        _check(_gpu(q, kcache, vcache, ck, cv, scale, fmt, T, t_cap, seq_lens=lens, split=split), ref)
+
+
+def test_few_rows_split_no_further_than_the_workspace_holds():
+    """The library's own split of a long context shrinks to the caller's workspace, down to none."""
+    c, b, hq, hkv, B, m, T, t_cap = 4, 8, 2, 2, 1, 5, 4000, 4032
+    fmt, q, kc, vc, ck, cv = _case(21, c, b, hq, hkv, B, m, T)
+    need = cq.cq_chunk_workspace_bytes(fmt, B, hq, m, T)
+    assert need > 2 * 4 * B * m * hq * 130
+    ref = O.chunk_attention(q, kc, vc, ck, cv, 0.1, hkv)
+    kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
+    for nbytes in (need, need // 2, 16):
+        out = cq.cq_chunk_attention(dev(q), kcache, vcache, dev(ck), dev(cv), 0.1, fmt, T, t_cap,
+                                    workspace=torch.zeros(nbytes, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        _check(out.cpu().numpy(), ref)
