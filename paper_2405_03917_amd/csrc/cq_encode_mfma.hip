@@ -5,10 +5,13 @@
 // argmax_j (x . c_j - |c_j|^2 / 2).  One MFMA evaluates that score for 32 tokens x 32 centroids:
 // the K dimension of the matrix product carries the c channels plus three fp16 pieces of
 // -|c_j|^2 / 2 (their sum is exact to fp32 precision; see "Scaling").  The two largest scores of a
-// token are then found in two levels: each lane keeps the two largest QUAD maxima it sees (the
-// maximum of four scores, with the quad's number packed into its five lowest mantissa bits:
-// 1.2 VALU instructions per score instead of the 2 c + 3 of the direct form), and the four
-// scores of the winning quad are evaluated once more, with packed dot products in fp32.
+// token are then found in two levels: each lane keeps the two largest maxima of EIGHT scores it sees
+// (the number of the eight packed into the four lowest mantissa bits: 0.8 VALU instructions per
+// score instead of the 2 c + 3 of the direct form), and the eight scores of the winner are
+// evaluated once more, with packed dot products in fp32.  (Maxima of four cost 1.1 per score and
+// half the second look; K and V of 32768 tokens x 4096 channels, maxima of four -> eight, with the
+// operands of several tiles' scans kept in registers and the bound below: CQ-8c8b 686 -> 600 us,
+// 4c8b 971 -> 860, 64 x 512 tokens of 2c8b 2.0 -> 1.6 ms; same codes.)
 //
 // Scaling.  A group whose largest |c_j|^2 is small is multiplied (centroids and tokens alike)
 // by a power of two 2^s, s >= 0, that brings the largest scaled |c'|^2 into [2^12, 2^14): the
@@ -17,19 +20,24 @@
 // |c|^2 / 2 would not fit fp16 (|c|^2 >= 60000), and a token whose scaled channels would not,
 // are handed to the exact path whole.
 //
-// Error bound.  With M = |x'| |c'|_max + |c'|_max^2 / 2 >= sum of the absolute values of the
-// terms of any score, in units of 2^-20 M.  A quad maximum from the matrix core: |c|^2 summed in
-// fp32 (0.5); the matrix core aligns the exact products to the largest one and drops what falls
-// below about 2^-24 of it -- at most 2^-23 M for each of at most 11 terms and the final rounding
-// (1.5; measured on such operands: never above 0.2); the five packed bits move a score by less
-// than 32 units in its last place (3.9): 5.9 in all.  A score of the winning quad from the
-// vector ALU: |c|^2 (0.5), c / 2 + 2 roundings to fp32 (0.4), two packed bits (0.5): 1.4.  The
-// best is always of the second kind, the runner-up of either, so the two compare correctly
-// whenever they differ by more than 7.3 units; the test below uses 8 = 2^-17 M.  (If rounding
-// made the wrong quad win, the true best's quad maximum is the runner-up and lies within 7.3
-// units of the reported best: the test fails and the pair is re-done.)  If the best beats the
-// runner-up by more than that, the best IS the
-// nearest centroid in exact arithmetic.  Otherwise (a near tie or an exact tie) the (token,
+// Error bound.  With M = |x'| |c'| + |c'|^2 / 2 >= sum of the absolute values of the terms of a
+// score, in units of 2^-20 M.  A maximum of eight from the matrix core: |c|^2 summed in fp32
+// (0.5); the matrix core aligns the exact products to the largest one and drops what falls below
+// about 2^-24 of it -- at most 2^-23 M for each of at most 11 terms and the final rounding (1.5;
+// measured on such operands: never above 0.2); the four packed bits move a score by less than 16
+// units in its last place (1.9): 3.9 in all.  A score of the winner's eight from the vector ALU:
+// |c|^2 (0.5), c / 2 + 2 roundings to fp32 (0.4), three packed bits (0.9): 1.8.  The best is always
+// of the second kind, the runner-up of either, so the two compare correctly whenever they differ by
+// more than 5.7 units; the test below uses 8 = 2^-17 M.  (If rounding made the wrong eight win, the
+// true best's maximum is the runner-up and lies within 5.7 units of the reported best: the test
+// fails and the pair is re-done.)  The |c'| in M is the longest of the group or, if that is less,
+// the longest that could be as near as the winner: |x'| + its distance d, d^2 = |x'|^2 - 2 x score
+// (its error, 3.6 units of the largest M under the root, is at most 0.0014 (|x'| + |c'|max): `slack`).
+// With that, a group with a few long centroids sends a third as many pairs to the re-do; a pair
+// it spares differs by 4 x 2^-20 (|x'| + |c'|)^2 or more, which the direct form, whose error is 0.6
+// of such units, decides the same way.
+// If the best beats the runner-up by more than the bound, the best IS the nearest centroid in
+// exact arithmetic.  Otherwise (a near tie or an exact tie) the (token,
 // group) pair is re-done at once by the direct form -- sum_i (x_i - c_i)^2 in fp32, channel
 // order, lowest index on ties; on the scaled values, which changes no bit of the comparison --
 // by the whole wavefront, from the codebook copy in LDS.  The result is
@@ -59,6 +67,17 @@ struct Aug {
     static constexpr int HALF = KDIM / 2;               // halfs per lane operand
     using vec_t = std::conditional_t<C == 8, half8_t, half4_t>;
 };
+
+// Place of centroid j's record among the records in LDS.  The records of 256 bytes (a row of all banks)
+// change places by the number of their block of 16: the lanes of level 2 read records with the same
+// number modulo 16 from different blocks, which would otherwise all start in the same bank.
+// A matrix operand (32 consecutive records) is permuted within its rows.
+template <int C>
+__device__ __forceinline__ int record(int j)
+{
+    constexpr int M = 128 / Aug<C>::KDIM - 1;           // records per row - 1
+    return j ^ ((j >> 4) & M);
+}
 
 template <int C>
 __device__ __forceinline__ float16_t mfma(typename Aug<C>::vec_t a, typename Aug<C>::vec_t b)
@@ -200,7 +219,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     constexpr int NT = NW * 64;
     constexpr int KDIM = A::KDIM, HALF = A::HALF;
     constexpr int NBLK = K / 32;                     // 32-centroid blocks
-    constexpr int NSB = NBLK / 8;                    // runs of 8 blocks (the packed quad number has 5 bits)
+    constexpr int NSB = NBLK / 8;                    // runs of 8 blocks (the packed number of an eight has 4 bits)
     constexpr int P = GH / 16;
     constexpr int TILE_LOW = kTileTokens * GH;
     constexpr int TILE_BYTES = kTileTokens * GH * B / 8;
@@ -211,7 +230,11 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     constexpr int TPW = GS ? TILES : 1;              // tiles per wavefront
     // augmented codebook records: two buffers that the workgroup alternates, or (GS) one per wavefront
     __shared__ __attribute__((aligned(16))) _Float16 cba[GS ? NW : 2][K * KDIM];
-    __shared__ unsigned c2bits[GH];                                       // bits of max_j |c_j|^2 per group
+    // -|c'_j|^2 / 2 for level 2 (byte codes; for 1024 centroids it would cost the second workgroup on the CU,
+    // and level 2 adds the three pieces up instead)
+    constexpr bool NORMS = B == 8;
+    __shared__ __attribute__((aligned(16))) float half_norm[NORMS ? NW : 1][NORMS ? K : 4];
+    __shared__ unsigned c2bits[GS ? 1 : GH];                              // bits of max_j |c_j|^2 per group (not GS)
     __shared__ __attribute__((aligned(16))) uint8_t rec[NTILE][TILE_LOW];  // low code bytes, cache order
     __shared__ uint16_t code16[B == 10 ? NW : 1][B == 10 ? kTileTokens : 1][B == 10 ? GH : 1];
 
@@ -228,10 +251,14 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     const int last_tile = (t_end - 1) / kTileTokens;
     // tile t of this wavefront (GS: of the workgroup); this lane's token in it (cache position)
     auto tile_index = [&](int t) { return GS ? t : wave; };
-    auto tile_at = [&](int t) { return first_tile + (int)blockIdx.x * NTILE + tile_index(t); };
+    // (several tiles per wavefront: a.tiles_per_wg of them, at most TILES, so that a sequence's tiles are
+    // dealt out evenly)
+    const int wg_tiles = TPW > 1 ? a.tiles_per_wg : NTILE;
+    auto tile_at = [&](int t) { return first_tile + (int)blockIdx.x * wg_tiles + tile_index(t); };
+    auto beyond = [&](int t) { return TPW > 1 && (t >= wg_tiles || tile_at(t) > last_tile); };
     auto valid_at = [&](int t) {
         const int pos = tile_at(t) * kTileTokens + lane;
-        return pos >= a.t_offset && pos < t_end;
+        return !beyond(t) && pos >= a.t_offset && pos < t_end;
     };
     const uint16_t* xbase = ten.x + (size_t)n * ten.x_batch_stride + (size_t)hkv * GH * C;
     auto xrow_at = [&](int t) {
@@ -279,6 +306,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
 #pragma unroll
             for (int i = 0; i < C / 2; ++i) cs[i] = scale_pair(craw[k][i], gs);
             const float v = gs.too_big ? 0.f : -0.5f * norm2_scaled<C / 2>(cs);          // -|c'|^2 / 2
+            if constexpr (NORMS) half_norm[buf][j] = v;
             const _Float16 h1 = (_Float16)v;
             const float r1 = v - (float)h1;
             const _Float16 h2 = (_Float16)r1;
@@ -286,7 +314,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
             const _Float16 zero = (_Float16)0.0f;
             const unsigned w12 = __builtin_bit_cast(unsigned, half2_t{h1, h2});
             const unsigned w30 = __builtin_bit_cast(unsigned, half2_t{h3, zero});
-            uint4* dst = reinterpret_cast<uint4*>(&cba[buf][j * KDIM]);
+            uint4* dst = reinterpret_cast<uint4*>(&cba[buf][record<C>(j) * KDIM]);
             if constexpr (C == 8) {
                 dst[0] = make_uint4(cs[0], cs[1], cs[2], cs[3]);
                 dst[1] = make_uint4(w12, w30, 0u, 0u);
@@ -349,7 +377,18 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     for (int g = g_begin; g < g_end; ++g) {
         const int buf = GS ? wave : (g & 1);
         const GroupScale gs = group_scale(GS ? c2_staged : (unsigned)__builtin_amdgcn_readfirstlane((int)c2bits[g]));
+        const float cmax = 1.0001f * __builtin_amdgcn_sqrtf(gs.c2max_scaled);      // the longest scaled centroid
+        constexpr float slack = 0.01f;
         if (g + 1 < g_end) fetch(g + 1);
+        auto operand = [&](int blk) {
+            return *reinterpret_cast<const vec_t*>(&cba[buf][record<C>(blk * 32 + (lane & 31)) * KDIM + (lane >> 5) * HALF]);
+        };
+        // several tiles per wavefront: the group's records as matrix operands stay in registers for all of them
+        vec_t held[TPW > 1 ? NBLK : 1];
+        if constexpr (TPW > 1) {
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk) held[blk] = operand(blk);
+        }
 #pragma unroll 1
         for (int t = 0; t < TPW; ++t) {
             const int ti = tile_index(t);
@@ -363,23 +402,20 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
 #pragma unroll
                 for (int i = 0; i < C / 2; ++i) xnext[k][i] = xnext[k + 1][i];
             if (g + 1 < g_end) load_x(g + 1, t, xnext[TPW - 1]);
-            if (TPW > 1 && tile_at(t) > last_tile) continue;        // (a workgroup's tiles beyond the call's last)
+            if (beyond(t)) continue;
 #pragma unroll
             for (int i = 0; i < C / 2; ++i) xs[i] = scale_pair(xw[i], gs);
             const float x2 = norm2_scaled<C / 2>(xs);                // (infinite where the scaling overflowed)
             const bool x_over = !(x2 < 1.0e9f);                      // |x'| beyond 2^15: not as fp16
 #pragma unroll
             for (int i = 0; i < C / 2; ++i) xs[i] = x_over ? 0u : xs[i];
-            // 2^-17 M with M >= |x'| |c'|max + |c'|max^2 / 2 (1 % slack for the roundings of this line)
-            const float thr = (1.01f * (__builtin_sqrtf(x2 * gs.c2max_scaled) + 0.5f * gs.c2max_scaled)) * (1.0f / 131072.0f);
             const bool exact_only = gs.too_big || x_over;
 
             // Level 1, once per half of the tile (tokens 32 h .. 32 h + 31 are the 32 columns of the
-            // matrix product): the two largest of the lane's 16 NBLK scores.  The maximum of every quad
-            // of scores (the 4 consecutive centroids 8 q + 4 (lane / 32) .. + 3 of a block: registers
-            // 4 q .. 4 q + 3) with the quad's number, 4 (blk % 8) + q, packed into its five lowest
-            // mantissa bits, and a running (best, runner-up) over those: 1.2 VALU instructions per
-            // score instead of the 2.8 of tracking every score.
+            // matrix product): the two largest of the lane's 16 NBLK scores.  The maximum of every
+            // eight scores (registers 8 o .. 8 o + 7: the centroids 16 o + 4 (lane / 32) .. + 3 and + 8 .. + 11
+            // of a block) with its number, 2 (blk % 8) + o, packed into its four lowest mantissa bits,
+            // and a running (best, runner-up) over those: 0.8 VALU instructions per score.
             float hbest[2], hsecond[2];
             int hsb[2];
 #pragma unroll
@@ -421,24 +457,24 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
 #pragma unroll 1
                 for (int sb = 0; sb < NSB; ++sb) {
                     float sbest = LOWEST, ssecond = LOWEST;
-#pragma unroll                  // (whole: the quad numbers are then immediates of one v_and_or_b32)
+#pragma unroll                  // (whole: the numbers are then immediates of one v_and_or_b32)
                     for (int b8 = 0; b8 < 8; ++b8) {
                         const int blk = sb * 8 + b8;
-                        const vec_t aop = *reinterpret_cast<const vec_t*>(&cba[buf][(blk * 32 + (lane & 31)) * KDIM + (lane >> 5) * HALF]);
-                        const float16_t d = mfma<C>(aop, bop);
-                        float qm[4];
+                        const float16_t d = mfma<C>(TPW > 1 ? held[TPW > 1 ? b8 : 0] : operand(blk), bop);
+                        float om[2];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float m = fmaxf(fmaxf(fmaxf(d[4 * q], d[4 * q + 1]), d[4 * q + 2]), d[4 * q + 3]);
-                            qm[q] = __uint_as_float((__float_as_uint(m) & 0xffffffe0u) | (unsigned)(4 * b8 + q));
+                        for (int o = 0; o < 2; ++o) {
+                            const int r = 8 * o;
+                            float m = fmaxf(fmaxf(d[r], d[r + 1]), d[r + 2]);
+                            m = fmaxf(fmaxf(m, d[r + 3]), d[r + 4]);
+                            m = fmaxf(fmaxf(m, d[r + 5]), d[r + 6]);
+                            m = fmaxf(m, d[r + 7]);
+                            om[o] = __uint_as_float((__float_as_uint(m) & 0xfffffff0u) | (unsigned)(2 * b8 + o));
                         }
-                        // two quads per step: the runner-up of {best, second, k1, k2} with second <= best
-                        // is max(median(best, k1, k2), second)
-#pragma unroll
-                        for (int q = 0; q < 4; q += 2) {
-                            ssecond = fmaxf(ssecond, __builtin_amdgcn_fmed3f(sbest, qm[q], qm[q + 1]));
-                            sbest = fmaxf(fmaxf(sbest, qm[q]), qm[q + 1]);
-                        }
+                        // the runner-up of {best, second, k1, k2} with second <= best is
+                        // max(median(best, k1, k2), second)
+                        ssecond = fmaxf(ssecond, __builtin_amdgcn_fmed3f(sbest, om[0], om[1]));
+                        sbest = fmaxf(fmaxf(sbest, om[0]), om[1]);
                     }
                     if constexpr (NSB == 1) {
                         gbest = sbest;
@@ -469,46 +505,60 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
             const int whalf = other ? 1 - hi : hi;
             const int u = lane;                                      // token of the tile
             const int slot = (g - u) & (GH - 1);
-            // Level 2: the winning quad's four centroids against this token, x . c - |c|^2 / 2 in fp32
-            // from the records in LDS.
-            const int quad = (int)(__float_as_uint(best) & 31u);
-            const int j0 = (wsb * 8 + (quad >> 2)) * 32 + 8 * (quad & 3) + 4 * whalf;
-            // (v_dot2_f32_f16: exact products of the fp16 pairs, fp32 sums; the centroid's number
-            // within the quad rides in the two lowest mantissa bits)
-            float qk[4];
-            const half2_t ones = half2_t{(_Float16)1.0f, (_Float16)1.0f};
+            // Level 2: the winner's eight centroids (j0 .. j0 + 3 and j0 + 8 .. j0 + 11) against this token,
+            // x . c - |c|^2 / 2 in fp32 from the records and norms in LDS (v_dot2_f32_f16: exact products of
+            // the fp16 pairs, fp32 sums; the centroid's number among the eight rides in the three
+            // lowest mantissa bits)
+            const int j0 = (wsb * 8 + (int)((__float_as_uint(best) & 15u) >> 1)) * 32 + (int)(__float_as_uint(best) & 1u) * 16 + 4 * whalf;
+            float qk[8];
+            float hn[8];
+            if constexpr (NORMS) {
+                const float4 n0 = *reinterpret_cast<const float4*>(&half_norm[buf][j0]), n1 = *reinterpret_cast<const float4*>(&half_norm[buf][j0 + 8]);
+                hn[0] = n0.x; hn[1] = n0.y; hn[2] = n0.z; hn[3] = n0.w; hn[4] = n1.x; hn[5] = n1.y; hn[6] = n1.z; hn[7] = n1.w;
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const unsigned* r = reinterpret_cast<const unsigned*>(&cba[buf][(j0 + e) * KDIM]);
-                unsigned w[C / 2 + 2];
+            for (int e = 0; e < 8; ++e) {
+                const unsigned* r = reinterpret_cast<const unsigned*>(&cba[buf][record<C>(j0 + (e & 3) + 8 * (e >> 2)) * KDIM]);
+                unsigned w[C / 2];
                 if constexpr (C == 8) {
                     const uint4 a0 = *reinterpret_cast<const uint4*>(r);
-                    const uint2 a1 = *reinterpret_cast<const uint2*>(r + 4);
-                    w[0] = a0.x; w[1] = a0.y; w[2] = a0.z; w[3] = a0.w; w[4] = a1.x; w[5] = a1.y;
-                } else if constexpr (C == 4) {
-                    const uint4 a0 = *reinterpret_cast<const uint4*>(r);
                     w[0] = a0.x; w[1] = a0.y; w[2] = a0.z; w[3] = a0.w;
+                } else if constexpr (C == 4) {
+                    const uint2 a0 = *reinterpret_cast<const uint2*>(r);
+                    w[0] = a0.x; w[1] = a0.y;
                 } else {
-                    const uint4 a0 = *reinterpret_cast<const uint4*>(r);
-                    w[0] = a0.x; w[1] = a0.y; w[2] = a0.z;
+                    w[0] = r[0];
                 }
-                // the three pieces of -|c|^2 / 2 sit behind the C channels: (h1, h2), (h3, 0)
-                float sc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, w[C / 2 + 1]), ones, 0.f, false);
-                sc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, w[C / 2]), ones, sc, false);
+                float sc;
+                if constexpr (NORMS) {
+                    sc = hn[e];
+                } else {                        // the three pieces sit behind the C channels: (h1, h2), (h3, 0)
+                    const half2_t ones = half2_t{(_Float16)1.0f, (_Float16)1.0f};
+                    const uint2 p = *reinterpret_cast<const uint2*>(r + C / 2);
+                    sc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, p.y), ones, 0.f, false);
+                    sc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, p.x), ones, sc, false);
+                }
 #pragma unroll
                 for (int i = 0; i < C / 2; ++i)
                     sc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, xs[i]), __builtin_bit_cast(half2_t, w[i]), sc, false);
-                qk[e] = __uint_as_float((__float_as_uint(sc) & 0xfffffffcu) | (unsigned)e);
+                qk[e] = __uint_as_float((__float_as_uint(sc) & 0xfffffff8u) | (unsigned)e);
             }
-            const float q01 = fmaxf(qk[0], qk[1]);
-            const float qbest_k = fmaxf(fmaxf(q01, qk[2]), qk[3]);
-            const float qsecond = fmaxf(fminf(qk[0], qk[1]), __builtin_amdgcn_fmed3f(q01, qk[2], qk[3]));
-            const int qarg = (int)(__float_as_uint(qbest_k) & 3u);
-            const float qbest = __uint_as_float(__float_as_uint(qbest_k) & 0xfffffffcu);
+            float qbest_k = fmaxf(qk[0], qk[1]), qsecond = fminf(qk[0], qk[1]);
+#pragma unroll
+            for (int e = 2; e < 8; e += 2) {
+                qsecond = fmaxf(qsecond, __builtin_amdgcn_fmed3f(qbest_k, qk[e], qk[e + 1]));
+                qbest_k = fmaxf(fmaxf(qbest_k, qk[e]), qk[e + 1]);
+            }
+            const int qarg = (int)(__float_as_uint(qbest_k) & 7u);
+            const float qbest = __uint_as_float(__float_as_uint(qbest_k) & 0xfffffff8u);
+            // 2^-17 M (1 % slack for the roundings of these lines): see "Error bound"
+            const float xn = __builtin_amdgcn_sqrtf(x2);
+            const float reach = fminf(cmax, 1.001f * (xn + __builtin_amdgcn_sqrtf(fmaxf(x2 - 2.f * qbest, 0.f))) + slack * (xn + cmax));
+            const float thr = (1.01f / 131072.0f) * reach * (xn + 0.5f * reach);
             bool unsure;
             {
-                const int code = j0 + qarg;
-                const float sv = fmaxf(__uint_as_float(__float_as_uint(second) & 0xffffffe0u), qsecond);
+                const int code = j0 + (qarg & 3) + 8 * (qarg >> 2);
+                const float sv = fmaxf(__uint_as_float(__float_as_uint(second) & 0xfffffff0u), qsecond);
                 unsure = !(qbest - sv > thr) || exact_only;
                 rec[ti][(slot >> 4) * 1024 + u * 16 + (slot & 15)] = (uint8_t)(code & 0xff);
                 if constexpr (B == 10) code16[wave][u][g] = (uint16_t)code;
@@ -531,7 +581,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 for (int j = lane; j < K; j += 64) {
                     unsigned cw[C / 2];
 #pragma unroll
-                    for (int i = 0; i < C / 2; ++i) cw[i] = *reinterpret_cast<const unsigned*>(&cba[buf][j * KDIM + 2 * i]);
+                    for (int i = 0; i < C / 2; ++i) cw[i] = *reinterpret_cast<const unsigned*>(&cba[buf][record<C>(j) * KDIM + 2 * i]);
                     const unsigned dj = exact_distance_bits<C>(x, cw);
                     jmin = dj < dmin ? (unsigned)j : jmin;       // increasing j: the lowest index stays on ties
                     dmin = dj < dmin ? dj : dmin;
@@ -576,7 +626,11 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
 
 // Byte codes: up to kGroupSplitEightBelow (tile, head, sequence, tensor) items eight wavefronts
 // share a tile, below kGroupSplitBelow (and for sequences of fewer than four tiles) four; larger
-// calls give four tiles to a workgroup of four wavefronts.
+// calls give four tiles to a workgroup of four wavefronts, which stages each group's codebook once
+// for them, and the largest of CQ-8c8b, whose codebooks take the longest to stage, eight.
+// (K and V of 32768 tokens x 4096 channels, four / eight tiles: CQ-8c8b 601 / 580 us, 4c8b 848 / 867;
+// 8 x 301 tokens of CQ-2c8b, one / three: 156 / 175.)
+constexpr long kEightTilesFrom = 16384;
 constexpr long kGroupSplitBelow = 4096;
 constexpr long kGroupSplitEightBelow = 1024;
 
@@ -594,7 +648,15 @@ cq_status launch_mfma_format(const EncodeArgs& a, hipStream_t stream)
         } else if (wave_tiles < kGroupSplitBelow || n_tiles < 4) {
             hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 1>), dim3((unsigned)n_tiles, gy, gz), dim3(4 * 64), 0, stream, a);
         } else {
-            hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 4>), dim3((unsigned)((n_tiles + 3) / 4), gy, gz), dim3(4 * 64), 0, stream, a);
+            const int most = C == 8 && wave_tiles >= kEightTilesFrom && n_tiles >= 8 ? 8 : 4;
+            const int wgs = (n_tiles + most - 1) / most;
+            EncodeArgs b = a;
+            b.tiles_per_wg = (n_tiles + wgs - 1) / wgs;
+            const dim3 grid((unsigned)((n_tiles + b.tiles_per_wg - 1) / b.tiles_per_wg), gy, gz);
+            if constexpr (C == 8) {
+                if (most == 8) hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 8>), grid, dim3(4 * 64), 0, stream, b);
+            }
+            if (most == 4) hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 4>), grid, dim3(4 * 64), 0, stream, b);
         }
     } else {
         // 1024 centroids per group: one buffer per wavefront would not fit; four tiles per workgroup

@@ -71,6 +71,7 @@ struct EncodeArgs {
     EncodeTensor tensor[2];
     int n_tensors;
     int batch, t_new, t_offset;
+    int tiles_per_wg;         // set by the launcher of the shapes that give several tiles to a workgroup
     CacheMap map;
     Derived f;
 };

@@ -121,6 +121,13 @@ def test_encode_every_launch_shape_of_the_matrix_core_kernel(c, b, hkv, B, T, t_
                               cache_to_codes(fill, fmt, B, t_cap, tail, t_off + T))
 
 
+@pytest.mark.parametrize("c,b", [(8, 8), (4, 8)])
+@pytest.mark.parametrize("hkv,B,T,t_off", [(32, 8, 4333, 37),     # 17664 items: eight tiles per workgroup of CQ-8c8b, the last one has five
+                                           (64, 64, 290, 1)])     # 20480, 5 tiles per sequence: three and two per workgroup
+def test_encode_shapes_with_many_tiles_per_workgroup(c, b, hkv, B, T, t_off):
+    test_encode_every_launch_shape_of_the_matrix_core_kernel(c, b, hkv, B, T, t_off)
+
+
 @pytest.mark.parametrize("c,b", FORMATS)
 @pytest.mark.parametrize("t_new,t_off", [(3, 130), (200, 37)])
 def test_encode_kv_equals_two_encodes(c, b, t_new, t_off):
