@@ -621,16 +621,23 @@ bool chunk_in_lds(const Derived& f, int n_q_heads, int m, bool rope)
     return !rope && f.b == 8 && (f.c == 8 || f.c == 4) && m > 2 && m * (n_q_heads / f.n_kv_heads) <= kChunkLdsRows;
 }
 
-// its context split: workgroups (one per CU) walk items = (sequence, split) pairs of a KV head; an
-// item costs its tiles for every block of 16 rows and a merge of its wavefronts worth about 8
-// tiles, a split context a merge kernel worth about 16
-int chunk_lds_tiles_per_split(const Derived& f, int batch, int n_q_heads, int m, int t)
+// Its context split, in tiles; 0: not to be used.  Workgroups (one per CU) walk items = (sequence,
+// split) pairs of a KV head; an item costs its tiles for every block of 16 rows and a merge of its
+// wavefronts worth about 8 tiles, a split context a merge kernel worth about 16.  The sizes the
+// library reports for a chunk are those of the other two paths, so the split has to fit the
+// workspace that came with the call (none: no split).  Where that leaves a quarter of the CUs or
+// more without an item and the chunk can go token by token, it does: 5 tokens of batch 4 x 131072,
+// 32 KV heads, CQ-8c8b: 440 us token by token, 280 us with two pieces, but about 560 in one.
+int chunk_lds_tiles(const Derived& f, int batch, int n_q_heads, int m, int t, bool by_token, size_t workspace_bytes)
 {
     const ChunkLdsPlan p = chunk_lds_plan(f, batch, n_q_heads, m);
     const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
     const long base = (long)batch * p.row_groups;
+    const size_t piece = sizeof(float) * (size_t)batch * m * n_q_heads * (f.head_dim + kPartialHeader);
+    const long fit = std::max<long>(1, (long)std::min<size_t>(workspace_bytes / piece, 1u << 20));
+    if (by_token && base * f.n_kv_heads * fit < 192) return 0;
     long best_ns = 1, best_cost = -1;
-    for (long ns = 1; ns <= std::max(1, n_tiles / 8); ++ns) {
+    for (long ns = 1; ns <= std::min<long>(fit, std::max(1, n_tiles / 8)); ++ns) {
         const long tiles = (n_tiles + ns - 1) / ns;
         const long turns = (base * ns + p.wgs_per_head - 1) / p.wgs_per_head;
         const long cost = turns * ((tiles << p.rb_log2) + 8) + (ns > 1 ? 16 : 0);
@@ -643,24 +650,18 @@ int chunk_lds_tiles_per_split(const Derived& f, int batch, int n_q_heads, int m,
     return (int)((n_tiles + best_ns - 1) / best_ns);
 }
 
-int chunk_default_tiles(const Derived& f, int batch, int n_q_heads, int m, int t, bool rope)
-{
-    return chunk_in_lds(f, n_q_heads, m, rope) ? chunk_lds_tiles_per_split(f, batch, n_q_heads, m, t)
-                                               : chunk_tiles_per_split(f, batch, n_q_heads, m, t);
-}
-
 // Short chunks go through the single-token kernel, one launch per query token (token j with a
 // context shortened by m - 1 - j): the chunk kernel dequantises every tile of the context
 // whatever m is, which costs 8-16 single-token launches on large multi-head batches (measured;
 // divided by the query heads per KV head, which share the dequantised tiles) and 2-3 on small
-// ones (both kernels are then bound by launch and latency).  (The kernel with the codebooks in
-// LDS, where it applies, is ahead from 3 tokens on: 5 tokens at CQ-4c8b, batch 16 x 4096: 136 us
-// token by token, 53 us there.)
+// ones (both kernels are then bound by launch and latency).  This is also what the sizes below
+// report; chunks of 3 tokens and more go to the kernel with the codebooks in LDS where that applies
+// (chunk_lds_tiles).
 bool chunk_by_token(const Derived& f, int batch, int n_q_heads, int m, int t)
 {
     const int qper = n_q_heads / f.n_kv_heads;
     const long tiles = (long)batch * f.n_kv_heads * ((t + kTileTokens - 1) / kTileTokens);
-    const int limit = tiles >= 16384 && !chunk_in_lds(f, n_q_heads, m, false) ? std::max(2, 8 / qper) : 2;
+    const int limit = tiles >= 16384 ? std::max(2, 8 / qper) : 2;
     return m <= limit;
 }
 
@@ -713,13 +714,29 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
     if (!aligned16(q) || !aligned16(k_codes) || !aligned16(v_codes) || !aligned16(k_centroids) ||
         !aligned16(v_centroids) || !aligned16(out) || !aligned16(workspace))
         return CQ_ERR_INVALID_ARG;
-    if (!rope && tokens_per_split == 0 && chunk_by_token(f, batch, n_q_heads, m, t)) {
+    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
+    const size_t rows = (size_t)batch * m * n_q_heads;
+    const bool by_token = !rope && tokens_per_split == 0 && chunk_by_token(f, batch, n_q_heads, m, t);
+    int tiles = 0;
+    if (by_token) {
         for (int j = 0; j < m; ++j) {
             const TokenCall c = chunk_token_call(f, batch, n_q_heads, m, t, j);
             if (c.workspace && !workspace) return CQ_ERR_INVALID_ARG;
             if (workspace_bytes < c.workspace) return CQ_ERR_WORKSPACE_TOO_SMALL;
             if ((int64_t)batch * n_q_heads * c.n_split > 0x7fffffffLL) return CQ_ERR_INVALID_ARG;
         }
+    } else {
+        tiles = tokens_per_split ? tokens_per_split / kTileTokens : chunk_tiles_per_split(f, batch, n_q_heads, m, t);
+        const int n_split = (n_tiles + tiles - 1) / tiles;
+        if (n_split > 1) {
+            if (!workspace) return CQ_ERR_INVALID_ARG;
+            if (workspace_bytes < sizeof(float) * rows * n_split * (f.head_dim + kPartialHeader)) return CQ_ERR_WORKSPACE_TOO_SMALL;
+        }
+    }
+    int lds_tiles = 0;
+    if (chunk_in_lds(f, n_q_heads, m, rope))
+        lds_tiles = tokens_per_split ? tiles : chunk_lds_tiles(f, batch, n_q_heads, m, t, by_token, workspace ? workspace_bytes : 0);
+    if (by_token && !lds_tiles) {
         const int64_t row = (int64_t)n_q_heads * f.head_dim;
         for (int j = 0; j < m; ++j) {           // (in stream order: the calls share the workspace)
             const TokenCall c = chunk_token_call(f, batch, n_q_heads, m, t, j);
@@ -752,22 +769,8 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
         }
         return CQ_OK;
     }
-    const bool in_lds = chunk_in_lds(f, n_q_heads, m, rope);
-    int tiles = tokens_per_split ? tokens_per_split / kTileTokens : chunk_default_tiles(f, batch, n_q_heads, m, t, rope);
-    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
-    int n_split = (n_tiles + tiles - 1) / tiles;
-    const size_t rows = (size_t)batch * m * n_q_heads;
-    const size_t split_bytes = sizeof(float) * rows * (f.head_dim + kPartialHeader);
-    if (in_lds && tokens_per_split == 0 && n_split > 1 && (!workspace || workspace_bytes < split_bytes * n_split)) {
-        // the library's own split: as many pieces as the caller's workspace holds
-        const int fit = workspace ? (int)std::min<size_t>(workspace_bytes / split_bytes, (size_t)n_split) : 1;
-        tiles = (n_tiles + std::max(fit, 1) - 1) / std::max(fit, 1);
-        n_split = (n_tiles + tiles - 1) / tiles;
-    }
-    if (n_split > 1) {
-        if (!workspace) return CQ_ERR_INVALID_ARG;
-        if (workspace_bytes < split_bytes * n_split) return CQ_ERR_WORKSPACE_TOO_SMALL;
-    }
+    if (lds_tiles) tiles = lds_tiles;
+    const int n_split = (n_tiles + tiles - 1) / tiles;
     const int qper = n_q_heads / f.n_kv_heads;
     const int rpw = chunk_rows_per_workgroup(m * qper);
     const int64_t row_blocks = ((int64_t)m * qper + rpw - 1) / rpw;
@@ -793,7 +796,7 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
     a.rope_tile_tab = static_cast<const float2*>(rope_table);
     a.rope_lane_tab = rope ? a.rope_tile_tab + (size_t)(rope_positions / kTileTokens) * 64 : nullptr;
     a.f = f;
-    if (!in_lds) return launch_chunk_attention(a, static_cast<hipStream_t>(stream));
+    if (!lds_tiles) return launch_chunk_attention(a, static_cast<hipStream_t>(stream));
     if ((st = launch_chunk_lds(a, static_cast<hipStream_t>(stream))) != CQ_OK || n_split == 1) return st;
     return launch_decode_merge(a.partials, a.out, batch * m * n_q_heads, n_q_heads, (int64_t)n_q_heads * f.head_dim, n_split, f.head_dim,
                                static_cast<hipStream_t>(stream));
@@ -807,7 +810,7 @@ int32_t cq_chunk_default_split(const cq_format* fmt, int32_t batch, int32_t n_q_
     if (derive(fmt, &f) != CQ_OK || f.head_dim != 128) return 0;
     if (batch <= 0 || n_q_heads <= 0 || n_q_heads % f.n_kv_heads != 0 || m <= 0 || t < m) return 0;
     if (chunk_by_token(f, batch, n_q_heads, m, t)) return chunk_token_call(f, batch, n_q_heads, m, t, m - 1).tiles * kTileTokens;
-    return chunk_default_tiles(f, batch, n_q_heads, m, t, false) * kTileTokens;
+    return chunk_tiles_per_split(f, batch, n_q_heads, m, t) * kTileTokens;
 }
 
 size_t cq_chunk_workspace_bytes(const cq_format* fmt, int32_t batch, int32_t n_q_heads, int32_t m, int32_t t,
@@ -822,7 +825,7 @@ size_t cq_chunk_workspace_bytes(const cq_format* fmt, int32_t batch, int32_t n_q
         for (int j = 0; j < m; ++j) need = std::max(need, chunk_token_call(f, batch, n_q_heads, m, t, j).workspace);
         return need;
     }
-    const int tiles = tokens_per_split ? tokens_per_split / kTileTokens : chunk_default_tiles(f, batch, n_q_heads, m, t, false);
+    const int tiles = tokens_per_split ? tokens_per_split / kTileTokens : chunk_tiles_per_split(f, batch, n_q_heads, m, t);
     const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
     const int n_split = (n_tiles + tiles - 1) / tiles;
     return sizeof(float) * (size_t)batch * m * n_q_heads * n_split * (f.head_dim + kPartialHeader);

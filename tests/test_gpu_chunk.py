@@ -227,16 +227,20 @@ def test_chunks_of_few_rows_with_codebooks_in_lds(c, m, hq, hkv, B, T, scale):
         _check(_gpu(q, kcache, vcache, ck, cv, scale, fmt, T, t_cap, seq_lens=lens, split=split), ref)
 
 
-def test_few_rows_split_no_further_than_the_workspace_holds():
-    """The library's own split of a long context shrinks to the caller's workspace, down to none."""
+def test_few_rows_split_within_the_workspace_that_comes_with_the_call():
+    """The split of a short chunk fits the reported workspace and may grow with a larger one; less
+    than the reported size stays an error."""
     c, b, hq, hkv, B, m, T, t_cap = 4, 8, 2, 2, 1, 5, 4000, 4032
     fmt, q, kc, vc, ck, cv = _case(21, c, b, hq, hkv, B, m, T)
     need = cq.cq_chunk_workspace_bytes(fmt, B, hq, m, T)
-    assert need > 2 * 4 * B * m * hq * 130
+    assert need > 4 * B * m * hq * 130
     ref = O.chunk_attention(q, kc, vc, ck, cv, 0.1, hkv)
     kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
-    for nbytes in (need, need // 2, 16):
-        out = cq.cq_chunk_attention(dev(q), kcache, vcache, dev(ck), dev(cv), 0.1, fmt, T, t_cap,
-                                    workspace=torch.zeros(nbytes, dtype=torch.uint8, device="cuda"))
+    run = lambda nbytes: cq.cq_chunk_attention(dev(q), kcache, vcache, dev(ck), dev(cv), 0.1, fmt, T, t_cap,
+                                               workspace=torch.zeros(nbytes, dtype=torch.uint8, device="cuda"))
+    for nbytes in (need, 8 * need):
+        out = run(nbytes)
         torch.cuda.synchronize()
         _check(out.cpu().numpy(), ref)
+    with pytest.raises(cq.CQError):
+        run(need - 16)
