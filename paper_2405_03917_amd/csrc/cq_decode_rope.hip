@@ -21,7 +21,7 @@
 // wavefronts per SIMD at most).  Phase V, the epilogue and the split-context merge are those of
 // the position-independent kernel.  Both trigonometric tables come from cq_rope_table (computed
 // in fp64).
-#include "cq_decode_common.hpp"
+#include "cq_lds_gather.hpp"
 
 namespace cq {
 namespace {
@@ -639,6 +639,227 @@ __device__ __forceinline__ float mixv_fma(bool HI, unsigned w, float s, float c)
     return d;
 }
 
+// Phase V of the grouped-query kernel for formats whose value codebook fits LDS next to the scores
+// (16 or 32 groups per head), on the matrix cores: the codebook takes the key centroids' place,
+// and for every 64-token tile
+//     O^T[channel][column] += V^T[channel][token] P[token][column]     (v_mfma_f32_16x16x32_f16)
+// with the values gathered and transposed by one LDS instruction and the probabilities of the four
+// heads as three fp16 numbers each (33 bits), one to a column: columns 0..3 the high parts of heads
+// 0..3, 4..7 the middle, 8..11 the low ones.  One pass serves all four heads; it replaces a scan
+// for the maximum, one for the sum, a clear of the bins, a pass over the value tiles for every two
+// heads and a bins x centroids epilogue per head.  A tile costs a wavefront 32 gathers, 16 matrix
+// products and about 150 vector instructions.  Measured: the fused step of CQ-8c8b, 32 / 8 heads,
+// batch 32 x 16384: 196 -> 164 us (key phase about 95 of them).
+// LDS: the codebook, the kernel's scratch (probabilities of wavefronts 0..4), the scores, the new
+// token's keys, the probabilities of wavefronts 5..7.
+constexpr unsigned kProbBytes = 12 * 32 * 2;        // one wavefront's half tile: 12 columns x 32 tokens
+constexpr int kProbInScratch = (int)(kScrBytes / kProbBytes);
+static_assert(kProbInScratch == 5, "places of the probabilities");
+constexpr unsigned kGqaKeyBytes(int gh) { return (unsigned)(kKeyFloats(gh) * 4 + 15) & ~15u; }
+constexpr unsigned kGqaOutBytes = kRopeThreads / 64 * 4 * 128 * 4;     // every wavefront's output rows, where the scores were
+template <int GH, int C, int NT>
+__device__ __forceinline__ void gqa_values(const DecodeArgs& a, float* smem, const float (&top)[4], const TileWalk<GH, 8>& vwalk, int n,
+                                           int hkv, int hq0, int heads, int split, int split_tokens, int tile0, int my_tiles, bool has_new,
+                                           bool writer, bool meets_new, int tile_new, int u_new)
+{
+    constexpr int QH = 4, NW = NT / 64, D = GH * C, K = 256, PL = GH / 16;
+    constexpr unsigned SC_BASE = kTabBytes + kScrBytes;
+    typedef __attribute__((address_space(3))) u32x4 lds_q;
+    typedef __attribute__((address_space(3))) _Float16 lds_h;
+    typedef __attribute__((address_space(3))) float4_t lds_f4;
+    float* scr = smem + kTabBytes / 4;
+    const float* sc = smem + SC_BASE / 4;
+    const unsigned keys_at = SC_BASE + (unsigned)(QH * split_tokens) * 4;
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem + keys_at / 4);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, blk = lane >> 4;
+
+    // ---- the value codebook on its way to LDS; the heads' maxima over the split
+    u32x4 book[8];
+    {
+        const u32x4* src = reinterpret_cast<const u32x4*>(a.v_centroids + (size_t)hkv * GH * K * C);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) book[i] = src[i * NT + tid];
+    }
+    // this lane's tokens of a tile: 32 t + 8 blk + 4 r + col / 4 for t, r = 0, 1; its channels: 4 (col % 4) ..
+    // of 16 (C = 8: half of group (col % 4) / 2, then every second group; C = 4: group col % 4, then every fourth)
+    const int g0 = C == 8 ? (col & 3) >> 1 : (col & 3);
+    const int u0 = 8 * blk + (col >> 2);
+    const CodePick<GH, C == 8 ? 2 : 4> pick0(g0, u0), pick1(g0, u0 + 4);
+    const unsigned vbase = C == 8 ? (unsigned)g0 * 4096 + (unsigned)(col & 1) * 8 : (unsigned)g0 * 2048;
+    u32x4 rec[2][2][PL];
+    auto request = [&](int k) {
+        const uint8_t* p = vwalk.at(k < my_tiles ? k : my_tiles - 1);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl)
+                    rec[t][r][pl] = *reinterpret_cast<const u32x4*>(p + pl * 1024 + (32 * t + 4 * r + u0) * 16);
+    };
+    if (my_tiles > 0) request(0);
+#pragma unroll
+    for (int h = 0; h < QH; ++h) {
+        const float w = wave_max(top[h]);
+        if (lane == 0) scr[h * NW + wave] = w;
+    }
+    lds_barrier();                                  // all key centroid reads are done, scores and maxima written
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *(lds_q*)((unsigned)(i * NT + tid) * 16) = book[i];
+    float m[QH], l[QH];
+#pragma unroll
+    for (int h = 0; h < QH; ++h) {
+        m[h] = scr[h * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m[h] = fmaxf(m[h], scr[h * NW + w]);
+        l[h] = 0.f;
+    }
+    lds_barrier();                                  // the codebook is in place, the maxima are read
+    NewTokenCodes<GH, 8> new_codes;
+    if (has_new) {
+        // the new value row against the codebook: ascending index per thread, 64-bit (distance, index) minimum
+        constexpr int TPG = NT / GH;
+        const int g = tid / TPG;
+        float xv[C];
+        load_row_slice<C>(a.xv_new + (size_t)n * a.x_new_stride + (size_t)hkv * GH * C + g * C, xv);
+        Nearest near;
+        for (int j = tid % TPG; j < K; j += TPG) {
+            const CenVec<C> cen = lds_centroid<C>((unsigned)(g * K + j) * (C * 2));
+            near.offer(centroid_distance<C>(xv, cen.w), j);
+        }
+        lds_min_u64(&keys[GH + g], near.key());
+        lds_barrier();
+        if (writer)
+            store_new_codes<GH, 8>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * Fmt<GH, 8>::TILE_BYTES, keys + GH,
+                                   u_new, tid);
+        if (meets_new) new_codes.build(keys + GH, u_new, lane);
+    }
+
+    // ---- the walk: one pass for the four heads
+    const unsigned probs = wave < kProbInScratch ? kTabBytes + (unsigned)wave * kProbBytes
+                                                 : keys_at + kGqaKeyBytes(GH) + (unsigned)(wave - kProbInScratch) * kProbBytes;
+    const unsigned prob_in = probs + (unsigned)(lane & 31) * 2;                                 // token of the half tile
+    const unsigned prob_out = probs + (unsigned)(col < 12 ? col : 0) * 64 + (unsigned)blk * 16;    // column, eight tokens
+    float4_t o[8];
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int k = 0; k < my_tiles; ++k) {
+        const int lt = wave + k * NW;
+        if (meets_new && tile0 + lt == tile_new) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const bool mine = 32 * t + 4 * r + u0 == u_new;
+#pragma unroll
+                    for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) rec[t][r][pl][i] = mine ? new_codes.lo[4 * pl + i] : rec[t][r][pl][i];
+                }
+        }
+        unsigned z[2][2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            pick0(rec[t][0], 0, z[t][0]);
+            pick1(rec[t][1], 0, z[t][1]);
+        }
+        request(k + 1);
+        half8_t av[2][8];
+        auto gather = [&](int t) {
+            unsigned at[2][8];
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) at[r][cb] = entry<C>(z[t][r][cb >> 2], cb & 3, vbase);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) {
+                const half4_t v0 = lds_transposed(at[0][cb] + (unsigned)cb * 8192), v1 = lds_transposed(at[1][cb] + (unsigned)cb * 8192);
+                av[t][cb] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        float s[QH];
+#pragma unroll
+        for (int h = 0; h < QH; ++h) s[h] = sc[h * split_tokens + lt * kTileTokens + lane];
+        gather(0);
+        // lane = token: p 2^12 of each head as the sum of three fp16 numbers
+        _Float16 part[3][QH];
+#pragma unroll
+        for (int h = 0; h < QH; ++h) {
+            const float p = __builtin_amdgcn_exp2f(s[h] - (m[h] - 12.f));
+            l[h] += p;
+            part[0][h] = (_Float16)p;
+            const float r1 = p - (float)part[0][h];
+            part[1][h] = (_Float16)r1;
+            part[2][h] = (_Float16)(r1 - (float)part[1][h]);
+        }
+        half8_t pb[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            // (a wavefront's LDS operations keep their order: the half tiles share the room)
+            if ((lane >> 5) == t) {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+#pragma unroll
+                    for (int h = 0; h < QH; ++h) *(lds_h*)(prob_in + (unsigned)(e * QH + h) * 64) = part[e][h];
+            }
+            // (the lanes read what other lanes wrote: without these statements the compiler takes a lane's
+            // second read for a repetition of its first)
+            asm volatile("" ::: "memory");
+            const half8_t v = *(__attribute__((address_space(3))) half8_t*)(prob_out);
+            pb[t] = col < 12 ? v : half8_t(0.f16);
+            asm volatile("" ::: "memory");
+        }
+        gather(1);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], pb[t], o[cb], 0, 0, 0);
+    }
+
+    // ---- the parts of a head are columns h, h + 4, h + 8; then the wavefronts, all relative to the same maximum
+    lds_barrier();                                  // scores and probabilities are read
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) {
+        float4_t v = o[cb];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));    // row_ror:8
+            v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x124, 0xf, 0xf, false));    // row_ror:4
+        }
+        if (col < QH) *(lds_f4*)(SC_BASE + (unsigned)((wave * QH + col) * D + 16 * cb + 4 * blk) * 4) = v;
+    }
+#pragma unroll
+    for (int h = 0; h < QH; ++h) {
+        const float w = wave_sum(l[h]);
+        if (lane == 0) scr[h * NW + wave] = w;
+    }
+    lds_barrier();
+    static_assert(NT == QH * D, "one output per thread");
+    const int h = tid / D, ch = tid % D;
+    if (h >= heads) return;
+    float sum = 0.f, ll = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        sum += smem[SC_BASE / 4 + (w * QH + h) * D + ch];
+        ll += scr[h * NW + w];
+    }
+    if (a.n_split == 1) {
+        a.out[(size_t)n * a.out_batch_stride + (size_t)(hq0 + h) * D + ch] = __builtin_bit_cast(uint16_t, (_Float16)(sum / ll));
+    } else {
+        float* dst = a.partials + ((size_t)(n * a.n_q_heads + hq0 + h) * a.n_split + split) * (D + kPartialHeader);
+        if (ch == 0) {
+            dst[0] = h == 0 ? m[0] : (h == 1 ? m[1] : (h == 2 ? m[2] : m[3]));
+            dst[1] = ll * 0x1p-12f;
+        }
+        dst[kPartialHeader + ch] = sum * 0x1p-12f;
+    }
+}
+
 // Grouped queries: the (up to) four query heads of a KV head that one workgroup serves share
 // every key rotation.  The roles of the two halves of the angle are swapped against the kernel
 // above: the KEY is rotated by the lane's part (cos / sin(u th_i): 128 registers per lane, from
@@ -653,8 +874,9 @@ __device__ __forceinline__ float mixv_fma(bool HI, unsigned w, float s, float c)
 // block of four lanes that holds pair i to all 16 blocks, the B operand (1 x 4 tokens per
 // block) the rotated key itself; lane = token also in the result, heads in its four registers.
 // Per pair: 4 vector instructions and 2 matrix instructions for four heads, against 6 vector
-// instructions per head.  Phase V and the epilogue run once per head over the split's scores
-// in LDS (the value tiles of the later heads come from L2).
+// instructions per head.  Phase V takes the split's scores of all four heads from LDS in one pass
+// (gqa_values); CQ-2c8b, whose 4-byte centroids the transposing read cannot gather, bins one head
+// after the other (the value tiles of the later heads come from L2).
 template <int GH, int C, int NT, bool STEP>
 __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const float2* tile_tab, const float2* lane_tab)
 {
@@ -816,6 +1038,7 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
     unrot.dwords = ((unsigned)(GH - lane) & (unsigned)(GH - 1)) >> 2;
     constexpr int kBatch = 8;                       // channel pairs per batch of centroids
     constexpr int GPB = kBatch / C;                 // groups (of each half of the head) per batch
+    float top[QH] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};      // this lane's largest score of each head
     stk.run(kwalk, my_tiles, lane, [&](const Tile<GH, B>& w_in, int k) {
         const int lt = wave + k * NW;
         Tile<GH, B> w = w_in;
@@ -883,8 +1106,17 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
         const int tok = (tile0 + lt) * kTileTokens + lane;
         const bool live = tok < t_n;
 #pragma unroll
-        for (int h = 0; h < QH; ++h) sc[h * split_tokens + lt * kTileTokens + lane] = live ? (acc0[h] + acc1[h]) + (acc2[h] + acc3[h]) : -INFINITY;
+        for (int h = 0; h < QH; ++h) {
+            const float s = live ? (acc0[h] + acc1[h]) + (acc2[h] + acc3[h]) : -INFINITY;
+            sc[h * split_tokens + lt * kTileTokens + lane] = s;
+            top[h] = fmaxf(top[h], s);
+        }
     }, [] {});
+    if constexpr (GH <= 32) {
+        gqa_values<GH, C, NT>(a, smem, top, vwalk, n, hkv, hq0, heads, split, split_tokens, tile0, my_tiles, has_new, writer, meets_new,
+                              tile_new, u_new);
+        return;
+    }
     lds_barrier();                                  // all centroid reads done, all scores written
 
     // ---- 3. per head: softmax reference, phase V, epilogue ----------------------------------
@@ -925,11 +1157,8 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
         if (writer)
             store_new_codes<GH, B>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * F::TILE_BYTES, keys + GH, u_new, tid);
     }
-    // Two heads per pass where the bins of two fit side by side (16 or 32 groups per head: words
-    // 0..31 of a 64-word row are the columns of one head's bins, words 32..63 the other's), so
-    // that the value tiles are streamed twice, not four times.  The value centroids of the
-    // epilogue are the same for every head: they stay in registers where they fit.
-    constexpr int HP = GH <= 32 ? 2 : 1;
+    // One head per pass: 64 groups fill the bins' rows.  The value centroids of the epilogue are the same
+    // for every head: they stay in registers where they fit.
     constexpr bool KEEP = IPT * NCH <= 8 && KB == IPT;
     Cent16 rawv[KEEP ? NCH : 1][KB];
     if constexpr (KEEP) {
@@ -940,157 +1169,118 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
             for (int k = 0; k < IPT; ++k) rawv[ch][k] = load_cent16(cv + (size_t)piece(k) * 8);
         }
     }
-    for (int h0 = 0; h0 < heads; h0 += HP) {
-        const int nh = min(HP, heads - h0);                 // heads of this pass
-        // scr: [0..16) sums, [16..32) maxima, [32..48) estimates of l; 8 wavefronts x 2 heads each
-        float m[HP], fx_scale[HP], fx_inv[HP];
-#pragma unroll
-        for (int e = 0; e < HP; ++e) {
-            const float* sch = sc + (h0 + (e < nh ? e : 0)) * split_tokens;
-            float lane_max = -INFINITY;
-            for (int i = tid; i < n_tok; i += NT) lane_max = fmaxf(lane_max, sch[i]);
-            lane_max = wave_max(lane_max);
-            if (lane == 0) scr[16 + e * NW + wave] = lane_max;
-        }
+    for (int h = 0; h < heads; ++h) {
+        // scr: [0..8) sums, [8..16) maxima, [16..24) estimates of l of the 8 wavefronts
+        const float* sch = sc + h * split_tokens;
+        float lane_max = -INFINITY;
+        for (int i = tid; i < n_tok; i += NT) lane_max = fmaxf(lane_max, sch[i]);
+        lane_max = wave_max(lane_max);
+        if (lane == 0) scr[NW + wave] = lane_max;
         st.begin(vwalk, my_tiles, lane);
         lds_barrier();
+        float m = scr[NW];
 #pragma unroll
-        for (int e = 0; e < HP; ++e) {
-            const float* sch = sc + (h0 + (e < nh ? e : 0)) * split_tokens;
-            float mm = scr[16 + e * NW];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) mm = fmaxf(mm, scr[16 + e * NW + w]);
-            m[e] = mm;
-            float l_est = 0.f;
-            for (int i = tid; i < n_tok; i += NT) l_est += __builtin_amdgcn_exp2f(sch[i] - mm);
-            l_est = wave_sum(l_est);
-            if (lane == 0) scr[32 + e * NW + wave] = l_est;
-        }
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, scr[NW + w]);
+        float l_est = 0.f;
+        for (int i = tid; i < n_tok; i += NT) l_est += __builtin_amdgcn_exp2f(sch[i] - m);
+        l_est = wave_sum(l_est);
+        if (lane == 0) scr[2 * NW + wave] = l_est;
         {
             float4* t4 = reinterpret_cast<float4*>(tab);
 #pragma unroll 4
             for (int i = tid; i < F::TAB_FLOATS / 4; i += NT) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
         lds_barrier();
+        l_est = 0.f;
 #pragma unroll
-        for (int e = 0; e < HP; ++e) {
-            float l_est = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) l_est += scr[32 + e * NW + w];
-            const int fx = fixed_point_exponent(l_est);
-            fx_scale[e] = ldexpf(1.f, fx);
-            fx_inv[e] = ldexpf(1.f, -fx);
-        }
+        for (int w = 0; w < NW; ++w) l_est += scr[2 * NW + w];
+        const int fx = fixed_point_exponent(l_est);
+        const float fx_scale = ldexpf(1.f, fx), fx_inv = ldexpf(1.f, -fx);
 
-        unsigned lane_sum[HP];
-#pragma unroll
-        for (int e = 0; e < HP; ++e) lane_sum[e] = 0;
-        const float* sc0 = sc + h0 * split_tokens;
-        const float* sc1 = sc + (h0 + (nh > 1 ? 1 : 0)) * split_tokens;
+        unsigned lane_sum = 0;
         st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
             const int lt = wave + k * NW;
-            unsigned pf[HP];
-#pragma unroll
-            for (int e = 0; e < HP; ++e) {
-                const float p = __builtin_amdgcn_exp2f((e ? sc1 : sc0)[lt * kTileTokens + lane] - m[e]);
-                pf[e] = (unsigned)__builtin_fmaf(p, fx_scale[e], 0.5f);
-                lane_sum[e] += pf[e];
-            }
+            const float p = __builtin_amdgcn_exp2f(sch[lt * kTileTokens + lane] - m);
+            unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
+            lane_sum += pf;
             if (has_new && tile0 + lt == tile_new && lane == u_new) {
-#pragma unroll
-                for (int e = 0; e < HP; ++e) {
-                    pf_new[e] = pf[e];
-                    pf[e] = 0;
-                }
+                *pf_new = pf;
+                pf = 0;
             }
 #pragma unroll
-            for (int s = 0; s < GH; ++s) {
-                const unsigned addr = slot_addr<GH, B, false>(w, col, s);
-                lds_add(addr, pf[0]);
-                if constexpr (HP == 2) lds_add(addr + 128u, pf[1]);
-            }
+            for (int s = 0; s < GH; ++s) lds_add(slot_addr<GH, B, false>(w, col, s), pf);
         }, [] {});
-#pragma unroll
-        for (int e = 0; e < HP; ++e) lane_sum[e] = wave_sum_u32(lane_sum[e]);
+        lane_sum = wave_sum_u32(lane_sum);
         lds_barrier();
-        if (lane == 0) {
-#pragma unroll
-            for (int e = 0; e < HP; ++e) scr[e * NW + wave] = __uint_as_float(lane_sum[e]);
-        }
+        if (lane == 0) scr[wave] = __uint_as_float(lane_sum);
         if (has_new) {
             if (tid < GH) {
                 const unsigned code = (unsigned)(keys[GH + tid] & 0xffffffffu);
-#pragma unroll
-                for (int e = 0; e < HP; ++e) lds_add((code * RW + tid * R) * 4u + 128u * e, pf_new[e]);
+                lds_add((code * RW + tid * R) * 4u, *pf_new);
             }
             lds_barrier();
         }
 
-        for (int e = 0; e < nh; ++e) {
-            float acc[NCH][C];
+        float acc[NCH][C];
 #pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
+        for (int ch = 0; ch < NCH; ++ch) {
 #pragma unroll
-                for (int i = 0; i < C; ++i) acc[ch][i] = 0.f;
-                const uint16_t* cv = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
+            for (int i = 0; i < C; ++i) acc[ch][i] = 0.f;
+            const uint16_t* cv = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
 #pragma unroll
-                for (int k0 = 0; k0 < IPT; k0 += KB) {
-                    if constexpr (!KEEP) {
+            for (int k0 = 0; k0 < IPT; k0 += KB) {
+                if constexpr (!KEEP) {
 #pragma unroll
-                        for (int k = 0; k < KB; ++k) rawv[0][k] = load_cent16(cv + (size_t)piece(k0 + k) * 8);
-                    }
-                    const Cent16 (&raw)[KB] = rawv[KEEP ? ch : 0];
+                    for (int k = 0; k < KB; ++k) rawv[0][k] = load_cent16(cv + (size_t)piece(k0 + k) * 8);
+                }
+                const Cent16 (&raw)[KB] = rawv[KEEP ? ch : 0];
 #pragma unroll
-                    for (int k = 0; k < KB; ++k) {
-                        const int j0 = piece(k0 + k) * JPL;
+                for (int k = 0; k < KB; ++k) {
+                    const int j0 = piece(k0 + k) * JPL;
 #pragma unroll
-                        for (int jj = 0; jj < JPL; ++jj) {
-                            const float* src = tab + (j0 + jj) * RW + (ch * 16 + gl16) * R + 32 * e;
-                            unsigned cnt;
-                            if constexpr (R == 2) { const uint2 x = *reinterpret_cast<const uint2*>(src); cnt = x.x + x.y; }
-                            else cnt = *reinterpret_cast<const unsigned*>(src);
-                            const float bin = (float)cnt * (e ? fx_inv[HP - 1] : fx_inv[0]);
+                    for (int jj = 0; jj < JPL; ++jj) {
+                        const float* src = tab + (j0 + jj) * RW + (ch * 16 + gl16) * R;
+                        const float bin = (float)*reinterpret_cast<const unsigned*>(src) * fx_inv;
 #pragma unroll
-                            for (int i = 0; i < C / 2; ++i) {
-                                const half2_t hv = __builtin_bit_cast(half2_t, raw[k].w[jj * (C / 2) + i]);
-                                acc[ch][2 * i] = __builtin_fmaf(bin, (float)hv.x, acc[ch][2 * i]);
-                                acc[ch][2 * i + 1] = __builtin_fmaf(bin, (float)hv.y, acc[ch][2 * i + 1]);
-                            }
+                        for (int i = 0; i < C / 2; ++i) {
+                            const half2_t hv = __builtin_bit_cast(half2_t, raw[k].w[jj * (C / 2) + i]);
+                            acc[ch][2 * i] = __builtin_fmaf(bin, (float)hv.x, acc[ch][2 * i]);
+                            acc[ch][2 * i + 1] = __builtin_fmaf(bin, (float)hv.y, acc[ch][2 * i + 1]);
                         }
                     }
                 }
-#pragma unroll
-                for (int i = 0; i < C; ++i) {
-                    acc[ch][i] += __shfl_xor(acc[ch][i], 1);
-                    acc[ch][i] += __shfl_xor(acc[ch][i], 2);
-                }
             }
-            if ((lane & 3) == 0) {
 #pragma unroll
-                for (int ch = 0; ch < NCH; ++ch)
-#pragma unroll
-                    for (int i = 0; i < C; ++i) scr[64 + wave * D + (ch * 16 + gl16) * C + i] = acc[ch][i];
+            for (int i = 0; i < C; ++i) {
+                acc[ch][i] += __shfl_xor(acc[ch][i], 1);
+                acc[ch][i] += __shfl_xor(acc[ch][i], 2);
             }
-            lds_barrier();
-            unsigned l_fix = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) l_fix += __float_as_uint(scr[e * NW + w]);
-            const float l = (float)l_fix * (e ? fx_inv[HP - 1] : fx_inv[0]);
-            const int hq = hq0 + h0 + e;
-            float* part = a.partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
-            if (tid == 0 && !direct) {
-                part[0] = e ? m[HP - 1] : m[0];
-                part[1] = l;
-            }
-            for (int chn = tid; chn < D; chn += NT) {
-                float o = 0.f;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) o += scr[64 + w * D + chn];
-                if (direct) a.out[(size_t)n * a.out_batch_stride + (size_t)hq * D + chn] = __builtin_bit_cast(uint16_t, (_Float16)(o / l));
-                else part[kPartialHeader + chn] = o;
-            }
-            lds_barrier();                          // the next head reuses the scratch, the next pass the bins
         }
+        if ((lane & 3) == 0) {
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                for (int i = 0; i < C; ++i) scr[64 + wave * D + (ch * 16 + gl16) * C + i] = acc[ch][i];
+        }
+        lds_barrier();
+        unsigned l_fix = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l_fix += __float_as_uint(scr[w]);
+        const float l = (float)l_fix * fx_inv;
+        const int hq = hq0 + h;
+        float* part = a.partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
+        if (tid == 0 && !direct) {
+            part[0] = m;
+            part[1] = l;
+        }
+        for (int chn = tid; chn < D; chn += NT) {
+            float o = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) o += scr[64 + w * D + chn];
+            if (direct) a.out[(size_t)n * a.out_batch_stride + (size_t)hq * D + chn] = __builtin_bit_cast(uint16_t, (_Float16)(o / l));
+            else part[kPartialHeader + chn] = o;
+        }
+        lds_barrier();                          // the next head reuses the scratch, the next pass the bins
     }
 }
 
@@ -1115,7 +1305,13 @@ cq_status launch_rope_gqa_variant(const DecodeArgs& a, const float2* tile_tab, c
     auto kernel = decode_rope_gqa_kernel<GH, C, NT, STEP>;
     static LdsKernelSetup setup;
     if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
-    const size_t smem = kTabBytes + kScrBytes + (size_t)4 * a.tiles_per_split * kTileTokens * 4 + (STEP ? kKeyFloats(GH) * 4 : 0);
+    size_t smem = kTabBytes + kScrBytes + (size_t)4 * a.tiles_per_split * kTileTokens * 4;
+    if (GH <= 32) {
+        smem += kGqaKeyBytes(GH) + (NT / 64 - kProbInScratch) * kProbBytes;
+        smem = smem > kTabBytes + kScrBytes + kGqaOutBytes ? smem : kTabBytes + kScrBytes + kGqaOutBytes;
+    } else if (STEP) {
+        smem += kKeyFloats(GH) * 4;
+    }
     if (smem > 160 * 1024) return CQ_ERR_INVALID_ARG;
     const int qper = a.n_q_heads / a.f.n_kv_heads;
     const unsigned grid = (unsigned)(a.batch * a.f.n_kv_heads * ((qper + 3) / 4) * a.n_split);
@@ -1133,6 +1329,8 @@ int decode_rope_max_tiles_per_split() { return 256; }
 constexpr int kGqaTiles = 88;
 int decode_rope_shared_max_tiles_per_split() { return kGqaTiles; }
 static_assert(kTabBytes + kScrBytes + 4 * kGqaTiles * kTileTokens * 4 + kKeyFloats(64) * 4 <= 160 * 1024, "LDS of the grouped-query kernel");
+static_assert(kTabBytes + kScrBytes + 4 * kGqaTiles * kTileTokens * 4 + kGqaKeyBytes(32) + (kRopeThreads / 64 - kProbInScratch) * kProbBytes <= 160 * 1024,
+              "LDS of the grouped-query kernel");
 
 size_t rope_table_floats(int t_cap) { return ((size_t)(t_cap / kTileTokens) * kPairs + (size_t)kPairs * 64) * 2; }
 

@@ -213,6 +213,15 @@ def test_rope_step_equals_encode_then_rope_attention(c, b, hq, hkv, T, split):
     assert torch.equal(got.view(torch.int16), want.view(torch.int16)), "outputs differ"
 
 
+@pytest.mark.parametrize("c", [8, 4, 2])
+@pytest.mark.parametrize("hq,hkv,T", [(8, 2, 1), (8, 2, 4), (6, 2, 5), (4, 2, 33), (10, 2, 64), (8, 2, 100), (8, 2, 517)])
+def test_rope_step_of_grouped_queries_wherever_the_new_token_lies(c, hq, hkv, T):
+    # the value phase of four heads reads a tile's codes eight lanes to a token, four tokens a lane:
+    # the new token in each of those places, two to five query heads per KV head
+    for split in (0, 64):
+        test_rope_step_equals_encode_then_rope_attention(c, 8, hq, hkv, T, split)
+
+
 @pytest.mark.parametrize("c,b", [(4, 8), (8, 10)])
 def test_rope_step_ragged_lengths_and_oracle(c, b):
     # sequences of different lengths: each new token lands at its own position; also against the
