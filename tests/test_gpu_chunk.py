@@ -227,6 +227,27 @@ def test_chunks_of_few_rows_with_codebooks_in_lds(c, m, hq, hkv, B, T, scale):
         _check(_gpu(q, kcache, vcache, ck, cv, scale, fmt, T, t_cap, seq_lens=lens, split=split), ref)
 
 
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("c,b", CHUNK_FORMATS)
+@pytest.mark.parametrize("m,scale", [(50, 0.09), (70, -0.09), (150, 0.0)])     # 100 rows: 4 wavefronts; 140, 300: 8
+def test_many_rows_over_few_tiles(c, b, m, scale, rope):
+    # the keys run two tiles ahead, the codes three: one to five tiles per workgroup, and wavefronts
+    # whose rows end before the workgroup's last tile
+    hq, hkv, B = 4, 2, 2
+    for tiles in (3, 4, 5):
+        T = 64 * tiles - 9
+        fmt, q, kc, vc, ck, cv = _case(900 + m + T, c, b, hq, hkv, B, m, T)
+        t_cap = 64 * tiles
+        lens = np.array([T, m], dtype=np.int32)
+        ref = O.chunk_attention(q, kc, vc, ck, cv, scale, hkv, seq_lens=lens, rope_base=10000.0 if rope else None)
+        args = (dev(q), codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap), dev(ck), dev(cv), scale, fmt, T, t_cap)
+        for split in (64, 128, t_cap):
+            kw = dict(seq_lens=dev(lens), tokens_per_split=split)
+            out = cq.cq_chunk_attention_rope(*args, cq.RopeTable(10000.0, t_cap), **kw) if rope else cq.cq_chunk_attention(*args, **kw)
+            torch.cuda.synchronize()
+            _check(out.cpu().numpy(), ref)
+
+
 def test_few_rows_split_within_the_workspace_that_comes_with_the_call():
     """The split of a short chunk fits the reported workspace and may grow with a larger one; less
     than the reported size stays an error."""
