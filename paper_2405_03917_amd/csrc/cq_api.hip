@@ -611,14 +611,20 @@ int chunk_tiles_per_split(const Derived& f, int batch, int n_q_heads, int m, int
 }
 
 // Chunks of few rows with both codebooks of a KV head in LDS (cq_chunk_lds.hip).  Its time grows
-// with the blocks of 16 rows, the many-row kernel's hardly below 128 rows; measured (many-row /
-// this one, us): CQ-4c8b, 32 KV heads, batch 16 x 4096: 264 / 58 at 16 rows, 266 / 98 at 32, 274 /
-// 180 at 64; CQ-8c8b, 8 KV heads, batch 32 x 16384: 479 / 84 at 16, 501 / 287 at 64; at 128 rows
-// it would be behind.  Up to 2 tokens the single-token kernel is faster (28 us a token).
+// with the blocks of 16 rows, the many-row kernel's hardly below 128 rows; measured: CQ-4c8b, 32 KV
+// heads, batch 16 x 4096: 259 us with many rows (65), here 58 at 16 rows, 98 at 32, 181 at 64; CQ-8c8b,
+// 8 KV heads, batch 32 x 16384: 450 with many (68), here 83 at 16, 290 at 64; at 128 rows it would be
+// behind.  Up to 2 tokens the single-token kernel is faster (28 us a token).  Over a few tiles the staging
+// of the codebooks is not repaid (batch 64, 32 KV heads, many-row / this one, us): CQ-8c8b, 16 rows: 28 / 38
+// over 1 tile, 45 / 38 over 2, 75 / 39 over 4; 64 rows: 35 / 52, 53 / 56, 84 / 74; CQ-4c8b, 16 rows: 30 / 49,
+// 48 / 51, 84 / 52; 64 rows: 38 / 60, 56 / 71, 91 / 96 and 160 / 131 over 8.
 constexpr int kChunkLdsRows = 64;
-bool chunk_in_lds(const Derived& f, int n_q_heads, int m, bool rope)
+bool chunk_in_lds(const Derived& f, int n_q_heads, int m, int t, bool rope)
 {
-    return !rope && f.b == 8 && (f.c == 8 || f.c == 4) && m > 2 && m * (n_q_heads / f.n_kv_heads) <= kChunkLdsRows;
+    const long rows = (long)m * (n_q_heads / f.n_kv_heads);
+    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
+    return !rope && f.b == 8 && (f.c == 8 || f.c == 4) && m > 2 && rows <= kChunkLdsRows &&
+           n_tiles >= (f.c == 4 && rows > 32 ? 8 : 4);
 }
 
 // Its context split, in tiles; 0: not to be used.  Workgroups (one per CU) walk items = (sequence,
@@ -734,7 +740,7 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
         }
     }
     int lds_tiles = 0;
-    if (chunk_in_lds(f, n_q_heads, m, rope))
+    if (chunk_in_lds(f, n_q_heads, m, t, rope))
         lds_tiles = tokens_per_split ? tiles : chunk_lds_tiles(f, batch, n_q_heads, m, t, by_token, workspace ? workspace_bytes : 0);
     if (by_token && !lds_tiles) {
         const int64_t row = (int64_t)n_q_heads * f.head_dim;

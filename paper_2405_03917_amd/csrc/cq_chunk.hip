@@ -72,7 +72,7 @@ __device__ __forceinline__ float half_wave_max(float x)
 }
 
 // Codes of 64 tokens -> fp16 keys and values [token][channel] in LDS.
-// The codes of a tile first go to LDS as they are (load_raw / store_raw: one 16-byte record per
+// The codes of a tile first go to LDS as they are (request_codes / store_codes: one 16-byte record per
 // thread).  Then thread (token u = tid % 64, wavefront e = tid / 64) expands groups
 // e Gh/NW .. (e + 1) Gh/NW - 1 of its token: the code of group g sits in slot (g - u) mod Gh of the
 // token's record.  A wavefront thus gathers from ONE group's centroids at a time: its 64 lanes
@@ -104,21 +104,26 @@ struct Dequant {
     static constexpr int LOADERS = TILE / 16;           // threads that carry one record of K and one of V
     static constexpr int RAW_STAGE = 2 * TILE;          // K tile, V tile
     static_assert(LOADERS <= NW * 64, "one record per thread");
-    u32x4 kraw, vraw;                                   // 16-byte records of codes on their way to LDS
+    struct Codes {
+        u32x4 k, v;
+    };
+    Codes raw;                                          // 16-byte records of codes on their way to LDS
     unsigned kw[GPT][C / 2], vw[GPT][C / 2];            // the centroids of this thread's (token, group) pairs
 
-    __device__ __forceinline__ void load_raw(const uint8_t* ktile, const uint8_t* vtile, int tid)
+    __device__ __forceinline__ static Codes request_codes(const uint8_t* ktile, const uint8_t* vtile, int tid)
     {
+        Codes c = {};
         if (tid < LOADERS) {
-            kraw = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ktile) + tid);
-            vraw = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vtile) + tid);
+            c.k = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ktile) + tid);
+            c.v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vtile) + tid);
         }
+        return c;
     }
-    __device__ __forceinline__ void store_raw(unsigned k_slot, unsigned v_slot, int tid) const
+    __device__ __forceinline__ static void store_codes(const Codes& c, unsigned k_slot, unsigned v_slot, int tid)
     {
         if (tid < LOADERS) {
-            *(lds_q*)(k_slot + (unsigned)tid * 16) = kraw;
-            *(lds_q*)(v_slot + (unsigned)tid * 16) = vraw;
+            *(lds_q*)(k_slot + (unsigned)tid * 16) = c.k;
+            *(lds_q*)(v_slot + (unsigned)tid * 16) = c.v;
         }
     }
 
@@ -138,20 +143,28 @@ struct Dequant {
             }
         }
     }
-    __device__ __forceinline__ void request(unsigned (&w)[GPT][C / 2], const uint16_t* c_head, int tid) const
+    // (not `wanted`: zeros, not the old contents, which would occupy their registers until here)
+    __device__ __forceinline__ void request(unsigned (&w)[GPT][C / 2], const uint16_t* c_head, int tid, bool wanted) const
     {
         const int e = __builtin_amdgcn_readfirstlane(tid >> 6);
+        if (wanted) {
 #pragma unroll
-        for (int gi = 0; gi < GPT; ++gi) {
-            const unsigned* src = reinterpret_cast<const unsigned*>(c_head + ((size_t)group(e, gi) * K + code[gi]) * C);
+            for (int gi = 0; gi < GPT; ++gi) {
+                const unsigned* src = reinterpret_cast<const unsigned*>(c_head + ((size_t)group(e, gi) * K + code[gi]) * C);
 #pragma unroll
-            for (int i = 0; i < C / 2; ++i) w[gi][i] = src[i];
+                for (int i = 0; i < C / 2; ++i) w[gi][i] = src[i];
+            }
+        } else {
+#pragma unroll
+            for (int gi = 0; gi < GPT; ++gi)
+#pragma unroll
+                for (int i = 0; i < C / 2; ++i) w[gi][i] = 0;
         }
     }
-    __device__ __forceinline__ void gather(unsigned (&w)[GPT][C / 2], unsigned raw, const uint16_t* c_head, int tid)
+    __device__ __forceinline__ void gather(unsigned (&w)[GPT][C / 2], unsigned raw, const uint16_t* c_head, int tid, bool wanted)
     {
         read_codes(raw, tid);
-        request(w, c_head, tid);
+        request(w, c_head, tid, wanted);
     }
 
     // ROPE: the angle of a rotation is the sum of two: u theta_i per lane, whose cos / sin lie in LDS ([pair][lane]),
@@ -297,15 +310,6 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     // A negative scale turns the queries' signs, so that the largest product is the largest score; a scale
     // of zero stands for one so small that every weight is 1 (0 times a masked -infinity is no number).
     const float scale = a.scale_log2e == 0.f ? 1e-37f : fabsf(a.scale_log2e);
-    const unsigned flip = a.scale_log2e < 0.f ? 0x80008000u : 0u;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        // (the queries arrive here: waited for in the loop, they would make its first product wait for the
-        // centroids of the next tile)
-        u32x4 w = __builtin_bit_cast(u32x4, qreg[s]) ^ flip;
-        asm volatile("" : "+v"(w));
-        qreg[s] = __builtin_bit_cast(half8_t, w);
-    }
 
     const uint16_t* ck_head = a.k_centroids + (size_t)hkv * GH * F::K * C;
     const uint16_t* cv_head = a.v_centroids + (size_t)hkv * GH * F::K * C;
@@ -419,12 +423,16 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
 
     size_t v_index = 0;                                     // tile index (of both code arrays) of tile + 2
     auto load_codes = [&](int tile) {                       // codes: keys of tile + 3, values of tile + 2
+        if (tile + 2 >= tile1) {
+            dq.raw = {};
+            return;
+        }
         const size_t k_index = a.map.tile_index(n, hkv, clamped(tile + 3));
-        dq.load_raw(a.k_codes + k_index * F::TILE_BYTES, a.v_codes + v_index * F::TILE_BYTES, tid);
+        dq.raw = D_::request_codes(a.k_codes + k_index * F::TILE_BYTES, a.v_codes + v_index * F::TILE_BYTES, tid);
         v_index = k_index;
     };
     auto end_tile = [&](int tile) {
-        dq.store_raw(k_slot(tile + 3), v_slot(tile + 2), tid);
+        if (tile + 2 < tile1) D_::store_codes(dq.raw, k_slot(tile + 3), v_slot(tile + 2), tid);
         dq.request_tile_angles(a.rope_tile_tab, clamped(tile + 2), tid);
         lds_barrier();
     };
@@ -433,6 +441,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         for (int q = 0; q < D_::kRotations; ++q) dq.rotate(D_::lane_angles(kAngles, tid, q), q);
     };
 
+    const bool paced = tile1 - tile0 > 8;
     auto multiply_tile = [&](int tile) {
         const unsigned stage = stage_of(tile), next_stage = stage_of(tile + 1);
         typename D_::Angles angles[2];
@@ -442,16 +451,18 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
             for (int i = 0; i < 16; ++i) acc[tb][i] = 0.f;
         // The priority falls from phase to phase, so that of the two wavefronts of a SIMD the one that lags goes
         // first: left to the age of the wavefront, one ran ahead and waited at the barrier for a third of the tile.
-        __builtin_amdgcn_s_setprio(3);
+        // (Not over a few tiles, where another workgroup's prologue would be what waits: CQ-8c8b, 40 x 70 tokens
+        // over 100, 39.9 us without and 42.9 with.)
+        if (paced) __builtin_amdgcn_s_setprio(3);
         read_keys(stage, 0);
         if constexpr (ROPE) angles[0] = D_::lane_angles(kAngles, tid, 0);
 #pragma unroll
         for (int g = 0; g < 2 * kGroups; ++g) {
             if (g == kGroups) {
-                dq.store_keys(next_stage, tid);
+                if (tile + 1 < tile1) dq.store_keys(next_stage, tid);
                 load_codes(tile);                           // (behind the wait for the keys' centroids, before the values')
                 mask(tile, 0);
-                __builtin_amdgcn_s_setprio(2);
+                if (paced) __builtin_amdgcn_s_setprio(2);
             }
             if (g == kGroups - 1) dq.read_codes(v_slot(tile + 1), tid);
             if (g + 1 < 2 * kGroups) read_keys(stage, g + 1);
@@ -460,7 +471,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 multiply_key(g, i);
-                if (g == kGroups && i == 0) dq.request(dq.vw, cv_head, tid);
+                if (g == kGroups && i == 0) dq.request(dq.vw, cv_head, tid, tile + 1 < tile1);
                 if (ROPE && g < kGroups) {                  // the next tile's keys behind the first products
                     constexpr int per = 16 / (D_::kRotations > 0 ? D_::kRotations : 16);
                     const int idx = 4 * g + i, q = idx / per;
@@ -477,7 +488,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         }
         mask(tile, 1);
         rescale(0);
-        __builtin_amdgcn_s_setprio(1);
+        if (paced) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             if (k == 4) read_values(stage, 0, 1);
@@ -491,42 +502,63 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         l_run = __builtin_fmaf(l_run, alpha_of[0], psum_of[0]);
         fence();
         rescale(1);
-        __builtin_amdgcn_s_setprio(0);
+        if (paced) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             if (k == 4) read_values(stage, 1, 1);
             fence();
             multiply_value(1, k);
-            if (k == 0) dq.request(dq.kw, ck_head, tid);
+            if (k == 0) dq.request(dq.kw, ck_head, tid, tile + 2 < tile1);
             if (k < 6 && k % 2 == 0) softmax_slice(1, 7 + k / 2);
         }
         l_run = __builtin_fmaf(l_run, alpha_of[1], psum_of[1]);
-        dq.store_values(next_stage, tid);
+        if (tile + 1 < tile1) dq.store_values(next_stage, tid);
     };
 
     if (tile0 < tile1) {
-        const size_t first = a.map.tile_index(n, hkv, tile0), second = a.map.tile_index(n, hkv, clamped(tile0 + 1));
-        v_index = a.map.tile_index(n, hkv, clamped(tile0 + 2));
-        dq.load_raw(a.k_codes + first * F::TILE_BYTES, a.v_codes + first * F::TILE_BYTES, tid);
-        dq.store_raw(k_slot(tile0), v_slot(tile0), tid);
-        dq.load_raw(a.k_codes + second * F::TILE_BYTES, a.v_codes + second * F::TILE_BYTES, tid);
-        dq.store_raw(k_slot(tile0 + 1), v_slot(tile0 + 1), tid);
+        // (all requests first: a short context waits for them once; and of a context of one or two tiles only what it has)
+        const bool two = tile0 + 1 < tile1, three = tile0 + 2 < tile1;
+        const size_t first = a.map.tile_index(n, hkv, tile0);
+        const typename D_::Codes c0 = D_::request_codes(a.k_codes + first * F::TILE_BYTES, a.v_codes + first * F::TILE_BYTES, tid);
+        typename D_::Codes c1 = {};
+        if (two) {
+            const size_t second = a.map.tile_index(n, hkv, tile0 + 1);
+            c1 = D_::request_codes(a.k_codes + second * F::TILE_BYTES, a.v_codes + second * F::TILE_BYTES, tid);
+        }
+        if (three) {
+            v_index = a.map.tile_index(n, hkv, tile0 + 2);
+            dq.raw = D_::request_codes(a.k_codes + v_index * F::TILE_BYTES, a.v_codes + v_index * F::TILE_BYTES, tid);
+        }
+        D_::store_codes(c0, k_slot(tile0), v_slot(tile0), tid);
+        if (two) D_::store_codes(c1, k_slot(tile0 + 1), v_slot(tile0 + 1), tid);
         if constexpr (ROPE) {
             for (int i = tid; i < (int)kAngleBytes / 16; i += NW * 64)
                 *(lds_q*)(kAngles + (unsigned)i * 16) = reinterpret_cast<const u32x4*>(a.rope_lane_tab)[i];
         }
         dq.request_tile_angles(a.rope_tile_tab, tile0, tid);
         lds_barrier();
-        dq.gather(dq.kw, k_slot(tile0), ck_head, tid);
-        dq.gather(dq.vw, v_slot(tile0), cv_head, tid);
-        if (tid < D_::LOADERS) dq.kraw = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(a.k_codes + v_index * F::TILE_BYTES) + tid);
+        dq.gather(dq.kw, k_slot(tile0), ck_head, tid, true);
+        dq.gather(dq.vw, v_slot(tile0), cv_head, tid, true);
         rotate_keys();
         dq.store_keys(stage_of(tile0), tid);
         dq.store_values(stage_of(tile0), tid);
-        dq.gather(dq.kw, k_slot(tile0 + 1), ck_head, tid);
-        dq.request_tile_angles(a.rope_tile_tab, clamped(tile0 + 1), tid);
-        lds_barrier();                                      // all have read the first tile's codes
-        if (tid < D_::LOADERS) *(lds_q*)(k_slot(tile0 + 2) + (unsigned)tid * 16) = dq.kraw;
+        if (two) {
+            dq.gather(dq.kw, k_slot(tile0 + 1), ck_head, tid, true);
+            dq.request_tile_angles(a.rope_tile_tab, tile0 + 1, tid);
+        }
+        if (three) {
+            lds_barrier();                                  // all have read the first tile's codes
+            if (tid < D_::LOADERS) *(lds_q*)(k_slot(tile0 + 2) + (unsigned)tid * 16) = dq.raw.k;
+        }
+    }
+    const unsigned flip = a.scale_log2e < 0.f ? 0x80008000u : 0u;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        // (the queries are waited for here, behind the first tile's requests: in the loop, they would make its
+        // first product wait for the centroids of the next tile)
+        u32x4 w = __builtin_bit_cast(u32x4, qreg[s]) ^ flip;
+        asm volatile("" : "+v"(w));
+        qreg[s] = __builtin_bit_cast(half8_t, w);
     }
     lds_barrier();
 
@@ -540,9 +572,9 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         rotate_keys();
         dq.store_keys(stage_of(tile + 1), tid);
         load_codes(tile);
-        dq.gather(dq.vw, v_slot(tile + 1), cv_head, tid);
+        dq.gather(dq.vw, v_slot(tile + 1), cv_head, tid, tile + 1 < tile1);
         dq.store_values(stage_of(tile + 1), tid);
-        dq.gather(dq.kw, k_slot(tile + 2), ck_head, tid);
+        dq.gather(dq.kw, k_slot(tile + 2), ck_head, tid, tile + 2 < tile1);
         end_tile(tile);
     }
 

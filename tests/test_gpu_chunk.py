@@ -207,14 +207,16 @@ def test_chunk_attention_sweep(case):
 
 @pytest.mark.parametrize("c", [8, 4])
 @pytest.mark.parametrize("m,hq,hkv,B,T,scale", [
-    (8, 2, 2, 2, 65, 0.09),            # 8 rows: both halves of the probabilities in one product
+    (8, 2, 2, 2, 250, 0.09),           # 8 rows: both halves of the probabilities in one product
     (3, 6, 2, 3, 640, 0.09),           # 9 rows
-    (4, 8, 2, 2, 129, -0.09),          # one block of 16, scores falling with the product
+    (4, 8, 2, 2, 229, -0.09),          # one block of 16, scores falling with the product
     (17, 2, 2, 1, 1000, 0.0),          # two blocks, all scores equal
-    (11, 12, 4, 1, 200, 0.09),         # 33 rows: four blocks, the last one empty
+    (11, 12, 4, 1, 500, 0.09),         # 33 rows: four blocks, the last one empty
     (16, 8, 2, 2, 777, 0.2),           # 64 rows
+    (8, 2, 2, 2, 65, 0.09),            # two tiles, three tiles of 64 rows: the kernel for many rows
+    (64, 2, 2, 2, 192, 0.09),
     (65, 2, 2, 1, 300, 0.09),          # 65: the kernel for many rows
-    (3, 64, 64, 7, 130, 0.09),         # several (sequence, split) items per workgroup
+    (3, 64, 64, 7, 240, 0.09),         # several (sequence, split) items per workgroup
 ])
 def test_chunks_of_few_rows_with_codebooks_in_lds(c, m, hq, hkv, B, T, scale):
     fmt, q, kc, vc, ck, cv = _case(300 + m + T, c, 8, hq, hkv, B, m, T)
