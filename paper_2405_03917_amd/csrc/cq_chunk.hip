@@ -416,15 +416,14 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     auto k_slot = [&](int t) { return kRawBase(ROPE) + (unsigned)((t - tile0) & 1) * kRawStageBytes; };
     auto v_slot = [&](int t) { return k_slot(t) + kTileRaw; };
     auto stage_of = [&](int t) { return (unsigned)((t - tile0) & 1) * kStageBytes(ROPE); };
-    // Tiles behind the last one stand for the last: the loop needs no conditions, which would keep registers
-    // occupied and loads uncounted; what is made of them goes to a stage that nobody reads.
+    // (tiles behind the last one stand for it where only an address is made of them)
     auto clamped = [&](int t) { return min(t, tile1 - 1); };
     constexpr unsigned kAngles = kRawBase(ROPE) + 2 * kRawStageBytes;
 
     size_t v_index = 0;                                     // tile index (of both code arrays) of tile + 2
     auto load_codes = [&](int tile) {                       // codes: keys of tile + 3, values of tile + 2
         if (tile + 2 >= tile1) {
-            dq.raw = {};
+            dq.raw = {};                                    // (not the old contents: they would stay in registers until here)
             return;
         }
         const size_t k_index = a.map.tile_index(n, hkv, clamped(tile + 3));
