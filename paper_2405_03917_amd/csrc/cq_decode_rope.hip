@@ -790,7 +790,7 @@ __device__ __forceinline__ void gqa_values(const DecodeArgs& a, float* smem, con
         _Float16 part[3][QH];
 #pragma unroll
         for (int h = 0; h < QH; ++h) {
-            const float p = __builtin_amdgcn_exp2f(s[h] - (m[h] - 12.f));
+            const float p = __builtin_amdgcn_exp2f(s[h] - m[h]) * 4096.f;      // (12 in the exponent would be lost in a large m)
             l[h] += p;
             part[0][h] = (_Float16)p;
             const float r1 = p - (float)part[0][h];
