@@ -39,8 +39,6 @@ constexpr unsigned kMergeBase = 2 * kBookBytes;         // (m, l) of every wavef
 constexpr unsigned kORow = 64 * 4;                      // output rows
 constexpr unsigned kLdsBytes = kMergeBase + kWaves * kRows * kORow;
 static_assert(kLdsBytes == 160 * 1024, "all of a CU's LDS");
-constexpr float kProbScale = 4096.f;                    // 2^12
-
 __device__ __forceinline__ half8_t lds_half8(unsigned a) { return *(__attribute__((address_space(3))) half8_t*)(a); }
 __device__ __forceinline__ half4_t lds_half4(unsigned a) { return *(__attribute__((address_space(3))) half4_t*)(a); }
 // maximum / sum over the four lanes l % 16 + 16 b
@@ -100,7 +98,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
     struct Item {
         int n, rg, split, pos, pos_first, tile0, tile1;
     };
-    const float scale = fabsf(a.scale_log2e);
+    // (a scale of zero stands for one so small that every weight is 1: 0 times a masked -infinity is no number)
+    const float scale = a.scale_log2e == 0.f ? 1e-37f : fabsf(a.scale_log2e);
     half8_t qreg[4];
     // the records of a tile on their way from memory, and the codes of one that this lane needs
     u32x4 rk[4][PL], rv[4][PL];                             // token 16 i + col, token 16 i + vtok
@@ -179,7 +178,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         float4_t o[8];
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
-        float m_run = -INFINITY, l_run = 0.f;
+        float ref = -INFINITY, l_run = 0.f;             // probabilities and their sum are relative to 2^ref
 
         // (a negative scale goes into the queries, so that the largest product is the largest score)
         if (a.scale_log2e < 0.f) {
@@ -189,6 +188,13 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         int tile = it.tile0 + slice;
         unpack();
         request(it, tile + cs);
+        // Scores that cannot reach 2^24 are scaled inside the exponent; others, whose rounding could carry the
+        // largest probability out of fp16's range there, before their maximum is taken
+        float q2 = 0.f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) q2 = sum_of_squares(qreg[s], q2);
+        const bool large = scores_may_be_large(q2 * 4.f, scale);
+        const float mult = large ? 1.f : scale, early = large ? scale : 1.f;
 #pragma unroll 1
         for (; tile < it.tile1; tile += cs) {
             // The gathers are issued in batches that the products behind them work off, one batch ahead
@@ -242,37 +248,32 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             gather_values(0);
             __builtin_amdgcn_sched_barrier(0);
             // ---- online softmax of the lane's query column
-            float bmax = -INFINITY, mult = scale;
-            if (tile * kTileTokens + kTileTokens - 1 > it.pos_first) {
-                mult = 1.f;
+            if (large || tile * kTileTokens + kTileTokens - 1 > it.pos_first) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int tok = tile * kTileTokens + 16 * i + 4 * blk + e;
-                        acc[i][e] = tok <= it.pos ? acc[i][e] * scale : -INFINITY;
-                        bmax = fmaxf(bmax, acc[i][e]);
+                        acc[i][e] = tok <= it.pos ? acc[i][e] * early : -INFINITY;
                     }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, acc[i][e]);
-                bmax *= scale;
             }
-            const float m_new = fmaxf(m_run, across_max(bmax));
-            const float m_safe = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: all weights 0
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-            m_run = m_new;
-            const float m_shift = m_safe - 12.f;
+            float bmax = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, acc[i][e]);
+            const float ref_new = fmaxf(ref, softmax_reference(across_max(bmax) * mult));
+            const float shift = ref_new == -INFINITY ? 0.f : ref_new;       // nothing visible yet: all weights 0
+            const float alpha = __builtin_amdgcn_exp2f(ref - shift);
+            ref = ref_new;
             float psum = 0.f;
-            half8_t ph[2], pl[2];                           // p 2^12 = ph + pl to 22 bits (HALF: ph of columns q, q + 8)
+            half8_t ph[2], pl[2];                           // p = ph + pl to 22 bits (HALF: ph of columns q, q + 8)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; e += 2) {
-                    const float2_t ps = {__builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][e], mult, -m_shift)),
-                                         __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][e + 1], mult, -m_shift))};
+                    const float2_t ps = {__builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][e], mult, -shift)),
+                                         __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][e + 1], mult, -shift))};
                     psum += ps[0];
                     psum += ps[1];
                     const half2_t hi = __builtin_convertvector(ps, half2_t);
@@ -311,7 +312,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             request(it, tile + 2 * cs);
         }
 
-        // ---- the next item's requests go out, then the context slices of every row block are merged: (m, l),
+        // ---- the next item's requests go out, then the context slices of every row block are merged: (ref, l),
         // then the rows, scaled to the common maximum, 64 channels at a time
         const Item done = it;
         item += stride;
@@ -330,7 +331,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         typedef __attribute__((address_space(3))) float2_t lds_f2;
         typedef __attribute__((address_space(3))) float4_t lds_f4;
         const float l = across_sum(l_run);
-        if (blk == 0) *(lds_f2*)(kMergeBase + (unsigned)(wave * kRows + col) * 8) = float2_t{m_run, l};
+        if (blk == 0) *(lds_f2*)(kMergeBase + (unsigned)(wave * kRows + col) * 8) = float2_t{ref, l};
         lds_barrier();
         float2_t ml[kWaves];                                // of the wavefronts that share this one's row block, this lane's row
 #pragma unroll
@@ -341,15 +342,15 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         const float mz = mm == -INFINITY ? 0.f : mm;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) ll += w < cs ? ml[w][1] * __builtin_amdgcn_exp2f(ml[w][0] - mz) : 0.f;
-        float weight = __builtin_amdgcn_exp2f(m_run - mz);
-        weight *= a.n_split == 1 ? 1.f / ll : 1.f / kProbScale;
+        float weight = __builtin_amdgcn_exp2f(ref - mz);
+        if (a.n_split == 1) weight *= 1.f / ll;
         const int row0 = (done.rg * rbs + rb) * kRows;
         if (a.n_split > 1 && slice == 0 && blk == 0 && row0 + col < rows_total) {
             const int j = row_token(row0 + col);
             const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (row0 + col - j * qper);
             float* dst = a.partials + (out_row * a.n_split + done.split) * (D + kPartialHeader);
             dst[0] = mm;
-            dst[1] = ll * (1.f / kProbScale);
+            dst[1] = ll;
         }
         lds_barrier();                                      // the pairs are read: their room is the rows'
         const int q = tid >> 5;                             // this thread's row and pair of channels

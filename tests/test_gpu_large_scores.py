@@ -74,3 +74,16 @@ def test_grouped_decode_over_rotated_keys(c, hq, magnitude):
     for split in (t_cap, 256):
         _check(cq.cq_decode_attention_rope(dev(q[:, 0]), kcache, vcache, dev(ck), dev(cv), scale, fmt, T, t_cap, rope,
                                            tokens_per_split=split), ref, clear)
+
+
+@pytest.mark.parametrize("magnitude,sign", [(x, 1.0) for x in MAGNITUDES] + [(2.0 ** 30, -1.0)])
+@pytest.mark.parametrize("c,m,hq", [(8, 5, 2), (8, 6, 8), (4, 5, 2), (4, 16, 4)])
+def test_chunks_of_few_rows(c, m, hq, magnitude, sign):
+    hkv, B, T = 2, 2, 500
+    fmt, q, kc, vc, ck, cv = _case(10 + c + m, c, 8, hq, hkv, B, m, T, 40)
+    t_cap = -(-T // 64) * 64
+    kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
+    scale = _scale(magnitude, sign)
+    ref, clear = _reference(q, kc, vc, ck, cv, scale, hkv)
+    for split in (0, 256, t_cap):
+        _check(cq.cq_chunk_attention(dev(q), kcache, vcache, dev(ck), dev(cv), scale, fmt, T, t_cap, tokens_per_split=split), ref, clear)
