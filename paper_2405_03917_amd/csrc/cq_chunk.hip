@@ -45,7 +45,6 @@ constexpr int kStageBytes(bool rope) { return kKsBytes + kVsBytes + (rope ? kKsB
 constexpr unsigned kRawBase(bool rope) { return 2 * kStageBytes(rope); }     // behind the two stages: the raw code tiles (K, V) of two tiles
 constexpr unsigned kAngleBytes = 64 * kTileTokens * 8;                       // behind those (rotated keys): cos / sin per pair and token of a tile
 typedef __attribute__((address_space(3))) u32x4 lds_q;
-constexpr float kProbScale = 4096.f;              // 2^12
 
 __device__ __forceinline__ half8_t lds_half8(unsigned byte_addr)
 {
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[cb][i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    float ref = -INFINITY, l_run = 0.f;                     // probabilities and their sum are relative to 2^ref
 
     // One tile of this wavefront, in straight lines of vector and matrix instructions so that the two
     // pipes overlap within the wavefront: while the scores of tokens 32 .. 63 are multiplied, the vector
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     constexpr int kGroups = 2 * kParts;                     // groups of four products per 32-token block
     float16_t acc[2];
     float bmax_of[2], alpha_of[2];
-    u32x4 ph[2][2], pl[2][2];                               // p * 2^12 = ph + pl to 22 bits
+    u32x4 ph[2][2], pl[2][2];                               // p = ph + pl to 22 bits
     half8_t kf[2][4];
     auto read_keys = [&](unsigned stage, int g) {           // group g of the tile: block, part, half of the head
         const int tb = g / kGroups, part = g % kGroups / 2, half = g & 1;
@@ -343,12 +342,14 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     };
     // softmax of a block in ten slices: the maximum; what follows from it; two probabilities in each of the others.
     // acc[tb][i] is token 8 (i / 4) + 4 kh + i % 4 of the block, query rc
-    float psum_of[2], m_shift_of[2];
+    float psum_of[2], shift_of[2];
+    bool large;                                             // (set below)
+    float mult, early;
     auto mask = [&](int tile, int tb) {                     // a tile on the causal diagonal of some query of this wavefront
-        if (tile * kTileTokens + kTileTokens - 1 > pos_first) {
+        if (large || tile * kTileTokens + kTileTokens - 1 > pos_first) {
             const int tok0 = tile * kTileTokens + tb * 32 + 4 * kh;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[tb][i] = tok0 + 8 * (i >> 2) + (i & 3) <= pos ? acc[tb][i] : -INFINITY;
+            for (int i = 0; i < 16; ++i) acc[tb][i] = tok0 + 8 * (i >> 2) + (i & 3) <= pos ? acc[tb][i] * early : -INFINITY;
         }
     };
     auto softmax_slice = [&](int tb, int k) {
@@ -358,17 +359,15 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
             for (int i = 0; i < 16; ++i) b = fmaxf(b, acc[tb][i]);
             bmax_of[tb] = b;
         } else if (k == 1) {
-            const float b = half_wave_max(bmax_of[tb]);
-            const float m_new = fmaxf(m_run, b * scale);
-            const float m_safe = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: all weights 0
-            alpha_of[tb] = __builtin_amdgcn_exp2f(m_run - m_safe);
-            m_run = m_new;
-            m_shift_of[tb] = m_safe - 12.f;        // probabilities times 2^12 (the sum l_run is kept in that scale too)
+            const float ref_new = fmaxf(ref, softmax_reference(half_wave_max(bmax_of[tb]) * mult));
+            shift_of[tb] = ref_new == -INFINITY ? 0.f : ref_new;        // nothing visible yet: all weights 0
+            alpha_of[tb] = __builtin_amdgcn_exp2f(ref - shift_of[tb]);
+            ref = ref_new;
             psum_of[tb] = 0.f;
         } else if (k < 10) {
             const int i = 2 * (k - 2);
-            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[tb][i], scale, -m_shift_of[tb]));
-            const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[tb][i + 1], scale, -m_shift_of[tb]));
+            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[tb][i], mult, -shift_of[tb]));
+            const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[tb][i + 1], mult, -shift_of[tb]));
             psum_of[tb] += p0;
             psum_of[tb] += p1;
             unsigned hi, lo;
@@ -559,6 +558,16 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         asm volatile("" : "+v"(w));
         qreg[s] = __builtin_bit_cast(half8_t, w);
     }
+    // Scores that cannot reach 2^24 are scaled inside the exponent; others, whose rounding could carry the largest
+    // probability out of fp16's range there, before their maximum is taken
+    {
+        float q2 = 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) q2 = sum_of_squares(qreg[s], q2);
+        large = scores_may_be_large(q2 * 2.f, scale);       // (the lane holds half of its query)
+        mult = large ? 1.f : scale;
+        early = large ? scale : 1.f;
+    }
     lds_barrier();
 
     int tile = tile0;
@@ -594,18 +603,18 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
             }
     } else {
         if (kh == 0) {
-            part[0] = m_run;
-            part[1] = l * (1.f / kProbScale);
+            part[0] = ref;
+            part[1] = l;
         }
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
                 float4 v;
-                v.x = o[cb][4 * i4 + 0] * (1.f / kProbScale);
-                v.y = o[cb][4 * i4 + 1] * (1.f / kProbScale);
-                v.z = o[cb][4 * i4 + 2] * (1.f / kProbScale);
-                v.w = o[cb][4 * i4 + 3] * (1.f / kProbScale);
+                v.x = o[cb][4 * i4 + 0];
+                v.y = o[cb][4 * i4 + 1];
+                v.z = o[cb][4 * i4 + 2];
+                v.w = o[cb][4 * i4 + 3];
                 float* dst = part + kPartialHeader + 32 * cb + 8 * i4 + 4 * kh;
                 dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
             }

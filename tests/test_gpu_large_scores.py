@@ -87,3 +87,22 @@ def test_chunks_of_few_rows(c, m, hq, magnitude, sign):
     ref, clear = _reference(q, kc, vc, ck, cv, scale, hkv)
     for split in (0, 256, t_cap):
         _check(cq.cq_chunk_attention(dev(q), kcache, vcache, dev(ck), dev(cv), scale, fmt, T, t_cap, tokens_per_split=split), ref, clear)
+
+
+@pytest.mark.parametrize("magnitude,sign", [(x, 1.0) for x in MAGNITUDES] + [(2.0 ** 30, -1.0)])
+@pytest.mark.parametrize("c,b", [(8, 8), (4, 8), (2, 8), (8, 10)])
+@pytest.mark.parametrize("rope", [False, True])
+def test_chunks_of_many_rows(rope, c, b, magnitude, sign):
+    hq, hkv, B, T = 4, 2, 2, 500
+    for m in (50, 70):                                       # 100 and 140 rows: four wavefronts and eight
+        fmt, q, kc, vc, ck, cv = _case(30 + c + m, c, b, hq, hkv, B, m, T, 0 if rope else 40)
+        t_cap = -(-T // 64) * 64
+        args = (dev(q), codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap), dev(ck), dev(cv))
+        scale = _scale(magnitude, sign)
+        ref, clear = _reference(q, kc, vc, ck, cv, scale, hkv, BASE if rope else None)
+        for split in (64, 256, t_cap):
+            if rope:
+                out = cq.cq_chunk_attention_rope(*args, scale, fmt, T, t_cap, cq.RopeTable(BASE, t_cap), tokens_per_split=split)
+            else:
+                out = cq.cq_chunk_attention(*args, scale, fmt, T, t_cap, tokens_per_split=split)
+            _check(out, ref, clear)
