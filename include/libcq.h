@@ -353,13 +353,16 @@ CQ_API cq_status cq_decode_step_paged(const void *q, const void *x_k_new, const 
  * The contraction runs on the matrix cores in fp16 with fp32 accumulation: scores are exact
  * products summed in fp32; probabilities enter the value product as two fp16 numbers (22 bits).
  * Short chunks with tokens_per_split = 0 are instead served token by token by the kernel of
- * cq_decode_attention, m launches in stream order, where that is faster: m <= 2 always, and on
- * large batches m <= 8 / (query heads per KV head) unless the library has a faster matrix-core
- * kernel for the format and size.  The results are then bit-identical to m calls of
- * cq_decode_attention with the contexts of the m tokens.  cq_chunk_default_split and
- * cq_chunk_workspace_bytes give a split and a workspace that serve either path (the library may
- * cut the context into fewer pieces than the split says); an explicit tokens_per_split always
- * runs a matrix-core kernel.
+ * cq_decode_attention, m launches in stream order, where that is faster; the results are then
+ * bit-identical to m calls of cq_decode_attention with the contexts of the m tokens.  That is the
+ * case for m <= 2, and on large batches (batch x KV heads x 64-token tiles of the context from
+ * 16384 on) of CQ-2c8b and CQ-8c10b for m <= 8 / (query heads per KV head); of CQ-8c8b and 4c8b
+ * only where the context cannot be cut into enough pieces for the matrix-core kernel.  A caller
+ * that wants the bits of cq_decode_attention for every size makes the m calls.
+ * Which kernel a call takes and how it cuts the context depend on the format and the sizes alone, not
+ * on how large the workspace is beyond cq_chunk_workspace_bytes.  cq_chunk_default_split is the
+ * largest number of pieces it may cut into, given as a split; an explicit tokens_per_split always
+ * runs a matrix-core kernel, with that split.
  * Formats: those of cq_decode_attention (b = 8, 10 at head_dim 128).
  * Errors: as cq_decode_attention; CQ_ERR_INVALID_ARG also for m <= 0 or m > t.
  */

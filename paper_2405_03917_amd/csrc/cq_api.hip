@@ -627,35 +627,6 @@ bool chunk_in_lds(const Derived& f, int n_q_heads, int m, int t, bool rope)
            n_tiles >= (f.c == 4 && rows > 32 ? 8 : 4);
 }
 
-// Its context split, in tiles; 0: not to be used.  Workgroups (one per CU) walk items = (sequence,
-// split) pairs of a KV head; an item costs its tiles for every block of 16 rows and a merge of its
-// wavefronts worth about 8 tiles, a split context a merge kernel worth about 16.  The sizes the
-// library reports for a chunk are those of the other two paths, so the split has to fit the
-// workspace that came with the call (none: no split).  Where that leaves a quarter of the CUs or
-// more without an item and the chunk can go token by token, it does: 5 tokens of batch 4 x 131072,
-// 32 KV heads, CQ-8c8b: 440 us token by token, 280 us with two pieces, but about 560 in one.
-int chunk_lds_tiles(const Derived& f, int batch, int n_q_heads, int m, int t, bool by_token, size_t workspace_bytes)
-{
-    const ChunkLdsPlan p = chunk_lds_plan(f, batch, n_q_heads, m);
-    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
-    const long base = (long)batch * p.row_groups;
-    const size_t piece = sizeof(float) * (size_t)batch * m * n_q_heads * (f.head_dim + kPartialHeader);
-    const long fit = std::max<long>(1, (long)std::min<size_t>(workspace_bytes / piece, 1u << 20));
-    if (by_token && base * f.n_kv_heads * fit < 192) return 0;
-    long best_ns = 1, best_cost = -1;
-    for (long ns = 1; ns <= std::min<long>(fit, std::max(1, n_tiles / 8)); ++ns) {
-        const long tiles = (n_tiles + ns - 1) / ns;
-        const long turns = (base * ns + p.wgs_per_head - 1) / p.wgs_per_head;
-        const long cost = turns * ((tiles << p.rb_log2) + 8) + (ns > 1 ? 16 : 0);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best_ns = ns;
-        }
-        if (turns >= 4) break;
-    }
-    return (int)((n_tiles + best_ns - 1) / best_ns);
-}
-
 // Short chunks go through the single-token kernel, one launch per query token (token j with a
 // context shortened by m - 1 - j): the chunk kernel dequantises every tile of the context
 // whatever m is, which costs 8-16 single-token launches on large multi-head batches (measured;
@@ -685,6 +656,50 @@ TokenCall chunk_token_call(const Derived& f, int batch, int n_q_heads, int m, in
     c.n_split = (n_tiles + c.tiles - 1) / c.tiles;
     c.workspace = c.n_split > 1 ? sizeof(float) * (size_t)batch * n_q_heads * c.n_split * (f.head_dim + kPartialHeader) : 0;
     return c;
+}
+
+// Workspace of a chunk as the library reports it: for the tokens one by one, or for the many-row kernel's split.
+size_t chunk_workspace(const Derived& f, int batch, int n_q_heads, int m, int t, int tokens_per_split)
+{
+    if (tokens_per_split == 0 && chunk_by_token(f, batch, n_q_heads, m, t)) {
+        size_t need = 0;
+        for (int j = 0; j < m; ++j) need = std::max(need, chunk_token_call(f, batch, n_q_heads, m, t, j).workspace);
+        return need;
+    }
+    const int tiles = tokens_per_split ? tokens_per_split / kTileTokens : chunk_tiles_per_split(f, batch, n_q_heads, m, t);
+    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
+    const int n_split = (n_tiles + tiles - 1) / tiles;
+    return sizeof(float) * (size_t)batch * m * n_q_heads * n_split * (f.head_dim + kPartialHeader);
+}
+
+// The context split of the kernel with the codebooks in LDS, in tiles; 0: not to be used.  Workgroups (one per CU)
+// walk items = (sequence, split) pairs of a KV head; an item costs its tiles for every block of 16 rows and a merge
+// of its wavefronts worth about 8 tiles, a split context a merge kernel worth about 16.  The sizes the
+// library reports for a chunk are those of the other two paths, and the split has to fit the reported workspace:
+// a function of format and sizes alone, so that a call gives the same bits with any workspace it accepts.  Where
+// that leaves a quarter of the CUs or more without an item and the chunk can go token by token, it does: 5 tokens
+// of batch 4 x 131072, 32 KV heads, CQ-8c8b: 440 us token by token, about 560 in one piece (280 us with two,
+// which that workspace does not hold).
+int chunk_lds_tiles(const Derived& f, int batch, int n_q_heads, int m, int t, bool by_token)
+{
+    const ChunkLdsPlan p = chunk_lds_plan(f, batch, n_q_heads, m);
+    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
+    const long base = (long)batch * p.row_groups;
+    const size_t piece = sizeof(float) * (size_t)batch * m * n_q_heads * (f.head_dim + kPartialHeader);
+    const long fit = std::max<long>(1, (long)(chunk_workspace(f, batch, n_q_heads, m, t, 0) / piece));
+    if (by_token && base * f.n_kv_heads * fit < 192) return 0;
+    long best_ns = 1, best_cost = -1;
+    for (long ns = 1; ns <= std::min<long>(fit, std::max(1, n_tiles / 8)); ++ns) {
+        const long tiles = (n_tiles + ns - 1) / ns;
+        const long turns = (base * ns + p.wgs_per_head - 1) / p.wgs_per_head;
+        const long cost = turns * ((tiles << p.rb_log2) + 8) + (ns > 1 ? 16 : 0);
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best_ns = ns;
+        }
+        if (turns >= 4) break;
+    }
+    return (int)((n_tiles + best_ns - 1) / best_ns);
 }
 
 cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
@@ -741,7 +756,7 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
     }
     int lds_tiles = 0;
     if (chunk_in_lds(f, n_q_heads, m, t, rope))
-        lds_tiles = tokens_per_split ? tiles : chunk_lds_tiles(f, batch, n_q_heads, m, t, by_token, workspace ? workspace_bytes : 0);
+        lds_tiles = tokens_per_split ? tiles : chunk_lds_tiles(f, batch, n_q_heads, m, t, by_token);
     if (by_token && !lds_tiles) {
         const int64_t row = (int64_t)n_q_heads * f.head_dim;
         for (int j = 0; j < m; ++j) {           // (in stream order: the calls share the workspace)
@@ -826,15 +841,7 @@ size_t cq_chunk_workspace_bytes(const cq_format* fmt, int32_t batch, int32_t n_q
     if (derive(fmt, &f) != CQ_OK || f.head_dim != 128) return 0;
     if (batch <= 0 || n_q_heads <= 0 || n_q_heads % f.n_kv_heads != 0 || m <= 0 || t < m) return 0;
     if (tokens_per_split < 0 || tokens_per_split % kTileTokens != 0) return 0;
-    if (tokens_per_split == 0 && chunk_by_token(f, batch, n_q_heads, m, t)) {
-        size_t need = 0;
-        for (int j = 0; j < m; ++j) need = std::max(need, chunk_token_call(f, batch, n_q_heads, m, t, j).workspace);
-        return need;
-    }
-    const int tiles = tokens_per_split ? tokens_per_split / kTileTokens : chunk_tiles_per_split(f, batch, n_q_heads, m, t);
-    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
-    const int n_split = (n_tiles + tiles - 1) / tiles;
-    return sizeof(float) * (size_t)batch * m * n_q_heads * n_split * (f.head_dim + kPartialHeader);
+    return chunk_workspace(f, batch, n_q_heads, m, t, tokens_per_split);
 }
 
 cq_status cq_chunk_attention(const void* q, const void* k_codes, const void* v_codes,

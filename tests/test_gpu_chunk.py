@@ -250,20 +250,35 @@ def test_many_rows_over_few_tiles(c, b, m, scale, rope):
             _check(out.cpu().numpy(), ref)
 
 
-def test_few_rows_split_within_the_workspace_that_comes_with_the_call():
-    """The split of a short chunk fits the reported workspace and may grow with a larger one; less
-    than the reported size stays an error."""
+def test_few_rows_give_the_same_bits_with_any_workspace():
+    """The split of a short chunk fits the reported workspace and does not follow a larger one; less
+    than the reported size is an error."""
     c, b, hq, hkv, B, m, T, t_cap = 4, 8, 2, 2, 1, 5, 4000, 4032
     fmt, q, kc, vc, ck, cv = _case(21, c, b, hq, hkv, B, m, T)
     need = cq.cq_chunk_workspace_bytes(fmt, B, hq, m, T)
     assert need > 4 * B * m * hq * 130
-    ref = O.chunk_attention(q, kc, vc, ck, cv, 0.1, hkv)
     kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
     run = lambda nbytes: cq.cq_chunk_attention(dev(q), kcache, vcache, dev(ck), dev(cv), 0.1, fmt, T, t_cap,
                                                workspace=torch.zeros(nbytes, dtype=torch.uint8, device="cuda"))
-    for nbytes in (need, 8 * need):
-        out = run(nbytes)
-        torch.cuda.synchronize()
-        _check(out.cpu().numpy(), ref)
+    outs = [run(nbytes) for nbytes in (need, need + 4 * B * m * hq * 130, 8 * need)]
+    torch.cuda.synchronize()
+    _check(outs[0].cpu().numpy(), O.chunk_attention(q, kc, vc, ck, cv, 0.1, hkv))
+    assert all(torch.equal(o.view(torch.int16), outs[0].view(torch.int16)) for o in outs)
     with pytest.raises(cq.CQError):
         run(need - 16)
+
+
+@pytest.mark.parametrize("B,hkv,m,T", [(1, 8, 5, 131072), (2, 16, 4, 40000), (6, 32, 3, 6000)])
+def test_short_chunks_of_large_batches_give_the_same_bits_with_any_workspace(B, hkv, m, T):
+    # 16384 tiles and more, where the reported workspace is that of one token's pieces (none in the last case)
+    fmt = cq.CQFormat(8, 8, 128, hkv)
+    t_cap = -(-T // 64) * 64
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()
+    caches = [torch.randint(0, 256, (cq.cq_cache_bytes(fmt, B, t_cap),), generator=gen, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    q, ck, cv = rand(B, m, hkv, 128), rand(fmt.groups, 256, 8), rand(fmt.groups, 256, 8)
+    need = max(16, cq.cq_chunk_workspace_bytes(fmt, B, hkv, m, T))
+    outs = [cq.cq_chunk_attention(q, *caches, ck, cv, 0.1, fmt, T, t_cap, workspace=torch.zeros(n, dtype=torch.uint8, device="cuda"))
+            for n in (need, 2 * need, need + (64 << 20))]
+    torch.cuda.synchronize()
+    assert all(torch.equal(o.view(torch.int16), outs[0].view(torch.int16)) for o in outs)
