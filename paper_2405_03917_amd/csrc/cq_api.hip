@@ -617,14 +617,17 @@ int chunk_tiles_per_split(const Derived& f, int batch, int n_q_heads, int m, int
 // behind.  Up to 2 tokens the single-token kernel is faster (28 us a token).  Over a few tiles the staging
 // of the codebooks is not repaid (batch 64, 32 KV heads, many-row / this one, us): CQ-8c8b, 16 rows: 28 / 38
 // over 1 tile, 45 / 38 over 2, 75 / 39 over 4; 64 rows: 35 / 52, 53 / 56, 84 / 74; CQ-4c8b, 16 rows: 30 / 49,
-// 48 / 51, 84 / 52; 64 rows: 38 / 60, 56 / 71, 91 / 96 and 160 / 131 over 8.
+// 48 / 51, 84 / 52; 64 rows: 38 / 60, 56 / 71, 91 / 96 and 160 / 131 over 8.  The same holds for the pieces of an
+// The pieces of an explicit split have to repay their merges too (context 4096, many-row / this one): 16 x 32 heads,
+// 3 rows, CQ-8c8b: 330 / 491 in pieces of one tile, 271 / 254 of two; 4c8b: 302 / 330 of two, 274 / 178 of four;
+// 16 x 8 heads, 32 rows: CQ-8c8b 91 / 101 of two, 83 / 73 of three, 4c8b 99 / 114 and 94 / 84; 64 rows: CQ-8c8b
+// 100 / 105 of three, 4c8b 109 / 124 of three, 98 / 97 of four.
 constexpr int kChunkLdsRows = 64;
-bool chunk_in_lds(const Derived& f, int n_q_heads, int m, int t, bool rope)
+bool chunk_in_lds(const Derived& f, int n_q_heads, int m, int n_tiles, int piece_tiles, bool rope)
 {
     const long rows = (long)m * (n_q_heads / f.n_kv_heads);
-    const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
     return !rope && f.b == 8 && (f.c == 8 || f.c == 4) && m > 2 && rows <= kChunkLdsRows &&
-           n_tiles >= (f.c == 4 && rows > 32 ? 8 : 4);
+           n_tiles >= (f.c == 4 && rows > 32 ? 8 : 4) && piece_tiles >= (rows > 32 ? 4 : (rows > 16 || f.c == 4 ? 3 : 2));
 }
 
 // Short chunks go through the single-token kernel, one launch per query token (token j with a
@@ -755,7 +758,7 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
         }
     }
     int lds_tiles = 0;
-    if (chunk_in_lds(f, n_q_heads, m, t, rope))
+    if (chunk_in_lds(f, n_q_heads, m, n_tiles, tokens_per_split ? std::min(tiles, n_tiles) : n_tiles, rope))
         lds_tiles = tokens_per_split ? tiles : chunk_lds_tiles(f, batch, n_q_heads, m, t, by_token);
     if (by_token && !lds_tiles) {
         const int64_t row = (int64_t)n_q_heads * f.head_dim;

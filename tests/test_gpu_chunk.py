@@ -225,7 +225,7 @@ def test_chunks_of_few_rows_with_codebooks_in_lds(c, m, hq, hkv, B, T, scale):
     lens[0] = T
     ref = O.chunk_attention(q, kc, vc, ck, cv, scale, hkv, seq_lens=lens)
     kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
-    for split in (0, 64, 192):
+    for split in (0, 64, 192, 256, 512):        # (pieces of one tile, three of many rows: the other kernel)
         _check(_gpu(q, kcache, vcache, ck, cv, scale, fmt, T, t_cap, seq_lens=lens, split=split), ref)
 
 
