@@ -192,6 +192,12 @@ struct Dequant {
         const f32x2 x = *(lds_f2*)at, y = *(lds_f2*)(at + 512);
         return {make_float2(x.x, x.y), make_float2(y.x, y.y)};
     }
+    // the same from the table in memory
+    __device__ __forceinline__ static Angles table_angles(const float2* lane_tab, int tid, int q)
+    {
+        const float2* t = lane_tab + (size_t)(__builtin_amdgcn_readfirstlane(tid >> 6) * NP + 2 * q) * 64 + (tid & 63);
+        return {t[0], t[64]};
+    }
     // rotate pairs 2 q and 2 q + 1 of the gathered keys:
     // (k_i, k_{i+64}) -> (k_i cos - k_{i+64} sin, k_{i+64} cos + k_i sin), fp32, then two fp16 parts
     __device__ __forceinline__ void rotate(const Angles& lane_part, int q)
@@ -247,7 +253,14 @@ struct Dequant {
 // the code tiles of CQ-2c8b: those take the registers of two wavefronts
 constexpr int chunk_waves_per_simd(int c, int nw, bool rope) { return nw == 4 && (rope || c == 2) ? 1 : 2; }
 
-template <int GH, int C, int NW, int B, bool ROPE>
+// SHORT: pieces of the context of up to kShortTiles tiles, without the look-ahead of the pipeline, whose registers
+// (the form of four wavefronts spills some) and prologue such a call does not repay.  Not rotated, pipeline / this:
+// CQ-8c8b 64 x 64 tokens over 64: 39.6 / 35.3 us, 40 x 70 over 100: 36.4 / 32.1, 16 x 100 over 190: 20.2 / 18.7,
+// CQ-8c10b 43.4 / 37.5, 41.6 / 36.5 and 24.3 / 24.2; over four tiles the pipeline is ahead.  Rotated keys, whose
+// pipeline repays itself from two tiles on: CQ-8c8b 64 x 64 over 64: 66.2 / 64.9.
+constexpr int kShortTiles(bool rope) { return rope ? 1 : 3; }
+
+template <int GH, int C, int NW, int B, bool ROPE, bool SHORT>
 __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void chunk_attention_kernel(ChunkArgs a)
 {
     constexpr int kRowsPerWg = NW * 32;
@@ -513,77 +526,152 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         if (tile + 1 < tile1) dq.store_values(next_stage, tid);
     };
 
-    if (tile0 < tile1) {
-        // (all requests first: a short context waits for them once; and of a context of one or two tiles only what it has)
-        const bool two = tile0 + 1 < tile1, three = tile0 + 2 < tile1;
-        const size_t first = a.map.tile_index(n, hkv, tile0);
-        const typename D_::Codes c0 = D_::request_codes(a.k_codes + first * F::TILE_BYTES, a.v_codes + first * F::TILE_BYTES, tid);
-        typename D_::Codes c1 = {};
-        if (two) {
-            const size_t second = a.map.tile_index(n, hkv, tile0 + 1);
-            c1 = D_::request_codes(a.k_codes + second * F::TILE_BYTES, a.v_codes + second * F::TILE_BYTES, tid);
-        }
-        if (three) {
-            v_index = a.map.tile_index(n, hkv, tile0 + 2);
-            dq.raw = D_::request_codes(a.k_codes + v_index * F::TILE_BYTES, a.v_codes + v_index * F::TILE_BYTES, tid);
-        }
-        D_::store_codes(c0, k_slot(tile0), v_slot(tile0), tid);
-        if (two) D_::store_codes(c1, k_slot(tile0 + 1), v_slot(tile0 + 1), tid);
-        if constexpr (ROPE) {
-            for (int i = tid; i < (int)kAngleBytes / 16; i += NW * 64)
-                *(lds_q*)(kAngles + (unsigned)i * 16) = reinterpret_cast<const u32x4*>(a.rope_lane_tab)[i];
-        }
-        dq.request_tile_angles(a.rope_tile_tab, tile0, tid);
-        lds_barrier();
-        dq.gather(dq.kw, k_slot(tile0), ck_head, tid, true);
-        dq.gather(dq.vw, v_slot(tile0), cv_head, tid, true);
-        rotate_keys();
-        dq.store_keys(stage_of(tile0), tid);
-        dq.store_values(stage_of(tile0), tid);
-        if (two) {
-            dq.gather(dq.kw, k_slot(tile0 + 1), ck_head, tid, true);
-            dq.request_tile_angles(a.rope_tile_tab, tile0 + 1, tid);
-        }
-        if (three) {
-            lds_barrier();                                  // all have read the first tile's codes
-            if (tid < D_::LOADERS) *(lds_q*)(k_slot(tile0 + 2) + (unsigned)tid * 16) = dq.raw.k;
-        }
-    }
     const unsigned flip = a.scale_log2e < 0.f ? 0x80008000u : 0u;
+    auto prepare_queries = [&] {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        // (the queries are waited for here, behind the first tile's requests: in the loop, they would make its
-        // first product wait for the centroids of the next tile)
-        u32x4 w = __builtin_bit_cast(u32x4, qreg[s]) ^ flip;
-        asm volatile("" : "+v"(w));
-        qreg[s] = __builtin_bit_cast(half8_t, w);
-    }
-    // Scores that cannot reach 2^24 are scaled inside the exponent; others, whose rounding could carry the largest
-    // probability out of fp16's range there, before their maximum is taken
-    {
-        float q2 = 0.f;
+        for (int s = 0; s < 8; ++s) {
+            // (the queries are waited for here, behind the first tile's requests: in the loop, they would make its
+            // first product wait for the centroids of the next tile)
+            u32x4 w = __builtin_bit_cast(u32x4, qreg[s]) ^ flip;
+            asm volatile("" : "+v"(w));
+            qreg[s] = __builtin_bit_cast(half8_t, w);
+        }
+        // Scores that cannot reach 2^24 are scaled inside the exponent; others, whose rounding could carry the largest
+        // probability out of fp16's range there, before their maximum is taken
+        {
+            float q2 = 0.f;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) q2 = sum_of_squares(qreg[s], q2);
-        large = scores_may_be_large(q2 * 2.f, scale);       // (the lane holds half of its query)
-        mult = large ? 1.f : scale;
-        early = large ? scale : 1.f;
-    }
-    lds_barrier();
+            for (int s = 0; s < 8; ++s) q2 = sum_of_squares(qreg[s], q2);
+            large = scores_may_be_large(q2 * 2.f, scale);       // (the lane holds half of its query)
+            mult = large ? 1.f : scale;
+            early = large ? scale : 1.f;
+        }
+    };
 
-    int tile = tile0;
-    for (; tile < min(tile1, wave_tiles); ++tile) {
-        multiply_tile(tile);
-        end_tile(tile);
-    }
-    // tiles behind this wavefront's rows: it still helps the others to theirs
-    for (; tile < tile1; ++tile) {
-        rotate_keys();
-        dq.store_keys(stage_of(tile + 1), tid);
-        load_codes(tile);
-        dq.gather(dq.vw, v_slot(tile + 1), cv_head, tid, tile + 1 < tile1);
-        dq.store_values(stage_of(tile + 1), tid);
-        dq.gather(dq.kw, k_slot(tile + 2), ck_head, tid, tile + 2 < tile1);
-        end_tile(tile);
+    if constexpr (SHORT) {
+        constexpr unsigned kRaw = kRawBase(ROPE);           // the raw code tiles, one behind the other
+        auto expand = [&](int k) {
+            dq.request_tile_angles(a.rope_tile_tab, tile0 + k, tid);
+            dq.gather(dq.kw, kRaw + (unsigned)k * kRawStageBytes, ck_head, tid, true);
+            dq.gather(dq.vw, kRaw + (unsigned)k * kRawStageBytes + kTileRaw, cv_head, tid, true);
+        };
+        auto store = [&](int k) {
+#pragma unroll
+            for (int q = 0; q < D_::kRotations; ++q) dq.rotate(D_::table_angles(a.rope_lane_tab, tid, q), q);
+            dq.store_keys(stage_of(tile0 + k), tid);
+            dq.store_values(stage_of(tile0 + k), tid);
+        };
+        const int tiles = tile1 - tile0;
+        if (tiles > 0) {
+            constexpr int N = kShortTiles(ROPE);
+            typename D_::Codes codes[N] = {};
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                if (k < tiles) {
+                    const size_t at = a.map.tile_index(n, hkv, tile0 + k) * F::TILE_BYTES;
+                    codes[k] = D_::request_codes(a.k_codes + at, a.v_codes + at, tid);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (k < tiles) D_::store_codes(codes[k], kRaw + (unsigned)k * kRawStageBytes, kRaw + (unsigned)k * kRawStageBytes + kTileRaw, tid);
+            lds_barrier();
+            expand(0);
+            store(0);
+        }
+        prepare_queries();
+        lds_barrier();
+#pragma unroll 1
+        for (int k = 0; k < tiles; ++k) {
+            if (k + 1 < tiles) expand(k + 1);
+            const unsigned stage = stage_of(tile0 + k);
+            if (tile0 + k < wave_tiles) {
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[tb][i] = 0.f;
+#pragma unroll
+                    for (int g = tb * kGroups; g < (tb + 1) * kGroups; ++g) {
+                        read_keys(stage, g);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) multiply_key(g, i);
+                    }
+                }
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb) {
+                    mask(tile0 + k, tb);
+#pragma unroll
+                    for (int q = 0; q < 10; ++q) softmax_slice(tb, q);
+                    l_run = __builtin_fmaf(l_run, alpha_of[tb], psum_of[tb]);
+                    rescale(tb);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        read_values(stage, tb, t);
+#pragma unroll
+                        for (int q = 8 * t; q < 8 * t + 8; ++q) multiply_value(tb, q);
+                    }
+                }
+            }
+            if (k + 1 < tiles) {
+                store(k + 1);
+                lds_barrier();
+            }
+        }
+    } else {
+        if (tile0 < tile1) {
+            // (all requests first: a short context waits for them once; and of a context of one or two tiles only what it has)
+            const bool two = tile0 + 1 < tile1, three = tile0 + 2 < tile1;
+            const size_t first = a.map.tile_index(n, hkv, tile0);
+            const typename D_::Codes c0 = D_::request_codes(a.k_codes + first * F::TILE_BYTES, a.v_codes + first * F::TILE_BYTES, tid);
+            typename D_::Codes c1 = {};
+            if (two) {
+                const size_t second = a.map.tile_index(n, hkv, tile0 + 1);
+                c1 = D_::request_codes(a.k_codes + second * F::TILE_BYTES, a.v_codes + second * F::TILE_BYTES, tid);
+            }
+            if (three) {
+                v_index = a.map.tile_index(n, hkv, tile0 + 2);
+                dq.raw = D_::request_codes(a.k_codes + v_index * F::TILE_BYTES, a.v_codes + v_index * F::TILE_BYTES, tid);
+            }
+            D_::store_codes(c0, k_slot(tile0), v_slot(tile0), tid);
+            if (two) D_::store_codes(c1, k_slot(tile0 + 1), v_slot(tile0 + 1), tid);
+            if constexpr (ROPE) {
+                for (int i = tid; i < (int)kAngleBytes / 16; i += NW * 64)
+                    *(lds_q*)(kAngles + (unsigned)i * 16) = reinterpret_cast<const u32x4*>(a.rope_lane_tab)[i];
+            }
+            dq.request_tile_angles(a.rope_tile_tab, tile0, tid);
+            lds_barrier();
+            dq.gather(dq.kw, k_slot(tile0), ck_head, tid, true);
+            dq.gather(dq.vw, v_slot(tile0), cv_head, tid, true);
+            rotate_keys();
+            dq.store_keys(stage_of(tile0), tid);
+            dq.store_values(stage_of(tile0), tid);
+            if (two) {
+                dq.gather(dq.kw, k_slot(tile0 + 1), ck_head, tid, true);
+                dq.request_tile_angles(a.rope_tile_tab, tile0 + 1, tid);
+            }
+            if (three) {
+                lds_barrier();                                  // all have read the first tile's codes
+                if (tid < D_::LOADERS) *(lds_q*)(k_slot(tile0 + 2) + (unsigned)tid * 16) = dq.raw.k;
+            }
+        }
+        prepare_queries();
+        lds_barrier();
+
+        int tile = tile0;
+        for (; tile < min(tile1, wave_tiles); ++tile) {
+            multiply_tile(tile);
+            end_tile(tile);
+        }
+        // tiles behind this wavefront's rows: it still helps the others to theirs
+        for (; tile < tile1; ++tile) {
+            rotate_keys();
+            dq.store_keys(stage_of(tile + 1), tid);
+            load_codes(tile);
+            dq.gather(dq.vw, v_slot(tile + 1), cv_head, tid, tile + 1 < tile1);
+            dq.store_values(stage_of(tile + 1), tid);
+            dq.gather(dq.kw, k_slot(tile + 2), ck_head, tid, tile + 2 < tile1);
+            end_tile(tile);
+        }
     }
 
     // ---- output: lane (rc, kh) holds channels 32 cb + 8 (i / 4) + 4 kh + i % 4 of query rc ----
@@ -621,18 +709,27 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     }
 }
 
-template <int GH, int C, int NW, int B, bool ROPE>
+template <int GH, int C, int NW, int B, bool ROPE, bool SHORT>
 cq_status launch_chunk_variant(const ChunkArgs& a, hipStream_t stream)
 {
-    auto kernel = chunk_attention_kernel<GH, C, NW, B, ROPE>;
+    auto kernel = chunk_attention_kernel<GH, C, NW, B, ROPE, SHORT>;
     static LdsKernelSetup setup;
     if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
     const int qper = a.n_q_heads / a.f.n_kv_heads;
     const int row_blocks = (a.m * qper + NW * 32 - 1) / (NW * 32);
     const unsigned grid = (unsigned)(a.batch * a.n_split * row_blocks * a.f.n_kv_heads);
-    const size_t lds = 2 * kStageBytes(ROPE) + 2 * Dequant<GH, C, NW, B, ROPE>::RAW_STAGE + (ROPE ? kAngleBytes : 0);
+    const size_t lds = 2 * kStageBytes(ROPE) + (SHORT ? kShortTiles(ROPE) : 2) * Dequant<GH, C, NW, B, ROPE>::RAW_STAGE +
+                       (ROPE && !SHORT ? kAngleBytes : 0);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(NW * 64), lds, stream, a);
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
+}
+
+template <int GH, int C, int NW, int B, bool ROPE>
+cq_status launch_chunk_tiles(const ChunkArgs& a, hipStream_t stream)
+{
+    const int n_tiles = (a.t + kTileTokens - 1) / kTileTokens;
+    if ((a.tiles_per_split < n_tiles ? a.tiles_per_split : n_tiles) <= kShortTiles(ROPE)) return launch_chunk_variant<GH, C, NW, B, ROPE, true>(a, stream);
+    return launch_chunk_variant<GH, C, NW, B, ROPE, false>(a, stream);
 }
 
 template <int GH, int C, int B>
@@ -640,11 +737,11 @@ cq_status launch_chunk_rows(const ChunkArgs& a, hipStream_t stream)
 {
     const int rows = a.m * (a.n_q_heads / a.f.n_kv_heads);
     if (a.rope_tile_tab) {
-        if (chunk_rows_per_workgroup(rows) == 128) return launch_chunk_variant<GH, C, 4, B, true>(a, stream);
-        return launch_chunk_variant<GH, C, 8, B, true>(a, stream);
+        if (chunk_rows_per_workgroup(rows) == 128) return launch_chunk_tiles<GH, C, 4, B, true>(a, stream);
+        return launch_chunk_tiles<GH, C, 8, B, true>(a, stream);
     }
-    if (chunk_rows_per_workgroup(rows) == 128) return launch_chunk_variant<GH, C, 4, B, false>(a, stream);
-    return launch_chunk_variant<GH, C, 8, B, false>(a, stream);
+    if (chunk_rows_per_workgroup(rows) == 128) return launch_chunk_tiles<GH, C, 4, B, false>(a, stream);
+    return launch_chunk_tiles<GH, C, 8, B, false>(a, stream);
 }
 
 }  // namespace
