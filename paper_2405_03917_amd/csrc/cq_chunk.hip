@@ -309,13 +309,11 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     const int wave_last_row = min(rb * kRowsPerWg + wave * 32 + 31, rows_total - 1);
     const int wave_tiles = (pos0 + wave_last_row / qper) / kTileTokens + 1;
 
-    const size_t out_row = ((size_t)n * a.m + j) * a.n_q_heads + hq;
-    float* part = a.partials + (out_row * a.n_split + split) * (D + kPartialHeader);
 
     // queries: B operand of S^T = K Q^T, lane (rc, kh) holds Q[row][16 s + 8 kh .. + 7] for the 8 steps
     half8_t qreg[8];
     {
-        const uint16_t* qrow = a.q + out_row * D;
+        const uint16_t* qrow = a.q + (((size_t)n * a.m + j) * a.n_q_heads + hq) * D;
 #pragma unroll
         for (int s = 0; s < 8; ++s) qreg[s] = *reinterpret_cast<const half8_t*>(qrow + 16 * s + 8 * kh);
     }
@@ -356,8 +354,8 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     // softmax of a block in ten slices: the maximum; what follows from it; two probabilities in each of the others.
     // acc[tb][i] is token 8 (i / 4) + 4 kh + i % 4 of the block, query rc
     float psum_of[2], shift_of[2];
-    bool large;                                             // (set below)
-    float mult, early;
+    bool large = false;                                     // (set below: see scores_may_be_large)
+    float mult = scale, early = 1.f, lead = 10.f;
     auto mask = [&](int tile, int tb) {                     // a tile on the causal diagonal of some query of this wavefront
         if (large || tile * kTileTokens + kTileTokens - 1 > pos_first) {
             const int tok0 = tile * kTileTokens + tb * 32 + 4 * kh;
@@ -372,7 +370,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
             for (int i = 0; i < 16; ++i) b = fmaxf(b, acc[tb][i]);
             bmax_of[tb] = b;
         } else if (k == 1) {
-            const float ref_new = fmaxf(ref, softmax_reference(half_wave_max(bmax_of[tb]) * mult));
+            const float ref_new = fmaxf(ref, __builtin_fmaf(half_wave_max(bmax_of[tb]), mult, -lead));
             shift_of[tb] = ref_new == -INFINITY ? 0.f : ref_new;        // nothing visible yet: all weights 0
             alpha_of[tb] = __builtin_amdgcn_exp2f(ref - shift_of[tb]);
             ref = ref_new;
@@ -526,6 +524,25 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
         if (tile + 1 < tile1) dq.store_values(next_stage, tid);
     };
 
+    // (The squares of the queries' norms are the diagonal of Q Q^T, and none of its elements is larger: products on
+    // the idle matrix cores, where the first tile's centroids are waited for.  As vector instructions in front of the
+    // loop they cost 1 % of a call over five tiles.)
+    auto bound_scores = [&] {
+        float16_t g;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) g[i] = 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) g = __builtin_amdgcn_mfma_f32_32x32x16_f16(qreg[s], qreg[s], g, 0, 0, 0);
+        float q2 = g[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) q2 = fmaxf(q2, g[i]);
+        // (below 2^26 the roundings of the largest score and of ref are 2 each at most, and the exponent of the largest
+        // probability 10 to within 4; from there on 10 would be lost in ref's)
+        large = scores_may_be_large(q2, scale, 0x1p26f);
+        mult = large ? 1.f : scale;
+        early = large ? scale : 1.f;
+        lead = large ? 0.f : 10.f;
+    };
     const unsigned flip = a.scale_log2e < 0.f ? 0x80008000u : 0u;
     auto prepare_queries = [&] {
 #pragma unroll
@@ -535,16 +552,6 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
             u32x4 w = __builtin_bit_cast(u32x4, qreg[s]) ^ flip;
             asm volatile("" : "+v"(w));
             qreg[s] = __builtin_bit_cast(half8_t, w);
-        }
-        // Scores that cannot reach 2^24 are scaled inside the exponent; others, whose rounding could carry the largest
-        // probability out of fp16's range there, before their maximum is taken
-        {
-            float q2 = 0.f;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) q2 = sum_of_squares(qreg[s], q2);
-            large = scores_may_be_large(q2 * 2.f, scale);       // (the lane holds half of its query)
-            mult = large ? 1.f : scale;
-            early = large ? scale : 1.f;
         }
     };
 
@@ -577,6 +584,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
                 if (k < tiles) D_::store_codes(codes[k], kRaw + (unsigned)k * kRawStageBytes, kRaw + (unsigned)k * kRawStageBytes + kTileRaw, tid);
             lds_barrier();
             expand(0);
+            bound_scores();
             store(0);
         }
         prepare_queries();
@@ -642,6 +650,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
             lds_barrier();
             dq.gather(dq.kw, k_slot(tile0), ck_head, tid, true);
             dq.gather(dq.vw, v_slot(tile0), cv_head, tid, true);
+            bound_scores();
             rotate_keys();
             dq.store_keys(stage_of(tile0), tid);
             dq.store_values(stage_of(tile0), tid);
@@ -676,7 +685,13 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
 
     // ---- output: lane (rc, kh) holds channels 32 cb + 8 (i / 4) + 4 kh + i % 4 of query rc ----
     const float l = l_run + __shfl_xor(l_run, 32);
-    if (!valid) return;
+    // (the row's place is formed again: held through the loop, it cost registers that spill)
+    int tid_o = threadIdx.x;
+    asm volatile("" : "+v"(tid_o));
+    const int row_o = rb * kRowsPerWg + (tid_o >> 6) * 32 + (tid_o & 31), kh_o = tid_o >> 5 & 1;
+    if (row_o >= rows_total) return;
+    const int j_o = row_o / qper;
+    const size_t out_row = ((size_t)n * a.m + j_o) * a.n_q_heads + hkv * qper + (row_o - j_o * qper);
     if (a.n_split == 1) {
         const float inv = 1.f / l;
         uint16_t* orow = a.out + out_row * D;
@@ -687,10 +702,11 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
                 half4_t h;
 #pragma unroll
                 for (int b = 0; b < 4; ++b) h[b] = (_Float16)(o[cb][4 * i4 + b] * inv);
-                *reinterpret_cast<half4_t*>(orow + 32 * cb + 8 * i4 + 4 * kh) = h;
+                *reinterpret_cast<half4_t*>(orow + 32 * cb + 8 * i4 + 4 * kh_o) = h;
             }
     } else {
-        if (kh == 0) {
+        float* part = a.partials + (out_row * a.n_split + split) * (D + kPartialHeader);
+        if (kh_o == 0) {
             part[0] = ref;
             part[1] = l;
         }
@@ -703,7 +719,7 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
                 v.y = o[cb][4 * i4 + 1];
                 v.z = o[cb][4 * i4 + 2];
                 v.w = o[cb][4 * i4 + 3];
-                float* dst = part + kPartialHeader + 32 * cb + 8 * i4 + 4 * kh;
+                float* dst = part + kPartialHeader + 32 * cb + 8 * i4 + 4 * kh_o;
                 dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
             }
     }

@@ -42,6 +42,9 @@ constexpr unsigned kLdsBytes = kMergeBase + kWaves * kRows * kORow;
 static_assert(kLdsBytes == 160 * 1024, "all of a CU's LDS");
 __device__ __forceinline__ half8_t lds_half8(unsigned a) { return *(__attribute__((address_space(3))) half8_t*)(a); }
 __device__ __forceinline__ half4_t lds_half4(unsigned a) { return *(__attribute__((address_space(3))) half4_t*)(a); }
+// The exponent that probabilities are relative to where the largest score (base 2) is m: 12 below m, so that
+// they fill fp16's range; m itself where 12 is lost in its rounding.
+__device__ __forceinline__ float softmax_reference(float m) { return m - (fabsf(m) < 0x1p22f ? 12.f : 0.f); }
 // maximum / sum over the four lanes l % 16 + 16 b
 __device__ __forceinline__ float across_max(float v)
 {
@@ -186,15 +189,14 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
 #pragma unroll
             for (int s = 0; s < 4; ++s) qreg[s] = -qreg[s];
         }
+        // (no element of Q Q^T is larger than the largest of its diagonal, the squares of the queries' norms)
+        float4_t g = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) g = __builtin_amdgcn_mfma_f32_16x16x32_f16(qreg[s], qreg[s], g, 0, 0, 0);
+        const bool large = scores_may_be_large(fmaxf(fmaxf(g[0], g[1]), fmaxf(g[2], g[3])), scale, 0x1p24f);
         int tile = it.tile0 + slice;
         unpack();
         request(it, tile + cs);
-        // Scores that cannot reach 2^24 are scaled inside the exponent; others, whose rounding could carry the
-        // largest probability out of fp16's range there, before their maximum is taken
-        float q2 = 0.f;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) q2 = sum_of_squares(qreg[s], q2);
-        const bool large = scores_may_be_large(q2 * 4.f, scale);
         const float mult = large ? 1.f : scale, early = large ? scale : 1.f;
 #pragma unroll 1
         for (; tile < it.tile1; tile += cs) {

@@ -77,22 +77,14 @@ struct CodePick {
     }
 };
 
-// The exponent that probabilities are relative to where the largest score (base 2) is m: 12 below m, so that
-// they fill fp16's range; m itself where 12 is lost in its rounding.
-__device__ __forceinline__ float softmax_reference(float m) { return m - (fabsf(m) < 0x1p22f ? 12.f : 0.f); }
-__device__ __forceinline__ float sum_of_squares(half8_t v, float sum)
+// Whether a score of some query of this wavefront could reach `limit` (wavefront-uniform): |q|^2 <= q2, and a key of
+// 128 channels is no longer than 65504 sqrt(128).  Scores that cannot are scaled inside the exponent of the
+// probability, fma(x, scale, -ref); others before their maximum is taken: in the exponent, half a unit of a large
+// score could carry the largest probability out of fp16's range.
+__device__ __forceinline__ bool scores_may_be_large(float q2, float scale, float limit)
 {
-    const u32x4 w = __builtin_bit_cast(u32x4, v);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, w[i]), __builtin_bit_cast(half2_t, w[i]), sum, false);
-    return sum;
-}
-// Whether a score of some query of this wavefront could reach 2^24 (wavefront-uniform): q2 is at least the sum of
-// the squares of the lane's query, a key of 128 channels is no longer than 65504 sqrt(128).
-__device__ __forceinline__ bool scores_may_be_large(float q2, float scale)
-{
-    constexpr float kLimit = 0x1p24f / 65504.f;
-    return __builtin_amdgcn_ballot_w64(!(q2 * (scale * scale) < kLimit * kLimit / 128.f)) != 0;
+    const float l = limit / 65504.f;
+    return __builtin_amdgcn_ballot_w64(!(q2 * (scale * scale) < l * l / 128.f)) != 0;
 }
 
 // LDS address of the entry of code byte k of z: code x entry size + `base`, the lane's part (codebook,
