@@ -31,6 +31,11 @@
 // share is at most 0.0068 sqrt(|x'|^2 + |c'|max^2) (`slack`).  That norm, `reach`, goes into M: with
 // M_max there a group with a few long centroids sent three times as many tokens to the re-do.
 //
+// Equal centroids (more centroids than distinct points, dead channels, coarse values) would tie for every token
+// near them; all but the first of them leave the scan, found by a hash table when the group's centroids are read.
+// 4096 tokens of 40 distinct points, 128 groups of 8 channels, per iteration: 76 us in the direct search of all, 419
+// when every tie was re-done, 60 now; half of the channels dead: 115, 434, 51.
+//
 // What bounds it: the vector ALU (547 instructions per 64 tokens and group: 208 in the scan, 150 in
 // the winner's eight, the rest merge, bound, sums and re-dos; the direct search took 2 c + 3 per
 // token and centroid).  The group's centroids sit in registers as matrix operands (32 registers)
@@ -54,6 +59,7 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 constexpr int kLloydWaves = 4;
 constexpr int kK = 256;                 // centroids per group
 constexpr int kNBlk = kK / 32;
+constexpr int kHashSlots = 1024;        // for finding equal centroids
 
 template <int CTRL>
 __device__ __forceinline__ unsigned dpp_mov(unsigned v)
@@ -139,6 +145,8 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     __shared__ __attribute__((aligned(16))) float cs[kK / 4 * QS];
     __shared__ __attribute__((aligned(16))) float norms[kK];
     __shared__ unsigned c2w[kLloydWaves];
+    __shared__ unsigned first_of[kHashSlots];
+    __shared__ unsigned kept[kLloydWaves];
     __shared__ unsigned long long sums[kK * SW];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -150,16 +158,18 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
 
     // ---- the group's centroids: fp32 in LDS, scale, norms, matrix operands
     static_assert(kLloydWaves * 64 == kK, "one centroid per thread");
-    float n2 = 0.f;
-    {
-        float c[C];
+    float n2 = 0.f, own[C];
+    unsigned hash = 0;
 #pragma unroll
-        for (int i = 0; i < C; ++i) {
-            c[i] = cent[(size_t)tid * C + i];
-            n2 = __builtin_fmaf(c[i], c[i], n2);
-            cs[(tid >> 2) * QS + (tid & 3) * C + i] = c[i];
-        }
+    for (int i = 0; i < C; ++i) {
+        own[i] = cent[(size_t)tid * C + i];
+        n2 = __builtin_fmaf(own[i], own[i], n2);
+        cs[(tid >> 2) * QS + (tid & 3) * C + i] = own[i];
+        hash = (hash ^ __float_as_uint(own[i])) * 0x9e3779b1u;
+        hash ^= hash >> 15;
     }
+    hash = (hash * 0x85ebca6bu) / (0xffffffffu / kHashSlots + 1u);
+    for (int i = tid; i < kHashSlots; i += kLloydWaves * 64) first_of[i] = ~0u;
     const unsigned wmax = wave_extreme_u32<true>(__float_as_uint(n2));
     if (lane == 0) c2w[wave] = wmax;
     for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = 0ull;
@@ -167,18 +177,34 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     unsigned c2bits = 0;
 #pragma unroll
     for (int w = 0; w < kLloydWaves; ++w) c2bits = c2w[w] > c2bits ? c2w[w] : c2bits;
+    atomicMin(&first_of[hash], (unsigned)tid);
     c2bits = (unsigned)__builtin_amdgcn_readfirstlane((int)c2bits);
     const int e = (int)((c2bits >> 23) & 0xffu) - 127;
     int s = (13 - e) >> 1;
-    const bool group_direct = s > 30 || s < -13;        // (nearly) all-zero centroids (or not finite)
+    const bool extreme = s > 30 || s < -13;             // (nearly) all-zero centroids (or not finite)
     s = s > 30 ? 30 : (s < -13 ? -13 : s);
     const int s1 = s >> 1, s2 = s - s1;
     const unsigned m1b = (unsigned)(15 + s1) << 10, m2b = (unsigned)(15 + s2) << 10;      // fp16 2^s1, 2^s2
     const half2_t m1 = __builtin_bit_cast(half2_t, m1b | (m1b << 16)), m2 = __builtin_bit_cast(half2_t, m2b | (m2b << 16));
     const float f1 = __uint_as_float((unsigned)(127 + s) << 23), f2 = f1 * f1;
     const float c2s = __uint_as_float(c2bits) * f2;     // the largest |c'|^2
-    norms[tid] = group_direct ? 0.f : -0.5f * (n2 * f2);
     __syncthreads();
+    // A centroid equal to an earlier one can never be the choice (lowest index among equals) and would only tie with
+    // it, so it leaves the scan.  (An earlier one behind another of the same hash stays unseen: its ties go to the
+    // re-do like all others.)
+    const int twin = (int)first_of[hash];
+    bool again = twin < tid;
+#pragma unroll
+    for (int i = 0; i < C; ++i) again = again && cs[(twin >> 2) * QS + (twin & 3) * C + i] == own[i];
+    norms[tid] = again ? -1.0e30f : (extreme ? 0.f : -0.5f * (n2 * f2));
+    {
+        const unsigned long long own_ones = __ballot(!again);
+        if (lane == 0) kept[wave] = (unsigned)__popcll(own_ones);
+    }
+    __syncthreads();
+    static_assert(kLloydWaves == 4, "the four counts");
+    // (a single centroid wins every scan, whatever its size)
+    const bool group_direct = extreme && __builtin_amdgcn_readfirstlane((int)(kept[0] + kept[1] + kept[2] + kept[3])) > 1;
 
     // A operands: lane l holds row l % 32 of each block of 32 centroids; lanes below 32 the high
     // parts, the others the low parts (C = 2: both in the lower lanes).  D's registers: row
@@ -336,16 +362,42 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
         // (many of them: duplicated points, dead channels) every lane its own token
         unsigned long long todo = __ballot(unsure);
         if (__popcll(todo) > 24) {
-            float c[C];
-            cent_at(0, c);
-            float db = dist2<C>(x, c);
-            int ag = 0;
-#pragma unroll 2
-            for (int j = 1; j < kK; ++j) {
-                cent_at(j, c);
-                const float d = dist2<C>(x, c);
-                ag = d < db ? j : ag;
-                db = d < db ? d : db;
+            // four centroids at a time, each with a nearest so far of its own: nothing waits for its neighbour
+            float db[4];
+            int fb[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                db[k] = 3.0e38f;
+                fb[k] = 0;
+            }
+#pragma unroll (C == 8 ? 1 : 2)
+            for (int f = 0; f < kK / 4; ++f) {
+                float c[4][C], d[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) cent_at(4 * f + k, c[k]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) d[k] = 0.f;
+#pragma unroll
+                for (int i = 0; i < C; ++i)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float e = x[i] - c[k][i];
+                        d[k] = __builtin_fmaf(e, e, d[k]);
+                    }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    fb[k] = d[k] < db[k] ? f : fb[k];
+                    db[k] = fminf(db[k], d[k]);
+                }
+            }
+            int ag = 4 * fb[0];
+            float dg = db[0];
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {               // (equal distances: the lowest index)
+                const int j = 4 * fb[k] + k;
+                const bool nearer = db[k] < dg || (db[k] == dg && j < ag);
+                ag = nearer ? j : ag;
+                dg = nearer ? db[k] : dg;
             }
             arg = unsure ? ag : arg;
         } else {

@@ -173,3 +173,39 @@ def test_lloyd_on_the_matrix_cores_decides_like_the_direct_form(c, n, weighted, 
     torch.cuda.synchronize()
     assert np.array_equal(out["assignment"].cpu().numpy().view(np.uint16), assign)
     assert np.array_equal(out["centroids_f32"].cpu().numpy(), cent)
+
+
+@pytest.mark.parametrize("c,n,weighted", [(8, 700, False), (8, 300, True), (4, 4096, False), (2, 1500, True), (2, 3000, False)])
+@pytest.mark.parametrize("centroids", ["coarse", "few", "pairs", "one", "zero", "signed zeros", "one large"])
+def test_equal_centroids_leave_the_scan(c, n, weighted, centroids):
+    """Centroids equal to an earlier one are never chosen: integers (ties at equal distances too), few
+    distinct points, every centroid twice in shuffled places, all equal, all zero (of both signs)."""
+    fmt = cq.CQFormat(c, 8, 128, 1)
+    G, K = fmt.groups, 256
+    rng = np.random.default_rng(c + n)
+    x = _data(70 + c, n, 128).astype(np.float32)
+    if centroids == "coarse":
+        x = np.round(x)
+    elif centroids == "few":
+        x = x[rng.integers(0, min(n, 30), size=n)]
+    elif centroids == "one large":
+        x *= 60000.0 / np.abs(x).max()
+    x = x.astype(np.float16)
+    init = np.stack([x.reshape(n, G, c)[rng.choice(n, size=K, replace=True), g] for g in range(G)]).astype(np.float32)
+    if centroids == "pairs":
+        init = np.concatenate([init[:, :128], init[:, :128]], axis=1)[:, rng.permutation(K)]
+    elif centroids.startswith("one"):
+        init[:] = init[:, 7:8]
+    elif centroids in ("zero", "signed zeros"):
+        init[:] = 0.0
+        if centroids == "signed zeros":
+            init[:, ::3] = -0.0
+    init = np.ascontiguousarray(init)
+    w = _weights(n + 1, n, G) if weighted else None
+    for iters in (1, 3):
+        cent, assign, _ = KO.lloyd(x, c, init, iters, w)
+        out = cq.cq_kmeans_fit(torch.from_numpy(x).cuda(), fmt, iters, init_centroids=torch.from_numpy(init).cuda(),
+                               weights=None if w is None else torch.from_numpy(w).cuda(), want_assignment=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(out["assignment"].cpu().numpy().view(np.uint16), assign)
+        assert np.array_equal(out["centroids_f32"].cpu().numpy(), cent)
