@@ -694,14 +694,15 @@ cq_status run_lloyd(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t 
     const int G = a.f.groups, K = a.f.k, n = a.n;
     if constexpr (C >= 2) {
         if (K == 256) {
-            // the nearest-centre distances are done with: their room holds the sums of token splits
+            // the nearest-centre distances are done with, and the assignment goes to the caller: their room holds the
+            // sums of token splits, with the weights' in front of it where all are one
             KMeansLloyd l;
             l.xg = ws.xg;
             l.wq = a.weights ? ws.wq : nullptr;
             l.cent = ws.cent;
             l.assign = a.assign_out;
-            l.scratch = ws.dmin;
-            l.scratch_bytes = sizeof(float) * (size_t)G * n;
+            l.scratch = a.weights ? static_cast<void*>(ws.dmin) : ws.wq;
+            l.scratch_bytes = (size_t)(reinterpret_cast<char*>(ws.assign + (size_t)G * n) - static_cast<char*>(l.scratch));
             l.groups = G;
             l.n = n;
             l.n_iter = a.n_iter;

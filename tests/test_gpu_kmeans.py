@@ -143,7 +143,7 @@ def test_picks_at_the_edges_of_the_register_resident_rounds(n, c, weighted):
 
 
 @pytest.mark.parametrize("c,n,weighted", [(8, 63, False), (8, 65, True), (4, 2047, False), (8, 5000, False), (4, 9217, True),
-                                          (2, 20001, False)])
+                                          (2, 20001, False), (8, 12001, True)])
 @pytest.mark.parametrize("data", ["plain", "tiny", "large", "far points", "dead groups", "duplicates"])
 def test_lloyd_on_the_matrix_cores_decides_like_the_direct_form(c, n, weighted, data):
     """Token splits, partial tiles, and data that leaves the filter: all-zero groups, duplicated
