@@ -265,24 +265,27 @@ __global__ __launch_bounds__(kPPThreads) void kmeanspp_kernel(const uint16_t* __
     }
 }
 
-// The same picks with the distances to the nearest centre (and the weights) in registers, for up to
-// 32 rounds of 1024 tokens: the form above walks three arrays in L2 and HBM per pick, and the walk
+// The same picks with the distances to the nearest centre in registers, for up to 32 rounds of 1024
+// tokens: the form above walks three arrays in L2 and HBM per pick, and the walk
 // of one wavefront to the chosen token is a chain of 32 reductions.  Here wavefront w still owns
 // the contiguous tokens [w W, (w + 1) W); a token's slice x is read again for every pick -- from
 // registers (the first kRegRounds rounds), from LDS (the next kLdsRounds) or from memory (the
 // rest, requested before the pick is known) -- and a pick is three barriers: the largest
 // weighted distance, the wavefronts' masses, the token.  The owner of the r-th unit of mass keeps
-// its mass in four sums of 8 rounds, so the search is 4 + 8 independent reductions and one scan.
-// 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 7.0 ms
-// (weighted, 64 more registers' worth of weights: 30.7 -> 18 ms); 1500 tokens, 256 groups of 4:
-// 1.3 -> 0.9 ms.  Bound by the vector ALU now (busy 74 %).
+// its mass in up to four sums, so the search is 4 + R / 4 independent reductions and one scan.
+// Weights sit in registers too, 32 rounds of them in LDS (as 32 more registers they spilled 50 to 61).
+// 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 6.7 ms, weighted 30.7 -> 9.0; 1500 tokens, 256
+// groups of 4: 1.05 -> 0.71 ms; 100 tokens 0.54 -> 0.56 (two barriers' worth of other wavefronts' numbers).
+// Slices of 4 (of 2: 8) weighted tokens per lane in registers instead of 2 (4), 32 rounds: 8 channels 11.0 -> 9.0 ms
+// at 512 groups, 4 channels 3.7 -> 4.6 ms at 256 groups (spills).
 constexpr int kPPRounds = 32;
-constexpr int kPPSegs = 4;
 constexpr int min_of(int a, int b) { return a < b ? a : b; }
+template <bool W, int R>
+constexpr bool kPPWeightsInLds = W && R == kPPRounds;
 template <int C, bool W, int R>
-constexpr int kPPRegRounds = min_of(R, (W ? 8 : 16) / (C / 2));
+constexpr int kPPRegRounds = min_of(R, (W && !(C == 8 && kPPWeightsInLds<W, R>) ? 8 : 16) / (C / 2));
 template <int C, bool W, int R>
-constexpr int kPPLdsRounds = min_of(R - kPPRegRounds<C, W, R>, 72 / C);     // at most 144 KB
+constexpr int kPPLdsRounds = min_of(R - kPPRegRounds<C, W, R>, (kPPWeightsInLds<W, R> ? 15 : 72) / C);     // at most 144 KB, or 30 next to the weights
 
 // floor(m 2^sh) of an integer below 2^46 (the result fits 62 bits)
 __device__ __forceinline__ unsigned long long shift_floor(unsigned long long m, int sh)
@@ -303,9 +306,12 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
     constexpr int kRegRounds = kPPRegRounds<C, W, R>;
     constexpr int kLdsRounds = kPPLdsRounds<C, W, R>;
     constexpr int kHeld = kRegRounds + kLdsRounds;
+    constexpr bool WL = kPPWeightsInLds<W, R>, WR = W && !WL;
+    constexpr int kSegs = min_of(R, 4);
     constexpr int kBatch = 4;                                // rounds requested together
-    extern __shared__ __attribute__((aligned(16))) unsigned xl[];       // [kLdsRounds][1024][XW], then the exchange slots
-    unsigned long long* const wave_tot = reinterpret_cast<unsigned long long*>(xl + (size_t)kLdsRounds * kPPThreads * XW);
+    extern __shared__ __attribute__((aligned(16))) unsigned xl[];       // [kLdsRounds][1024][XW], the weights [R][1024] if here, the exchange slots
+    unsigned* const wl = xl + (size_t)kLdsRounds * kPPThreads * XW;
+    unsigned long long* const wave_tot = reinterpret_cast<unsigned long long*>(wl + (WL ? R * kPPThreads : 0));
     unsigned long long* const wave_max = wave_tot + NWAVE;
     int& pick_sh = *reinterpret_cast<int*>(wave_max + NWAVE);
 
@@ -335,14 +341,19 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
 
     unsigned dmin[R];                                        // bits of the fp32 distance (they order like it); 0 where
                                                              // there is no token: no mass, never the largest
-    unsigned wr[W ? R : 1];
+    unsigned wr[WR ? R : 1];
+    auto weight = [&](int p) -> unsigned { return WL ? wl[p * kPPThreads + tid] : (W ? wr[WR ? p : 0] : 1u); };
     unsigned xr[kRegRounds][XW];
 #pragma unroll
     for (int p = 0; p < R; ++p) {
         const int i = t0 + p * 64 + lane;
         const bool there = p < rounds && i < n;
         dmin[p] = there ? 0x7f800000u : 0u;
-        if constexpr (W) wr[p] = there ? wq_all[(size_t)g * n + i] : 0u;
+        if constexpr (W) {
+            const unsigned w = there ? wq_all[(size_t)g * n + i] : 0u;
+            if constexpr (WL) wl[p * kPPThreads + tid] = w;
+            else wr[p] = w;
+        }
         if (p < kRegRounds) {
             load_words(p, xr[p < kRegRounds ? p : 0]);
         } else if (p < kHeld) {
@@ -362,18 +373,21 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
         return shift_floor(W ? (unsigned long long)w * m : (unsigned long long)m, sh);
     };
     auto draw = [&](uint64_t word, int kq) {
-        unsigned long long seg[kPPSegs];
+        unsigned long long seg[kSegs];
 #pragma unroll
-        for (int s = 0; s < kPPSegs; ++s) {
+        for (int s = 0; s < kSegs; ++s) {
             seg[s] = 0;
 #pragma unroll
-            for (int k = 0; k < R / kPPSegs; ++k) {
-                const int p = s * (R / kPPSegs) + k;
-                seg[s] += mass_of(dmin[p], W ? wr[W ? p : 0] : 1u, kq);
+            for (int k = 0; k < R / kSegs; ++k) {
+                const int p = s * (R / kSegs) + k;
+                seg[s] += mass_of(dmin[p], weight(p), kq);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        const unsigned long long wtot = wave_sum_u64(seg[0] + seg[1] + seg[2] + seg[3]);
+        unsigned long long mass = seg[0];
+#pragma unroll
+        for (int s = 1; s < kSegs; ++s) mass += seg[s];
+        const unsigned long long wtot = wave_sum_u64(mass);
         if (lane == 0) wave_tot[wave] = wtot;
         __syncthreads();
         unsigned long long off = 0, total = 0;
@@ -388,25 +402,29 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
             unsigned long long run = off;
             int s_hit = 0;
             {
-                unsigned long long st[kPPSegs];
+                unsigned long long st[kSegs];
 #pragma unroll
-                for (int s = 0; s < kPPSegs; ++s) st[s] = wave_sum_u64(seg[s]);
+                for (int s = 0; s < kSegs; ++s) st[s] = wave_sum_u64(seg[s]);
 #pragma unroll
-                for (int s = 0; s + 1 < kPPSegs; ++s)
+                for (int s = 0; s + 1 < kSegs; ++s)
                     if (s_hit == s && run + st[s] <= r) { run += st[s]; s_hit = s + 1; }
             }
             s_hit = __builtin_amdgcn_readfirstlane(s_hit);
-            constexpr int RS = R / kPPSegs;
+            constexpr int RS = R / kSegs;
             unsigned sd[RS], sw[RS];
 #pragma unroll
-            for (int s = 0; s < kPPSegs; ++s)
+            for (int s = 0; s < kSegs; ++s)
                 if (s_hit == s) {
 #pragma unroll
                     for (int k = 0; k < RS; ++k) {
                         sd[k] = dmin[s * RS + k];
-                        sw[k] = W ? wr[W ? s * RS + k : 0] : 1u;
+                        if constexpr (!WL) sw[k] = weight(s * RS + k);
                     }
                 }
+            if constexpr (WL) {
+#pragma unroll
+                for (int k = 0; k < RS; ++k) sw[k] = weight(s_hit * RS + k);
+            }
             unsigned long long q[RS], qt[RS];
 #pragma unroll
             for (int k = 0; k < RS; ++k) {
@@ -481,7 +499,7 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
 #pragma unroll
             for (int i2 = 0; i2 < XW; ++i2)
                 w[i2] = p < kRegRounds ? xr[p < kRegRounds ? p : 0][i2] : xl[((p - kRegRounds) * kPPThreads + tid) * XW + i2];
-            visit(w, dmin[p], W ? wr[W ? p : 0] : 1u);
+            visit(w, dmin[p], weight(p));
             __builtin_amdgcn_sched_barrier(0);               // (one round's widened channels live at a time)
         }
 #pragma unroll
@@ -493,7 +511,7 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
             }
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                if (p + k < R) visit(xb[k], dmin[p + k < R ? p + k : 0], W ? wr[W && p + k < R ? p + k : 0] : 1u);
+                if (p + k < R) visit(xb[k], dmin[p + k < R ? p + k : 0], weight(p + k < R ? p + k : 0));
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (p + kBatch < R) {
@@ -656,7 +674,9 @@ template <int C, bool W, int R>
 cq_status launch_kmeanspp_resident(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
 {
     auto kernel = kmeanspp_resident_kernel<C, W, R>;
-    constexpr size_t lds = (size_t)kPPLdsRounds<C, W, R> * kPPThreads * C * 2 + (2 * (kPPThreads / 64) + 1) * sizeof(uint64_t);
+    constexpr size_t lds = (size_t)kPPLdsRounds<C, W, R> * kPPThreads * C * 2 + (kPPWeightsInLds<W, R> ? (size_t)R * kPPThreads * 4 : 0) +
+                           (2 * (kPPThreads / 64) + 1) * sizeof(uint64_t);
+    static_assert(lds <= 160 * 1024, "one workgroup's LDS");
     static LdsKernelSetup setup;
     if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
     hipLaunchKernelGGL(kernel, dim3(a.f.groups), dim3(kPPThreads), lds, st, ws.xg, ws.wq, a.rnd, a.picks, ws.cent, a.n, a.f.k,
@@ -664,10 +684,12 @@ cq_status launch_kmeanspp_resident(const KMeansArgs& a, const KMeansWorkspace& w
     return launch_ok() ? CQ_OK : CQ_ERR_HIP;
 }
 
-// rounds of 1024 tokens: the smallest of the four unrolled forms that holds the call's tokens
+// rounds of 1024 tokens: the smallest of the six unrolled forms that holds the call's tokens
 template <int C, bool W>
 cq_status launch_kmeanspp_rounds(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
 {
+    if (a.n <= kPPThreads) return launch_kmeanspp_resident<C, W, 1>(a, ws, st);
+    if (a.n <= kPPThreads * 2) return launch_kmeanspp_resident<C, W, 2>(a, ws, st);
     if (a.n <= kPPThreads * 4) return launch_kmeanspp_resident<C, W, 4>(a, ws, st);
     if (a.n <= kPPThreads * 8) return launch_kmeanspp_resident<C, W, 8>(a, ws, st);
     if (a.n <= kPPThreads * 16) return launch_kmeanspp_resident<C, W, 16>(a, ws, st);

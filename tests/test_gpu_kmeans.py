@@ -126,11 +126,12 @@ def test_strided_rows_and_repeatability():
     assert torch.equal(a, b_) and torch.equal(b_, c_)
 
 
-@pytest.mark.parametrize("n", [4096, 4097, 8193, 16385, 32768, 32769])
-@pytest.mark.parametrize("c,weighted", [(8, False), (4, True)])
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 2049, 4096, 4097, 8193, 16385, 32768, 32769])
+@pytest.mark.parametrize("c,weighted", [(c, w) for c in (8, 4, 2) for w in (False, True)])
 def test_picks_at_the_edges_of_the_register_resident_rounds(n, c, weighted):
-    """1024 tokens per round; forms for 4, 8, 16 and 32 rounds in registers, memory beyond."""
-    fmt = cq.CQFormat(c, 4 if c == 4 else 8, 128, 1)         # (16 picks per group suffice for c = 4)
+    """1024 tokens per round; forms for 1, 2, 4, 8, 16 and 32 rounds in registers, memory beyond; every form keeps
+    its tokens (and weights) in other parts of registers, LDS and memory."""
+    fmt = cq.CQFormat(c, 8 if c == 8 else 4, 128, 1)         # (16 picks per group suffice; groups of 8 have 256 centroids)
     G, K = fmt.groups, 1 << fmt.b
     x = _data(50 + c, n, 128)
     rnd = _rnd(n + c, G, K)
