@@ -11,7 +11,10 @@
 // evaluated once more, with packed dot products in fp32.  (Maxima of four cost 1.1 per score and
 // half the second look; K and V of 32768 tokens x 4096 channels, maxima of four -> eight, with the
 // operands of several tiles' scans kept in registers and the bound below: CQ-8c8b 686 -> 600 us,
-// 4c8b 971 -> 860, 64 x 512 tokens of 2c8b 2.0 -> 1.6 ms; same codes.)
+// 4c8b 971 -> 860, 64 x 512 tokens of 2c8b 2.0 -> 1.6 ms; same codes.)  CQ-8c10b with a tile per workgroup, a single
+// wavefront that mostly waits for its codebook, keeps maxima of four, with five packed bits: eight second looks
+// and the records' places (below) cost it more than the scan saves (4 x 512 tokens x 4096 channels: 416 / 430 us; four
+// wavefronts, 16384 tokens: 960 / 876).
 //
 // Scaling.  A group whose largest |c_j|^2 is small is multiplied (centroids and tokens alike)
 // by a power of two 2^s, s >= 0, that brings the largest scaled |c'|^2 into [2^12, 2^14): the
@@ -28,7 +31,8 @@
 // units in its last place (1.9): 3.9 in all.  A score of the winner's eight from the vector ALU:
 // |c|^2 (0.5), c / 2 + 2 roundings to fp32 (0.4), three packed bits (0.9): 1.8.  The best is always
 // of the second kind, the runner-up of either, so the two compare correctly whenever they differ by
-// more than 5.7 units; the test below uses 8 = 2^-17 M.  (If rounding made the wrong eight win, the
+// more than 5.7 units; the test below uses 8 = 2^-17 M.  (Maxima of four: five packed bits 3.9, 5.9 in all, and 1.4
+// for a second look at four, 7.3 together; the test uses 10.  If rounding made the wrong eight win, the
 // true best's maximum is the runner-up and lies within 5.7 units of the reported best: the test
 // fails and the pair is re-done.)  The |c'| in M is the longest of the group or, if that is less,
 // the longest that could be as near as the winner: |x'| + its distance d, d^2 = |x'|^2 - 2 x score
@@ -68,14 +72,14 @@ struct Aug {
     using vec_t = std::conditional_t<C == 8, half8_t, half4_t>;
 };
 
-// Place of centroid j's record among the records in LDS.  The records of 256 bytes (a row of all banks)
-// change places by the number of their block of 16: the lanes of level 2 read records with the same
+// Place of centroid j's record among the records in LDS.  Where level 2 looks at eight, the records of 256
+// bytes (a row of all banks) change places by the number of their block of 16: its lanes read records with the same
 // number modulo 16 from different blocks, which would otherwise all start in the same bank.
 // A matrix operand (32 consecutive records) is permuted within its rows.
-template <int C>
+template <int C, int PER>
 __device__ __forceinline__ int record(int j)
 {
-    constexpr int M = 128 / Aug<C>::KDIM - 1;           // records per row - 1
+    constexpr int M = PER == 8 ? 128 / Aug<C>::KDIM - 1 : 0;        // records per row - 1
     return j ^ ((j >> 4) & M);
 }
 
@@ -219,7 +223,10 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     constexpr int NT = NW * 64;
     constexpr int KDIM = A::KDIM, HALF = A::HALF;
     constexpr int NBLK = K / 32;                     // 32-centroid blocks
-    constexpr int NSB = NBLK / 8;                    // runs of 8 blocks (the packed number of an eight has 4 bits)
+    // scores per maximum of level 1, and the mantissa bits that hold its number among the 128 / PER of 8 blocks
+    constexpr int PER = B == 8 || NW > 1 ? 8 : 4;
+    constexpr unsigned PACK = 128u / PER - 1u;
+    constexpr int NSB = NBLK / 8;                    // runs of 8 blocks (what a packed number can tell apart)
     constexpr int P = GH / 16;
     constexpr int TILE_LOW = kTileTokens * GH;
     constexpr int TILE_BYTES = kTileTokens * GH * B / 8;
@@ -314,7 +321,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
             const _Float16 zero = (_Float16)0.0f;
             const unsigned w12 = __builtin_bit_cast(unsigned, half2_t{h1, h2});
             const unsigned w30 = __builtin_bit_cast(unsigned, half2_t{h3, zero});
-            uint4* dst = reinterpret_cast<uint4*>(&cba[buf][record<C>(j) * KDIM]);
+            uint4* dst = reinterpret_cast<uint4*>(&cba[buf][record<C, PER>(j) * KDIM]);
             if constexpr (C == 8) {
                 dst[0] = make_uint4(cs[0], cs[1], cs[2], cs[3]);
                 dst[1] = make_uint4(w12, w30, 0u, 0u);
@@ -381,7 +388,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
         constexpr float slack = 0.01f;
         if (g + 1 < g_end) fetch(g + 1);
         auto operand = [&](int blk) {
-            return *reinterpret_cast<const vec_t*>(&cba[buf][record<C>(blk * 32 + (lane & 31)) * KDIM + (lane >> 5) * HALF]);
+            return *reinterpret_cast<const vec_t*>(&cba[buf][record<C, PER>(blk * 32 + (lane & 31)) * KDIM + (lane >> 5) * HALF]);
         };
         // several tiles per wavefront: the group's records as matrix operands stay in registers for all of them
         vec_t held[TPW > 1 ? NBLK : 1];
@@ -461,20 +468,34 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                     for (int b8 = 0; b8 < 8; ++b8) {
                         const int blk = sb * 8 + b8;
                         const float16_t d = mfma<C>(TPW > 1 ? held[TPW > 1 ? b8 : 0] : operand(blk), bop);
-                        float om[2];
-#pragma unroll
-                        for (int o = 0; o < 2; ++o) {
-                            const int r = 8 * o;
-                            float m = fmaxf(fmaxf(d[r], d[r + 1]), d[r + 2]);
-                            m = fmaxf(fmaxf(m, d[r + 3]), d[r + 4]);
-                            m = fmaxf(fmaxf(m, d[r + 5]), d[r + 6]);
-                            m = fmaxf(m, d[r + 7]);
-                            om[o] = __uint_as_float((__float_as_uint(m) & 0xfffffff0u) | (unsigned)(2 * b8 + o));
-                        }
                         // the runner-up of {best, second, k1, k2} with second <= best is
                         // max(median(best, k1, k2), second)
-                        ssecond = fmaxf(ssecond, __builtin_amdgcn_fmed3f(sbest, om[0], om[1]));
-                        sbest = fmaxf(fmaxf(sbest, om[0]), om[1]);
+                        if constexpr (PER == 8) {
+                            float om[2];
+#pragma unroll
+                            for (int o = 0; o < 2; ++o) {
+                                const int r = 8 * o;
+                                float m = fmaxf(fmaxf(d[r], d[r + 1]), d[r + 2]);
+                                m = fmaxf(fmaxf(m, d[r + 3]), d[r + 4]);
+                                m = fmaxf(fmaxf(m, d[r + 5]), d[r + 6]);
+                                m = fmaxf(m, d[r + 7]);
+                                om[o] = __uint_as_float((__float_as_uint(m) & ~PACK) | (unsigned)(2 * b8 + o));
+                            }
+                            ssecond = fmaxf(ssecond, __builtin_amdgcn_fmed3f(sbest, om[0], om[1]));
+                            sbest = fmaxf(fmaxf(sbest, om[0]), om[1]);
+                        } else {
+                            float qm[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const float m = fmaxf(fmaxf(fmaxf(d[4 * q], d[4 * q + 1]), d[4 * q + 2]), d[4 * q + 3]);
+                                qm[q] = __uint_as_float((__float_as_uint(m) & ~PACK) | (unsigned)(4 * b8 + q));
+                            }
+#pragma unroll
+                            for (int q = 0; q < 4; q += 2) {
+                                ssecond = fmaxf(ssecond, __builtin_amdgcn_fmed3f(sbest, qm[q], qm[q + 1]));
+                                sbest = fmaxf(fmaxf(sbest, qm[q]), qm[q + 1]);
+                            }
+                        }
                     }
                     if constexpr (NSB == 1) {
                         gbest = sbest;
@@ -509,16 +530,17 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
             // x . c - |c|^2 / 2 in fp32 from the records and norms in LDS (v_dot2_f32_f16: exact products of
             // the fp16 pairs, fp32 sums; the centroid's number among the eight rides in the three
             // lowest mantissa bits)
-            const int j0 = (wsb * 8 + (int)((__float_as_uint(best) & 15u) >> 1)) * 32 + (int)(__float_as_uint(best) & 1u) * 16 + 4 * whalf;
-            float qk[8];
-            float hn[8];
+            const unsigned number = __float_as_uint(best) & PACK;
+            const int j0 = (wsb * 8 + (int)(number / (32 / PER / 2))) * 32 + (int)(number % (32 / PER / 2)) * (2 * PER) + 4 * whalf;
+            float qk[PER];
+            float hn[PER];
             if constexpr (NORMS) {
                 const float4 n0 = *reinterpret_cast<const float4*>(&half_norm[buf][j0]), n1 = *reinterpret_cast<const float4*>(&half_norm[buf][j0 + 8]);
                 hn[0] = n0.x; hn[1] = n0.y; hn[2] = n0.z; hn[3] = n0.w; hn[4] = n1.x; hn[5] = n1.y; hn[6] = n1.z; hn[7] = n1.w;
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned* r = reinterpret_cast<const unsigned*>(&cba[buf][record<C>(j0 + (e & 3) + 8 * (e >> 2)) * KDIM]);
+            for (int e = 0; e < PER; ++e) {
+                const unsigned* r = reinterpret_cast<const unsigned*>(&cba[buf][record<C, PER>(j0 + (e & 3) + 8 * (e >> 2)) * KDIM]);
                 unsigned w[C / 2];
                 if constexpr (C == 8) {
                     const uint4 a0 = *reinterpret_cast<const uint4*>(r);
@@ -541,24 +563,24 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
 #pragma unroll
                 for (int i = 0; i < C / 2; ++i)
                     sc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, xs[i]), __builtin_bit_cast(half2_t, w[i]), sc, false);
-                qk[e] = __uint_as_float((__float_as_uint(sc) & 0xfffffff8u) | (unsigned)e);
+                qk[e] = __uint_as_float((__float_as_uint(sc) & ~(PER - 1u)) | (unsigned)e);
             }
             float qbest_k = fmaxf(qk[0], qk[1]), qsecond = fminf(qk[0], qk[1]);
 #pragma unroll
-            for (int e = 2; e < 8; e += 2) {
+            for (int e = 2; e < PER; e += 2) {
                 qsecond = fmaxf(qsecond, __builtin_amdgcn_fmed3f(qbest_k, qk[e], qk[e + 1]));
                 qbest_k = fmaxf(fmaxf(qbest_k, qk[e]), qk[e + 1]);
             }
-            const int qarg = (int)(__float_as_uint(qbest_k) & 7u);
-            const float qbest = __uint_as_float(__float_as_uint(qbest_k) & 0xfffffff8u);
-            // 2^-17 M (1 % slack for the roundings of these lines): see "Error bound"
+            const int qarg = (int)(__float_as_uint(qbest_k) & (PER - 1u));
+            const float qbest = __uint_as_float(__float_as_uint(qbest_k) & ~(PER - 1u));
+            // 8 (maxima of four: 10) 2^-20 M, 1 % slack for the roundings of these lines: see "Error bound"
             const float xn = __builtin_amdgcn_sqrtf(x2);
             const float reach = fminf(cmax, 1.001f * (xn + __builtin_amdgcn_sqrtf(fmaxf(x2 - 2.f * qbest, 0.f))) + slack * (xn + cmax));
-            const float thr = (1.01f / 131072.0f) * reach * (xn + 0.5f * reach);
+            const float thr = (PER == 8 ? 1.01f : 1.26f) / 131072.0f * reach * (xn + 0.5f * reach);
             bool unsure;
             {
                 const int code = j0 + (qarg & 3) + 8 * (qarg >> 2);
-                const float sv = fmaxf(__uint_as_float(__float_as_uint(second) & 0xfffffff0u), qsecond);
+                const float sv = fmaxf(__uint_as_float(__float_as_uint(second) & ~PACK), qsecond);
                 unsure = !(qbest - sv > thr) || exact_only;
                 rec[ti][(slot >> 4) * 1024 + u * 16 + (slot & 15)] = (uint8_t)(code & 0xff);
                 if constexpr (B == 10) code16[wave][u][g] = (uint16_t)code;
@@ -581,7 +603,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 for (int j = lane; j < K; j += 64) {
                     unsigned cw[C / 2];
 #pragma unroll
-                    for (int i = 0; i < C / 2; ++i) cw[i] = *reinterpret_cast<const unsigned*>(&cba[buf][record<C>(j) * KDIM + 2 * i]);
+                    for (int i = 0; i < C / 2; ++i) cw[i] = *reinterpret_cast<const unsigned*>(&cba[buf][record<C, PER>(j) * KDIM + 2 * i]);
                     const unsigned dj = exact_distance_bits<C>(x, cw);
                     jmin = dj < dmin ? (unsigned)j : jmin;       // increasing j: the lowest index stays on ties
                     dmin = dj < dmin ? dj : dmin;
