@@ -648,11 +648,10 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
 
 // Byte codes: up to kGroupSplitEightBelow (tile, head, sequence, tensor) items eight wavefronts
 // share a tile, below kGroupSplitBelow (and for sequences of fewer than four tiles) four; larger
-// calls give four tiles to a workgroup of four wavefronts, which stages each group's codebook once
-// for them, and the largest of CQ-8c8b, whose codebooks take the longest to stage, eight.
-// (K and V of 32768 tokens x 4096 channels, four / eight tiles: CQ-8c8b 601 / 580 us, 4c8b 848 / 867;
-// 8 x 301 tokens of CQ-2c8b, one / three: 156 / 175.)
-constexpr long kEightTilesFrom = 16384;
+// calls give up to four tiles to a workgroup of four wavefronts, which stages each group's codebook once
+// for them, and a sequence's tiles are dealt out evenly.  (8 x 301 tokens of CQ-2c8b, one / three tiles: 156 / 175 us;
+// four / eight, CQ-8c8b of 32 heads: 16384 tokens 243 / 250, 32 x 520 281 / 298, 32768 tokens 523 / 525, 65536 tokens
+// 1020 / 1026.)
 constexpr long kGroupSplitBelow = 4096;
 constexpr long kGroupSplitEightBelow = 1024;
 
@@ -670,15 +669,11 @@ cq_status launch_mfma_format(const EncodeArgs& a, hipStream_t stream)
         } else if (wave_tiles < kGroupSplitBelow || n_tiles < 4) {
             hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 1>), dim3((unsigned)n_tiles, gy, gz), dim3(4 * 64), 0, stream, a);
         } else {
-            const int most = C == 8 && wave_tiles >= kEightTilesFrom && n_tiles >= 8 ? 8 : 4;
-            const int wgs = (n_tiles + most - 1) / most;
+            const int wgs = (n_tiles + 3) / 4;
             EncodeArgs b = a;
             b.tiles_per_wg = (n_tiles + wgs - 1) / wgs;
             const dim3 grid((unsigned)((n_tiles + b.tiles_per_wg - 1) / b.tiles_per_wg), gy, gz);
-            if constexpr (C == 8) {
-                if (most == 8) hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 8>), grid, dim3(4 * 64), 0, stream, b);
-            }
-            if (most == 4) hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 4>), grid, dim3(4 * 64), 0, stream, b);
+            hipLaunchKernelGGL((encode_mfma_kernel<GH, C, B, 4, true, 4>), grid, dim3(4 * 64), 0, stream, b);
         }
     } else {
         // 1024 centroids per group: one buffer per wavefront would not fit; four tiles per workgroup

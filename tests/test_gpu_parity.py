@@ -122,7 +122,7 @@ def test_encode_every_launch_shape_of_the_matrix_core_kernel(c, b, hkv, B, T, t_
 
 
 @pytest.mark.parametrize("c,b", [(8, 8), (4, 8)])
-@pytest.mark.parametrize("hkv,B,T,t_off", [(32, 8, 4333, 37),     # 17664 items: eight tiles per workgroup of CQ-8c8b, the last one has five
+@pytest.mark.parametrize("hkv,B,T,t_off", [(32, 8, 4333, 37),     # 17664 items, 69 tiles per sequence: four tiles per workgroup, the last one has one
                                            (64, 64, 290, 1)])     # 20480, 5 tiles per sequence: three and two per workgroup
 def test_encode_shapes_with_many_tiles_per_workgroup(c, b, hkv, B, T, t_off):
     test_encode_every_launch_shape_of_the_matrix_core_kernel(c, b, hkv, B, T, t_off)
