@@ -21,6 +21,8 @@
 // wavefronts per SIMD at most).  Phase V, the epilogue and the split-context merge are those of
 // the position-independent kernel.  Both trigonometric tables come from cq_rope_table (computed
 // in fp64).
+#include <type_traits>
+
 #include "cq_lds_gather.hpp"
 
 namespace cq {
@@ -745,81 +747,87 @@ __device__ __forceinline__ void gqa_values(const DecodeArgs& a, float* smem, con
     float4_t o[8];
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
+    // (the columns of heads beyond NH hold anything, and are not read out)
+    auto walk = [&](auto n_heads) {
+        constexpr int NH = decltype(n_heads)::value;
 #pragma unroll 1
-    for (int k = 0; k < my_tiles; ++k) {
-        const int lt = wave + k * NW;
-        if (meets_new && tile0 + lt == tile_new) {
+        for (int k = 0; k < my_tiles; ++k) {
+            const int lt = wave + k * NW;
+            if (meets_new && tile0 + lt == tile_new) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const bool mine = 32 * t + 4 * r + u0 == u_new;
+#pragma unroll
+                        for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) rec[t][r][pl][i] = mine ? new_codes.lo[4 * pl + i] : rec[t][r][pl][i];
+                    }
+            }
+            unsigned z[2][2][2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                pick0(rec[t][0], 0, z[t][0]);
+                pick1(rec[t][1], 0, z[t][1]);
+            }
+            request(k + 1);
+            half8_t av[2][8];
+            auto gather = [&](int t) {
+                unsigned at[2][8];
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int cb = 0; cb < 8; ++cb) at[r][cb] = entry<C>(z[t][r][cb >> 2], cb & 3, vbase);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) {
+                    const half4_t v0 = lds_transposed(at[0][cb] + (unsigned)cb * 8192), v1 = lds_transposed(at[1][cb] + (unsigned)cb * 8192);
+                    av[t][cb] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            float s[NH];
+#pragma unroll
+            for (int h = 0; h < NH; ++h) s[h] = sc[h * split_tokens + lt * kTileTokens + lane];
+            gather(0);
+            // lane = token: p 2^12 of each head as the sum of three fp16 numbers
+            _Float16 part[3][NH];
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                const float p = __builtin_amdgcn_exp2f(s[h] - m[h]) * 4096.f;      // (12 in the exponent would be lost in a large m)
+                l[h] += p;
+                part[0][h] = (_Float16)p;
+                const float r1 = p - (float)part[0][h];
+                part[1][h] = (_Float16)r1;
+                part[2][h] = (_Float16)(r1 - (float)part[1][h]);
+            }
+            half8_t pb[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                // (a wavefront's LDS operations keep their order: the half tiles share the room)
+                if ((lane >> 5) == t) {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+#pragma unroll
+                        for (int h = 0; h < NH; ++h) *(lds_h*)(prob_in + (unsigned)(e * QH + h) * 64) = part[e][h];
+                }
+                // (the lanes read what other lanes wrote: without these statements the compiler takes a lane's
+                // second read for a repetition of its first)
+                asm volatile("" ::: "memory");
+                const half8_t v = *(__attribute__((address_space(3))) half8_t*)(prob_out);
+                pb[t] = col < 12 ? v : half8_t(0.f16);
+                asm volatile("" ::: "memory");
+            }
+            gather(1);
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    const bool mine = 32 * t + 4 * r + u0 == u_new;
-#pragma unroll
-                    for (int pl = 0; pl < PL; ++pl)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) rec[t][r][pl][i] = mine ? new_codes.lo[4 * pl + i] : rec[t][r][pl][i];
-                }
+                for (int cb = 0; cb < 8; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], pb[t], o[cb], 0, 0, 0);
         }
-        unsigned z[2][2][2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            pick0(rec[t][0], 0, z[t][0]);
-            pick1(rec[t][1], 0, z[t][1]);
-        }
-        request(k + 1);
-        half8_t av[2][8];
-        auto gather = [&](int t) {
-            unsigned at[2][8];
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-#pragma unroll
-                for (int cb = 0; cb < 8; ++cb) at[r][cb] = entry<C>(z[t][r][cb >> 2], cb & 3, vbase);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                const half4_t v0 = lds_transposed(at[0][cb] + (unsigned)cb * 8192), v1 = lds_transposed(at[1][cb] + (unsigned)cb * 8192);
-                av[t][cb] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        float s[QH];
-#pragma unroll
-        for (int h = 0; h < QH; ++h) s[h] = sc[h * split_tokens + lt * kTileTokens + lane];
-        gather(0);
-        // lane = token: p 2^12 of each head as the sum of three fp16 numbers
-        _Float16 part[3][QH];
-#pragma unroll
-        for (int h = 0; h < QH; ++h) {
-            const float p = __builtin_amdgcn_exp2f(s[h] - m[h]) * 4096.f;      // (12 in the exponent would be lost in a large m)
-            l[h] += p;
-            part[0][h] = (_Float16)p;
-            const float r1 = p - (float)part[0][h];
-            part[1][h] = (_Float16)r1;
-            part[2][h] = (_Float16)(r1 - (float)part[1][h]);
-        }
-        half8_t pb[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            // (a wavefront's LDS operations keep their order: the half tiles share the room)
-            if ((lane >> 5) == t) {
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-#pragma unroll
-                    for (int h = 0; h < QH; ++h) *(lds_h*)(prob_in + (unsigned)(e * QH + h) * 64) = part[e][h];
-            }
-            // (the lanes read what other lanes wrote: without these statements the compiler takes a lane's
-            // second read for a repetition of its first)
-            asm volatile("" ::: "memory");
-            const half8_t v = *(__attribute__((address_space(3))) half8_t*)(prob_out);
-            pb[t] = col < 12 ? v : half8_t(0.f16);
-            asm volatile("" ::: "memory");
-        }
-        gather(1);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], pb[t], o[cb], 0, 0, 0);
-    }
+    };
+    if (heads <= 2) walk(std::integral_constant<int, 2>{});
+    else walk(std::integral_constant<int, 4>{});
 
     // ---- the parts of a head are columns h, h + 4, h + 8; then the wavefronts, all relative to the same maximum
     lds_barrier();                                  // scores and probabilities are read

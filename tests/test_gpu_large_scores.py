@@ -62,7 +62,7 @@ def _check(out, ref, clear):
 
 
 @pytest.mark.parametrize("magnitude", MAGNITUDES)
-@pytest.mark.parametrize("c,hq", [(8, 8), (4, 6), (2, 4)])
+@pytest.mark.parametrize("c,hq", [(8, 8), (8, 4), (4, 6), (4, 4), (2, 4)])
 def test_grouped_decode_over_rotated_keys(c, hq, magnitude):
     hkv, B, T = 2, 2, 700
     fmt, q, kc, vc, ck, cv = _case(c, c, 8, hq, hkv, B, 1, T, 0)
