@@ -891,11 +891,10 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
     constexpr int B = 8, QH = 4;
     using F = Fmt<GH, B>;
     typedef float f4 __attribute__((ext_vector_type(4)));
-    constexpr int K = F::K, RW = F::RW, R = F::R;
+    constexpr int K = F::K;
     constexpr int NW = NT / 64;
     constexpr int D = GH * C;
     constexpr int HALF = GH / 2;
-    constexpr int PF = GH == 16 ? 4 : (GH == 32 ? 2 : 1);
     constexpr int JPL = 8 / C;
     constexpr int NCH = GH / 16;
     constexpr int UNITS = 16 * K / JPL;
@@ -954,16 +953,15 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
     const int split_tokens = a.tiles_per_split * kTileTokens;
     // fused step (as in the kernel above): the workgroup whose split holds the newest position encodes
     // the new key row against the centroids it has just brought into LDS and patches the tile
-    // that holds the position in registers; the new value row is encoded before the per-head
-    // passes, which leave the position out of the bins and add its weight to the bins of the
-    // codes found.  The workgroup of the KV head's first four query heads stores the codes.
+    // that holds the position in registers; the value phase encodes the new value row against its codebook first
+    // and puts the codes found into that tile, or (bins) leaves the position out of the bins and adds its weight
+    // to those of the codes.  The workgroup of the KV head's first four query heads stores the codes.
     const int pos_new = t_n - 1;
     const int tile_new = pos_new / kTileTokens, u_new = pos_new % kTileTokens;
     const bool has_new = STEP && tile_new >= tile0 && tile_new < tile1;
     const bool writer = has_new && quad == 0;
     if (has_new && tid < 2 * GH) keys[tid] = ~0ull;         // (ordered by the barrier behind the table copy)
 
-    Columns<GH, B> col;
     const int my_tiles = (tile1 - tile0 - wave + NW - 1) / NW;
     TileWalk<GH, B> kwalk, vwalk;
     kwalk.first = tile0 + wave;
@@ -983,7 +981,6 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
         vwalk.base = a.v_codes + stream_idx;
     }
     Streamer<GH, B, 1> stk;
-    Streamer<GH, B, PF> st;
 
     // ---- 1. the head's key centroids go to LDS; the lane's cosines and sines; this lane's query slices ----
     {
@@ -1123,172 +1120,159 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
     if constexpr (GH <= 32) {
         gqa_values<GH, C, NT>(a, smem, top, vwalk, n, hkv, hq0, heads, split, split_tokens, tile0, my_tiles, has_new, writer, meets_new,
                               tile_new, u_new);
-        return;
-    }
-    lds_barrier();                                  // all centroid reads done, all scores written
+    } else {
+        lds_barrier();                                  // all centroid reads done, all scores written
 
-    // ---- 3. per head: softmax reference, phase V, epilogue ----------------------------------
-    col.init(lane);
-    // (the four lanes of a group are neighbours and read four neighbouring 16-byte pieces of its
-    // value codebook: 64 contiguous bytes, four cache lines per 16 lanes instead of sixteen)
-    const int gl16 = (tid >> 2) & 15;
-    auto piece = [&](int k) { return (((tid + k * NT) >> 6) << 2) + (tid & 3); };
-    constexpr int KB = IPT < 8 ? IPT : 8;
-    const int n_tok = (tile1 - tile0) * kTileTokens;
-    unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
-    if (has_new) {
-        // the new value row against the value codebook (global memory): the walk of the epilogue,
-        // ascending index per thread, 64-bit minimum over the threads of a group
+        // ---- 3. per head: softmax reference, phase V, epilogue ----------------------------------
+        constexpr int RW = F::RW;
+        static_assert(F::R == 1 && NCH == 4, "CQ-2c8b");
+        Columns<GH, B> col;
+        Streamer<GH, B, 1> st;
+        col.init(lane);
+        // (the four lanes of a group are neighbours and read four neighbouring 16-byte pieces of its
+        // value codebook: 64 contiguous bytes, four cache lines per 16 lanes instead of sixteen)
+        const int gl16 = (tid >> 2) & 15;
+        auto piece = [&](int k) { return (((tid + k * NT) >> 6) << 2) + (tid & 3); };
+        const int n_tok = (tile1 - tile0) * kTileTokens;
+        unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
+        if (has_new) {
+            // the new value row against the value codebook (global memory): the walk of the epilogue,
+            // ascending index per thread, 64-bit minimum over the threads of a group
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-            const size_t xrow = (size_t)n * a.x_new_stride + (size_t)hkv * GH * C;
-            float xv[C];
-            load_row_slice<C>(a.xv_new + xrow + (ch * 16 + gl16) * C, xv);
-            const uint16_t* cvg = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
-            Nearest vnear;
+            for (int ch = 0; ch < NCH; ++ch) {
+                const size_t xrow = (size_t)n * a.x_new_stride + (size_t)hkv * GH * C;
+                float xv[C];
+                load_row_slice<C>(a.xv_new + xrow + (ch * 16 + gl16) * C, xv);
+                const uint16_t* cvg = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
+                Nearest vnear;
+                Cent16 rawb[IPT];
 #pragma unroll
-            for (int k0 = 0; k0 < IPT; k0 += KB) {
-                Cent16 rawb[KB];
+                for (int k = 0; k < IPT; ++k) rawb[k] = load_cent16(cvg + (size_t)piece(k) * 8);
 #pragma unroll
-                for (int k = 0; k < KB; ++k) rawb[k] = load_cent16(cvg + (size_t)piece(k0 + k) * 8);
-#pragma unroll
-                for (int k = 0; k < KB; ++k) {
-                    const int j0 = piece(k0 + k) * JPL;
+                for (int k = 0; k < IPT; ++k) {
+                    const int j0 = piece(k) * JPL;
 #pragma unroll
                     for (int jj = 0; jj < JPL; ++jj) vnear.offer(centroid_distance<C>(xv, &rawb[k].w[jj * (C / 2)]), j0 + jj);
                 }
+                const unsigned long long vkey = group_lanes_min<4>(vnear.key());
+                if ((lane & 3) == 0) lds_min_u64(&keys[GH + ch * 16 + gl16], vkey);
             }
-            const unsigned long long vkey = group_lanes_min<4>(vnear.key());
-            if ((lane & 3) == 0) lds_min_u64(&keys[GH + ch * 16 + gl16], vkey);
+            lds_barrier();
+            if (writer)
+                store_new_codes<GH, B>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * F::TILE_BYTES, keys + GH, u_new, tid);
         }
-        lds_barrier();
-        if (writer)
-            store_new_codes<GH, B>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * F::TILE_BYTES, keys + GH, u_new, tid);
-    }
-    // One head per pass: 64 groups fill the bins' rows.  The value centroids of the epilogue are the same
-    // for every head: they stay in registers where they fit.
-    constexpr bool KEEP = IPT * NCH <= 8 && KB == IPT;
-    Cent16 rawv[KEEP ? NCH : 1][KB];
-    if constexpr (KEEP) {
+        // One head per pass: 64 groups fill the bins' rows.  The value centroids of the epilogue are the same
+        // for every head and stay in registers.
+        Cent16 rawv[NCH][IPT];
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
             const uint16_t* cv = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
 #pragma unroll
             for (int k = 0; k < IPT; ++k) rawv[ch][k] = load_cent16(cv + (size_t)piece(k) * 8);
         }
-    }
-    for (int h = 0; h < heads; ++h) {
-        // scr: [0..8) sums, [8..16) maxima, [16..24) estimates of l of the 8 wavefronts
-        const float* sch = sc + h * split_tokens;
-        float lane_max = -INFINITY;
-        for (int i = tid; i < n_tok; i += NT) lane_max = fmaxf(lane_max, sch[i]);
-        lane_max = wave_max(lane_max);
-        if (lane == 0) scr[NW + wave] = lane_max;
-        st.begin(vwalk, my_tiles, lane);
-        lds_barrier();
-        float m = scr[NW];
+        for (int h = 0; h < heads; ++h) {
+            // scr: [0..8) sums, [8..16) maxima, [16..24) estimates of l of the 8 wavefronts
+            const float* sch = sc + h * split_tokens;
+            float lane_max = -INFINITY;
+            for (int i = tid; i < n_tok; i += NT) lane_max = fmaxf(lane_max, sch[i]);
+            lane_max = wave_max(lane_max);
+            if (lane == 0) scr[NW + wave] = lane_max;
+            st.begin(vwalk, my_tiles, lane);
+            lds_barrier();
+            float m = scr[NW];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) m = fmaxf(m, scr[NW + w]);
-        float l_est = 0.f;
-        for (int i = tid; i < n_tok; i += NT) l_est += __builtin_amdgcn_exp2f(sch[i] - m);
-        l_est = wave_sum(l_est);
-        if (lane == 0) scr[2 * NW + wave] = l_est;
-        {
-            float4* t4 = reinterpret_cast<float4*>(tab);
+            for (int w = 1; w < NW; ++w) m = fmaxf(m, scr[NW + w]);
+            float l_est = 0.f;
+            for (int i = tid; i < n_tok; i += NT) l_est += __builtin_amdgcn_exp2f(sch[i] - m);
+            l_est = wave_sum(l_est);
+            if (lane == 0) scr[2 * NW + wave] = l_est;
+            {
+                float4* t4 = reinterpret_cast<float4*>(tab);
 #pragma unroll 4
-            for (int i = tid; i < F::TAB_FLOATS / 4; i += NT) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        lds_barrier();
-        l_est = 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) l_est += scr[2 * NW + w];
-        const int fx = fixed_point_exponent(l_est);
-        const float fx_scale = ldexpf(1.f, fx), fx_inv = ldexpf(1.f, -fx);
-
-        unsigned lane_sum = 0;
-        st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
-            const int lt = wave + k * NW;
-            const float p = __builtin_amdgcn_exp2f(sch[lt * kTileTokens + lane] - m);
-            unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
-            lane_sum += pf;
-            if (has_new && tile0 + lt == tile_new && lane == u_new) {
-                *pf_new = pf;
-                pf = 0;
-            }
-#pragma unroll
-            for (int s = 0; s < GH; ++s) lds_add(slot_addr<GH, B, false>(w, col, s), pf);
-        }, [] {});
-        lane_sum = wave_sum_u32(lane_sum);
-        lds_barrier();
-        if (lane == 0) scr[wave] = __uint_as_float(lane_sum);
-        if (has_new) {
-            if (tid < GH) {
-                const unsigned code = (unsigned)(keys[GH + tid] & 0xffffffffu);
-                lds_add((code * RW + tid * R) * 4u, *pf_new);
+                for (int i = tid; i < F::TAB_FLOATS / 4; i += NT) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
             lds_barrier();
-        }
+            l_est = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) l_est += scr[2 * NW + w];
+            const int fx = fixed_point_exponent(l_est);
+            const float fx_scale = ldexpf(1.f, fx), fx_inv = ldexpf(1.f, -fx);
 
-        float acc[NCH][C];
-#pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-#pragma unroll
-            for (int i = 0; i < C; ++i) acc[ch][i] = 0.f;
-            const uint16_t* cv = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
-#pragma unroll
-            for (int k0 = 0; k0 < IPT; k0 += KB) {
-                if constexpr (!KEEP) {
-#pragma unroll
-                    for (int k = 0; k < KB; ++k) rawv[0][k] = load_cent16(cv + (size_t)piece(k0 + k) * 8);
+            unsigned lane_sum = 0;
+            st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
+                const int lt = wave + k * NW;
+                const float p = __builtin_amdgcn_exp2f(sch[lt * kTileTokens + lane] - m);
+                unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
+                lane_sum += pf;
+                if (has_new && tile0 + lt == tile_new && lane == u_new) {
+                    *pf_new = pf;
+                    pf = 0;
                 }
-                const Cent16 (&raw)[KB] = rawv[KEEP ? ch : 0];
 #pragma unroll
-                for (int k = 0; k < KB; ++k) {
-                    const int j0 = piece(k0 + k) * JPL;
+                for (int s = 0; s < GH; ++s) lds_add(slot_addr<GH, B, false>(w, col, s), pf);
+            }, [] {});
+            lane_sum = wave_sum_u32(lane_sum);
+            lds_barrier();
+            if (lane == 0) scr[wave] = __uint_as_float(lane_sum);
+            if (has_new) {
+                if (tid < GH) {
+                    const unsigned code = (unsigned)(keys[GH + tid] & 0xffffffffu);
+                    lds_add((code * RW + tid) * 4u, *pf_new);
+                }
+                lds_barrier();
+            }
+
+            float acc[NCH][C];
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch) {
+#pragma unroll
+                for (int i = 0; i < C; ++i) acc[ch][i] = 0.f;
+#pragma unroll
+                for (int k = 0; k < IPT; ++k) {
+                    const int j0 = piece(k) * JPL;
 #pragma unroll
                     for (int jj = 0; jj < JPL; ++jj) {
-                        const float* src = tab + (j0 + jj) * RW + (ch * 16 + gl16) * R;
-                        const float bin = (float)*reinterpret_cast<const unsigned*>(src) * fx_inv;
+                        const float bin = (float)*reinterpret_cast<const unsigned*>(tab + (j0 + jj) * RW + ch * 16 + gl16) * fx_inv;
 #pragma unroll
                         for (int i = 0; i < C / 2; ++i) {
-                            const half2_t hv = __builtin_bit_cast(half2_t, raw[k].w[jj * (C / 2) + i]);
+                            const half2_t hv = __builtin_bit_cast(half2_t, rawv[ch][k].w[jj * (C / 2) + i]);
                             acc[ch][2 * i] = __builtin_fmaf(bin, (float)hv.x, acc[ch][2 * i]);
                             acc[ch][2 * i + 1] = __builtin_fmaf(bin, (float)hv.y, acc[ch][2 * i + 1]);
                         }
                     }
                 }
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    acc[ch][i] += __shfl_xor(acc[ch][i], 1);
+                    acc[ch][i] += __shfl_xor(acc[ch][i], 2);
+                }
             }
+            if ((lane & 3) == 0) {
 #pragma unroll
-            for (int i = 0; i < C; ++i) {
-                acc[ch][i] += __shfl_xor(acc[ch][i], 1);
-                acc[ch][i] += __shfl_xor(acc[ch][i], 2);
+                for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                    for (int i = 0; i < C; ++i) scr[64 + wave * D + (ch * 16 + gl16) * C + i] = acc[ch][i];
             }
-        }
-        if ((lane & 3) == 0) {
+            lds_barrier();
+            unsigned l_fix = 0;
 #pragma unroll
-            for (int ch = 0; ch < NCH; ++ch)
+            for (int w = 0; w < NW; ++w) l_fix += __float_as_uint(scr[w]);
+            const float l = (float)l_fix * fx_inv;
+            const int hq = hq0 + h;
+            float* part = a.partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
+            if (tid == 0 && !direct) {
+                part[0] = m;
+                part[1] = l;
+            }
+            for (int chn = tid; chn < D; chn += NT) {
+                float o = 0.f;
 #pragma unroll
-                for (int i = 0; i < C; ++i) scr[64 + wave * D + (ch * 16 + gl16) * C + i] = acc[ch][i];
+                for (int w = 0; w < NW; ++w) o += scr[64 + w * D + chn];
+                if (direct) a.out[(size_t)n * a.out_batch_stride + (size_t)hq * D + chn] = __builtin_bit_cast(uint16_t, (_Float16)(o / l));
+                else part[kPartialHeader + chn] = o;
+            }
+            lds_barrier();                          // the next head reuses the scratch, the next pass the bins
         }
-        lds_barrier();
-        unsigned l_fix = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) l_fix += __float_as_uint(scr[w]);
-        const float l = (float)l_fix * fx_inv;
-        const int hq = hq0 + h;
-        float* part = a.partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
-        if (tid == 0 && !direct) {
-            part[0] = m;
-            part[1] = l;
-        }
-        for (int chn = tid; chn < D; chn += NT) {
-            float o = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) o += scr[64 + w * D + chn];
-            if (direct) a.out[(size_t)n * a.out_batch_stride + (size_t)hq * D + chn] = __builtin_bit_cast(uint16_t, (_Float16)(o / l));
-            else part[kPartialHeader + chn] = o;
-        }
-        lds_barrier();                          // the next head reuses the scratch, the next pass the bins
     }
 }
 
