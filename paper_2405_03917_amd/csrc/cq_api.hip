@@ -622,7 +622,6 @@ int chunk_tiles_per_split(const Derived& f, int batch, int n_q_heads, int m, int
 // 3 rows, CQ-8c8b: 330 / 491 in pieces of one tile, 271 / 254 of two; 4c8b: 302 / 330 of two, 274 / 178 of four;
 // 16 x 8 heads, 32 rows: CQ-8c8b 91 / 101 of two, 83 / 73 of three, 4c8b 99 / 114 and 94 / 84; 64 rows: CQ-8c8b
 // 100 / 105 of three, 4c8b 109 / 124 of three, 98 / 97 of four.
-constexpr int kChunkLdsRows = 64;
 bool chunk_in_lds(const Derived& f, int n_q_heads, int m, int n_tiles, int piece_tiles, bool rope)
 {
     const long rows = (long)m * (n_q_heads / f.n_kv_heads);
@@ -685,9 +684,9 @@ size_t chunk_workspace(const Derived& f, int batch, int n_q_heads, int m, int t,
 // which that workspace does not hold).
 int chunk_lds_tiles(const Derived& f, int batch, int n_q_heads, int m, int t, bool by_token)
 {
-    const ChunkLdsPlan p = chunk_lds_plan(f, batch, n_q_heads, m);
+    const ChunkLdsPlan p = chunk_lds_plan(f, n_q_heads, m);
     const int n_tiles = (t + kTileTokens - 1) / kTileTokens;
-    const long base = (long)batch * p.row_groups;
+    const long base = batch;
     const size_t piece = sizeof(float) * (size_t)batch * m * n_q_heads * (f.head_dim + kPartialHeader);
     const long fit = std::max<long>(1, (long)(chunk_workspace(f, batch, n_q_heads, m, t, 0) / piece));
     if (by_token && base * f.n_kv_heads * fit < 192) return 0;

@@ -26,7 +26,7 @@
 // waited for every gather by itself (5800 clocks per tile and wavefront, 61 us); values gathered
 // ahead of the softmax in one batch of 64 registers spilled at CQ-4c8b and gained nothing.
 //
-// A workgroup of 8 wavefronts (one per CU) serves RB blocks of 16 rows; the 8 / RB wavefronts of
+// A workgroup of 8 wavefronts (one per CU) serves RB = 1, 2 or 4 blocks of 16 rows; the 8 / RB wavefronts of
 // a block take every (8 / RB)-th tile and are merged through LDS at the end.  Workgroups walk
 // several (sequence, split) items of one KV head, so the codebooks are staged once per workgroup.
 #include "cq_lds_gather.hpp"
@@ -75,13 +75,12 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, blk = lane >> 4;
 
-    const int rbs = 1 << rb_log2, cs = kWaves >> rb_log2;   // row blocks, context slices of the workgroup
+    const int cs = kWaves >> rb_log2;                       // context slices of each of the 2^rb_log2 row blocks
     const int rb = wave >> (3 - rb_log2), slice = wave & (cs - 1);
     const int hkv = blockIdx.x % a.f.n_kv_heads;
     const int stride = gridDim.x / a.f.n_kv_heads;
     const int qper = a.n_q_heads / a.f.n_kv_heads;
     const int rows_total = a.m * qper;
-    const int row_groups = (rows_total + kRows * rbs - 1) / (kRows * rbs);
 
     // ---- this lane's places: keys, token col of a block of 16, groups blk, blk + 4, ...; values, token
     // 4 blk + col / 4 of a block, channels 4 (col % 4) .. of 16 (C = 8: half of group (col % 4) / 2, then
@@ -93,14 +92,15 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
     const unsigned vbase = kBookBytes + (C == 8 ? ((unsigned)(col & 3) >> 1) * 4096 + (unsigned)(col & 1) * 8 : (unsigned)(col & 3) * 2048);
 
 
-    // ---- the items of this workgroup: (sequence, split, group of row blocks), advanced without divisions
+    // ---- the items of this workgroup: (sequence, split), advanced without divisions
     const float inv_qper = 1.f / (float)qper;
     const auto row_token = [&](int row) { return (int)(((float)row + 0.5f) * inv_qper); };     // row / qper (few rows: exact)
     int item = blockIdx.x / a.f.n_kv_heads;
-    int rg = item % row_groups, split = item / row_groups % a.n_split, n = item / row_groups / a.n_split;
-    const int d_rg = stride % row_groups, d_split = stride / row_groups % a.n_split, d_n = stride / row_groups / a.n_split;
+    int split = item % a.n_split, n = item / a.n_split;
+    const int d_split = stride % a.n_split, d_n = stride / a.n_split;
+    int row0 = rb * kRows;                                  // (a block beyond the last row repeats it and stores nothing)
     struct Item {
-        int n, rg, split, pos, pos_first, tile0, tile1;
+        int n, split, pos, pos_first, tile0, tile1;
     };
     // (a scale of zero stands for one so small that every weight is 1: 0 times a masked -infinity is no number)
     const float scale = a.scale_log2e == 0.f ? 1e-37f : fabsf(a.scale_log2e);
@@ -128,14 +128,14 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
     // an item's places, its queries and its first tile's records (requested ahead of the codebooks or of
     // the previous item's merge)
     auto open_item = [&]() {
+        // (opaque per item: what follows from it would be kept in registers through the tiles, which spill then)
+        asm volatile("" : "+s"(row0));
         Item it;
         it.n = n;
-        it.rg = rg;
         it.split = split;
         int t_n = a.t;
         if (a.seq_lens) t_n = min(max(a.seq_lens[n], a.m), a.t);
         const int pos0 = t_n - a.m;                         // position of query token 0
-        const int row0 = (rg * rbs + rb) * kRows;           // (a block beyond the last row repeats it and stores nothing)
         const int row = min(row0 + (HALF ? col & 7 : col), rows_total - 1);
         const int j = row_token(row);
         it.pos = pos0 + j;
@@ -321,10 +321,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         item += stride;
         const bool more = item < items;
         if (more) {
-            rg += d_rg;
-            const int c0 = rg >= row_groups;
-            rg -= c0 ? row_groups : 0;
-            split += d_split + c0;
+            split += d_split;
             const int c1 = split >= a.n_split;
             split -= c1 ? a.n_split : 0;
             n += d_n + c1;
@@ -347,7 +344,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         for (int w = 0; w < kWaves; ++w) ll += w < cs ? ml[w][1] * __builtin_amdgcn_exp2f(ml[w][0] - mz) : 0.f;
         float weight = __builtin_amdgcn_exp2f(ref - mz);
         if (a.n_split == 1) weight *= 1.f / ll;
-        const int row0 = (done.rg * rbs + rb) * kRows;
         if (a.n_split > 1 && slice == 0 && blk == 0 && row0 + col < rows_total) {
             const int j = row_token(row0 + col);
             const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (row0 + col - j * qper);
@@ -356,8 +352,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             dst[1] = ll;
         }
         lds_barrier();                                      // the pairs are read: their room is the rows'
-        const int q = tid >> 5;                             // this thread's row and pair of channels
-        const unsigned osrc = kMergeBase + (unsigned)q * kORow + (((unsigned)(tid & 31) >> 1) ^ (unsigned)q) * 16 + (tid & 1) * 8;
+        int tid_o = tid, lane_o = lane;                     // (opaque, as above; all of it only where registers are short)
+        if constexpr (C == 4) asm volatile("" : "+v"(tid_o), "+v"(lane_o));
+        int q = tid_o >> 5;                                 // this thread's row and pair of channels
+        if constexpr (C != 4) asm volatile("" : "+v"(q));
+        const unsigned osrc = kMergeBase + (unsigned)q * kORow + (((unsigned)(tid_o & 31) >> 1) ^ (unsigned)q) * 16 + (tid_o & 1) * 8;
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
 #pragma unroll
@@ -369,7 +368,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
                         v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));
                 }
                 // (16-byte pieces of a row change places by the row's number: 16 rows, 16 different banks)
-                *(lds_f4*)(kMergeBase + (unsigned)(wave * kRows + col) * kORow + (unsigned)((4 * h + blk) ^ col) * 16) = v * weight;
+                *(lds_f4*)(kMergeBase + (unsigned)(wave * kRows + (lane_o & 15)) * kORow + (unsigned)((4 * h + (lane_o >> 4)) ^ (lane_o & 15)) * 16) = v * weight;
             }
             lds_barrier();
             float2_t sum = {0.f, 0.f};
@@ -377,11 +376,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             for (int w = 0; w < kWaves; ++w) {
                 sum += *(lds_f2*)(osrc + (unsigned)(w * kRows) * kORow);
                 if (((w + 1) & (cs - 1)) != 0) continue;    // (the row block's last slice)
-                const int r2 = (done.rg * rbs + (w >> (3 - rb_log2))) * kRows + q;
+                const int r2 = (w >> (3 - rb_log2)) * kRows + q;
                 if (r2 < rows_total) {
                     const int j = row_token(r2);
                     const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (r2 - j * qper);
-                    const int ch = part * 64 + 2 * (tid & 31);
+                    const int ch = part * 64 + 2 * (tid_o & 31);
                     if (a.n_split == 1)
                         *reinterpret_cast<half2_t*>(a.out + out_row * D + ch) = __builtin_convertvector(sum, half2_t);
                     else
@@ -401,8 +400,8 @@ cq_status launch(const ChunkArgs& a, hipStream_t stream)
     auto kernel = chunk_lds_kernel<C, HALF>;
     static LdsKernelSetup setup;
     if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
-    const ChunkLdsPlan p = chunk_lds_plan(a.f, a.batch, a.n_q_heads, a.m);
-    const int items = a.batch * a.n_split * p.row_groups;
+    const ChunkLdsPlan p = chunk_lds_plan(a.f, a.n_q_heads, a.m);
+    const int items = a.batch * a.n_split;
     const int per_head = items < p.wgs_per_head ? items : p.wgs_per_head;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(per_head * a.f.n_kv_heads)), dim3(kWaves * 64), kLdsBytes, stream, a, p.rb_log2, items);
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
@@ -410,22 +409,21 @@ cq_status launch(const ChunkArgs& a, hipStream_t stream)
 
 }  // namespace
 
-ChunkLdsPlan chunk_lds_plan(const Derived& f, int batch, int n_q_heads, int m)
+ChunkLdsPlan chunk_lds_plan(const Derived& f, int n_q_heads, int m)
 {
-    (void)batch;
     ChunkLdsPlan p;
     const int blocks = (m * (n_q_heads / f.n_kv_heads) + kRows - 1) / kRows;
-    p.rb_log2 = blocks <= 1 ? 0 : (blocks <= 2 ? 1 : (blocks <= 4 ? 2 : 3));
-    p.row_groups = (blocks + (1 << p.rb_log2) - 1) >> p.rb_log2;
+    p.rb_log2 = blocks <= 1 ? 0 : (blocks <= 2 ? 1 : 2);
     p.wgs_per_head = f.n_kv_heads < 256 ? 256 / f.n_kv_heads : 1;      // one workgroup per CU
     return p;
 }
 
 cq_status launch_chunk_lds(const ChunkArgs& a, hipStream_t stream)
 {
-    if (a.f.b != 8 || a.f.head_dim != 128) return CQ_ERR_UNSUPPORTED;
     // (row / qper is formed in floating point: exact for far more rows than are served here)
-    const bool half = a.m * (a.n_q_heads / a.f.n_kv_heads) <= kRows / 2;
+    const int64_t rows = (int64_t)a.m * (a.n_q_heads / a.f.n_kv_heads);
+    if (a.f.b != 8 || a.f.head_dim != 128 || rows > kChunkLdsRows) return CQ_ERR_UNSUPPORTED;
+    const bool half = rows <= kRows / 2;
     if (a.f.c == 8) return half ? launch<8, true>(a, stream) : launch<8, false>(a, stream);
     if (a.f.c == 4) return half ? launch<4, true>(a, stream) : launch<4, false>(a, stream);
     return CQ_ERR_UNSUPPORTED;

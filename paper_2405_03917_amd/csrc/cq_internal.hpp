@@ -151,12 +151,12 @@ struct ChunkArgs {
 int chunk_rows_per_workgroup(int rows_per_kv_head);
 cq_status launch_chunk_attention(const ChunkArgs& a, hipStream_t stream);
 // Few rows per KV head, codebooks in LDS (cq_chunk_lds.hip: CQ-8c8b and CQ-4c8b).
+constexpr int kChunkLdsRows = 64;
 struct ChunkLdsPlan {
-    int rb_log2;              // log2 of the blocks of 16 rows a workgroup serves
-    int row_groups;           // workgroups' worth of rows per KV head
+    int rb_log2;              // log2 of the blocks of 16 rows of a KV head
     int wgs_per_head;         // workgroups that share a KV head's items
 };
-ChunkLdsPlan chunk_lds_plan(const Derived& f, int batch, int n_q_heads, int m);
+ChunkLdsPlan chunk_lds_plan(const Derived& f, int n_q_heads, int m);
 cq_status launch_chunk_lds(const ChunkArgs& a, hipStream_t stream);
 
 // Largest tokens_per_split the decode kernel's on-chip score buffer can hold.
