@@ -45,6 +45,8 @@ LAST_LEVEL_CACHE_BYTES = 256e6
 # 157.3 TFLOP/s of fp32 counts a packed FMA, 4 flops, per lane-instruction)
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 MFMA_SCORE_OPS = 1.08
+# vector instructions of a Lloyd iteration per (token, group) of 8 channels and 256 centroids (SQ_INSTS_VALU / dispatch)
+LLOYD_LANE_OPS = 547.0
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 FP16_MFMA_PEAK_TFLOPS = 2500.0
 METRIC = "decode-attn KV tokens/s & achieved HBM GB/s (% peak); cq_encode tokens/s"
@@ -341,7 +343,7 @@ def extra_measurements(cq, synth, torch):
     xk = synth.sample_activations_torch(st0["rk"], chunk, 777, "cuda").view(1, chunk, D)
     scratch_cache = cq.alloc_cache(fmt, 1, chunk)
     enc_ms, _ = time_calls(torch, lambda: cq.cq_encode(xk, st0["ck"], fmt, scratch_cache, 0, chunk), 5, 1)
-    enc_r, enc_pairs = encode_roofline("encode_mfma_kernel<16, 8, 8, 4, true, 8>", chunk, D, 256, enc_ms, True)
+    enc_r, enc_pairs = encode_roofline("encode_mfma_kernel<16, 8, 8, 4, true, 4>", chunk, D, 256, enc_ms, True)
     enc_r.update(achieved=MFMA_SCORE_OPS * enc_pairs / 8 / 1e12, frac=MFMA_SCORE_OPS * enc_pairs / 8 / VALU_PEAK_LANE_OPS)
     out["encode_prefill"] = {"workload": "CQ-8c8b, 32768 tokens x 4096 channels, one tensor, one cq_encode call",
                              "ms": enc_ms, "tokens_per_s": chunk / (enc_ms * 1e-3), "roofline": enc_r}
@@ -385,7 +387,7 @@ def extra_measurements(cq, synth, torch):
                     "(cq_chunk_attention)",
         "ms": med_c, "query_token_pairs_per_s": pairs / (med_c * 1e-3),
         "useful_TFLOPs": pairs * 4 * cfg.head_dim / (med_c * 1e-3) / 1e12,
-        "roofline": {"bound": "mfma", "kernel": "chunk_attention_kernel<16, 8, 8, 8, false>", "achieved": executed, "peak": FP16_MFMA_PEAK_TFLOPS,
+        "roofline": {"bound": "mfma", "kernel": "chunk_attention_kernel<16, 8, 8, 8, false, false>", "achieved": executed, "peak": FP16_MFMA_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": executed / FP16_MFMA_PEAK_TFLOPS, "traffic": None,
                      "note": "executed fp16 MFMA work (probabilities split into two fp16 parts: 6 d flops per pair, 4 d useful)"}}
     # the same chunk over the caches read as pre-RoPE keys: each key tile is rotated once in LDS
@@ -394,7 +396,7 @@ def extra_measurements(cq, synth, torch):
     out["chunk_attention_long_context_pre_rope_keys"] = {
         "workload": "as chunk_attention_long_context, keys cached before RoPE (cq_chunk_attention_rope, base 10000)",
         "ms": med_cr, "query_token_pairs_per_s": pairs / (med_cr * 1e-3), "slowdown_vs_position_independent": med_cr / med_c,
-        "roofline": {"bound": "mfma", "kernel": "chunk_attention_kernel<16, 8, 8, 8, true>",
+        "roofline": {"bound": "mfma", "kernel": "chunk_attention_kernel<16, 8, 8, 8, true, false>",
                      "achieved": pairs * 6 * cfg.head_dim / (med_cr * 1e-3) / 1e12, "peak": FP16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": pairs * 6 * cfg.head_dim / (med_cr * 1e-3) / 1e12 / FP16_MFMA_PEAK_TFLOPS, "traffic": None}}
     del qc, call_c, call_cr, sets, st0
@@ -477,10 +479,11 @@ def extra_measurements(cq, synth, torch):
                     "iterations in each of 512 groups (cq_kmeans_fit)",
         "ms": fit_ms, "kmeanspp_ms": init_ms, "ms_per_iteration": per_iter,
         "seconds_for_64_tensors": fit_ms * 64 / 1e3,
-        "roofline": {"bound": "alu", "kernel": "kmeans_lloyd_kernel, per iteration (counted as the direct form: fp32 subtract, multiply, add per "
-                                               "(token channel, centroid) pair, 3 flops; the matrix cores filter, so that it can exceed the peak)",
-                     "achieved": 3 * 8 * pairs_iter / (per_iter * 1e-3) / 1e12, "peak": FP32_VECTOR_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": 3 * 8 * pairs_iter / (per_iter * 1e-3) / 1e12 / FP32_VECTOR_PEAK_TFLOPS, "traffic": None}}
+        "direct_form_TFLOPs": 3 * 8 * pairs_iter / (per_iter * 1e-3) / 1e12,
+        "roofline": {"bound": "alu", "kernel": "kmeans_lloyd_kernel<8, false>, per iteration (vector instructions issued; the matrix cores score "
+                                               "the centroids, so that most of the direct form's flops are not executed)",
+                     "achieved": LLOYD_LANE_OPS * n_cal * fmt.groups / (per_iter * 1e-3) / 1e12, "peak": VALU_PEAK_LANE_OPS / 1e12,
+                     "unit": "T lane-instr/s", "frac": LLOYD_LANE_OPS * n_cal * fmt.groups / (per_iter * 1e-3) / VALU_PEAK_LANE_OPS, "traffic": None}}
     return out
 
 

@@ -109,9 +109,8 @@ def test_short_chunk_equals_token_by_token_decode_attention(c, b, hq, hkv):
 
 
 @pytest.mark.parametrize("m", [8, 9])
-def test_chunk_around_the_token_by_token_limit_of_a_large_batch(m):
-    # 16 sequences x 32 KV heads x 32 tiles = 16384 tiles: a large batch, where chunks of up to
-    # 8 tokens (one query head per KV head) go token by token and 9 tokens go to the matrix cores
+def test_chunk_of_few_tokens_of_a_large_batch(m):
+    # 16 sequences x 32 KV heads x 32 tiles: the kernel with the codebooks in LDS, up to 8 rows and above
     c, b, hq, hkv, B, T, t_cap = 8, 8, 32, 32, 16, 2048, 2048
     fmt, q, kc, vc, ck, cv = _case(13, c, b, hq, hkv, B, m, T)
     out = _gpu(q, codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap), ck, cv, 0.09, fmt, T, t_cap)
@@ -119,6 +118,32 @@ def test_chunk_around_the_token_by_token_limit_of_a_large_batch(m):
     pick = [0, 7, 15]
     ref = O.chunk_attention(q[pick], kc[pick], vc[pick], ck, cv, 0.09, hkv)
     _check(out[pick], ref)
+
+
+@pytest.mark.parametrize("c,b", [(2, 8), (8, 10)])
+@pytest.mark.parametrize("m,hq,hkv,B,T", [(3, 32, 32, 8, 4096), (5, 8, 8, 2, 65536), (8, 32, 32, 16, 2048), (4, 16, 8, 33, 4000)])
+def test_chunks_of_large_batches_go_token_by_token(c, b, m, hq, hkv, B, T):
+    """From 16384 tiles on, m <= 8 / (query heads per KV head) tokens of these formats are m calls of the
+    single-token kernel: the same bits, ragged lengths (one as short as the chunk) included.  The matrix-core
+    kernel (explicit split) agrees within the tolerance."""
+    fmt = cq.CQFormat(c, b, 128, hkv)
+    t_cap = -(-T // 64) * 64
+    assert B * hkv * (t_cap // 64) >= 16384 and m <= 8 // (hq // hkv)
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()
+    caches = [torch.randint(0, 256, (cq.cq_cache_bytes(fmt, B, t_cap),), generator=gen, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    q, ck, cv = rand(B, m, hq, 128), rand(fmt.groups, 1 << b, c), rand(fmt.groups, 1 << b, c)
+    lens = torch.randint(m, T + 1, (B,), generator=gen, device="cuda", dtype=torch.int32)
+    lens[0], lens[1] = T, m
+    out = cq.cq_chunk_attention(q, *caches, ck, cv, 0.09, fmt, T, t_cap, seq_lens=lens)
+    for j in range(m):
+        back = m - 1 - j
+        dec = cq.cq_decode_attention(q[:, j].contiguous(), *caches, ck, cv, 0.09, fmt, T - back, t_cap, seq_lens=lens - back)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, j].contiguous().view(torch.int16), dec.view(torch.int16))
+    alt = cq.cq_chunk_attention(q, *caches, ck, cv, 0.09, fmt, T, t_cap, seq_lens=lens, tokens_per_split=t_cap)
+    torch.cuda.synchronize()
+    assert (alt.double() - out.double()).abs().max() <= 2e-3 * out.double().abs().max()
 
 
 def test_short_chunk_splits_long_contexts():
