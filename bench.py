@@ -46,7 +46,7 @@ LAST_LEVEL_CACHE_BYTES = 256e6
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 MFMA_SCORE_OPS = 1.08
 # vector instructions of a Lloyd iteration per (token, group) of 8 channels and 256 centroids (SQ_INSTS_VALU / dispatch)
-LLOYD_LANE_OPS = 547.0
+LLOYD_LANE_OPS = 535.0
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 FP16_MFMA_PEAK_TFLOPS = 2500.0
 METRIC = "decode-attn KV tokens/s & achieved HBM GB/s (% peak); cq_encode tokens/s"

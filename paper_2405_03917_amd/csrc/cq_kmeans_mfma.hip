@@ -36,7 +36,7 @@
 // 4096 tokens of 40 distinct points, 128 groups of 8 channels, per iteration: 76 us in the direct search of all, 419
 // when every tie was re-done, 60 now; half of the channels dead: 115, 434, 51.
 //
-// What bounds it: the vector ALU (547 instructions per 64 tokens and group: 208 in the scan, 150 in
+// What bounds it: the vector ALU (535 instructions per 64 tokens and group: 208 in the scan, 150 in
 // the winner's eight, the rest merge, bound, sums and re-dos; the direct search took 2 c + 3 per
 // token and centroid).  The group's centroids sit in registers as matrix operands (32 registers)
 // with the norms in accumulator layout (128): two wavefronts per SIMD and no LDS reads in the
