@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
         own[i] = cent[(size_t)tid * C + i];
         n2 = __builtin_fmaf(own[i], own[i], n2);
         cs[(tid >> 2) * QS + (tid & 3) * C + i] = own[i];
-        hash = (hash ^ __float_as_uint(own[i])) * 0x9e3779b1u;
+        hash = (hash ^ __float_as_uint(own[i] + 0.f)) * 0x9e3779b1u;        // (zeros of both signs are equal)
         hash ^= hash >> 15;
     }
     hash = (hash * 0x85ebca6bu) / (0xffffffffu / kHashSlots + 1u);
