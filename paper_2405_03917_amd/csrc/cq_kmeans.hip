@@ -275,7 +275,8 @@ __global__ __launch_bounds__(kPPThreads) void kmeanspp_kernel(const uint16_t* __
 // its mass in up to four sums, so the search is 4 + R / 4 independent reductions and one scan.
 // Weights sit in registers too, 32 rounds of them in LDS (as 32 more registers they spilled 50 to 61).
 // 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 6.7 ms, weighted 30.7 -> 9.0; 1500 tokens, 256
-// groups of 4: 1.05 -> 0.71 ms; 100 tokens 0.54 -> 0.56 (two barriers' worth of other wavefronts' numbers).
+// groups of 4: 1.05 -> 0.71 ms; 100 tokens 0.54 -> 0.56 (two barriers' worth of other wavefronts' numbers), so that
+// up to 128 go to the general kernel (run_kmeanspp).
 // Slices of 4 (of 2: 8) weighted tokens per lane in registers instead of 2 (4), 32 rounds: 8 channels 11.0 -> 9.0 ms
 // at 512 groups, 4 channels 3.7 -> 4.6 ms at 256 groups (spills).
 constexpr int kPPRounds = 32;
@@ -700,8 +701,12 @@ template <int C>
 cq_status run_kmeanspp(const KMeansArgs& a, const KMeansWorkspace& ws, hipStream_t st)
 {
     if constexpr (C >= 2) {
-        // the tokens' distances fit the registers of one workgroup
-        if (a.n <= kPPThreads * kPPRounds) {
+        // The tokens' distances fit the registers of one workgroup.  Up to 128 tokens of groups that all run at once, one
+        // per CU, the general kernel's picks wait for fewer barriers' worth of idle wavefronts (8 channels, 16 groups,
+        // general / resident: 1 token 395 / 518 us, 64 484 / 556, 100 550 / 577, 128 586 / 592, 160 640 / 611); of more groups
+        // two share a CU here and not there (512 groups, 100 tokens: 1096 / 885).
+        const bool few = a.n <= 128 && a.f.groups <= 256;
+        if (!few && a.n <= kPPThreads * kPPRounds) {
             return a.weights ? launch_kmeanspp_rounds<C, true>(a, ws, st) : launch_kmeanspp_rounds<C, false>(a, ws, st);
         }
     }

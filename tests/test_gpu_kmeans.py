@@ -143,6 +143,23 @@ def test_picks_at_the_edges_of_the_register_resident_rounds(n, c, weighted):
     assert np.array_equal(out["picks"].cpu().numpy(), picks)
 
 
+@pytest.mark.parametrize("n", [1, 2, 65, 128, 129])
+@pytest.mark.parametrize("c,heads,weighted", [(8, 1, False), (8, 1, True), (8, 17, True), (4, 8, False), (4, 9, True),
+                                              (2, 4, False), (2, 5, False), (2, 5, True)])
+def test_picks_of_few_tokens(n, c, heads, weighted):
+    """Up to 128 tokens and 256 groups take the general kernel, more of either the register-resident one."""
+    fmt = cq.CQFormat(c, 8 if c == 8 else 4, 128, heads)
+    G, K = fmt.groups, 1 << fmt.b
+    x = _data(80 + c, n, 128 * heads)
+    rnd = _rnd(n + c, G, K)
+    w = _weights(n, n, G) if weighted else None
+    picks, _ = KO.kmeanspp(x, c, K, rnd, w)
+    out = cq.cq_kmeans_fit(torch.from_numpy(x).cuda(), fmt, 0, rnd=_dev_rnd(rnd),
+                           weights=None if w is None else torch.from_numpy(w).cuda(), want_picks=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(out["picks"].cpu().numpy(), picks)
+
+
 @pytest.mark.parametrize("c,n,weighted", [(8, 63, False), (8, 65, True), (4, 2047, False), (8, 5000, False), (4, 9217, True),
                                           (2, 20001, False), (8, 12001, True)])
 @pytest.mark.parametrize("data", ["plain", "tiny", "large", "far points", "dead groups", "duplicates"])
