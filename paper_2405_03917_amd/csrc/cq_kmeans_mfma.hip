@@ -38,11 +38,31 @@
 // (A table of 4096 slots misses fewer of them, 617 -> 532 us for 10 iterations of 4096 weighted tokens of integers in
 // 256 groups of 4, but its clearing costs calls of 300 to 1500 tokens, groups of 2, 3 to 6 %.)
 //
+// Skipping.  In a fit of many iterations most tokens keep their centroid.  When a token has been looked at, its
+// distance d to its centroid a and a lower bound b of its distance to every other are known (the runner-up's score
+// and the winner's eight, less the bound above for the longest centroid).  Until a has moved by D_a and no centroid by
+// more than D in all, with D_a + D < b - d, a is still the nearest (Hamerly, "Making k-means even faster", 2010).
+// So each token keeps one number, its threshold t = (b - d) + D_a + D at that time, and is skipped while
+// t > D_a + D; the sums of the clusters stay from one iteration to the next, and only tokens that change cluster are
+// moved (integers: the same sums, and the same centroids, whatever the order).  The choice must be that of the
+// direct form in fp32, so nothing is left to rounding: lengths carry 2^-18 of themselves as a margin (the direct
+// form's error is 3 x 2^-22 of the squares), moves are rounded up, thresholds down (fp16, scaled; at most 65504);
+// near ties and every token of a group with equal centroids (which a twin that stays behind could win) get 0 and are
+// looked at again.
+// A wavefront lists its tokens that are not skipped and takes 64 of the list at a time.  Such an iteration costs
+// 1.2 times a plain one when it skips nothing, and 0.15 when it skips everything; of 100 iterations over the
+// calibration tokens (32768, groups of 8) 0.4 of the tokens are looked at, 0.8 in the first ten.  32768 tokens, 512
+// groups, 100 iterations: 31.8 -> 22.2 ms, weighted 40.4 -> 20.1; 6000 tokens 6.5 -> 2.9; 30 iterations 1.0-1.2 times
+// as fast, 20 iterations 0.85-1.07 (hence kStateIterations, kPlainIterations).  Weighted fits of few tokens
+// (below about 12000 of 8 channels) have no room for the sums in their scratch and run plain.
+// A group's only workgroup runs all iterations that are left in one launch: 100 launches waited for their busiest
+// group each (26.3 against 30.3 ms).
+//
 // What bounds it: the vector ALU (535 instructions per 64 tokens and group: 208 in the scan, 150 in
 // the winner's eight, the rest merge, bound, sums and re-dos; the direct search took 2 c + 3 per
 // token and centroid).  The group's centroids sit in registers as matrix operands (32 registers)
-// with the norms in accumulator layout (128): two wavefronts per SIMD and no LDS reads in the
-// scan.  32768 tokens, 512 groups of 8 channels: 1.36 + 0.30 ms per iteration in two kernels ->
+// with the norms in accumulator layout (128; half of them read from LDS where tokens are skipped): two wavefronts per
+// SIMD and no other LDS reads in the scan.  32768 tokens, 512 groups of 8 channels: 1.36 + 0.30 ms per iteration in two kernels ->
 // 0.31 ms (maxima over quads instead of eights: 17 instructions per 16 scores in the scan for 4
 // fewer distances per token, slower by the count).
 //
@@ -62,6 +82,9 @@ constexpr int kLloydWaves = 4;
 constexpr int kK = 256;                 // centroids per group
 constexpr int kNBlk = kK / 32;
 constexpr int kHashSlots = 1024;        // for finding equal centroids
+constexpr int kStateIterations = 30;    // a fit of at least as many iterations skips tokens, ...
+constexpr int kPlainIterations = 10;    // ... from this iteration on
+static_assert(kStateIterations >= kPlainIterations + 2, "one iteration fills the state, at least one uses it");
 
 template <int CTRL>
 __device__ __forceinline__ unsigned dpp_mov(unsigned v)
@@ -130,14 +153,33 @@ struct Operand<8> {
 template <int C, bool W>
 constexpr int kSumWords = (W ? 2 * C : C) + 1;
 
+// What the iterations of one fit hand on from each to the next where tokens may be skipped ("Skipping" above).
+// Per group g: sums [256][kSumWords] of the present assignment; travel, kTravelWords floats: how far each centroid
+// has moved since the first iteration, the sum of the longest moves, and the scale of lengths of the first
+// iteration; per token its threshold (fp16) and its cluster.
+constexpr int kTravelWords = kK + 4;
+struct LloydState {
+    unsigned long long* sums;
+    float* travel;
+    unsigned* arrived;                  // workgroups of the group that are done (several splits per group)
+    uint16_t* threshold;                // [group][n_pad]
+    uint8_t* own;                       // [group][n_pad]
+    int n_pad;
+};
+enum LloydMode { kPlain, kFirst, kNext };       // without state; fills it; uses it
+
+constexpr int kScanTokens = 8;          // tokens whose thresholds a lane looks at together (16 bytes)
+constexpr int kListTokens = 64 * kScanTokens + 64;
+
 // One workgroup: tokens [split * tokens_per_split, ...) of one group.  One split per group: the new
-// centroids are written at once; else the sums go to `partials` [group][split][256][kSumWords].
-template <int C, bool W>
+// centroids are written at once; else the sums go to `partials` [group][split][256][kSumWords], or (with state) are
+// added to the group's, and the last of its workgroups writes the centroids.
+template <int C, bool W, int MODE>
 __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const uint16_t* __restrict__ xg_all,
                                                                         const uint32_t* __restrict__ wq_all,
                                                                         float* cent_all, uint16_t* __restrict__ assign_all,
-                                                                        unsigned long long* __restrict__ partials, int n,
-                                                                        int tokens_per_split)
+                                                                        unsigned long long* __restrict__ partials, LloydState state,
+                                                                        int n, int tokens_per_split, int iterations)
 {
     using vec_t = typename Operand<C>::type;
     constexpr int QS = 4 * C + 4;                       // floats per four centroids (16 bytes of padding: lanes that read
@@ -150,13 +192,33 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     __shared__ unsigned first_of[kHashSlots];
     __shared__ unsigned kept[kLloydWaves];
     __shared__ unsigned long long sums[kK * SW];
+    __shared__ float need[MODE == kNext ? kK : 1];      // a token of cluster k is skipped if its threshold is above need[k]
+    __shared__ unsigned long long changed[MODE == kNext ? kLloydWaves : 1][MODE == kNext ? 128 : 1];    // token, old cluster, new cluster
+    __shared__ unsigned list[MODE == kNext ? kLloydWaves : 1][MODE == kNext ? kListTokens : 1];     // tokens to look at, cluster << 24
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.y, split = blockIdx.x;
     const uint16_t* xg = xg_all + (size_t)g * n * C;
     const uint32_t* wq = W ? wq_all + (size_t)g * n : nullptr;
     float* cent = cent_all + (size_t)g * kK * C;
+    float* travel = MODE == kPlain ? nullptr : state.travel + (size_t)g * kTravelWords;
+    uint16_t* threshold = MODE == kPlain ? nullptr : state.threshold + (size_t)g * state.n_pad;
+    uint8_t* own_cluster = MODE == kPlain ? nullptr : state.own + (size_t)g * state.n_pad;
+    float travelled = MODE == kNext ? travel[tid] : 0.f, longest = MODE == kNext ? travel[kK] : 0.f;
+    const float f0 = MODE == kNext ? travel[kK + 1] : 0.f;
+    unsigned long long* all_sums = MODE == kPlain ? nullptr : state.sums + (size_t)g * (kK * SW);
+    const bool alone = gridDim.x == 1;                  // the group's only workgroup
+    for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = MODE == kNext && alone ? all_sums[i] : 0ull;
+
+    // A group's only workgroup takes all iterations that are left (groups end when they are done: no launch waits for the
+    // busiest of them); else `iterations` is 1.
+#pragma unroll 1
+    for (int it = 0;; ++it) {
+    // (opaque: addresses that follow from them would be kept in registers through all iterations)
+    if constexpr (MODE == kNext) asm volatile("" : "+v"(tid), "+v"(lane));
+    const bool last_iteration = it + 1 >= iterations;
+    uint16_t* assign_now = last_iteration ? assign_all : nullptr;
 
     // ---- the group's centroids: fp32 in LDS, scale, norms, matrix operands
     static_assert(kLloydWaves * 64 == kK, "one centroid per thread");
@@ -164,7 +226,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     unsigned hash = 0;
 #pragma unroll
     for (int i = 0; i < C; ++i) {
-        own[i] = cent[(size_t)tid * C + i];
+        own[i] = it == 0 ? cent[(size_t)tid * C + i] : cs[(tid >> 2) * QS + (tid & 3) * C + i];
         n2 = __builtin_fmaf(own[i], own[i], n2);
         cs[(tid >> 2) * QS + (tid & 3) * C + i] = own[i];
         hash = (hash ^ __float_as_uint(own[i] + 0.f)) * 0x9e3779b1u;        // (zeros of both signs are equal)
@@ -174,7 +236,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     for (int i = tid; i < kHashSlots; i += kLloydWaves * 64) first_of[i] = ~0u;
     const unsigned wmax = wave_extreme_u32<true>(__float_as_uint(n2));
     if (lane == 0) c2w[wave] = wmax;
-    for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = 0ull;
+    if constexpr (MODE == kNext) need[tid] = (travelled + longest) * (1.f + 0x1p-22f);
     __syncthreads();
     unsigned c2bits = 0;
 #pragma unroll
@@ -206,13 +268,23 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     __syncthreads();
     static_assert(kLloydWaves == 4, "the four counts");
     // (a single centroid wins every scan, whatever its size)
-    const bool group_direct = extreme && __builtin_amdgcn_readfirstlane((int)(kept[0] + kept[1] + kept[2] + kept[3])) > 1;
+    const int distinct = __builtin_amdgcn_readfirstlane((int)(kept[0] + kept[1] + kept[2] + kept[3]));
+    const bool group_direct = extreme && distinct > 1;
 
     // A operands: lane l holds row l % 32 of each block of 32 centroids; lanes below 32 the high
     // parts, the others the low parts (C = 2: both in the lower lanes).  D's registers: row
     // 8 (i / 4) + 4 (lane / 32) + i % 4.
     vec_t aop[kNBlk];
+    // (the norms of every second block come from LDS where 128 registers for all of them are too many)
+    constexpr bool HALF_LDS = MODE == kNext || (C == 8 && MODE != kPlain);
     float16_t nrm[kNBlk];
+    auto load_norms = [&](int b, int row) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 v = *reinterpret_cast<const float4*>(&norms[row + b * 32 + 8 * q]);
+            nrm[b][4 * q] = v.x; nrm[b][4 * q + 1] = v.y; nrm[b][4 * q + 2] = v.z; nrm[b][4 * q + 3] = v.w;
+        }
+    };
 #pragma unroll
     for (int b = 0; b < kNBlk; ++b) {
         const int j = b * 32 + (lane & 31);
@@ -232,11 +304,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
 #pragma unroll
             for (int i = 0; i < C; ++i) aop[b][i] = lane < 32 ? hi[i] : lo[i];
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4*>(&norms[b * 32 + 8 * q + 4 * (lane >> 5)]);
-            nrm[b][4 * q] = v.x; nrm[b][4 * q + 1] = v.y; nrm[b][4 * q + 2] = v.z; nrm[b][4 * q + 3] = v.w;
-        }
+        if (!HALF_LDS || b % 2 == 0) load_norms(b, 4 * (lane >> 5));
     }
 
     auto cent_at = [&](int j, float (&c)[C]) {
@@ -254,15 +322,49 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     };
 
     const int t_begin = split * tokens_per_split, t_end = min(t_begin + tokens_per_split, n);
-    unsigned xa[C / 2], xb[C / 2];                          // tokens base + lane % 32 and base + 32 + lane % 32
-    auto load_tile = [&](int at, unsigned (&lo)[C / 2], unsigned (&up)[C / 2]) {
-        load_words<C>(xg + (size_t)min(at + (lane & 31), n - 1) * C, lo);
-        load_words<C>(xg + (size_t)min(at + 32 + (lane & 31), n - 1) * C, up);
+    // (the unit of lengths in the state is that of the first iteration)
+    const float to_state = MODE == kNext ? f0 / f1 : 1.f, c_longest = __builtin_amdgcn_sqrtf(c2s);
+    // 64 tokens at a time: two sets of 32 as they are stored, xa of lanes % 32, xb of 32 + lanes % 32 (this lane's own
+    // token: number i0, of cluster `old` so far, if `valid`).  request() is called once their words have been read.
+    // What it finds is stored by put() ahead of the next request: a store behind it would be waited for with it.
+    int put_at = -1;
+    unsigned put_threshold = 0, put_cluster = 0;
+    auto put = [&] {
+        if (put_at < 0) return;
+        const unsigned at = (unsigned)put_at;
+        if constexpr (MODE != kPlain) threshold[at] = (uint16_t)put_threshold;
+        if constexpr (MODE == kFirst) own_cluster[at] = (uint8_t)put_cluster;
+        if (assign_now) assign_now[(size_t)g * n + at] = (uint16_t)put_cluster;
     };
-    int base = t_begin + wave * 64;
-    load_tile(base, xa, xb);
-#pragma unroll 1
-    for (; base < t_end; base += kLloydWaves * 64) {
+    // ---- the clusters' sums: x 2^24 is an integer, hi 2^20 + lo with hi = floor(16 x).  A token joins cluster `to` and
+    // (kNext) leaves cluster `from`.
+    auto add_token = [&](const float (&x)[C], int i0, int from, int to) {
+        unsigned long long* sj = &sums[to * SW];
+        unsigned long long* so = &sums[from * SW];
+        const auto move = [&](int i, unsigned long long v) {
+            atomicAdd(sj + i, v);
+            if constexpr (MODE == kNext) atomicAdd(so + i, 0ull - v);
+        };
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if constexpr (W) {
+                const float x16 = x[i] * 16.f, fl = __builtin_floorf(x16);
+                const long long xhi = (long long)(int)fl, xlo = (long long)(int)((x16 - fl) * 1048576.f);
+                const long long w = (long long)wq[i0];
+                move(2 * i, (unsigned long long)(w * xhi));
+                move(2 * i + 1, (unsigned long long)(w * xlo));
+            } else {
+                // 16 x and the rest in units of 2^-24 as the mantissas of 1.5 2^23 + (integer): exact, and
+                // the constants of the bit patterns go back out with the count
+                const float t = __builtin_fmaf(x[i], 16.f, kMagic);
+                const float u = __builtin_fmaf(__builtin_fmaf(x[i], 16.f, kMagic - t), 1048576.f, kMagic);
+                move(i, ((unsigned long long)__float_as_uint(t) << 20) + __float_as_uint(u));
+            }
+        }
+        move(SW - 1, W ? (unsigned long long)wq[i0] : 1ull);
+    };
+    int n_changed = 0;                      // kNext: tokens of `changed` whose move is still to be made
+    auto tokens = [&](unsigned (&xa)[C / 2], unsigned (&xb)[C / 2], int i0, int old, bool valid, auto&& request) {
         unsigned xw[C / 2], xs[2][C / 2];
 #pragma unroll
         for (int i = 0; i < C / 2; ++i) {
@@ -271,7 +373,8 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
             xs[0][i] = __builtin_bit_cast(unsigned, __builtin_bit_cast(half2_t, wa) * m1 * m2);
             xs[1][i] = __builtin_bit_cast(unsigned, __builtin_bit_cast(half2_t, wb) * m1 * m2);
         }
-        load_tile(base + kLloydWaves * 64, xa, xb);         // (clamped to the last token)
+        put();
+        request();
 
         float x2 = 0.f;                                     // |x'|^2 of this lane's own token (infinite where the scaling overflowed)
 #pragma unroll
@@ -284,27 +387,32 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
         const float slack = 0.01f * __builtin_amdgcn_sqrtf(c2s + x2);
 
         // ---- scan: the two largest maxima of eight, for tokens 32 h + lane % 32
-        float hbest[2], hsecond[2];
+        float hbest[2] = {LOWEST, LOWEST}, hsecond[2] = {LOWEST, LOWEST};
+        vec_t bop[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            vec_t bop;
             if constexpr (C == 8) {
                 const half2_t p0 = __builtin_bit_cast(half2_t, xs[h][0]), p1 = __builtin_bit_cast(half2_t, xs[h][1]);
                 const half2_t p2 = __builtin_bit_cast(half2_t, xs[h][2]), p3 = __builtin_bit_cast(half2_t, xs[h][3]);
-                bop = vec_t{p0.x, p0.y, p1.x, p1.y, p2.x, p2.y, p3.x, p3.y};
+                bop[h] = vec_t{p0.x, p0.y, p1.x, p1.y, p2.x, p2.y, p3.x, p3.y};
             } else if constexpr (C == 4) {
                 const half2_t p0 = __builtin_bit_cast(half2_t, xs[h][0]), p1 = __builtin_bit_cast(half2_t, xs[h][1]);
-                bop = vec_t{p0.x, p0.y, p1.x, p1.y};
+                bop[h] = vec_t{p0.x, p0.y, p1.x, p1.y};
             } else {
                 const half2_t p0 = __builtin_bit_cast(half2_t, xs[h][0]);
-                bop = vec_t{p0.x, p0.y, p0.x, p0.y};
+                bop[h] = vec_t{p0.x, p0.y, p0.x, p0.y};
             }
-            float best = LOWEST, second = LOWEST;
+        }
+        int norm_row = 4 * (lane >> 5);
+        asm volatile("" : "+v"(norm_row));                   // (read again for every 64 tokens)
 #pragma unroll
-            for (int b = 0; b < kNBlk; ++b) {
+        for (int b = 0; b < kNBlk; ++b) {
+            if (HALF_LDS && b % 2 == 0) load_norms(b + 1, norm_row);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
                 float16_t d;
-                if constexpr (C == 8) d = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop[b], bop, nrm[b], 0, 0, 0);
-                else d = __builtin_amdgcn_mfma_f32_32x32x8f16(aop[b], bop, nrm[b], 0, 0, 0);
+                if constexpr (C == 8) d = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop[b], bop[h], nrm[b], 0, 0, 0);
+                else d = __builtin_amdgcn_mfma_f32_32x32x8f16(aop[b], bop[h], nrm[b], 0, 0, 0);
                 float om[2];
 #pragma unroll
                 for (int o = 0; o < 2; ++o) {
@@ -316,11 +424,9 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
                     om[o] = __uint_as_float((__float_as_uint(m) & 0xfffffff0u) | (unsigned)(2 * b + o));
                 }
                 // the runner-up of {best, second, k1, k2}, second <= best, is max(median(best, k1, k2), second)
-                second = fmaxf(second, __builtin_amdgcn_fmed3f(best, om[0], om[1]));
-                best = fmaxf(fmaxf(best, om[0]), om[1]);
+                hsecond[h] = fmaxf(hsecond[h], __builtin_amdgcn_fmed3f(hbest[h], om[0], om[1]));
+                hbest[h] = fmaxf(fmaxf(hbest[h], om[0]), om[1]);
             }
-            hbest[h] = best;
-            hsecond[h] = second;
         }
         // each lane takes its own token: its own scan of that half and the partner lane's (the other rows)
         const int hi = lane >> 5;
@@ -332,12 +438,10 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
         const unsigned bb = __float_as_uint(best);
         const int j0 = (int)(bb & 15u) * 16 + 4 * (other ? 1 - hi : hi);
         const float gap = __uint_as_float(bb & 0xfffffff0u) - __uint_as_float(__float_as_uint(second) & 0xfffffff0u);
-        const bool valid = base + lane < t_end;
-
         // ---- the winner's eight centroids (j0 .. j0 + 3, j0 + 8 .. j0 + 11) in the direct form
         float x[C];
         widen_words<C>(xw, x);
-        float dbest = 0.f;
+        float dbest = 0.f, dsecond = 3.0e38f;
         int arg = j0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -348,6 +452,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
             if (k == 0) {
                 dbest = d;
             } else {
+                if constexpr (MODE != kPlain) dsecond = __builtin_amdgcn_fmed3f(dbest, dsecond, d);
                 arg = d < dbest ? j : arg;
                 dbest = d < dbest ? d : dbest;
             }
@@ -431,32 +536,181 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
         }
         arg &= kK - 1;
 
-        // ---- the cluster's sums: x 2^24 is an integer, hi 2^20 + lo with hi = floor(16 x)
-        if (valid) {
-            unsigned long long* sj = &sums[arg * SW];
-            const int i0 = base + lane;
+        // ---- the token's threshold ("Skipping"): how much farther the next nearest centroid is at least, less the
+        // error of everything here, ahead of what the centroids have travelled so far
+        if constexpr (MODE != kPlain) {
+            const float err = 0x1p-20f * (11.1f * c_longest * (xn + 0.5f * c_longest) + 0.76f * x2);
+            const float other2 = fminf(x2 - 2.f * (__uint_as_float(__float_as_uint(second) & 0xfffffff0u) + err), dsecond * f2 * (1.f - 0x1p-20f));
+            const float to_other = __builtin_amdgcn_sqrtf(fmaxf(other2, 0.f)), to_own = __builtin_amdgcn_sqrtf(dbest * f2);
+            const float ahead = (to_other - to_own) - 0x1p-18f * (to_other + to_own);
+            const float moved = MODE == kNext ? need[arg] * (1.f - 0x1p-20f) : 0.f;
+            const float t = unsure || distinct < kK || !(ahead > 0.f) ? 0.f : (ahead * to_state + moved) * (1.f - 0x1p-20f);
+            put_threshold = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(t, t));     // (towards zero, at most 65504)
+        }
+        put_at = valid ? i0 : -1;
+        put_cluster = (unsigned)arg;
+        if constexpr (MODE == kNext) {
+            const bool other_now = valid && arg != old;
+            const unsigned long long mask = __ballot(other_now);
+            if (other_now)
+                changed[wave][n_changed + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u))] =
+                    (unsigned)i0 | ((unsigned long long)((unsigned)old | ((unsigned)arg << 8)) << 32);
+            n_changed += __popcll(mask);
+        } else {
+            if (valid) add_token(x, i0, 0, arg);
+        }
+    };
+    // kNext: the moves of up to 64 changed tokens (one in twenty changes: together they cost what those of one would)
+    auto make_moves = [&] {
+        const int count = min(n_changed, 64);
+        n_changed -= count;
+        if (lane < count) {
+            const unsigned long long e = changed[wave][n_changed + lane];
+            const unsigned i0 = (unsigned)e, from = (unsigned)(e >> 32) & 255u, to = (unsigned)(e >> 40) & 255u;
+            unsigned xw[C / 2];
+            load_words<C>(reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(xg) + i0 * (2u * C)), xw);
+            float x[C];
+            widen_words<C>(xw, x);
+            own_cluster[i0] = (uint8_t)to;
+            add_token(x, (int)i0, (int)from, (int)to);
+        }
+    };
+
+    if constexpr (MODE != kNext) {
+        unsigned xa[C / 2], xb[C / 2];
+        auto load_tile = [&](int at) {
+            load_words<C>(xg + (size_t)min(at + (lane & 31), n - 1) * C, xa);
+            load_words<C>(xg + (size_t)min(at + 32 + (lane & 31), n - 1) * C, xb);
+        };
+        int base = t_begin + wave * 64;
+        load_tile(base);
+#pragma unroll 1
+        for (; base < t_end; base += kLloydWaves * 64)
+            tokens(xa, xb, base + lane, 0, base + lane < t_end, [&] { load_tile(base + kLloydWaves * 64); });   // (clamped to the last token)
+        put();
+    } else {
+        // Each wavefront has a quarter of the tokens to itself: it looks at the thresholds of 512 at a time, lists
+        // the tokens that could have a new cluster, and takes 64 of the list at a time.  Thresholds and tokens are
+        // requested one step ahead.
+        const int share = ((t_end - t_begin + kLloydWaves - 1) / kLloydWaves + kScanTokens - 1) / kScanTokens * kScanTokens;
+        int at = t_begin + wave * share;
+        const int end = min(at + share, t_end);
+        uint4 th;
+        uint2 cl;
+        auto load_thresholds = [&] {
+            const size_t i = (size_t)min(at + kScanTokens * lane, state.n_pad - kScanTokens);
+            th = *(const uint4*)(threshold + i);
+            cl = *(const uint2*)(own_cluster + i);
+        };
+        load_thresholds();
+        unsigned* todo_list = list[wave];
+        unsigned xa[C / 2] = {}, xb[C / 2] = {}, ea = 0, eb = 0;
+        int listed = 0, flying = 0;
+#pragma unroll 1
+        for (;;) {
+            // (the tokens' words, requested long ago, are waited for ahead of the next thresholds' request)
+            unsigned ya[C / 2], yb[C / 2];
 #pragma unroll
-            for (int i = 0; i < C; ++i) {
-                if constexpr (W) {
-                    const float x16 = x[i] * 16.f, fl = __builtin_floorf(x16);
-                    const long long xhi = (long long)(int)fl, xlo = (long long)(int)((x16 - fl) * 1048576.f);
-                    const long long w = (long long)wq[i0];
-                    atomicAdd(sj + 2 * i, (unsigned long long)(w * xhi));
-                    atomicAdd(sj + 2 * i + 1, (unsigned long long)(w * xlo));
-                } else {
-                    // 16 x and the rest in units of 2^-24 as the mantissas of 1.5 2^23 + (integer): exact, and
-                    // the constants of the bit patterns go back out with the count
-                    const float t = __builtin_fmaf(x[i], 16.f, kMagic);
-                    const float u = __builtin_fmaf(__builtin_fmaf(x[i], 16.f, kMagic - t), 1048576.f, kMagic);
-                    atomicAdd(sj + i, ((unsigned long long)__float_as_uint(t) << 20) + __float_as_uint(u));
+            for (int i = 0; i < C / 2; ++i) {
+                ya[i] = xa[i];
+                yb[i] = xb[i];
+                asm volatile("" : "+v"(ya[i]), "+v"(yb[i]));
+            }
+#pragma unroll 1
+            while (listed < 64 && at < end) {
+                const uint4 t4 = th;
+                const uint2 c8 = cl;
+                const int first = at + kScanTokens * lane;
+                at += 64 * kScanTokens;
+                load_thresholds();
+#pragma unroll
+                for (int k = 0; k < kScanTokens; ++k) {
+                    const unsigned tw = k < 2 ? t4.x : k < 4 ? t4.y : k < 6 ? t4.z : t4.w, cw = k < 4 ? c8.x : c8.y;
+                    const float t = (float)__builtin_bit_cast(half2_t, tw)[k & 1];
+                    const unsigned c = (cw >> (8 * (k & 3))) & 255u;
+                    const bool here = first + k < end, look = here && !(t > need[c]);
+                    const unsigned long long mask = __ballot(look);
+                    if (look) todo_list[listed + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u))] = (unsigned)(first + k) | (c << 24);
+                    if (assign_now && here && !look) assign_now[(size_t)g * n + first + k] = (uint16_t)c;
+                    listed += __popcll(mask);
                 }
             }
-            atomicAdd(sj + SW - 1, W ? (unsigned long long)wq[i0] : 1ull);
-            if (assign_all) assign_all[(size_t)g * n + i0] = (uint16_t)arg;
+            const int now = flying;
+            const unsigned mine = lane < 32 ? ea : eb;
+            auto request = [&] {
+                flying = min(listed, 64);
+                listed -= flying;
+                if (flying) {                               // (lanes beyond the last one listed repeat it)
+                    ea = todo_list[listed + min(lane & 31, flying - 1)];
+                    eb = todo_list[listed + min(32 + (lane & 31), flying - 1)];
+                    load_words<C>(reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(xg) + (ea & 0xffffffu) * (2u * C)), xa);
+                    load_words<C>(reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(xg) + (eb & 0xffffffu) * (2u * C)), xb);
+                }
+            };
+            if (now) tokens(ya, yb, (int)(mine & 0xffffffu), (int)(mine >> 24), lane < now, request);
+            else request();
+            if (n_changed >= 64) make_moves();
+            if (!flying) break;
         }
+        put();
+        make_moves();
     }
     __syncthreads();
-    if (partials) {
+    if constexpr (MODE != kPlain) {
+        // the group's sums so far and the changes of this launch; then each thread has a centroid
+        if (!alone) {
+            unsigned* flag = first_of;
+            for (int i = tid; i < kK * SW; i += kLloydWaves * 64)
+                if (sums[i] != 0ull) __hip_atomic_fetch_add(all_sums + i, sums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (all of them have been carried out)
+            __syncthreads();
+            if (tid == 0) {
+                const bool last = __hip_atomic_fetch_add(state.arrived + g, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
+                if (last) __hip_atomic_store(state.arrived + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                *flag = last;
+            }
+            __syncthreads();
+            if (!*flag) return;
+            for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = __hip_atomic_load(all_sums + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+        } else if constexpr (MODE == kFirst) {
+            for (int i = tid; i < kK * SW; i += kLloydWaves * 64) all_sums[i] = sums[i];
+        }
+        const unsigned long long* sj = &sums[tid * SW];
+        const long long wk = (long long)sj[SW - 1];
+        float step2 = 0.f;
+        if (wk != 0) {                                      // a cluster without tokens keeps its centroid
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                float* at = &cs[(tid >> 2) * QS + (tid & 3) * C + i];
+                const float v = W ? kmeans_mean((long long)sj[2 * i], (long long)sj[2 * i + 1], wk) : kmeans_mean(plain_sum(sj[i], sj[SW - 1]), wk);
+                const float d = (v - *at) * (MODE == kNext ? f0 : f1);
+                step2 = __builtin_fmaf(d, d, step2);
+                *at = v;
+                if (last_iteration) cent[(size_t)tid * C + i] = v;
+            }
+        } else if (last_iteration) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) cent[(size_t)tid * C + i] = cs[(tid >> 2) * QS + (tid & 3) * C + i];
+        }
+        // (rounded up, so that no sum of steps comes out too short)
+        const float step = __builtin_amdgcn_sqrtf(step2) * (1.f + 0x1p-16f);
+        if (step > 0.f) travelled = (travelled + step) * (1.f + 0x1p-22f);
+        const unsigned wstep = wave_extreme_u32<true>(__float_as_uint(step));
+        if (lane == 0) c2w[wave] = wstep;
+        __syncthreads();
+        float m = 0.f;
+#pragma unroll
+        for (int w = 0; w < kLloydWaves; ++w) m = fmaxf(m, __uint_as_float(c2w[w]));
+        if (m > 0.f) longest = (longest + m) * (1.f + 0x1p-22f);
+        if (last_iteration) {
+            travel[tid] = travelled;
+            if (tid == 0) {
+                travel[kK] = longest;
+                travel[kK + 1] = MODE == kNext ? f0 : f1;
+            }
+        }
+    } else if (partials) {
         unsigned long long* dst = partials + ((size_t)g * gridDim.x + split) * (kK * SW);
         for (int i = tid; i < kK * SW; i += kLloydWaves * 64) dst[i] = sums[i];
     } else {
@@ -467,6 +721,9 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
             if (wk == 0) continue;                          // a cluster without tokens keeps its centroid
             cent[i] = W ? kmeans_mean((long long)sj[2 * ch], (long long)sj[2 * ch + 1], wk) : kmeans_mean(plain_sum(sj[ch], sj[SW - 1]), wk);
         }
+    }
+    if (MODE != kNext || last_iteration) break;
+    __syncthreads();
     }
 }
 
@@ -488,6 +745,12 @@ __global__ __launch_bounds__(256) void kmeans_combine_kernel(const unsigned long
     cent_all[(size_t)g * kK * C + i] = W ? kmeans_mean((long long)a, (long long)b, (long long)w) : kmeans_mean(plain_sum(a, w), (long long)w);
 }
 
+__global__ __launch_bounds__(256) void kmeans_clear_words_kernel(unsigned* p, size_t words)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < words) p[i] = 0u;
+}
+
 template <int C, bool W>
 cq_status launch_lloyd(const KMeansLloyd& a, hipStream_t st)
 {
@@ -495,20 +758,54 @@ cq_status launch_lloyd(const KMeansLloyd& a, hipStream_t st)
     // G >= 512 groups need no split; fewer groups split their tokens as far as the sums of the
     // splits fit the scratch and a split keeps 16 tiles
     constexpr size_t kSums = sizeof(unsigned long long) * kK * kSumWords<C, W>;
-    int n_split = a.groups >= 512 ? 1 : (512 + a.groups - 1) / a.groups;
+    int wanted = a.groups >= 512 ? 1 : (512 + a.groups - 1) / a.groups;
     const int by_tokens = a.n / 1024, by_scratch = (int)(a.scratch_bytes / ((size_t)a.groups * kSums));
-    n_split = n_split < by_tokens ? n_split : by_tokens;
-    n_split = n_split < by_scratch ? n_split : by_scratch;
-    n_split = n_split < 1 ? 1 : n_split;
-    const int tps = ((a.n + n_split - 1) / n_split + 63) / 64 * 64;
-    n_split = (a.n + tps - 1) / tps;
-    unsigned long long* partials = n_split > 1 ? static_cast<unsigned long long*>(a.scratch) : nullptr;
-    for (int it = 0; it < a.n_iter; ++it) {
-        uint16_t* assign = it + 1 == a.n_iter ? a.assign : nullptr;
-        hipLaunchKernelGGL((kmeans_lloyd_kernel<C, W>), dim3(n_split, a.groups), dim3(kLloydWaves * 64), 0, st, a.xg, a.wq, a.cent,
-                           assign, partials, a.n, tps);
+    wanted = wanted < by_tokens ? wanted : by_tokens;
+    struct Split {
+        int n, tokens;
+        Split(int n_split, int tokens_all)
+        {
+            n_split = n_split < 1 ? 1 : n_split;
+            tokens = ((tokens_all + n_split - 1) / n_split + 63) / 64 * 64;
+            n = (tokens_all + tokens - 1) / tokens;
+        }
+    };
+
+    // from iteration kPlainIterations on with state, where there are enough of them and the scratch holds it
+    LloydState state = {};
+    state.n_pad = (a.n + kScanTokens - 1) / kScanTokens * kScanTokens;
+    const size_t G = (size_t)a.groups, cleared = G * (kSums + kTravelWords * sizeof(float) + sizeof(unsigned));
+    const size_t threshold_at = (cleared + 15) / 16 * 16;
+    const bool stateful = a.n_iter >= kStateIterations && a.n < (1 << 24) && threshold_at + G * state.n_pad * 3 <= a.scratch_bytes;
+    const int plain = stateful ? kPlainIterations : a.n_iter;
+    const dim3 block(kLloydWaves * 64);
+
+    const Split ps(wanted < by_scratch ? wanted : by_scratch, a.n);
+    unsigned long long* partials = ps.n > 1 ? static_cast<unsigned long long*>(a.scratch) : nullptr;
+    for (int it = 0; it < plain; ++it) {
+        hipLaunchKernelGGL((kmeans_lloyd_kernel<C, W, kPlain>), dim3(ps.n, a.groups), block, 0, st, a.xg, a.wq, a.cent,
+                           it + 1 == a.n_iter ? a.assign : nullptr, partials, state, a.n, ps.tokens, 1);
         if (partials)
-            hipLaunchKernelGGL((kmeans_combine_kernel<C, W>), dim3(C, a.groups), dim3(256), 0, st, partials, a.cent, n_split);
+            hipLaunchKernelGGL((kmeans_combine_kernel<C, W>), dim3(C, a.groups), dim3(256), 0, st, partials, a.cent, ps.n);
+    }
+    if (stateful) {
+        char* base = static_cast<char*>(a.scratch);
+        state.sums = reinterpret_cast<unsigned long long*>(base);
+        state.travel = reinterpret_cast<float*>(base + G * kSums);
+        state.arrived = reinterpret_cast<unsigned*>(state.travel + G * kTravelWords);
+        state.threshold = reinterpret_cast<uint16_t*>(base + threshold_at);
+        state.own = reinterpret_cast<uint8_t*>(state.threshold + G * state.n_pad);
+        hipLaunchKernelGGL(kmeans_clear_words_kernel, dim3((unsigned)((cleared / 4 + 255) / 256)), dim3(256), 0, st,
+                           reinterpret_cast<unsigned*>(base), cleared / 4);
+        const Split ss(wanted, a.n);
+        const dim3 grid(ss.n, a.groups);
+        unsigned long long* none = nullptr;
+        hipLaunchKernelGGL((kmeans_lloyd_kernel<C, W, kFirst>), grid, block, 0, st, a.xg, a.wq, a.cent, static_cast<uint16_t*>(nullptr),
+                           none, state, a.n, ss.tokens, 1);
+        const int left = a.n_iter - plain - 1, per_launch = ss.n == 1 ? left : 1;
+        for (int it = 0; it < left; it += per_launch)
+            hipLaunchKernelGGL((kmeans_lloyd_kernel<C, W, kNext>), grid, block, 0, st, a.xg, a.wq, a.cent,
+                               it + per_launch == left ? a.assign : nullptr, none, state, a.n, ss.tokens, per_launch);
     }
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
 }

@@ -227,3 +227,47 @@ def test_equal_centroids_leave_the_scan(c, n, weighted, centroids):
         torch.cuda.synchronize()
         assert np.array_equal(out["assignment"].cpu().numpy().view(np.uint16), assign)
         assert np.array_equal(out["centroids_f32"].cpu().numpy(), cent)
+
+
+@pytest.mark.parametrize("c,heads,n,weighted", [(8, 1, 9001, False), (8, 32, 5003, False), (8, 2, 20000, True), (4, 1, 4000, False),
+                                                (4, 16, 2500, False), (4, 2, 9000, True), (2, 1, 6001, True), (2, 8, 1025, False),
+                                                (8, 1, 300, False)])
+@pytest.mark.parametrize("data", ["plain", "tiny", "large", "far points", "far start", "dead groups", "duplicates", "coarse"])
+def test_iterations_that_skip_tokens_equal_those_that_look_at_all(c, heads, n, weighted, data):
+    """A fit of 47 iterations skips tokens from its eleventh on; chained fits of 16, 16 and 15 never do.
+    Every byte is equal: with several workgroups per group and with one, ragged sizes, fits whose scratch has no room
+    for the sums, centroids that start far off (long moves), twins, and data that leaves the filter."""
+    fmt = cq.CQFormat(c, 8, 128, heads)
+    G, K = fmt.groups, 256
+    rng = np.random.default_rng(n + c)
+    x = np.tile(_data(90 + c, n, 128).astype(np.float32), (1, heads)) * (1.0 + np.arange(128 * heads) % 3).astype(np.float32)
+    if data == "tiny":
+        x *= 1e-6
+    elif data == "large":
+        x *= 60000.0 / np.abs(x).max()
+    elif data == "far points":
+        x *= 1e-2
+    elif data == "dead groups":
+        x[:, :64 * heads] = 0.0
+    elif data == "duplicates":
+        x = x[np.arange(n) % min(n, 40)]
+    elif data == "coarse":
+        x = np.round(x)
+    x = x.astype(np.float16)
+    init = np.stack([x.reshape(n, G, c)[rng.choice(n, size=K, replace=n < K), g] for g in range(G)]).astype(np.float32)
+    if data == "far points":
+        x[::7] = (x[::7].astype(np.float32) * 3e4).clip(-6e4, 6e4).astype(np.float16)
+    elif data == "far start":
+        init = (init * rng.uniform(0.0, 6.0, size=(G, K, 1)) + 2.0).astype(np.float32)
+    xd = torch.from_numpy(x).cuda()
+    w = None
+    if weighted:
+        w = torch.from_numpy(np.ascontiguousarray(np.tile(_weights(n + 1, n, fmt.groups // heads), (1, heads)))).cuda()
+    whole = cq.cq_kmeans_fit(xd, fmt, 47, init_centroids=torch.from_numpy(init).cuda(), weights=w, want_assignment=True)
+    cent = torch.from_numpy(init).cuda()
+    for iters in (16, 16, 15):
+        part = cq.cq_kmeans_fit(xd, fmt, iters, init_centroids=cent, weights=w, want_assignment=True)
+        cent = part["centroids_f32"]
+    torch.cuda.synchronize()
+    assert torch.equal(whole["assignment"], part["assignment"])
+    assert torch.equal(whole["centroids_f32"].view(torch.int32), cent.view(torch.int32))
