@@ -684,7 +684,8 @@ __global__ __launch_bounds__(NW * 64, chunk_waves_per_simd(C, NW, ROPE)) void ch
     }
 
     // ---- output: lane (rc, kh) holds channels 32 cb + 8 (i / 4) + 4 kh + i % 4 of query rc ----
-    const float l = l_run + __shfl_xor(l_run, 32);
+    const auto lr = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+    const float l = __uint_as_float(lr[0]) + __uint_as_float(lr[1]);
     // (the row's place is formed again: held through the loop, it cost registers that spill)
     int tid_o = threadIdx.x;
     asm volatile("" : "+v"(tid_o));

@@ -48,13 +48,11 @@ __device__ __forceinline__ float softmax_reference(float m) { return m - (fabsf(
 // maximum / sum over the four lanes l % 16 + 16 b
 __device__ __forceinline__ float across_max(float v)
 {
-    v = fmaxf(v, __shfl_xor(v, 16));
-    return fmaxf(v, __shfl_xor(v, 32));
+    return rows_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ float across_sum(float v)
 {
-    v += __shfl_xor(v, 16);
-    return v + __shfl_xor(v, 32);
+    return rows_reduce(v, [](float a, float b) { return a + b; });
 }
 
 // HALF: at most 8 rows in all.  Columns q and q + 8 of the score product hold the same query, and in the

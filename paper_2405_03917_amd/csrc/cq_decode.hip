@@ -355,6 +355,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     // runs -- 2 to 12 %.)
     constexpr int GPC = 16;
     constexpr int LPG = 64 / GPC;
+    static_assert(LPG == 4, "lanes_sum<2>, group_lanes_min");
     constexpr int NCH = GH / GPC;       // chunks of the codebook walk
     constexpr int UNITS = GPC * K / JPL;    // 16-byte loads per chunk
     constexpr int IPT = UNITS / NT;     // ... per thread
@@ -740,13 +741,8 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
         }
         lds_barrier();              // the chunk's pairs are visible; every bin update of the chunk before is done
         {
-            const float* sl = slots + (c & 1) * 2 * NW;
-            float m_c = sl[0], l_c = 0.f;
-#pragma unroll
-            for (int w = 1; w < NW; ++w) m_c = fmaxf(m_c, sl[w]);
-            // (every chunk holds at least one valid token, so m_c is a score)
-#pragma unroll
-            for (int w = 0; w < NW; ++w) l_c = __builtin_fmaf(sl[NW + w], __builtin_amdgcn_exp2f(sl[w] - m_c), l_c);
+            float m_c, l_c;         // (every chunk holds at least one valid token, so m_c is a score)
+            merge_pairs<NW>(slots + (c & 1) * 2 * NW, lane, m_c, l_c);
             if (c == 0) {
                 m0 = m_run = m_c;
                 l_run = l_c;
@@ -921,10 +917,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
             }
         }
 #pragma unroll
-        for (int i = 0; i < C; ++i) {
-#pragma unroll
-            for (int m = 1; m < LPG; m <<= 1) acc[ch][i] += __shfl_xor(acc[ch][i], m);
-        }
+        for (int i = 0; i < C; ++i) acc[ch][i] = lanes_sum<2>(acc[ch][i]);
     }
     // per-wave results: scr[64 + wave * D + channel]
     if (lane % LPG == 0) {

@@ -43,23 +43,60 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ __forceinline__ float wave_max(float v)
+// Reductions across lanes in the vector ALU (DPP inside a row of 16 lanes, lane swaps between rows): every lane gets
+// the result of its neighbourhood of 2^STEPS lanes.  (As shuffles, i.e. LDS round trips, a wavefront's maximum and sum
+// took about 1200 clocks per chunk of the decode kernels.)
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp_from(unsigned v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+template <int STEPS, class T, class Op>
+__device__ __forceinline__ T lanes_reduce(T v, Op&& op)
+{
+    static_assert(sizeof(T) == 4 && STEPS <= 6, "one register, 64 lanes");
+    auto bits = [](T x) { return __builtin_bit_cast(unsigned, x); };
+    auto val = [](unsigned x) { return __builtin_bit_cast(T, x); };
+    if constexpr (STEPS >= 1) v = op(v, val(dpp_from<0xB1>(bits(v))));      // quad_perm [1,0,3,2]
+    if constexpr (STEPS >= 2) v = op(v, val(dpp_from<0x4E>(bits(v))));      // quad_perm [2,3,0,1]
+    if constexpr (STEPS >= 3) v = op(v, val(dpp_from<0x141>(bits(v))));     // row_half_mirror
+    if constexpr (STEPS >= 4) v = op(v, val(dpp_from<0x140>(bits(v))));     // row_mirror
+    if constexpr (STEPS >= 5) {
+        const auto r = __builtin_amdgcn_permlane16_swap(bits(v), bits(v), false, false);
+        v = op(val(r[0]), val(r[1]));
+    }
+    if constexpr (STEPS >= 6) {
+        const auto r = __builtin_amdgcn_permlane32_swap(bits(v), bits(v), false, false);
+        v = op(val(r[0]), val(r[1]));
+    }
     return v;
 }
-__device__ __forceinline__ float wave_sum(float v)
+// over the four lanes l % 16 + 16 b
+template <class Op>
+__device__ __forceinline__ float rows_reduce(float v, Op&& op)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
-__device__ __forceinline__ unsigned wave_sum_u32(unsigned v)
+template <int STEPS>
+__device__ __forceinline__ float lanes_max(float v) { return lanes_reduce<STEPS>(v, [](float a, float b) { return fmaxf(a, b); }); }
+template <int STEPS>
+__device__ __forceinline__ float lanes_sum(float v) { return lanes_reduce<STEPS>(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return lanes_max<6>(v); }
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum<6>(v); }
+__device__ __forceinline__ unsigned wave_sum_u32(unsigned v) { return lanes_reduce<6>(v, [](unsigned a, unsigned b) { return a + b; }); }
+// (maximum, sum of 2^(score - maximum)) of a workgroup from its NW wavefronts' pairs (sl[w], sl[NW + w]): every lane takes
+// one pair
+template <int NW>
+__device__ __forceinline__ void merge_pairs(const float* sl, int lane, float& m, float& l)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    static_assert(NW == 4 || NW == 8 || NW == 16, "a power of two of lanes in a row");
+    constexpr int STEPS = NW == 4 ? 2 : NW == 8 ? 3 : 4;
+    const float mw = sl[lane & (NW - 1)], lw = sl[NW + (lane & (NW - 1))];
+    m = lanes_max<STEPS>(mw);
+    l = lanes_sum<STEPS>(lw * __builtin_amdgcn_exp2f(mw - m));
 }
 
 __device__ __forceinline__ void lds_min_u64(unsigned long long* p, unsigned long long v)
@@ -116,12 +153,13 @@ __device__ __forceinline__ void load_row_slice(const uint16_t* p, float (&x)[C])
 template <int LPG>
 __device__ __forceinline__ unsigned long long group_lanes_min(unsigned long long key)
 {
-#pragma unroll
-    for (int m = 1; m < LPG; m <<= 1) {
-        const unsigned long long o = __shfl_xor(key, m);
-        key = o < key ? o : key;
-    }
-    return key;
+    static_assert(LPG == 4, "a quad of lanes");
+    auto smaller = [](unsigned long long k, unsigned lo, unsigned hi) {
+        const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+        return o < k ? o : k;
+    };
+    key = smaller(key, dpp_from<0xB1>((unsigned)key), dpp_from<0xB1>((unsigned)(key >> 32)));
+    return smaller(key, dpp_from<0x4E>((unsigned)key), dpp_from<0x4E>((unsigned)(key >> 32)));
 }
 
 // Fixed-point scale for the probabilities of one split: with l_est = sum_t 2^(s_t - m) (fp32),

@@ -555,8 +555,7 @@ __global__ __launch_bounds__(NT) void decode_rope_kernel(DecodeArgs a, const flo
         }
 #pragma unroll
         for (int i = 0; i < C; ++i) {
-            acc[ch][i] += __shfl_xor(acc[ch][i], 1);
-            acc[ch][i] += __shfl_xor(acc[ch][i], 2);
+            acc[ch][i] = lanes_sum<2>(acc[ch][i]);
         }
     }
     if ((lane & 3) == 0) {
@@ -1243,8 +1242,7 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
                 }
 #pragma unroll
                 for (int i = 0; i < C; ++i) {
-                    acc[ch][i] += __shfl_xor(acc[ch][i], 1);
-                    acc[ch][i] += __shfl_xor(acc[ch][i], 2);
+                    acc[ch][i] = lanes_sum<2>(acc[ch][i]);
                 }
             }
             if ((lane & 3) == 0) {

@@ -432,7 +432,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 // -|c|^2 / 2
                 unsigned xh[C / 2];
 #pragma unroll
-                for (int i = 0; i < C / 2; ++i) xh[i] = h == 0 ? xs[i] : __shfl_xor(xs[i], 32);
+                for (int i = 0; i < C / 2; ++i) xh[i] = h == 0 ? xs[i] : __builtin_amdgcn_permlane32_swap(xs[i], xs[i], false, false)[1];
                 const _Float16 one = (_Float16)1.0f, zero = (_Float16)0.0f;
                 vec_t bop;
                 if constexpr (C == 8) {
@@ -511,19 +511,28 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 hsb[h] = gsb;
             }
             // Lanes l and l + 32 saw the two halves of every block's rows for tokens l % 32 (h = 0) and
-            // 32 + l % 32 (h = 1).  Each lane now takes its OWN token (token `lane`, in half lane / 32):
-            // its own scan of that half, and the partner lane's, which sends it in exchange for the
-            // other half's.  Everything below runs once per tile and group, on all 64 lanes.
-            const int hi = lane >> 5;
-            const float gbest = hi ? hbest[1] : hbest[0], gsecond = hi ? hsecond[1] : hsecond[0];
-            const float obest = __shfl_xor(hi ? hbest[0] : hbest[1], 32), osecond = __shfl_xor(hi ? hsecond[0] : hsecond[1], 32);
-            const int gsb = hi ? hsb[1] : hsb[0];
-            const int osb = NSB == 1 ? 0 : __shfl_xor(hi ? hsb[0] : hsb[1], 32);
+            // 32 + l % 32 (h = 1).  Each lane now takes its OWN token (token `lane`, in half lane / 32): the scans of the
+            // two lanes that saw it, rows of the lower and of the upper lanes (a swap of the registers' halves: one
+            // instruction for both).  Everything below runs once per tile and group, on all 64 lanes.
+            auto halves = [](float a, float b, float& lower, float& upper) {
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+                lower = __uint_as_float(r[0]);
+                upper = __uint_as_float(r[1]);
+            };
+            float gbest, obest, gsecond, osecond;
+            halves(hbest[0], hbest[1], gbest, obest);
+            halves(hsecond[0], hsecond[1], gsecond, osecond);
+            int gsb = 0, osb = 0;
+            if constexpr (NSB > 1) {
+                const auto r = __builtin_amdgcn_permlane32_swap((unsigned)hsb[0], (unsigned)hsb[1], false, false);
+                gsb = (int)r[0];
+                osb = (int)r[1];
+            }
             const bool other = obest > gbest;
             const float best = fmaxf(gbest, obest);
             const float second = fmaxf(fmaxf(fminf(gbest, obest), gsecond), osecond);
             const int wsb = other ? osb : gsb;
-            const int whalf = other ? 1 - hi : hi;
+            const int whalf = other ? 1 : 0;
             const int u = lane;                                      // token of the tile
             const int slot = (g - u) & (GH - 1);
             // Level 2: the winner's eight centroids (j0 .. j0 + 3 and j0 + 8 .. j0 + 11) against this token,

@@ -428,15 +428,21 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
                 hbest[h] = fmaxf(fmaxf(hbest[h], om[0]), om[1]);
             }
         }
-        // each lane takes its own token: its own scan of that half and the partner lane's (the other rows)
-        const int hi = lane >> 5;
-        const float gbest = hi ? hbest[1] : hbest[0], gsecond = hi ? hsecond[1] : hsecond[0];
-        const float obest = __shfl_xor(hi ? hbest[0] : hbest[1], 32), osecond = __shfl_xor(hi ? hsecond[0] : hsecond[1], 32);
+        // each lane takes its own token: the scans of the two lanes that saw it, the rows of the lower and of the upper
+        // lanes (a swap of the registers' halves: one instruction for both)
+        auto halves = [](float a, float b, float& lower, float& upper) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+            lower = __uint_as_float(r[0]);
+            upper = __uint_as_float(r[1]);
+        };
+        float gbest, obest, gsecond, osecond;
+        halves(hbest[0], hbest[1], gbest, obest);
+        halves(hsecond[0], hsecond[1], gsecond, osecond);
         const bool other = obest > gbest;
         const float best = fmaxf(gbest, obest);
         const float second = fmaxf(fmaxf(fminf(gbest, obest), gsecond), osecond);
         const unsigned bb = __float_as_uint(best);
-        const int j0 = (int)(bb & 15u) * 16 + 4 * (other ? 1 - hi : hi);
+        const int j0 = (int)(bb & 15u) * 16 + 4 * (other ? 1 : 0);
         const float gap = __uint_as_float(bb & 0xfffffff0u) - __uint_as_float(__float_as_uint(second) & 0xfffffff0u);
         // ---- the winner's eight centroids (j0 .. j0 + 3, j0 + 8 .. j0 + 11) in the direct form
         float x[C];
