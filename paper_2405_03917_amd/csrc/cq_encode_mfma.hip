@@ -235,6 +235,9 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     constexpr int SNT = GS ? 64 : NT;                // threads that stage a group's codebook together
     constexpr int NTILE = GS ? TILES : NW;           // tiles per workgroup
     constexpr int TPW = GS ? TILES : 1;              // tiles per wavefront
+    // exchanges between the lane halves by v_permlane32_swap; where a wavefront has a tile to itself and mostly waits, as
+    // shuffles (CQ-2c8b, 64 x 512 tokens 1608 / 1565 us, 8 x 301 150.3 / 151.7; CQ-8c10b, 2 x 600 145.9 / 147.7)
+    constexpr bool SWAP = TPW > 1;
     // augmented codebook records: two buffers that the workgroup alternates, or (GS) one per wavefront
     __shared__ __attribute__((aligned(16))) _Float16 cba[GS ? NW : 2][K * KDIM];
     // -|c'_j|^2 / 2 for level 2 (byte codes; for 1024 centroids it would cost the second workgroup on the CU,
@@ -432,7 +435,7 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 // -|c|^2 / 2
                 unsigned xh[C / 2];
 #pragma unroll
-                for (int i = 0; i < C / 2; ++i) xh[i] = h == 0 ? xs[i] : __builtin_amdgcn_permlane32_swap(xs[i], xs[i], false, false)[1];
+                for (int i = 0; i < C / 2; ++i) xh[i] = h == 0 ? xs[i] : SWAP ? __builtin_amdgcn_permlane32_swap(xs[i], xs[i], false, false)[1] : __shfl_xor(xs[i], 32);
                 const _Float16 one = (_Float16)1.0f, zero = (_Float16)0.0f;
                 vec_t bop;
                 if constexpr (C == 8) {
@@ -512,27 +515,30 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
             }
             // Lanes l and l + 32 saw the two halves of every block's rows for tokens l % 32 (h = 0) and
             // 32 + l % 32 (h = 1).  Each lane now takes its OWN token (token `lane`, in half lane / 32): the scans of the
-            // two lanes that saw it, rows of the lower and of the upper lanes (a swap of the registers' halves: one
-            // instruction for both).  Everything below runs once per tile and group, on all 64 lanes.
-            auto halves = [](float a, float b, float& lower, float& upper) {
-                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-                lower = __uint_as_float(r[0]);
-                upper = __uint_as_float(r[1]);
+            // two lanes that saw it (SWAP: the lower and the upper lane's, a swap of the registers' halves; else its own
+            // and the partner lane's).  Everything below runs once per tile and group, on all 64 lanes.
+            const int hi = lane >> 5, ghalf = SWAP ? 0 : hi;        // the half of the rows that g... saw
+            auto exchange = [&](unsigned a, unsigned b, unsigned& g, unsigned& o) {
+                if constexpr (SWAP) {
+                    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+                    g = r[0];
+                    o = r[1];
+                } else {
+                    g = hi ? b : a;
+                    o = __shfl_xor(hi ? a : b, 32);
+                }
             };
-            float gbest, obest, gsecond, osecond;
-            halves(hbest[0], hbest[1], gbest, obest);
-            halves(hsecond[0], hsecond[1], gsecond, osecond);
-            int gsb = 0, osb = 0;
-            if constexpr (NSB > 1) {
-                const auto r = __builtin_amdgcn_permlane32_swap((unsigned)hsb[0], (unsigned)hsb[1], false, false);
-                gsb = (int)r[0];
-                osb = (int)r[1];
-            }
+            unsigned g0, o0, g1, o1, g2 = 0, o2 = 0;
+            exchange(__float_as_uint(hbest[0]), __float_as_uint(hbest[1]), g0, o0);
+            exchange(__float_as_uint(hsecond[0]), __float_as_uint(hsecond[1]), g1, o1);
+            if constexpr (NSB > 1) exchange((unsigned)hsb[0], (unsigned)hsb[1], g2, o2);
+            const float gbest = __uint_as_float(g0), obest = __uint_as_float(o0), gsecond = __uint_as_float(g1), osecond = __uint_as_float(o1);
+            const int gsb = (int)g2, osb = (int)o2;
             const bool other = obest > gbest;
             const float best = fmaxf(gbest, obest);
             const float second = fmaxf(fmaxf(fminf(gbest, obest), gsecond), osecond);
             const int wsb = other ? osb : gsb;
-            const int whalf = other ? 1 : 0;
+            const int whalf = other ? 1 - ghalf : ghalf;
             const int u = lane;                                      // token of the tile
             const int slot = (g - u) & (GH - 1);
             // Level 2: the winner's eight centroids (j0 .. j0 + 3 and j0 + 8 .. j0 + 11) against this token,
@@ -608,8 +614,14 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                     x[2 * i + 1] = (float)hh.y * gs.f1;
                 }
                 unsigned dmin = ~0u, jmin = 0;
+                // (The centroids' reads and conversions do not depend on the token: the compiler makes them ahead of this loop,
+                // for every tile and group.  Right for groups of 2 and 4 channels, whose tokens need a re-do more often
+                // (opaque there: 8 x 301 tokens of CQ-2c8b 150 -> 160 us); of 8 channels, 48 instructions of 446 that hardly
+                // any tile needs where it has the CU's vector ALU to itself no longer: opaque, CQ-8c8b 32768 tokens 604 -> 580 us.
+                int first = lane;
+                if constexpr (C == 8 && TPW > 1) asm volatile("" : "+v"(first));
 #pragma unroll 4
-                for (int j = lane; j < K; j += 64) {
+                for (int j = first; j < K; j += 64) {
                     unsigned cw[C / 2];
 #pragma unroll
                     for (int i = 0; i < C / 2; ++i) cw[i] = *reinterpret_cast<const unsigned*>(&cba[buf][record<C, PER>(j) * KDIM + 2 * i]);
