@@ -43,6 +43,10 @@ static __device__ __align__(256) unsigned merge_counters[16 * 8192];
 namespace cq {
 namespace {
 
+// Tiles per wavefront of the shortest splits (see ONCE), 2048 tokens of CQ-8c8b: batch 1 x 2000, 32 heads 8.95 -> 8.68 us, its
+// step 10.9 -> 10.5; step of batch 2 x 1000 9.6 -> 9.0.  None for the other formats: their codebook is walked in two and
+// four parts, which the tiles' requests then hold up (CQ-4c8b, batch 16 x 900: 12.4 -> 13.2), and CQ-2c8b has no registers left.
+constexpr int kOnceTiles(int gh) { return gh == 16 ? 4 : 0; }
 constexpr int kMergeRows = 8192;        // arrival counters per set (rows of one launch)
 constexpr int kMergeSets = 16;          // sets (streams served) per device
 static_assert(sizeof(merge_counters) == sizeof(unsigned) * kMergeRows * kMergeSets, "size of the counter array");
@@ -217,7 +221,10 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     constexpr int NW = kDecodeWaves;    // wavefronts
     constexpr int D = GH * C;           // head_dim
     // tiles in flight per wavefront (about 4 KB)
-    constexpr int PF = B == 10 ? 2 : (GH == 16 ? 4 : (GH == 32 ? 2 : 1));
+    // ONCE: a split so short that all its tiles, of both streams, and the value codebook are requested while the score
+    // table is built, instead of each when the phase before it is done
+    constexpr bool ONCE = B == 8 && NS <= kOnceTiles(GH);
+    constexpr int PF = ONCE ? NS : (B == 10 ? 2 : (GH == 16 ? 4 : (GH == 32 ? 2 : 1)));
     static_assert(NS % PF == 0 && NS >= PF, "the ring of tiles in flight must divide a chunk");
     constexpr int JPL = 8 / C;          // centroids per 16-byte load
     // groups per chunk of the codebook walk; 64 / GPC neighbouring lanes are on a group and read as
@@ -386,7 +393,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
         asm volatile("" : "+s"(k));
         return k < my_tiles;
     };
-    Tile<GH, B> buf[PF];
+    Tile<GH, B> buf[PF], vbuf[ONCE ? NS : 1];
 
     // ---- 1. score table ------------------------------------------------------------------
     // A chunk of the walk is GPC groups; a thread stays on group gl of every chunk.  16-byte piece
@@ -427,12 +434,21 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
                 // the first key tiles are requested behind the first centroids: tile requests must
                 // go out as early as possible (the kernel is bound by HBM from its first
                 // microsecond), but not in front of the loads the table build waits for
-                if (ch == 0 && k0 == 0) {
+                if (ch == (ONCE ? NCH - 1 : 0) && k0 == 0) {
 #pragma unroll
                     for (int i = 0; i < PF; ++i) {
                         buf[i] = request(kbase, 0, i, pages);
                         __builtin_amdgcn_sched_barrier(0);      // keep request order == consumption order
                     }
+                    if constexpr (ONCE) {
+#pragma unroll
+                        for (int i = 0; i < NS; ++i) {
+                            vbuf[i] = request(vbase, 0, i, pages);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+                if (ch == 0 && k0 == 0) {
                     // the bins start at zero (the barrier behind the table build covers these stores)
                     if constexpr (F::SEPARATE) {
                         float4* t4 = reinterpret_cast<float4*>(tab);
@@ -473,6 +489,23 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
             }
         }
     }
+    constexpr bool EARLY = IPT * NCH <= 8 && KB == IPT;
+    static_assert(EARLY || !ONCE, "the value codebook in registers");
+    Cent16 rawv[EARLY ? NCH : 1][KB];
+    auto load_value_centroids = [&] {
+        if constexpr (EARLY) {
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch) {
+                const uint16_t* cv = v_centroids + (size_t)(hkv * GH + ch * GPC + gl) * K * C;
+#pragma unroll
+                for (int kk = 0; kk < IPT; ++kk) rawv[ch][kk] = load_cent16(cv + (size_t)piece(kk) * 8);
+            }
+        }
+    };
+    if constexpr (ONCE) {
+        load_value_centroids();
+        __builtin_amdgcn_sched_barrier(0);
+    }
     lds_barrier();
 
     // fused step: the key codes of the new token are known; the first query head of the KV head
@@ -495,8 +528,6 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     // (and the running integer sum) is shifted right, rounding to nearest, so that U comes to lie
     // in [2^28, 2^29), and fx drops by the shift.  No bin can overflow 32 bits, and each
     // probability is kept to an absolute error of at most 2^-29 of the softmax denominator.
-    constexpr bool EARLY = IPT * NCH <= 8 && KB == IPT;
-    Cent16 rawv[EARLY ? NCH : 1][KB];
     unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
     float m0 = 0.f, m_run = 0.f, l_run = 0.f, fxf = 0.f;
     int fx = 0;
@@ -544,14 +575,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     // latency overlaps the last tiles and the wait for the slowest wavefront (where registers
     // allow: not with 1024 rows)
     auto request_value_centroids = [&] {
-        if constexpr (EARLY) {
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const uint16_t* cv = v_centroids + (size_t)(hkv * GH + ch * GPC + gl) * K * C;
-#pragma unroll
-                for (int kk = 0; kk < IPT; ++kk) rawv[ch][kk] = load_cent16(cv + (size_t)piece(kk) * 8);
-            }
-        }
+        if constexpr (!ONCE) load_value_centroids();
     };
 
     // Chunk c.  FULL: all NS tiles of this wavefront exist (always so before the last chunk): the
@@ -570,7 +594,13 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
         // wavefronts have exchanged one pair each.
         lane_m = -1e30f;                            // (finite start: a lane without valid tokens stays at l = 0)
         lane_l = 0.f;
-        if constexpr (FULL) {
+        if constexpr (ONCE) {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                sreg[i] = tile_exists(0, i) ? score_tile(buf[i], i) : -INFINITY;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (FULL) {
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
                 // (the tile exists; the test keeps each tile's arithmetic in a block of its own, which the
@@ -663,7 +693,13 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
             lds_barrier();
         }
         // -- bins
-        if constexpr (FULL) {
+        if constexpr (ONCE) {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                if (tile_exists(0, i)) bin_tile(vbuf[i], i, sreg[i]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (FULL) {
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
                 if (tile_exists(c, i)) bin_tile(buf[i % PF], c * NS + i, sreg[i]);
@@ -695,11 +731,15 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
         }
         pages = pages_next;
     };
-    if constexpr (F::SEPARATE) {
+    if constexpr (F::SEPARATE && !ONCE) {
         for (int c = 0; c + 1 < n_chunks; ++c) chunk(c, std::false_type{}, std::true_type{});
     }
-    if (my_tiles >= n_chunks * NS) chunk(n_chunks - 1, std::true_type{}, std::true_type{});
-    else chunk(n_chunks - 1, std::true_type{}, std::false_type{});
+    if constexpr (ONCE) {
+        chunk(0, std::true_type{}, std::false_type{});
+    } else {
+        if (my_tiles >= n_chunks * NS) chunk(n_chunks - 1, std::true_type{}, std::true_type{});
+        else chunk(n_chunks - 1, std::true_type{}, std::false_type{});
+    }
 
     // ---- 3. epilogue: o = bins . C_V -----------------------------------------------------
     // same walk as the table build; thread-private sums over its centroids of group gl in every
@@ -903,6 +943,9 @@ template <int GH, int C, int B, int NS, bool STEP, bool LAYERS>
 cq_status launch_by_length(const DecodeArgs& a, hipStream_t stream)
 {
     const int tiles_per_wave = (a.tiles_per_split + kDecodeWaves - 1) / kDecodeWaves;
+    if constexpr (B == 8 && !LAYERS && kOnceTiles(GH) > 0) {
+        if (tiles_per_wave <= kOnceTiles(GH)) return launch_variant<GH, C, B, kOnceTiles(GH), STEP, LAYERS>(a, stream);
+    }
     if (tiles_per_wave <= NS / 2) return launch_variant<GH, C, B, NS / 2, STEP, LAYERS>(a, stream);
     return launch_variant<GH, C, B, NS, STEP, LAYERS>(a, stream);
 }
