@@ -245,6 +245,11 @@ def kernel_name(cfg, step=False, ns=None):
         per_wave = (min(split, tiles) + 7) // 8
         full = 32 if cfg.b == 10 else 16
         ns = full // 2 if per_wave <= full // 2 else full
+        rounds = cfg.batch * (cfg.n_q_heads // 2) * ((tiles + split - 1) // split) / 256
+        if (cfg.n_q_heads // cfg.n_kv_heads) % 2 == 0 and rounds >= 1 and (cfg.b == 10 or rounds / math.ceil(rounds) >= 0.85):
+            return f"decode_pair_kernel<{gh}, {cfg.c}, {cfg.b}, {ns // 2}, {'true' if step else 'false'}, false>"
+        if gh == 16 and cfg.b == 8 and per_wave <= 4:
+            ns = 4
     return f"decode_split_kernel<{gh}, {cfg.c}, {cfg.b}, {ns}, {'true' if step else 'false'}, false>"
 
 
@@ -480,8 +485,8 @@ def extra_measurements(cq, synth, torch):
         "ms": fit_ms, "kmeanspp_ms": init_ms, "ms_per_iteration": per_iter,
         "seconds_for_64_tensors": fit_ms * 64 / 1e3,
         "direct_form_TFLOPs": 3 * 8 * pairs_iter / (per_iter * 1e-3) / 1e12,
-        "roofline": {"bound": "alu", "kernel": "kmeans_lloyd_kernel<8, false>, per iteration (vector instructions issued; the matrix cores score "
-                                               "the centroids, so that most of the direct form's flops are not executed)",
+        "roofline": {"bound": "alu", "kernel": "kmeans_lloyd_kernel<8, false, 0..2>, per iteration (vector instructions of an iteration that looks at every token, "
+                                               "as the first ten do; later ones skip most tokens, so that this exceeds what is executed)",
                      "achieved": LLOYD_LANE_OPS * n_cal * fmt.groups / (per_iter * 1e-3) / 1e12, "peak": VALU_PEAK_LANE_OPS / 1e12,
                      "unit": "T lane-instr/s", "frac": LLOYD_LANE_OPS * n_cal * fmt.groups / (per_iter * 1e-3) / VALU_PEAK_LANE_OPS, "traffic": None}}
     return out

@@ -294,6 +294,31 @@ def test_decode_split_invariance_and_ragged_lengths(c, b):
         assert np.max(np.abs(o - outs[0])) <= 2e-3 * np.max(np.abs(outs[0]))
 
 
+@pytest.mark.parametrize("T,split", [(1, 0), (64, 64), (65, 64), (511, 512), (513, 576), (2047, 2048), (2048, 2048), (2049, 2112), (4097, 2048)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_decode_short_splits_of_16_groups(T, split, paged):
+    """CQ-8c8b splits of up to 32 tiles request all their tiles at once (the last: two such splits and a piece); one tile
+    more takes the walk with tiles in flight.  A ragged batch: splits with one tile and with none."""
+    c, b, hq, hkv, B, t_cap = 8, 8, 4, 2, 3, (T + 63) // 64 * 64
+    fmt, q, kc, vc, ck, cv = _attn_case(T, c, b, hq, hkv, B, T)
+    lens = np.array([T, 1, max(1, T // 2)], dtype=np.int32)
+    ref = O.attention(q, kc, vc, ck, cv, 0.09, hkv, seq_lens=lens)
+    kcache, vcache = codes_to_cache(kc, fmt, t_cap), codes_to_cache(vc, fmt, t_cap)
+    if not paged:
+        out = gpu_attention(q, kcache, vcache, ck, cv, 0.09, fmt, T, t_cap, seq_lens=lens, tokens_per_split=split)
+    else:
+        tiles = t_cap // 64
+        table = torch.randperm(B * tiles, generator=torch.Generator().manual_seed(T)).view(B, tiles).int()
+        pools = []
+        for cache in (kcache, vcache):
+            pool = torch.empty_like(cache).view(B * tiles, hkv, -1)
+            pool[table.flatten().long().cuda()] = cache.view(B, hkv, tiles, -1).transpose(1, 2).reshape(B * tiles, hkv, -1)
+            pools.append(pool.flatten())
+        out = cq.cq_decode_attention_paged(dev(q), *pools, dev(ck), dev(cv), 0.09, fmt, T, cq.PageTable(table.cuda(), B * tiles),
+                                           seq_lens=dev(lens), tokens_per_split=split).cpu().numpy()
+    check_attention(out, ref)
+
+
 @pytest.mark.parametrize("c,b", DECODE_FORMATS)
 @pytest.mark.parametrize("gain", [1e-3, 40.0])
 def test_decode_extreme_score_ranges(c, b, gain):
