@@ -615,9 +615,11 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 }
                 unsigned dmin = ~0u, jmin = 0;
                 // (The centroids' reads and conversions do not depend on the token: the compiler makes them ahead of this loop,
-                // for every tile and group.  Right for groups of 2 and 4 channels, whose tokens need a re-do more often
-                // (opaque there: 8 x 301 tokens of CQ-2c8b 150 -> 160 us); of 8 channels, 48 instructions of 446 that hardly
-                // any tile needs where it has the CU's vector ALU to itself no longer: opaque, CQ-8c8b 32768 tokens 604 -> 580 us.
+                // for every tile and group, and holds their values in registers.  With 8 channels and several tiles per wavefront
+                // those registers cost a wavefront per SIMD (3 resident -> 4: wave cycles per busy cycle 2.9 -> 3.8), which is worth
+                // more than the reads that a tile's second and later re-dos make again (445 -> 457 instructions per 64 tokens and
+                // group): opaque there, CQ-8c8b 32768 tokens, K and V 523 -> 514 us.  With 2 and 4 channels the values are fewer and
+                // the re-dos more: opaque 8 x 301 tokens of CQ-2c8b took 160 us instead of 150.)
                 int first = lane;
                 if constexpr (C == 8 && TPW > 1) asm volatile("" : "+v"(first));
 #pragma unroll 4
