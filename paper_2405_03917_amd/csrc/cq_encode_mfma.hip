@@ -518,22 +518,27 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
             // two lanes that saw it (SWAP: the lower and the upper lane's, a swap of the registers' halves; else its own
             // and the partner lane's).  Everything below runs once per tile and group, on all 64 lanes.
             const int hi = lane >> 5, ghalf = SWAP ? 0 : hi;        // the half of the rows that g... saw
-            auto exchange = [&](unsigned a, unsigned b, unsigned& g, unsigned& o) {
-                if constexpr (SWAP) {
-                    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-                    g = r[0];
-                    o = r[1];
-                } else {
-                    g = hi ? b : a;
-                    o = __shfl_xor(hi ? a : b, 32);
-                }
-            };
-            unsigned g0, o0, g1, o1, g2 = 0, o2 = 0;
-            exchange(__float_as_uint(hbest[0]), __float_as_uint(hbest[1]), g0, o0);
-            exchange(__float_as_uint(hsecond[0]), __float_as_uint(hsecond[1]), g1, o1);
-            if constexpr (NSB > 1) exchange((unsigned)hsb[0], (unsigned)hsb[1], g2, o2);
-            const float gbest = __uint_as_float(g0), obest = __uint_as_float(o0), gsecond = __uint_as_float(g1), osecond = __uint_as_float(o1);
-            const int gsb = (int)g2, osb = (int)o2;
+            float gbest, gsecond, obest, osecond;
+            int gsb, osb = 0;
+            if constexpr (SWAP) {
+                auto swap = [](auto a, auto b, auto& g, auto& o) {
+                    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+                    const unsigned lower = r[0], upper = r[1];      // (a bit cast of r[1] itself gave r[0])
+                    g = __builtin_bit_cast(decltype(a), lower);
+                    o = __builtin_bit_cast(decltype(a), upper);
+                };
+                swap(hbest[0], hbest[1], gbest, obest);
+                swap(hsecond[0], hsecond[1], gsecond, osecond);
+                gsb = hsb[0];
+                if constexpr (NSB > 1) swap(hsb[0], hsb[1], gsb, osb);
+            } else {
+                gbest = hi ? hbest[1] : hbest[0];
+                gsecond = hi ? hsecond[1] : hsecond[0];
+                obest = __shfl_xor(hi ? hbest[0] : hbest[1], 32);
+                osecond = __shfl_xor(hi ? hsecond[0] : hsecond[1], 32);
+                gsb = hi ? hsb[1] : hsb[0];
+                if constexpr (NSB > 1) osb = __shfl_xor(hi ? hsb[0] : hsb[1], 32);
+            }
             const bool other = obest > gbest;
             const float best = fmaxf(gbest, obest);
             const float second = fmaxf(fmaxf(fminf(gbest, obest), gsecond), osecond);
