@@ -274,17 +274,20 @@ __global__ __launch_bounds__(kPPThreads) void kmeanspp_kernel(const uint16_t* __
 // weighted distance, the wavefronts' masses, the token.  The owner of the r-th unit of mass keeps
 // its mass in up to four sums, so the search is 4 + R / 4 independent reductions and one scan.
 // Weights sit in registers too, 32 rounds of them in LDS (as 32 more registers they spilled 50 to 61).
-// 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 6.7 ms, weighted 30.7 -> 9.0; 1500 tokens, 256
+// 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 6.7 ms, weighted 30.7 -> 9.0 (and see draw() and visit()
+// for the vector instructions, which bound it: 6.7 -> 5.4, at 12000 tokens 3.6 -> 2.9); 1500 tokens, 256
 // groups of 4: 1.05 -> 0.71 ms; 100 tokens 0.54 -> 0.56 (two barriers' worth of other wavefronts' numbers), so that
 // up to 128 go to the general kernel (run_kmeanspp).
 // Slices of 4 (of 2: 8) weighted tokens per lane in registers instead of 2 (4), 32 rounds: 8 channels 11.0 -> 9.0 ms
 // at 512 groups, 4 channels 3.7 -> 4.6 ms at 256 groups (spills).
+// Unweighted slices of 4 channels: 14 per lane instead of 8, so that all 32 rounds are held, 8.36 -> 8.24 ms at 1024 groups; of 8
+// channels 5 instead of 4: 5.8 -> 6.05 at 512 groups.
 constexpr int kPPRounds = 32;
 constexpr int min_of(int a, int b) { return a < b ? a : b; }
 template <bool W, int R>
 constexpr bool kPPWeightsInLds = W && R == kPPRounds;
 template <int C, bool W, int R>
-constexpr int kPPRegRounds = min_of(R, (W && !(C == 8 && kPPWeightsInLds<W, R>) ? 8 : 16) / (C / 2));
+constexpr int kPPRegRounds = min_of(R, (W && !(C == 8 && kPPWeightsInLds<W, R>) ? 8 : !W && C == 4 ? 28 : 16) / (C / 2));
 template <int C, bool W, int R>
 constexpr int kPPLdsRounds = min_of(R - kPPRegRounds<C, W, R>, (kPPWeightsInLds<W, R> ? 15 : 72) / C);     // at most 144 KB, or 30 next to the weights
 
@@ -375,14 +378,38 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
     };
     auto draw = [&](uint64_t word, int kq) {
         unsigned long long seg[kSegs];
+        // A mass without weight is v = dmin 2^kq < 2^(62 - log2n) rounded down: 2^(63 - log2n) + v rounds v to units of
+        // 2^(40 - log2n) (hi: the sum's mantissa), the rest lo is exact, at most half a unit and signed; both sums of a
+        // segment fit 32 bits from 1025 tokens on.  Distances that are not finite or whose 2^kq is not an fp32 number
+        // go the general way.  Eight instructions per token instead of about 20 (with v_fma_mix_f32 below, one iteration
+        // after the picks: 12000 tokens of 512 groups of 8 channels 3.90 -> 3.17 ms, 16385 6.88 -> 5.45, of 2 channels, 2048 groups 18.0 -> 13.3).
+        const bool split = !W && R > 1 && kq >= -126 && kq <= 100;
+        if (split) {
+            const float unit = __uint_as_float((unsigned)(127 + kq) << 23);
+            const unsigned big_bits = (unsigned)(127 + 63 - log2n) << 23;
+            const float big = __uint_as_float(big_bits);
 #pragma unroll
-        for (int s = 0; s < kSegs; ++s) {
-            seg[s] = 0;
+            for (int s = 0; s < kSegs; ++s) {
+                unsigned hi = 0;
+                int lo = 0;
 #pragma unroll
-            for (int k = 0; k < R / kSegs; ++k) {
-                const int p = s * (R / kSegs) + k;
-                seg[s] += mass_of(dmin[p], weight(p), kq);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int k = 0; k < R / kSegs; ++k) {
+                    const float v = __uint_as_float(dmin[s * (R / kSegs) + k]) * unit, t = v + big;
+                    hi += __float_as_uint(t) - big_bits;
+                    lo += (int)__builtin_floorf(v - (t - big));
+                }
+                seg[s] = ((unsigned long long)hi << (40 - log2n)) + (unsigned long long)(long long)lo;
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < kSegs; ++s) {
+                seg[s] = 0;
+#pragma unroll
+                for (int k = 0; k < R / kSegs; ++k) {
+                    const int p = s * (R / kSegs) + k;
+                    seg[s] += mass_of(dmin[p], weight(p), kq);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         }
         unsigned long long mass = seg[0];
@@ -479,14 +506,29 @@ __global__ __launch_bounds__(kPPThreads, 4) void kmeanspp_resident_kernel(const 
         double pmax = 0.0;
         unsigned fmx = 0;
         auto visit = [&](const unsigned (&w)[XW], unsigned& dm, unsigned wgt) {
-            float xi[C];
+            if constexpr (W) {
+                float xi[C];
 #pragma unroll
-            for (int i = 0; i < XW; ++i) {
-                const half2_t h = __builtin_bit_cast(half2_t, w[i]);
-                xi[2 * i] = (float)h.x;
-                xi[2 * i + 1] = (float)h.y;
+                for (int i = 0; i < XW; ++i) {
+                    const half2_t h = __builtin_bit_cast(half2_t, w[i]);
+                    xi[2 * i] = (float)h.x;
+                    xi[2 * i + 1] = (float)h.y;
+                }
+                dm = min(__float_as_uint(dist2<C>(xi, cj)), dm);
+            } else {
+                // x - c in one v_fma_mix_f32: conversion and subtraction, the same single rounding (with weights 512 groups
+                // of 8 channels were slower by it, 9.0 -> 10.6 ms at 16385 tokens, others 1-8 % faster)
+                float acc = 0.f;
+#pragma unroll
+                for (int i = 0; i < XW; ++i) {
+                    float d0, d1;
+                    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(d0) : "v"(w[i]), "v"(cj[2 * i]));
+                    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d1) : "v"(w[i]), "v"(cj[2 * i + 1]));
+                    acc = __builtin_fmaf(d0, d0, acc);
+                    acc = __builtin_fmaf(d1, d1, acc);
+                }
+                dm = min(__float_as_uint(acc), dm);
             }
-            dm = min(__float_as_uint(dist2<C>(xi, cj)), dm);
             if constexpr (W) {
                 const double pr = (double)wgt * (double)__uint_as_float(dm);
                 pmax = pr > pmax ? pr : pmax;

@@ -143,6 +143,26 @@ def test_picks_at_the_edges_of_the_register_resident_rounds(n, c, weighted):
     assert np.array_equal(out["picks"].cpu().numpy(), picks)
 
 
+@pytest.mark.parametrize("n", [1025, 2049, 5000, 20000])
+@pytest.mark.parametrize("c,spread", [(c, s) for c in (8, 4, 2) for s in ("denormal", "large", "both", "few")])
+def test_picks_over_the_range_of_distances(n, c, spread):
+    """The masses of unweighted tokens are split sums in fp32 (exact, whatever the scale): steps of the smallest fp16
+    denormal, values near the largest, both in one group (masses that round down to 0 beside ones near 2^62 / n), and
+    few distinct points (distances of 0)."""
+    fmt = cq.CQFormat(c, 8 if c == 8 else 4, 128, 1)
+    G, K = fmt.groups, 1 << fmt.b
+    x = _data(70 + c, n, 128).astype(np.float32)
+    tiny = np.clip(np.round(x * 3), -9, 9) * 2.0 ** -24
+    big = np.clip(x * 9000, -60000, 60000)
+    x = {"denormal": tiny, "large": big, "both": np.where(np.arange(n)[:, None] % 7 == 0, big, tiny), "few": x[np.arange(n) % 40]}[spread]
+    x = x.astype(np.float16)
+    rnd = _rnd(n + 2 * c, G, K)
+    picks, _ = KO.kmeanspp(x, c, K, rnd, None)
+    out = cq.cq_kmeans_fit(torch.from_numpy(x).cuda(), fmt, 0, rnd=_dev_rnd(rnd), want_picks=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(out["picks"].cpu().numpy(), picks)
+
+
 @pytest.mark.parametrize("n", [1, 2, 65, 128, 129])
 @pytest.mark.parametrize("c,heads,weighted", [(8, 1, False), (8, 1, True), (8, 17, True), (4, 8, False), (4, 9, True),
                                               (2, 4, False), (2, 5, False), (2, 5, True)])
