@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kPPThreads) void kmeanspp_kernel(const uint16_t* __
 // its mass in up to four sums, so the search is 4 + R / 4 independent reductions and one scan.
 // Weights sit in registers too, 32 rounds of them in LDS (as 32 more registers they spilled 50 to 61).
 // 32768 tokens, 512 groups of 8 channels, 256 picks: 30.6 ms -> 6.7 ms, weighted 30.7 -> 9.0 (and see draw() and visit()
-// for the vector instructions, which bound it: 6.7 -> 5.4, at 12000 tokens 3.6 -> 2.9); 1500 tokens, 256
+// for the vector instructions, which bound it: 6.7-7.0 -> 5.4-6.4, at 12000 tokens 3.6 -> 2.9); 1500 tokens, 256
 // groups of 4: 1.05 -> 0.71 ms; 100 tokens 0.54 -> 0.56 (two barriers' worth of other wavefronts' numbers), so that
 // up to 128 go to the general kernel (run_kmeanspp).
 // Slices of 4 (of 2: 8) weighted tokens per lane in registers instead of 2 (4), 32 rounds: 8 channels 11.0 -> 9.0 ms
