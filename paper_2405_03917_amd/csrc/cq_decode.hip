@@ -317,11 +317,12 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     // stores (write-through) and the merging workgroup reads them with device-scope loads, so
     // no cache has to be written back or invalidated as a whole (a device-scope release fence
     // per workgroup, which writes the whole L2 back, cost 50 us on a 90 us launch).  Order:
-    // every thread's stores are complete at the barrier (it waits for them), then one thread
+    // every wavefront waits for its stores, then all meet at the barrier, then one thread
     // counts the workgroup in; the workgroup that counts the last split takes the counter back
     // to zero for the next call and merges.
     auto count_and_merge = [&] {
         if (!a.merge_counters) return;
+        wait_for_stores();
         __syncthreads();
         unsigned* flag = sums;
         if (tid == 0) {

@@ -32,10 +32,9 @@ __device__ __forceinline__ void lds_add(unsigned byte_addr, unsigned v)
     __hip_atomic_fetch_add((lds_u32*)(byte_addr), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() would also wait for every
-// outstanding global load, i.e. for the code tiles that are deliberately kept in flight across
-// the barriers of this kernel.  (No barrier here orders global memory: what the workgroup
-// exchanges lives in LDS.)
+// Workgroup barrier that orders LDS traffic only, and says so: the code tiles are deliberately
+// kept in flight across the barriers of these kernels.  (No barrier here orders global memory: what
+// the workgroup exchanges lives in LDS.  __syncthreads() waits for no global access either.)
 __device__ __forceinline__ void lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");

@@ -69,6 +69,13 @@ __device__ __forceinline__ void partial_store(float* p, float v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Until every store of this wavefront has been carried out: a barrier (__syncthreads() too) does not wait for them, and
+// the workgroup that counts the last split reads what all of them wrote.  (A release fence of device scope would also
+// wait, and write the whole L2 back.)
+__device__ __forceinline__ void wait_for_stores()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
 
 // Fused step: the key codes of the new token as the cache layout would hold them (slot s of token
 // u carries group (s + u) mod Gh), from keys[g] = group g's (distance, index) minimum.  Built in LDS
