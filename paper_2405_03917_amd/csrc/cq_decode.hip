@@ -150,7 +150,7 @@ struct Lay {
     static constexpr int SCR = SUMS + kDecodeWaves;                 // 64 + NW * head_dim floats
     static constexpr int KEYS(int head_dim) { return SCR + 64 + kDecodeWaves * head_dim; }   // fused step only
     // fused step: the keys, the new token's fixed-point weight, its record of key codes in cache order
-    static constexpr int FLOATS(int head_dim, bool step) { return KEYS(head_dim) + (step ? kKeyFloats(GH) + GH / 4 + 2 : 0); }
+    static constexpr int FLOATS(int head_dim, bool step) { return KEYS(head_dim) + (step ? NewTokenWords<GH, B>::END : 0); }
     // Word of code value j in word column `col`.  b = 8: row j.  b = 10: row = the low 8 bits,
     // and the two high bits pick one of four 16-word quarters of the row, which makes the byte
     // address (low << 8) | (high << 6) | (4 * column): the b = 8 address plus one shift-or.
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     // fused step: the wavefront whose walk meets the new token's tile patches that tile in registers
     // as if the codes just found were already in the cache
     const bool meets_new = has_new && (tile_new - tile0) % NW == wave;
-    const NewTokenRecord<GH, B> new_codes{reinterpret_cast<unsigned*>(keys + 2 * GH) + 4};
+    const NewTokenRecord<GH, B> new_codes{reinterpret_cast<unsigned*>(keys) + NewTokenWords<GH, B>::RECORD};
     if (meets_new) new_codes.build(keys, u_new, lane);
 
     // ---- 2. the walk: per chunk, scores from the key tiles, then bins from the value tiles ----
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(kDecodeThreads, 4) void decode_split_kernel(DecodeA
     // (and the running integer sum) is shifted right, rounding to nearest, so that U comes to lie
     // in [2^28, 2^29), and fx drops by the shift.  No bin can overflow 32 bits, and each
     // probability is kept to an absolute error of at most 2^-29 of the softmax denominator.
-    unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
+    unsigned* pf_new = reinterpret_cast<unsigned*>(keys) + NewTokenWords<GH, B>::WEIGHT;
     float m0 = 0.f, m_run = 0.f, l_run = 0.f, fxf = 0.f;
     int fx = 0;
     unsigned lane_sum = 0, l_carry = 0;

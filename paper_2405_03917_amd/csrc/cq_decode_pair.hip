@@ -43,7 +43,7 @@ struct Lay {
     static constexpr int SCR = SUMS + H * NW;                       // 64 + H * NW * head_dim floats
     static constexpr int KEYS(int head_dim) { return SCR + 64 + H * NW * head_dim; }   // fused step only
     // fused step: the keys, the new token's fixed-point weights, its record of key codes in cache order
-    static constexpr int FLOATS(int head_dim, bool step) { return KEYS(head_dim) + (step ? kKeyFloats(GH) + GH / 4 + 4 : 0); }
+    static constexpr int FLOATS(int head_dim, bool step) { return KEYS(head_dim) + (step ? NewTokenWords<GH, B>::END : 0); }
     // Byte address of the cell of code value j in column `col`.  b = 8: row j.  b = 10: row = the low 8 bits,
     // and the two high bits pick one of four 16-cell quarters of the row.
     __device__ __forceinline__ static constexpr unsigned cell(int j, int col)
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
     // fused step: the wavefront whose walk meets the new token's tile patches that tile in registers
     // as if the codes just found were already in the cache
     const bool meets_new = has_new && (tile_new - tile0) % NW == wave;
-    const NewTokenRecord<GH, B> new_codes{reinterpret_cast<unsigned*>(keys + 2 * GH) + 4};
+    const NewTokenRecord<GH, B> new_codes{reinterpret_cast<unsigned*>(keys) + NewTokenWords<GH, B>::RECORD};
     if (meets_new) new_codes.build(keys, u_new, lane);
 
     // ---- 2. the walk: per chunk, scores from the key tiles, then bins from the value tiles ----
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
     // probability is kept to an absolute error of at most 2^-29 of the softmax denominator.
     constexpr bool EARLY = IPT * NCH <= 8 && KB == IPT;
     Cent16 rawv[EARLY ? NCH : 1][KB];
-    unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
+    unsigned* pf_new = reinterpret_cast<unsigned*>(keys) + NewTokenWords<GH, B>::WEIGHT;
     float m0[H] = {}, m_run[H] = {}, l_run[H] = {}, fxf[H] = {};
     int fx[H] = {};
     unsigned lane_sum[H] = {}, l_carry[H] = {};

@@ -77,6 +77,15 @@ __device__ __forceinline__ void wait_for_stores()
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// Fused step: words of LDS from the keys on.  The 2 Gh 64-bit minima; the new token's fixed-point weight, one per query
+// head of the workgroup, in 16 bytes; the record of its key codes (NewTokenRecord), read 16 bytes at a time.
+template <int GH, int B>
+struct NewTokenWords {
+    static constexpr int WEIGHT = 2 * 2 * GH;
+    static constexpr int RECORD = WEIGHT + 4;
+    static constexpr int END = RECORD + GH / 4 + (B == 10 ? 1 : 0);
+};
+
 // Fused step: the key codes of the new token as the cache layout would hold them (slot s of token
 // u carries group (s + u) mod Gh), from keys[g] = group g's (distance, index) minimum.  Built in LDS
 // by the one wavefront whose walk meets the token's tile, before its walk starts (lane i builds word
