@@ -533,7 +533,9 @@ CQ_API cq_status cq_dequantize(const void *codes, const void *centroids, const c
  *                     iteration's assignment step (untouched when n_iter = 0)
  *   workspace         at least cq_kmeans_workspace_bytes(fmt, n_points) bytes (0: invalid arguments)
  * All pointers are device pointers, 16-byte aligned.  A cluster that owns no token keeps its
- * centroid.  Errors: CQ_ERR_INVALID_ARG, CQ_ERR_UNSUPPORTED (format), CQ_ERR_WORKSPACE_TOO_SMALL,
+ * centroid.  A fit's launches fill the GPU: k-means++ is one of them, and where every group has one workgroup
+ * (512 groups and more, or fewer than 2048 tokens) fits of 30 iterations and more take up to 128 iterations (2^22 tokens
+ * times iterations) in each, so that work on other streams may have to wait for some tens of milliseconds.  Errors: CQ_ERR_INVALID_ARG, CQ_ERR_UNSUPPORTED (format), CQ_ERR_WORKSPACE_TOO_SMALL,
  * CQ_ERR_HIP.
  */
 #define CQ_KMEANS_MAX_POINTS 524288

@@ -55,7 +55,7 @@
 // groups, 100 iterations: 31.8 -> 22.2 ms, weighted 40.4 -> 20.1; 6000 tokens 6.5 -> 2.9; 30 iterations 1.0-1.2 times
 // as fast, 20 iterations 0.85-1.07 (hence kStateIterations, kPlainIterations).  Weighted fits of few tokens
 // (below about 12000 of 8 channels) have no room for the sums in their scratch and run plain.
-// A group's only workgroup runs all iterations that are left in one launch: 100 launches waited for their busiest
+// A group's only workgroup runs many iterations in one launch: 100 launches waited for their busiest
 // group each (26.3 against 30.3 ms).
 //
 // What bounds it: the vector ALU (535 instructions per 64 tokens and group: 208 in the scan, 150 in
@@ -84,6 +84,8 @@ constexpr int kNBlk = kK / 32;
 constexpr int kHashSlots = 1024;        // for finding equal centroids
 constexpr int kStateIterations = 30;    // a fit of at least as many iterations skips tokens, ...
 constexpr int kPlainIterations = 10;    // ... from this iteration on
+constexpr int kLaunchIterations = 128;  // one launch takes at most so many iterations, ...
+constexpr int kLaunchTokens = 1 << 22;  // ... and so many tokens of a group times iterations (see launch_lloyd)
 static_assert(kStateIterations >= kPlainIterations + 2, "one iteration fills the state, at least one uses it");
 
 template <int CTRL>
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     const bool alone = gridDim.x == 1;                  // the group's only workgroup
     for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = MODE == kNext && alone ? all_sums[i] : 0ull;
 
-    // A group's only workgroup takes all iterations that are left (groups end when they are done: no launch waits for the
+    // A group's only workgroup takes several iterations (groups end when they are done: the launch waits once for the
     // busiest of them); else `iterations` is 1.
 #pragma unroll 1
     for (int it = 0;; ++it) {
@@ -679,7 +681,7 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
             if (!*flag) return;
             for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = __hip_atomic_load(all_sums + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
-        } else if constexpr (MODE == kFirst) {
+        } else if (last_iteration) {                        // (for the next launch)
             for (int i = tid; i < kK * SW; i += kLloydWaves * 64) all_sums[i] = sums[i];
         }
         const unsigned long long* sj = &sums[tid * SW];
@@ -808,10 +810,19 @@ cq_status launch_lloyd(const KMeansLloyd& a, hipStream_t st)
         unsigned long long* none = nullptr;
         hipLaunchKernelGGL((kmeans_lloyd_kernel<C, W, kFirst>), grid, block, 0, st, a.xg, a.wq, a.cent, static_cast<uint16_t*>(nullptr),
                            none, state, a.n, ss.tokens, 1);
-        const int left = a.n_iter - plain - 1, per_launch = ss.n == 1 ? left : 1;
-        for (int it = 0; it < left; it += per_launch)
+        // A workgroup holds its CU (all registers of two wavefronts per SIMD) until its launch ends, and the caller sets the
+        // number of iterations: the two bounds keep what other streams' work has to wait for to 15-40 ms, which is in
+        // the range of the k-means++ launch ahead of it.  The bounds leave the usual 100 iterations over 32768 tokens whole: every cut
+        // waits for the busiest group (32768 tokens, 512 groups, 89 iterations in two, three or six launches: 24.3 -> 24.8, 24.8 ->
+        // 25.4, 25.9 -> 26.5 ms for the fit, weighted 28.7 -> 29.4, 29.3 -> 30.4, 31.0 -> 32.2).
+        const int left = a.n_iter - plain - 1;
+        const int by_length = a.n >= kLaunchTokens ? 1 : kLaunchTokens / a.n;
+        const int most = ss.n > 1 ? 1 : by_length < kLaunchIterations ? by_length : kLaunchIterations;
+        for (int it = 0; it < left; it += most) {
+            const int now = left - it < most ? left - it : most;
             hipLaunchKernelGGL((kmeans_lloyd_kernel<C, W, kNext>), grid, block, 0, st, a.xg, a.wq, a.cent,
-                               it + per_launch == left ? a.assign : nullptr, none, state, a.n, ss.tokens, per_launch);
+                               it + now == left ? a.assign : nullptr, none, state, a.n, ss.tokens, now);
+        }
     }
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
 }

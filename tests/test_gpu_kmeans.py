@@ -2,6 +2,8 @@
 every pick of k-means++, every fp32 centroid after every tested number of Lloyd iterations and
 every assignment must be IDENTICAL (both sides take each decision in the same arithmetic; sums are
 exact integers), on sizes that are not multiples of any tile, with and without Eq. 6 weights."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -291,3 +293,44 @@ def test_iterations_that_skip_tokens_equal_those_that_look_at_all(c, heads, n, w
     torch.cuda.synchronize()
     assert torch.equal(whole["assignment"], part["assignment"])
     assert torch.equal(whole["centroids_f32"].view(torch.int32), cent.view(torch.int32))
+
+
+def _kernel_nodes(graph):
+    """Nodes of a captured graph (torch.cuda.CUDAGraph(keep_graph=True))."""
+    runtime = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    count = ctypes.c_size_t(0)
+    status = ctypes.CDLL(runtime).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count))
+    assert status == 0
+    return count.value
+
+
+@pytest.mark.parametrize("c,heads,n,weighted", [(8, 32, 40000, False), (4, 16, 9001, True), (2, 8, 1500, False)])
+def test_a_long_fit_is_cut_into_launches_of_bounded_length(c, heads, n, weighted):
+    """A group's only workgroup holds its CU through all iterations of a launch: at most 128 iterations, and 2^22 tokens
+    times iterations.  The launches hand the clusters' sums on: the fit equals chained fits too short to skip, byte for byte."""
+    fmt = cq.CQFormat(c, 8, 128, heads)
+    iters, most = 280, min(128, 2 ** 22 // n)
+    x = torch.from_numpy(np.tile(_data(70 + c, n, 128), (1, heads))).cuda()
+    w = torch.from_numpy(np.ascontiguousarray(np.tile(_weights(n, n, fmt.groups // heads), (1, heads)))).cuda() if weighted else None
+    init = x[:256].view(256, fmt.groups, c).transpose(0, 1).float().contiguous()
+    ws = torch.empty(cq.cq_kmeans_workspace_bytes(fmt, n), dtype=torch.uint8, device="cuda")
+
+    def fit(count, start, stream=None):
+        return cq.cq_kmeans_fit(x, fmt, count, init_centroids=start, weights=w, want_assignment=True, workspace=ws, stream=stream)
+
+    whole, cent, done = fit(iters, init), init, 0
+    while done < iters:
+        part = fit(min(28, iters - done), cent)
+        cent, done = part["centroids_f32"], done + min(28, iters - done)
+    torch.cuda.synchronize()
+    assert torch.equal(whole["assignment"], part["assignment"])
+    assert torch.equal(whole["centroids_f32"].view(torch.int32), cent.view(torch.int32))
+
+    nodes = []
+    for count in (iters, iters + 10 * most):
+        graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=side):
+            fit(count, init, side)
+        nodes.append(_kernel_nodes(graph))
+    assert nodes[1] == nodes[0] + 10
+    assert nodes[0] >= 10 + 1 + -(-(iters - 11) // most)
