@@ -236,22 +236,12 @@ def fill_cache_set(cq, synth, torch, cfg, fmt, set_id, chunk_tokens):
     return dict(ck=ck, cv=cv, kcache=kcache, vcache=vcache, q=q, out=out, ws=ws, rk=rk, rv=rv)
 
 
-def kernel_name(cfg, step=False, ns=None):
-    gh = cfg.head_dim // cfg.c
-    if ns is None:
-        tiles = (cfg.context + 63) // 64
-        import paper_2405_03917_amd as cq
-        fmt = cq.CQFormat(cfg.c, cfg.b, cfg.head_dim, cfg.n_kv_heads)
-        split = cq.cq_decode_default_split(fmt, cfg.batch, cfg.n_q_heads, cfg.context) // 64
-        per_wave = (min(split, tiles) + 7) // 8
-        full = 32 if cfg.b == 10 else 16
-        ns = full // 2 if per_wave <= full // 2 else full
-        rounds = cfg.batch * (cfg.n_q_heads // 2) * ((tiles + split - 1) // split) / 256
-        if (cfg.n_q_heads // cfg.n_kv_heads) % 2 == 0 and rounds >= 1 and (cfg.b == 10 or rounds / math.ceil(rounds) >= 0.85):
-            return f"decode_pair_kernel<{gh}, {cfg.c}, {cfg.b}, {ns // 2}, {'true' if step else 'false'}, false>"
-        if gh == 16 and cfg.b == 8 and per_wave <= 4:
-            ns = 4
-    return f"decode_split_kernel<{gh}, {cfg.c}, {cfg.b}, {ns}, {'true' if step else 'false'}, false>"
+def kernel_name(cfg, step=False):
+    import paper_2405_03917_amd as cq
+    fmt = cq.CQFormat(cfg.c, cfg.b, cfg.head_dim, cfg.n_kv_heads)
+    heads, tiles = cq.cq_probe_decode_plan(fmt, cfg.batch, cfg.n_q_heads, cfg.context)
+    name = {1: "decode_split_kernel", 2: "decode_pair_kernel"}[heads]
+    return f"{name}<{cfg.head_dim // cfg.c}, {cfg.c}, {cfg.b}, {tiles}, {'true' if step else 'false'}, false>"
 
 
 def decode_config_entry(cq, synth, torch, cfg_id, rounds, label):

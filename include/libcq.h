@@ -558,12 +558,19 @@ CQ_API cq_status cq_kmeans_fit(const void *x, int64_t x_row_stride, const float 
  *                       for kdim 8; zero accumulator): a fp16 [32][kdim] row-major, b fp16
  *                       [kdim][32] row-major, d fp32 [32][32] row-major, all device.  Tests pin
  *                       the rounding model that the encode kernel's error bound assumes to it.
+ * cq_probe_decode_plan  which kernel a cq_decode_attention / cq_decode_step call of these sizes (layers != 0: a
+ *                       cq_decode_step_layers call) runs: query heads per workgroup (1:
+ *                       decode_split_kernel, 2: decode_pair_kernel) and tiles per wavefront and chunk, the
+ *                       kernel's template argument.  Host only.
  * Errors: CQ_ERR_INVALID_ARG for null / misaligned pointers, a size that is zero or not a
- * multiple of 16, or a kdim other than 8 and 16; CQ_ERR_HIP if the launch fails.
+ * multiple of 16, or a kdim other than 8 and 16; of cq_probe_decode_plan as of cq_decode_attention; CQ_ERR_HIP if
+ * the launch fails.
  */
 CQ_API cq_status cq_probe_stream_read(const void *src, size_t bytes, void *sink, void *stream);
 CQ_API cq_status cq_probe_copy(const void *src, void *dst, size_t bytes, void *stream);
 CQ_API cq_status cq_probe_mfma(const void *a, const void *b, void *d, int32_t kdim, void *stream);
+CQ_API cq_status cq_probe_decode_plan(const cq_format *fmt, int32_t batch, int32_t n_q_heads, int32_t t, int32_t tokens_per_split,
+                               int32_t layers, int32_t *heads_per_workgroup, int32_t *chunk_tiles);
 
 #ifdef __cplusplus
 }

@@ -34,7 +34,7 @@ EXPORTS = (
     "cq_rope_table_bytes", "cq_rope_table", "cq_decode_rope_default_split", "cq_decode_attention_rope",
     "cq_decode_attention_rope_paged", "cq_decode_step_rope", "cq_decode_step_rope_paged",
     "cq_chunk_rope_workspace_bytes", "cq_chunk_attention_rope", "cq_chunk_attention_rope_paged",
-    "cq_probe_stream_read", "cq_probe_copy", "cq_probe_mfma",
+    "cq_probe_stream_read", "cq_probe_copy", "cq_probe_mfma", "cq_probe_decode_plan",
 )
 
 
@@ -193,6 +193,8 @@ def load() -> ctypes.CDLL:
     lib.cq_probe_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
     lib.cq_probe_mfma.restype = ctypes.c_int
     lib.cq_probe_mfma.argtypes = [vp, vp, vp, i32, vp]
+    lib.cq_probe_decode_plan.restype = ctypes.c_int
+    lib.cq_probe_decode_plan.argtypes = [fp, i32, i32, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     _lib = lib
     return lib
 
@@ -796,6 +798,18 @@ def cq_probe_copy(src, dst, stream=None) -> None:
     st = load().cq_probe_copy(src.data_ptr(), dst.data_ptr(), src.numel(), _stream_handle(stream))
     if st != CQ_OK:
         raise CQError(st, "cq_probe_copy")
+
+
+def cq_probe_decode_plan(fmt: CQFormat, batch: int, n_q_heads: int, t: int, tokens_per_split: int = 0,
+                         layers: bool = False) -> tuple[int, int]:
+    """(query heads per workgroup, tiles per wavefront and chunk) of the kernel that a cq_decode_attention or
+    cq_decode_step call of these sizes runs (measurement aid; host only)."""
+    heads, tiles = ctypes.c_int32(), ctypes.c_int32()
+    st = load().cq_probe_decode_plan(ctypes.byref(fmt._c()), batch, n_q_heads, t, tokens_per_split, int(layers),
+                                     ctypes.byref(heads), ctypes.byref(tiles))
+    if st != CQ_OK:
+        raise CQError(st, "cq_probe_decode_plan")
+    return heads.value, tiles.value
 
 
 class PageTable:

@@ -429,6 +429,30 @@ size_t cq_decode_workspace_bytes(const cq_format* fmt, int32_t batch, int32_t n_
     return sizeof(float) * (size_t)batch * n_q_heads * n_split * (f.head_dim + kPartialHeader);
 }
 
+cq_status cq_probe_decode_plan(const cq_format* fmt, int32_t batch, int32_t n_q_heads, int32_t t, int32_t tokens_per_split,
+                               int32_t layers, int32_t* heads_per_workgroup, int32_t* chunk_tiles)
+{
+    Derived f;
+    const cq_status st = derive(fmt, &f);
+    if (st != CQ_OK) return st;
+    if (!heads_per_workgroup || !chunk_tiles || batch <= 0 || n_q_heads <= 0 || n_q_heads % f.n_kv_heads != 0 || t <= 0) return CQ_ERR_INVALID_ARG;
+    if (tokens_per_split < 0 || tokens_per_split % kTileTokens != 0) return CQ_ERR_INVALID_ARG;
+    DecodeArgs a = {};
+    a.f = f;
+    a.batch = batch;
+    a.n_q_heads = n_q_heads;
+    a.t = t;
+    a.tiles_per_split = tokens_per_split ? tokens_per_split / kTileTokens : default_tiles_per_split(f, batch, n_q_heads, t);
+    if (a.tiles_per_split > decode_max_tiles_per_split(f)) return CQ_ERR_INVALID_ARG;
+    a.n_split = ((t + kTileTokens - 1) / kTileTokens + a.tiles_per_split - 1) / a.tiles_per_split;
+    const LayerPtrs one = {};                    // (only whether there is a table matters)
+    a.layers = layers ? &one : nullptr;
+    const DecodePlan p = decode_plan(a);
+    *heads_per_workgroup = p.heads;
+    *chunk_tiles = p.chunk_tiles;
+    return CQ_OK;
+}
+
 namespace {
 
 // One query token of a chunk served token by token: q and out rows of the token inside

@@ -940,14 +940,23 @@ cq_status launch_variant(const DecodeArgs& a, hipStream_t stream)
     return CQ_OK;
 }
 
+// tiles per wavefront and chunk that a call's splits take
+int chunk_tiles(const DecodeArgs& a)
+{
+    const int full = a.f.b == 10 ? kChunkTiles10 : kChunkTiles8;
+    const int tiles_per_wave = (a.tiles_per_split + kDecodeWaves - 1) / kDecodeWaves;
+    if (a.f.b == 8 && !a.layers && tiles_per_wave <= kOnceTiles(a.f.gh)) return kOnceTiles(a.f.gh);
+    return tiles_per_wave <= full / 2 ? full / 2 : full;
+}
+
 template <int GH, int C, int B, int NS, bool STEP, bool LAYERS>
 cq_status launch_by_length(const DecodeArgs& a, hipStream_t stream)
 {
-    const int tiles_per_wave = (a.tiles_per_split + kDecodeWaves - 1) / kDecodeWaves;
+    const int ns = chunk_tiles(a);
     if constexpr (B == 8 && !LAYERS && kOnceTiles(GH) > 0) {
-        if (tiles_per_wave <= kOnceTiles(GH)) return launch_variant<GH, C, B, kOnceTiles(GH), STEP, LAYERS>(a, stream);
+        if (ns == kOnceTiles(GH)) return launch_variant<GH, C, B, kOnceTiles(GH), STEP, LAYERS>(a, stream);
     }
-    if (tiles_per_wave <= NS / 2) return launch_variant<GH, C, B, NS / 2, STEP, LAYERS>(a, stream);
+    if (ns == NS / 2) return launch_variant<GH, C, B, NS / 2, STEP, LAYERS>(a, stream);
     return launch_variant<GH, C, B, NS, STEP, LAYERS>(a, stream);
 }
 
@@ -988,6 +997,11 @@ int decode_max_tiles_per_split(const Derived& f)
     if (f.b == 10) return kChunkTiles10 * kDecodeWaves;                // 16384 tokens
     if (f.gh == 64) return kChunkTiles8 * kDecodeWaves;                // 8192 tokens
     return 1 << 20;
+}
+
+DecodePlan decode_plan(const DecodeArgs& a)
+{
+    return decode_takes_pairs(a) ? DecodePlan{2, decode_pair_chunk_tiles(a)} : DecodePlan{1, chunk_tiles(a)};
 }
 
 cq_status launch_decode(const DecodeArgs& a_in, hipStream_t stream)

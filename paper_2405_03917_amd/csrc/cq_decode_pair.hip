@@ -818,12 +818,10 @@ cq_status launch_variant(const DecodeArgs& a, hipStream_t stream)
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
 }
 
-// (twice the wavefronts: half the tiles per wavefront and chunk, of two heads each, so as many score registers)
 template <int GH, int C, int B, int NS, bool STEP, bool LAYERS>
 cq_status launch_by_length(const DecodeArgs& a, hipStream_t stream)
 {
-    const int tiles_per_wave = (a.tiles_per_split + Lay<GH, B>::NW - 1) / Lay<GH, B>::NW;
-    if (tiles_per_wave <= NS / 4) return launch_variant<GH, C, B, NS / 4, STEP, LAYERS>(a, stream);
+    if (decode_pair_chunk_tiles(a) == NS / 4) return launch_variant<GH, C, B, NS / 4, STEP, LAYERS>(a, stream);
     return launch_variant<GH, C, B, NS / 2, STEP, LAYERS>(a, stream);
 }
 
@@ -854,6 +852,13 @@ bool decode_takes_pairs(const DecodeArgs& a)
     const int64_t wgs = (int64_t)a.batch * (a.n_q_heads / H) * a.n_split, rounds = (wgs + 255) / 256;
     if (qper % H != 0 || wgs < 256) return false;
     return a.f.b == 10 || wgs * 20 >= rounds * 256 * 17;
+}
+
+// (twice the wavefronts: half the tiles per wavefront and chunk, of two heads each, so as many score registers)
+int decode_pair_chunk_tiles(const DecodeArgs& a)
+{
+    const int full = (a.f.b == 10 ? kChunkTiles10 : kChunkTiles8) / H, nw = kDecodeWaves * H;
+    return (a.tiles_per_split + nw - 1) / nw <= full / 2 ? full / 2 : full;
 }
 
 cq_status launch_decode_pair(const DecodeArgs& a, hipStream_t stream)

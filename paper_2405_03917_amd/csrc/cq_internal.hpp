@@ -206,6 +206,12 @@ cq_status launch_encode_tiles(const EncodeArgs& a, hipStream_t stream);
 cq_status launch_decode(const DecodeArgs& a, hipStream_t stream);
 // grouped queries, two query heads per workgroup (cq_decode_pair.hip): whether a call goes there, and the launch
 bool decode_takes_pairs(const DecodeArgs& a);
+int decode_pair_chunk_tiles(const DecodeArgs& a);
+// how launch_decode serves a call: query heads per workgroup, tiles per wavefront and chunk (the kernels' NS)
+struct DecodePlan {
+    int heads, chunk_tiles;
+};
+DecodePlan decode_plan(const DecodeArgs& a);
 cq_status launch_decode_pair(const DecodeArgs& a, hipStream_t stream);
 // centroids fp16 [G][2^b][c] of a sub-byte format -> fp16 [G / fuse][256][c fuse] of its fused format
 cq_status launch_expand_codebook(const uint16_t* centroids, const Derived& f, uint16_t* fused, hipStream_t stream);

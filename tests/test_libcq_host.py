@@ -363,6 +363,26 @@ def test_chunk_attention_sizes_and_argument_checks_without_launching():
     assert run(fm=cq.CQFormat(2, 4, 128, 4)._c()) == cq.CQ_ERR_UNSUPPORTED
 
 
+def test_decode_plan_names_the_kernel_of_a_call():
+    plan, gqa, mha = cq.cq_probe_decode_plan, cq.CQFormat(4, 8, 128, 8), cq.CQFormat(4, 8, 128, 32)
+    assert plan(mha, 16, 32, 4096) == (1, 8) and plan(mha, 16, 32, 16384) == (1, 16)           # one query head per KV head
+    # grouped queries: from 256 workgroups of two heads on, byte codes with a last round at least 0.85 full
+    assert [plan(gqa, b, 32, 2000)[0] for b in (15, 16, 20, 27, 28, 32)] == [1, 2, 1, 1, 2, 2]
+    assert [plan(cq.CQFormat(8, 10, 128, 8), b, 32, 2000) for b in (15, 16, 20)] == [(1, 16), (2, 8), (2, 8)]
+    assert plan(gqa, 32, 32, 4096) == (2, 4) and plan(gqa, 32, 32, 4097) == (2, 8)
+    assert plan(gqa, 8, 32, 4096)[0] == 1 and plan(gqa, 8, 32, 4096, 2048)[0] == 2             # two splits
+    assert plan(cq.CQFormat(4, 8, 128, 8), 64, 24, 2000)[0] == 1                               # three heads per KV head
+    # the shortest splits of CQ-8c8b have a form of their own, not in layer-batched launches
+    short = cq.CQFormat(8, 8, 128, 32)
+    assert [plan(short, 1, 32, t, t)[1] for t in (64, 2048, 2112, 4096, 4160)] == [4, 4, 8, 8, 16]
+    assert plan(short, 1, 32, 2048, 2048, layers=True) == (1, 8)
+    for bad in (dict(batch=0), dict(n_q_heads=12), dict(t=0), dict(tokens_per_split=100)):
+        with pytest.raises(cq.CQError):
+            plan(gqa, **{**dict(batch=1, n_q_heads=32, t=100), **bad})
+    f = gqa._c()
+    assert cq.load().cq_probe_decode_plan(ctypes.byref(f), 1, 32, 100, 0, 0, None, None) == cq.CQ_ERR_INVALID_ARG
+
+
 def test_subbyte_formats_sizes_and_argument_checks_without_launching():
     lib = cq.load()
     for (c, b), (cf, bytes_th) in {(1, 2): (4, 32), (2, 2): (8, 16), (1, 4): (2, 64), (2, 4): (4, 32), (4, 4): (8, 16)}.items():
