@@ -107,3 +107,89 @@ def test_the_fused_step_of_pairs_and_of_layers(c, b, t, split):
     for lay, (ref, k1, v1) in zip(layers, want):
         assert torch.equal(lay["out"].view(torch.int16), ref.view(torch.int16))
         assert torch.equal(lay["k_codes"], k1) and torch.equal(lay["v_codes"], v1)
+
+
+def _pools(fmt, k1, v1, B, tiles, seed):
+    """The caches of `distinct` sequences as pools for B sequences (sequence n holds what n % distinct does) on permuted
+    pages, a table with a row stride of its own, and the pages that no sequence has."""
+    distinct = k1.shape[0]
+    n_pages = B * tiles + 5
+    perm = torch.from_numpy(np.random.default_rng(seed).permutation(n_pages)).cuda()
+    wide = torch.full((B, tiles + 3), -7, dtype=torch.int32, device="cuda")
+    wide[:, :tiles] = perm[:B * tiles].view(B, tiles).int()
+    pools = []
+    for cache in (k1, v1):
+        tiles_of = cache.view(distinct, fmt.n_kv_heads, tiles, -1).transpose(1, 2)          # [n, tile, head, bytes]
+        pool = torch.full((n_pages, fmt.n_kv_heads, tiles_of.shape[-1]), 0xA5, dtype=torch.uint8, device="cuda")
+        pool[perm[:B * tiles]] = tiles_of[torch.arange(B, device="cuda") % distinct].reshape(B * tiles, fmt.n_kv_heads, -1)
+        pools.append(pool)
+    return pools, cq.PageTable(wide[:, :tiles], n_pages), perm[B * tiles:]
+
+
+# (16 wavefronts of at most 8 tiles, of 16 with 10-bit codes, make a chunk: 8192 or 16384 tokens)
+PAGED = [(4, 1, 128, 8900, 8960, "growing"), (4, 1, 128, 8900, 8960, "opposed"), (4, 2, 64, 3000, 768, "plain"),
+         (8, 2, 64, 130, 0, "plain"), (4, 1, 250, 700, 0, "plain"), (32, 8, 8, 2100, 1088, "plain")]
+
+
+@pytest.mark.parametrize("c,b", [(8, 8), (4, 8), (2, 8), (8, 10)])
+@pytest.mark.parametrize("hq,hkv,B,t,split,data", PAGED)
+def test_pairs_over_pages_and_ragged_lengths(c, b, hq, hkv, B, t, split, data):
+    """Paged attention of pairs equals the contiguous call bit for bit (splits of several chunks, several splits, splits
+    beyond a sequence's end), and the paged fused step at ragged positions equals cq_encode_kv_paged, sequence by
+    sequence, then the paged attention; pages of no sequence stay as they are."""
+    if split > 8192 and c == 2:
+        split = 4480                          # (CQ-2c8b walks one chunk)
+    distinct = 5
+    fmt, ck, cv, q, kc, vc = _problem(t + 7 * c, c, b, hq, hkv, distinct, t, data)
+    tiles = (t + 63) // 64
+    t_cap = tiles * 64
+    assert cq.cq_probe_decode_plan(fmt, B, hq, t, split)[0] == 2 and cq.cq_probe_decode_plan(fmt, 1, hq, t, split)[0] == 1
+    k1, v1 = (codes_to_cache(x, fmt, t_cap).view(distinct, -1) for x in (kc, vc))
+    at = torch.arange(B, device="cuda") % distinct
+    lens1 = torch.tensor([t, max(1, t // 3), 1, max(1, t - 64), max(1, t // 2)], dtype=torch.int32, device="cuda")
+    lens = lens1[at].contiguous()
+    ckd, cvd, qd = dev(ck), dev(cv), dev(q)[at].contiguous()
+    (kp, vp), pages, unused = _pools(fmt, k1, v1, B, tiles, t)
+    flat = lambda p: p.view(-1)
+
+    for sl in (None, lens):
+        got = cq.cq_decode_attention_paged(qd, flat(kp), flat(vp), ckd, cvd, SCALE, fmt, t, pages, seq_lens=sl, tokens_per_split=split)
+        want = _attend(fmt, ckd, cvd, qd, k1[at].flatten(), v1[at].flatten(), t, t_cap, sl, split)
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    for n in range(distinct):                 # (the kernel for one head, by itself)
+        _close(got[n:n + 1], _attend(fmt, ckd, cvd, qd[n:n + 1], k1[n], v1[n], t, t_cap, lens1[n:n + 1],
+                                     split if split else cq.cq_decode_default_split(fmt, B, hq, t)))
+
+    rng = np.random.default_rng(t)
+    xk, xv = (dev(rng.standard_normal((distinct, fmt.channels)).astype(np.float16))[at].contiguous() for _ in range(2))
+    k2, v2 = kp.clone(), vp.clone()
+    for n in range(B):
+        row = cq.PageTable(pages.block_table[n:n + 1], pages.n_pages)
+        cq.cq_encode_kv_paged(xk[n:n + 1, None], xv[n:n + 1, None], ckd, cvd, fmt, flat(k2), flat(v2), row, int(lens1[n % distinct]) - 1)
+    want = cq.cq_decode_attention_paged(qd, flat(k2), flat(v2), ckd, cvd, SCALE, fmt, t, pages, seq_lens=lens, tokens_per_split=split)
+    k3, v3 = kp.clone(), vp.clone()
+    got = cq.cq_decode_step_paged(qd, xk, xv, flat(k3), flat(v3), ckd, cvd, SCALE, fmt, t, pages, seq_lens=lens, tokens_per_split=split)
+    torch.cuda.synchronize()
+    assert torch.isfinite(got.float()).all()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(k3, k2) and torch.equal(v3, v2)
+    assert bool((k3[unused] == 0xA5).all()) and bool((v3[unused] == 0xA5).all())
+    rows = got[1::distinct]
+    assert torch.equal(rows, rows[:1].expand_as(rows))
+
+
+@pytest.mark.parametrize("c,b", [(8, 8), (4, 8), (2, 8), (8, 10)])
+def test_a_given_split_fixes_the_bits_of_ungrouped_heads_in_every_batch(c, b):
+    hq = hkv = 8
+    B, t, split = 64, 1500, 512
+    fmt, ck, cv, q, kc, vc = _problem(c, c, b, hq, hkv, 3, t)
+    t_cap = 1536
+    k1, v1 = (codes_to_cache(x, fmt, t_cap).view(3, -1) for x in (kc, vc))
+    at = torch.arange(B, device="cuda") % 3
+    lens = torch.tensor([t, 700, 1], dtype=torch.int32, device="cuda")
+    ckd, cvd, qd = dev(ck), dev(cv), dev(q)
+    out = _attend(fmt, ckd, cvd, qd[at].contiguous(), k1[at].flatten(), v1[at].flatten(), t, t_cap, lens[at].contiguous(), split)
+    for n in range(3):
+        one = _attend(fmt, ckd, cvd, qd[n:n + 1], k1[n], v1[n], t, t_cap, lens[n:n + 1], split)
+        assert torch.equal(out[n::3].view(torch.int16), one.expand_as(out[n::3]).contiguous().view(torch.int16))
