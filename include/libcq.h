@@ -162,6 +162,13 @@ CQ_API size_t cq_decode_workspace_bytes(const cq_format *fmt, int32_t batch, int
  *                     need not be initialised and are overwritten
  *   Arithmetic: fp32 lookup tables, scores, softmax and accumulation; the result is rounded to
  *   fp16 once (round to nearest even).
+ *   Equal sizes give equal bits: which kernel a call takes, and how it cuts the context, depend on the
+ *   format and the sizes alone (batch, heads, t, tokens_per_split), not on contents, lengths, pages or the workspace.
+ *   Another batch can give a sequence other bits.  With tokens_per_split = 0 the split follows the batch.  With an
+ *   even number of query heads per KV head so does the kernel, also where tokens_per_split is given: from 256
+ *   workgroups of two query heads on, calls may take the kernel that serves two heads per workgroup
+ *   (cq_probe_decode_plan tells), which sums the same fp32 terms in another order; the results then agree to a unit in
+ *   the last place of fp16.  With an odd number (one among them) a given tokens_per_split fixes the bits.
  * Errors: as cq_encode, plus CQ_ERR_INVALID_ARG when n_q_heads is not a multiple of
  * n_kv_heads or tokens_per_split is not a positive multiple of 64 (or too large for the
  * kernel's on-chip score buffer), and CQ_ERR_WORKSPACE_TOO_SMALL.
