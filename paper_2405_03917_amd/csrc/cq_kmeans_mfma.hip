@@ -50,15 +50,21 @@
 // near ties and every token of a group with equal centroids (which a twin that stays behind could win) get 0 and are
 // looked at again.
 // A wavefront lists its tokens that are not skipped and takes 64 of the list at a time.  Such an iteration costs
-// 1.2 times a plain one when it skips nothing, and 0.15 when it skips everything; of 100 iterations over the
-// calibration tokens (32768, groups of 8) 0.4 of the tokens are looked at, 0.8 in the first ten.  32768 tokens, 512
-// groups, 100 iterations: 31.8 -> 22.2 ms, weighted 40.4 -> 20.1; 6000 tokens 6.5 -> 2.9; 30 iterations 1.0-1.2 times
-// as fast, 20 iterations 0.85-1.07 (hence kStateIterations, kPlainIterations).  Weighted fits of few tokens
-// (below about 12000 of 8 channels) have no room for the sums in their scratch and run plain.
+// 1.2 to 1.3 times a plain one when it skips nothing, and 0.15 when it skips everything; of 100 iterations over the
+// calibration tokens (32768, groups of 8) 0.4 of the tokens are looked at, 0.8 in the first ten.  An iteration that moves
+// no centroid at all is the same as every later one: the group is done, in this launch and in those behind it.  (Without
+// that, groups of more centroids than distinct points, all of whose tokens are looked at again, took longer than plain
+// iterations: 100 iterations of 32768 tokens of 40 points, 512 groups 57.2 ms plain, 68.6, and 6.4 now; of 4000 tokens of
+// integers, 2048 groups of 2, 11.7, 14.3 and 1.4.)
+// All iterations, plain -> now (starts from k-means++): 32768 tokens, 512 groups, 100 iterations 32.9 -> 20.8 ms, weighted
+// 41.3 -> 18.7; 6000 tokens 6.6 -> 2.2; 30 iterations 1.06 to 1.7 times as fast; 20 iterations, were they to skip, 0.88 to 1.13
+// times (hence kStateIterations, kPlainIterations).  What stays slower are unweighted starts far from the tokens (random
+// tokens stretched up to six times and shifted), 8 channels: 30 iterations 0.85 to 0.96, 60 0.89 to 1.03, 100 from 1.00 on.
+// Weighted fits of few tokens (below about 12000 of 8 channels) have no room for the sums in their scratch and run plain.
 // A group's only workgroup runs many iterations in one launch: 100 launches waited for their busiest
 // group each (26.3 against 30.3 ms).
 //
-// What bounds it: the vector ALU (535 instructions per 64 tokens and group: 208 in the scan, 150 in
+// What bounds it: the vector ALU (a plain iteration 545 instructions per 64 tokens and group: 208 in the scan, 150 in
 // the winner's eight, the rest merge, bound, sums and re-dos; the direct search took 2 c + 3 per
 // token and centroid).  The group's centroids sit in registers as matrix operands (32 registers)
 // with the norms in accumulator layout (128; half of them read from LDS where tokens are skipped): two wavefronts per
@@ -157,8 +163,8 @@ constexpr int kSumWords = (W ? 2 * C : C) + 1;
 
 // What the iterations of one fit hand on from each to the next where tokens may be skipped ("Skipping" above).
 // Per group g: sums [256][kSumWords] of the present assignment; travel, kTravelWords floats: how far each centroid
-// has moved since the first iteration, the sum of the longest moves, and the scale of lengths of the first
-// iteration; per token its threshold (fp16) and its cluster.
+// has moved since the first iteration, the sum of the longest moves, the scale of lengths of the first
+// iteration, and whether an iteration has moved no centroid; per token its threshold (fp16) and its cluster.
 constexpr int kTravelWords = kK + 4;
 struct LloydState {
     unsigned long long* sums;
@@ -210,6 +216,13 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
     float travelled = MODE == kNext ? travel[tid] : 0.f, longest = MODE == kNext ? travel[kK] : 0.f;
     const float f0 = MODE == kNext ? travel[kK + 1] : 0.f;
     unsigned long long* all_sums = MODE == kPlain ? nullptr : state.sums + (size_t)g * (kK * SW);
+    auto write_assignment = [&](int from, int to) {
+        for (int i = from + tid; i < to; i += kLloydWaves * 64) assign_all[(size_t)g * n + i] = own_cluster[i];
+    };
+    if (MODE == kNext && travel[kK + 2] != 0.f) {           // an earlier launch moved no centroid
+        if (assign_all) write_assignment(split * tokens_per_split, min((split + 1) * tokens_per_split, n));
+        return;
+    }
     const bool alone = gridDim.x == 1;                  // the group's only workgroup
     for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = MODE == kNext && alone ? all_sums[i] : 0ull;
 
@@ -681,12 +694,11 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
             if (!*flag) return;
             for (int i = tid; i < kK * SW; i += kLloydWaves * 64) sums[i] = __hip_atomic_load(all_sums + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
-        } else if (last_iteration) {                        // (for the next launch)
-            for (int i = tid; i < kK * SW; i += kLloydWaves * 64) all_sums[i] = sums[i];
         }
         const unsigned long long* sj = &sums[tid * SW];
         const long long wk = (long long)sj[SW - 1];
         float step2 = 0.f;
+        bool moved = false;
         if (wk != 0) {                                      // a cluster without tokens keeps its centroid
 #pragma unroll
             for (int i = 0; i < C; ++i) {
@@ -694,15 +706,12 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
                 const float v = W ? kmeans_mean((long long)sj[2 * i], (long long)sj[2 * i + 1], wk) : kmeans_mean(plain_sum(sj[i], sj[SW - 1]), wk);
                 const float d = (v - *at) * (MODE == kNext ? f0 : f1);
                 step2 = __builtin_fmaf(d, d, step2);
+                moved = moved || __float_as_uint(v) != __float_as_uint(*at);
                 *at = v;
-                if (last_iteration) cent[(size_t)tid * C + i] = v;
             }
-        } else if (last_iteration) {
-#pragma unroll
-            for (int i = 0; i < C; ++i) cent[(size_t)tid * C + i] = cs[(tid >> 2) * QS + (tid & 3) * C + i];
         }
         // (rounded up, so that no sum of steps comes out too short)
-        const float step = __builtin_amdgcn_sqrtf(step2) * (1.f + 0x1p-16f);
+        const float step = moved ? fmaxf(__builtin_amdgcn_sqrtf(step2) * (1.f + 0x1p-16f), 0x1p-126f) : 0.f;
         if (step > 0.f) travelled = (travelled + step) * (1.f + 0x1p-22f);
         const unsigned wstep = wave_extreme_u32<true>(__float_as_uint(step));
         if (lane == 0) c2w[wave] = wstep;
@@ -711,12 +720,23 @@ __global__ __launch_bounds__(kLloydWaves * 64, 2) void kmeans_lloyd_kernel(const
 #pragma unroll
         for (int w = 0; w < kLloydWaves; ++w) m = fmaxf(m, __uint_as_float(c2w[w]));
         if (m > 0.f) longest = (longest + m) * (1.f + 0x1p-22f);
-        if (last_iteration) {
+        const bool done = m == 0.f;                         // ("Skipping": every later iteration is this one again)
+        if (last_iteration || done) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) cent[(size_t)tid * C + i] = cs[(tid >> 2) * QS + (tid & 3) * C + i];
             travel[tid] = travelled;
             if (tid == 0) {
                 travel[kK] = longest;
                 travel[kK + 1] = MODE == kNext ? f0 : f1;
+                travel[kK + 2] = done ? 1.f : 0.f;
             }
+            if (alone) {                                    // (for the next launch)
+                for (int i = tid; i < kK * SW; i += kLloydWaves * 64) all_sums[i] = sums[i];
+            }
+        }
+        if (MODE == kNext && done && !last_iteration) {
+            if (assign_all) write_assignment(0, n);
+            break;
         }
     } else if (partials) {
         unsigned long long* dst = partials + ((size_t)g * gridDim.x + split) * (kK * SW);

@@ -295,6 +295,29 @@ def test_iterations_that_skip_tokens_equal_those_that_look_at_all(c, heads, n, w
     assert torch.equal(whole["centroids_f32"].view(torch.int32), cent.view(torch.int32))
 
 
+@pytest.mark.parametrize("c,heads,n,weighted", [(8, 32, 700, False), (2, 8, 4000, False), (4, 2, 9000, True), (8, 1, 5000, False)])
+def test_a_fit_whose_centroids_stand_still_ends_where_it_stands(c, heads, n, weighted):
+    """Once an iteration has moved no centroid, all later ones are the same: a group is done, in its launch and in those
+    behind it (300 iterations are three launches where a group has one workgroup, 290 where it has several).  Equal to
+    chained short fits, byte for byte; one half of the groups still moves."""
+    fmt = cq.CQFormat(c, 8, 128, heads)
+    x = np.tile(_data(30 + c, n, 128), (1, heads)).astype(np.float32)
+    x[:, :64 * heads] = np.round(x[np.arange(n) % 50, :64 * heads])
+    x = torch.from_numpy(x.astype(np.float16)).cuda()
+    w = torch.from_numpy(np.ascontiguousarray(np.tile(_weights(n, n, fmt.groups // heads), (1, heads)))).cuda() if weighted else None
+    init = x[torch.arange(256) % n].view(256, fmt.groups, c).transpose(0, 1).float().contiguous()
+    whole = cq.cq_kmeans_fit(x, fmt, 300, init_centroids=init, weights=w, want_assignment=True)
+    cent = init
+    for _ in range(15):
+        before = cent
+        part = cq.cq_kmeans_fit(x, fmt, 20, init_centroids=cent, weights=w, want_assignment=True)
+        cent = part["centroids_f32"]
+    torch.cuda.synchronize()
+    assert torch.equal(before[:fmt.groups // 2], cent[:fmt.groups // 2])
+    assert torch.equal(whole["assignment"], part["assignment"])
+    assert torch.equal(whole["centroids_f32"].view(torch.int32), cent.view(torch.int32))
+
+
 def _kernel_nodes(graph):
     """Nodes of a captured graph (torch.cuda.CUDAGraph(keep_graph=True))."""
     runtime = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
