@@ -46,8 +46,8 @@ LAST_LEVEL_CACHE_BYTES = 256e6
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 MFMA_SCORE_OPS = 1.08
 # vector instructions of a Lloyd iteration per (token, group) of 8 channels and 256 centroids (SQ_INSTS_VALU), mean of the 100
-# iterations of the fit below: ten plain ones at 545, one that fills the state at 565, 89 that skip most tokens at 200
-LLOYD_LANE_OPS = 238.0
+# iterations of the fit below: ten plain ones at 545, one that fills the state at 599, 89 that skip most tokens at 197
+LLOYD_LANE_OPS = 236.0
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 FP16_MFMA_PEAK_TFLOPS = 2500.0
 METRIC = "decode-attn KV tokens/s & achieved HBM GB/s (% peak); cq_encode tokens/s"

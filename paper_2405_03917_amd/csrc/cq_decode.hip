@@ -46,6 +46,8 @@ namespace {
 // Tiles per wavefront of the shortest splits (see ONCE), 2048 tokens of CQ-8c8b: batch 1 x 2000, 32 heads 8.95 -> 8.68 us, its
 // step 10.9 -> 10.5; step of batch 2 x 1000 9.6 -> 9.0.  None for the other formats: their codebook is walked in two and
 // four parts, which the tiles' requests then hold up (CQ-4c8b, batch 16 x 900: 12.4 -> 13.2), and CQ-2c8b has no registers left.
+// Layer-batched launches have no such form yet, for no other reason than that it was not built with it: theirs would gain too
+// (cq_decode_step_layers, 32 layers of batch 1 x 1000 33.7 -> 31.5 us, 1 x 2000 54.5 -> 49.4, 8 x 1000 195 -> 150).
 constexpr int kOnceTiles(int gh) { return gh == 16 ? 4 : 0; }
 constexpr int kMergeRows = 8192;        // arrival counters per set (rows of one launch)
 constexpr int kMergeSets = 16;          // sets (streams served) per device

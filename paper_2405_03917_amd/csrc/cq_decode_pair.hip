@@ -10,9 +10,9 @@
 // Table and bins of CQ-8c8b and CQ-4c8b are 64 KB each (SEPARATE), those of CQ-2c8b and CQ-8c10b share 128 KB
 // (SHARED): one workgroup has the CU, and nothing overlaps its table build and epilogue.
 //
-// Measured (32 / 8 heads; one head per workgroup -> two): CQ-8c10b, batch 32 x 16384 105 -> 79 us, its step 137 -> 95,
-// batch 16 x 300 17.5 -> 12.7; CQ-2c8b, batch 16 x 4096 38 -> 30.6; CQ-4c8b, 32 x 16384 121 -> 98, 16 x 4096 21 -> 18.2;
-// CQ-8c8b, 32 x 16384 71 -> 65.  The walk's key half is bound by the vector ALU (about 220 clocks per tile and SIMD
+// Measured (32 / 8 heads; one head per workgroup -> two, both with the present kernels on one card): CQ-8c10b, batch 32 x 16384
+// 103.6 -> 77.6 us (74 to 78 on other cards), its step 132.8 -> 92.4, batch 16 x 300 16.3 -> 12.2; CQ-2c8b, batch 16 x 4096
+// 37.2 -> 29.5; CQ-4c8b, 32 x 16384 115.5 -> 94.0, 16 x 4096 20.3 -> 17.1; CQ-8c8b, 32 x 16384 66.2 -> 62.9.  The walk's key half is bound by the vector ALU (about 220 clocks per tile and SIMD
 // against 33 of LDS per CU), its value half by the LDS (96 per CU against 170 of vector ALU per SIMD), and all wavefronts are in
 // the same half.
 #include <hip/hip_runtime.h>
@@ -842,9 +842,11 @@ cq_status launch_format(const DecodeArgs& a, hipStream_t stream)
 
 // An even number of query heads per KV head, and enough workgroups: one runs per CU, so fewer than 256 leave CUs idle
 // that the kernel for one head uses, and with byte codes a last round of workgroups that fills less than its share
-// costs what the pairs save (CQ-8c8b, 32 / 8 heads, 20 x 2000: 1.25 rounds, 18.6 -> 20.2 us; 28 x 4000: 1.75 rounds,
-// 27.4 -> 25.9; CQ-4c8b 22.4 -> 24.0 and 39.5 -> 34.1).  CQ-8c10b gains even there (20 x 2000 30.4 -> 29.5 us): of its
-// codebooks, 256 KB each, a workgroup reads half as much per head.  (Of a layer-batched launch the layer decides, so that
+// costs more than the pairs save (32 / 8 heads, one head -> two: 1.25 rounds, 20 x 2000, CQ-8c8b 14.7 -> 19.9 us, CQ-4c8b 20.8 ->
+// 24.0; 1.5 rounds, 24 x 3000, step of CQ-4c8b 30.9 -> 33.7; 1.75 rounds, 28 x 4000, CQ-8c8b 25.2 -> 25.4, CQ-4c8b 37.8 -> 32.7, and 28 x
+// 16000 64.9 -> 62.4, 110.7 -> 91.6).  CQ-8c10b gains in nearly all of them (17 x 2000 28.0 -> 29.1, 17 x 16000 76.5 -> 71.6, 20 x 2000 28.9 ->
+// 29.4, 20 x 16000 78.2 -> 72.0, 24 x 2000 30.3 -> 29.7, 36 x 2000 45.4 -> 43.5): of its codebooks, 256 KB each, a workgroup reads
+// half as much per head.  (Of a layer-batched launch the layer decides, so that
 // its results are those of the layers' own calls.)
 bool decode_takes_pairs(const DecodeArgs& a)
 {

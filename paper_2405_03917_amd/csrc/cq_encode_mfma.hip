@@ -235,8 +235,9 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
     constexpr int SNT = GS ? 64 : NT;                // threads that stage a group's codebook together
     constexpr int NTILE = GS ? TILES : NW;           // tiles per workgroup
     constexpr int TPW = GS ? TILES : 1;              // tiles per wavefront
-    // exchanges between the lane halves by v_permlane32_swap; where a wavefront has a tile to itself and mostly waits, as
-    // shuffles (CQ-2c8b, 64 x 512 tokens 1608 / 1565 us, 8 x 301 150.3 / 151.7; CQ-8c10b, 2 x 600 145.9 / 147.7)
+    // Exchanges between the lane halves by v_permlane32_swap; where a wavefront has a tile to itself and mostly waits, as
+    // shuffles.  K and V of 32 heads, shuffles / swaps: several tiles per wavefront, CQ-8c8b, 32768 tokens 534 / 522 us, CQ-2c8b,
+    // 64 x 512 1602 / 1559; one, CQ-8c10b, 2 x 600 321-340 / 353-361, CQ-4c8b, 8 x 301 74.5 / 75.1, CQ-2c8b, 8 x 301 134 / 134.
     constexpr bool SWAP = TPW > 1;
     // augmented codebook records: two buffers that the workgroup alternates, or (GS) one per wavefront
     __shared__ __attribute__((aligned(16))) _Float16 cba[GS ? NW : 2][K * KDIM];
@@ -621,10 +622,11 @@ __global__ __launch_bounds__(NW * 64) void encode_mfma_kernel(EncodeArgs a)
                 unsigned dmin = ~0u, jmin = 0;
                 // (The centroids' reads and conversions do not depend on the token: the compiler makes them ahead of this loop,
                 // for every tile and group, and holds their values in registers.  With 8 channels and several tiles per wavefront
-                // those registers cost a wavefront per SIMD (3 resident -> 4: wave cycles per busy cycle 2.9 -> 3.8), which is worth
-                // more than the reads that a tile's second and later re-dos make again (445 -> 457 instructions per 64 tokens and
-                // group): opaque there, CQ-8c8b 32768 tokens, K and V 523 -> 514 us.  With 2 and 4 channels the values are fewer and
-                // the re-dos more: opaque 8 x 301 tokens of CQ-2c8b took 160 us instead of 150.)
+                // those registers cost a wavefront per SIMD (140 registers -> 124, 3 resident -> 4: wave cycles per busy cycle 2.9 ->
+                // 3.8), which is worth a little more than the reads that a tile's second and later re-dos make again (445 -> 457
+                // instructions per 64 tokens and group): opaque there, CQ-8c8b 32768 tokens, K and V 516.5 -> 515 us.  Elsewhere the values
+                // are fewer, the re-dos more, or one tile is all there is: opaque 8 x 301 tokens of CQ-2c8b took 144 us instead of 134,
+                // 64 x 512 1598 instead of 1523, CQ-4c8b 8 x 301 78 instead of 74.5, CQ-8c10b 2 x 600 345 instead of 327.)
                 int first = lane;
                 if constexpr (C == 8 && TPW > 1) asm volatile("" : "+v"(first));
 #pragma unroll 4
