@@ -196,28 +196,9 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
     // heads hq and hq + 1, whose rows are neighbours
     float* part = partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
     const size_t part_head = (size_t)a.n_split * (D + kPartialHeader);
-    // The last split of a (sequence, query head) to finish merges them all (when the launch
-    // brought counters; else a merge kernel follows).  Partials are written with device-scope
-    // stores (write-through) and the merging workgroup reads them with device-scope loads, so
-    // no cache has to be written back or invalidated as a whole (a device-scope release fence
-    // per workgroup, which writes the whole L2 back, cost 50 us on a 90 us launch).  Order:
-    // every wavefront waits for its stores, then all meet at the barrier, then one thread
-    // counts the workgroup in; the workgroup that counts the last split takes the counter back
-    // to zero for the next call and merges.
+    // (when the launch brought counters; else a merge kernel follows)
     auto count_and_merge = [&] {
-        if (!a.merge_counters) return;
-        wait_for_stores();
-        __syncthreads();
-        unsigned* flag = sums;
-        if (tid == 0) {
-            const size_t row = (size_t)(part - a.partials) / ((size_t)(D + kPartialHeader) * a.n_split);
-            const unsigned arrived = __hip_atomic_fetch_add(a.merge_counters + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const bool last = arrived == (unsigned)a.n_split - 1u;
-            if (last) __hip_atomic_store(a.merge_counters + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *flag = last;
-        }
-        __syncthreads();
-        if (!*flag) return;
+        if (!a.merge_counters || !counted_last<D>(a, part, sums, tid)) return;
         const int h = tid / D;              // (a thread per channel and head)
         if (h < H)
             merge_splits<true>(part + h * part_head - (size_t)split * (D + kPartialHeader), a.n_split, D,

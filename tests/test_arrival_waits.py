@@ -81,7 +81,7 @@ def unwaited(code):
     return len(counts), sorted(faults)
 
 
-def test_the_checker_follows_both_sides_of_a_branch():
+def test_the_walk_follows_both_sides_of_a_branch():
     store, count = "global_store_dword v0, v1, s[0:1] sc1", "global_atomic_add v0, v1, v2, s[2:3] sc0"
 
     def run(*text):
