@@ -240,6 +240,8 @@ def kernel_name(cfg, step=False):
     import paper_2405_03917_amd as cq
     fmt = cq.CQFormat(cfg.c, cfg.b, cfg.head_dim, cfg.n_kv_heads)
     heads, tiles = cq.cq_probe_decode_plan(fmt, cfg.batch, cfg.n_q_heads, cfg.context)
+    if heads == 4:
+        return f"decode_quad_kernel<{cfg.head_dim // cfg.c}, {cfg.c}, false, {'true' if step else 'false'}, false>"
     name = {1: "decode_split_kernel", 2: "decode_pair_kernel"}[heads]
     return f"{name}<{cfg.head_dim // cfg.c}, {cfg.c}, {cfg.b}, {tiles}, {'true' if step else 'false'}, false>"
 
@@ -448,7 +450,7 @@ def extra_measurements(cq, synth, torch):
         "ms": ms_sh, "tokens_per_split": split_g, "kv_tokens_per_s": Bg * Tg / (ms_sh * 1e-3),
         "ms_one_query_head_per_workgroup": ms_ph, "speedup_from_sharing": ms_ph / ms_sh,
         "buffer_sets": 3, "cache_resident": False,
-        "roofline": hbm_roofline("decode_rope_gqa_kernel<16, 8, 512, false>", "decode_rope_gqa_kernel<16, 8, 512, false>", code_bytes_g, ms_sh, 9,
+        "roofline": hbm_roofline("decode_quad_kernel<16, 8, true, false, false>", "decode_quad_kernel<16, 8, true, false, false>", code_bytes_g, ms_sh, 9,
                                  note="bound by vector and matrix instruction issue (per channel pair 4 vector + 2 matrix "
                                       "instructions for four heads), not by HBM")}
     del keep, shared_calls, per_head_calls, qg

@@ -166,9 +166,9 @@ CQ_API size_t cq_decode_workspace_bytes(const cq_format *fmt, int32_t batch, int
  *   format and the sizes alone (batch, heads, t, tokens_per_split), not on contents, lengths, pages or the workspace.
  *   Another batch can give a sequence other bits.  With tokens_per_split = 0 the split follows the batch.  With an
  *   even number of query heads per KV head so does the kernel, also where tokens_per_split is given: from 256
- *   workgroups of two query heads on, calls may take the kernel that serves two heads per workgroup
- *   (cq_probe_decode_plan tells), which sums the same fp32 terms in another order; the results then agree to a unit in
- *   the last place of fp16.  With an odd number (one among them) a given tokens_per_split fixes the bits.
+ *   workgroups of two query heads on, calls may take the kernel that serves two heads per workgroup, and with a multiple
+ *   of four, from 140 workgroups of four on, the one that serves four (cq_probe_decode_plan tells); these form the same
+ *   sums in fp32 in another order, and the results agree to a unit in the last place of fp16.  With an odd number (one among them) a given tokens_per_split fixes the bits.
  * Errors: as cq_encode, plus CQ_ERR_INVALID_ARG when n_q_heads is not a multiple of
  * n_kv_heads or tokens_per_split is not a positive multiple of 64 (or too large for the
  * kernel's on-chip score buffer), and CQ_ERR_WORKSPACE_TOO_SMALL.
@@ -567,8 +567,8 @@ CQ_API cq_status cq_kmeans_fit(const void *x, int64_t x_row_stride, const float 
  *                       the rounding model that the encode kernel's error bound assumes to it.
  * cq_probe_decode_plan  which kernel a cq_decode_attention / cq_decode_step call of these sizes (layers != 0: a
  *                       cq_decode_step_layers call) runs: query heads per workgroup (1:
- *                       decode_split_kernel, 2: decode_pair_kernel) and tiles per wavefront and chunk, the
- *                       kernel's template argument.  Host only.
+ *                       decode_split_kernel, 2: decode_pair_kernel, 4: decode_quad_kernel) and tiles per wavefront and
+ *                       chunk, a template argument of the first two (the last goes tile by tile: 1).  Host only.
  * Errors: CQ_ERR_INVALID_ARG for null / misaligned pointers, a size that is zero or not a
  * multiple of 16, or a kdim other than 8 and 16; of cq_probe_decode_plan as of cq_decode_attention; CQ_ERR_HIP if
  * the launch fails.

@@ -965,6 +965,14 @@ cq_status launch_layer_table_write(const LayerChunk& chunk, int count, LayerPtrs
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
 }
 
+cq_status launch_decode_merge(const DecodeArgs& a, hipStream_t stream)
+{
+    const int rows = a.batch * a.n_q_heads;
+    hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(rows * (a.layers ? a.n_layers : 1))), dim3(128), 0, stream,
+                       a.partials, a.out, a.n_split, a.f.head_dim, a.layers, rows, a.n_q_heads, a.out_batch_stride);
+    return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
+}
+
 cq_status launch_decode_merge(const float* partials, uint16_t* out, int rows, int n_q_heads, int64_t out_batch_stride,
                               int n_split, int head_dim, hipStream_t stream)
 {
@@ -982,26 +990,24 @@ int decode_max_tiles_per_split(const Derived& f)
     return 1 << 20;
 }
 
+unsigned* decode_merge_counters(hipStream_t stream, int rows) { return g_merge_counters.for_stream(stream, rows); }
+
 DecodePlan decode_plan(const DecodeArgs& a)
 {
+    if (decode_takes_quads(a)) return DecodePlan{4, 1};
     return decode_takes_pairs(a) ? DecodePlan{2, decode_pair_chunk_tiles(a)} : DecodePlan{1, chunk_tiles(a)};
 }
 
 cq_status launch_decode(const DecodeArgs& a_in, hipStream_t stream)
 {
+    if (decode_takes_quads(a_in)) return launch_decode_quad(a_in, nullptr, nullptr, stream);
     DecodeArgs a = a_in;
-    const int rows = a.batch * a.n_q_heads;
-    const int all_rows = rows * (a.layers ? a.n_layers : 1);
-    a.merge_counters = a.n_split > 1 ? g_merge_counters.for_stream(stream, all_rows) : nullptr;
+    a.merge_counters = a.n_split > 1 ? decode_merge_counters(stream, a.batch * a.n_q_heads * (a.layers ? a.n_layers : 1)) : nullptr;
     // (a layer-batched launch is always a fused step: its table holds the new rows)
     const cq_status st = decode_takes_pairs(a) ? launch_decode_pair(a, stream)
                          : a.layers ? launch_format<true, true>(a, stream) : a.xk_new ? launch_format<true, false>(a, stream) : launch_format<false, false>(a, stream);
     if (st != CQ_OK || a.n_split == 1 || a.merge_counters) return st;
-    const int threads = a.f.head_dim <= 64 ? 64 : (a.f.head_dim <= 128 ? 128 : 256);
-    hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)all_rows), dim3(threads), 0, stream,
-                       a.partials, a.out, a.n_split, a.f.head_dim, a.layers, rows, a.n_q_heads, a.out_batch_stride);
-    if (hipGetLastError() != hipSuccess) return CQ_ERR_HIP;
-    return CQ_OK;
+    return launch_decode_merge(a, stream);
 }
 
 }  // namespace cq

@@ -23,12 +23,11 @@
 // in fp64).
 #include <type_traits>
 
-#include "cq_lds_gather.hpp"
+#include "cq_key_gather.hpp"
 
 namespace cq {
 namespace {
 
-constexpr int kPairs = 64;                        // head_dim / 2
 constexpr unsigned kTabBytes = 65536;             // centroids (phase K), then bins (phase V)
 constexpr int kRopeThreads = 512;
 struct CosSin { float c, s; };
@@ -56,28 +55,6 @@ __global__ void rope_tables_kernel(double base, int n_tiles, float2* tile_tab, f
     *dst = make_float2((float)cos(ang), (float)sin(ang));
 }
 
-template <int C>
-struct CenVec {
-    unsigned w[C / 2];
-};
-template <int C>
-__device__ __forceinline__ CenVec<C> lds_centroid(unsigned byte_addr)
-{
-    typedef __attribute__((address_space(3))) unsigned lds_u;
-    CenVec<C> v;
-    if constexpr (C == 8) {
-        typedef unsigned u4 __attribute__((ext_vector_type(4)));
-        const u4 a = *(__attribute__((address_space(3))) u4*)(byte_addr);
-        v.w[0] = a.x; v.w[1] = a.y; v.w[2] = a.z; v.w[3] = a.w;
-    } else if constexpr (C == 4) {
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        const u2 a = *(__attribute__((address_space(3))) u2*)(byte_addr);
-        v.w[0] = a.x; v.w[1] = a.y;
-    } else {
-        v.w[0] = *(lds_u*)(byte_addr);
-    }
-    return v;
-}
 template <int C>
 __device__ __forceinline__ CenVec<C> global_centroid(const uint16_t* p)
 {
@@ -108,39 +85,6 @@ __device__ __forceinline__ float mix_fma(bool HI, unsigned w, float s, float c)
     else if (MINUS) asm volatile("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "s"(s), "v"(c));
     else asm volatile("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "s"(s), "v"(c));
     return d;
-}
-
-// A token's codes in group order.  The cache stores the code of group (s + u) mod Gh in slot s
-// of token u (the position-independent kernel wants neighbouring lanes on different groups);
-// here every lane should work on the same channel pair at the same time (the rotated query is
-// then a scalar, and every table address a compile-time offset), so the token's Gh bytes are
-// rotated by u positions once per tile: bytes first (v_alignbyte), then whole dwords (selects).
-struct Unrotate {
-    unsigned bytes;             // (Gh - u) mod 4
-    unsigned dwords;            // ((Gh - u) mod Gh) / 4
-};
-template <int GH, int B>
-__device__ __forceinline__ void group_order(const Tile<GH, B>& w, const Unrotate& r, unsigned (&d)[GH / 4])
-{
-    constexpr int N = GH / 4;
-    unsigned x[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const u32x4 q = w.lo[i >> 2];
-        x[i] = (i & 3) == 0 ? q.x : (i & 3) == 1 ? q.y : (i & 3) == 2 ? q.z : q.w;
-    }
-    // group g sits in slot (g - u) mod Gh = (g + r) mod Gh with r = (Gh - u) mod Gh
-#pragma unroll
-    for (int i = 0; i < N; ++i) d[i] = __builtin_amdgcn_alignbyte(x[(i + 1) % N], x[i], r.bytes);
-#pragma unroll
-    for (int bit = 1; bit < N; bit <<= 1) {
-        const bool on = (r.dwords & bit) != 0;
-        unsigned y[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) y[i] = on ? d[(i + bit) % N] : d[i];
-#pragma unroll
-        for (int i = 0; i < N; ++i) d[i] = y[i];
-    }
 }
 
 // STEP = true is the fused decode step, as in cq_decode.hip: the workgroup whose split holds the
@@ -583,290 +527,6 @@ __global__ __launch_bounds__(NT) void decode_rope_kernel(DecodeArgs a, const flo
     }
 }
 
-// acc += (the query values of pair i, one head per row) x (the rotated key of pair i, one token per
-// column): the A operand is register i / 16 of the per-tile query registers, broadcast from the
-// block of four lanes i % 16.
-typedef float mfma_f4 __attribute__((ext_vector_type(4)));
-template <int ABID>
-__device__ __forceinline__ mfma_f4 mfma_bcast(float a, float b, mfma_f4 c)
-{
-    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, ABID, 0);
-}
-__device__ __forceinline__ mfma_f4 mfma_pair(const float (&q)[4], float x, mfma_f4 c, int i)
-{
-    const float a = q[i >> 4];
-    switch (i & 15) {
-        case 0: return mfma_bcast<0>(a, x, c);
-        case 1: return mfma_bcast<1>(a, x, c);
-        case 2: return mfma_bcast<2>(a, x, c);
-        case 3: return mfma_bcast<3>(a, x, c);
-        case 4: return mfma_bcast<4>(a, x, c);
-        case 5: return mfma_bcast<5>(a, x, c);
-        case 6: return mfma_bcast<6>(a, x, c);
-        case 7: return mfma_bcast<7>(a, x, c);
-        case 8: return mfma_bcast<8>(a, x, c);
-        case 9: return mfma_bcast<9>(a, x, c);
-        case 10: return mfma_bcast<10>(a, x, c);
-        case 11: return mfma_bcast<11>(a, x, c);
-        case 12: return mfma_bcast<12>(a, x, c);
-        case 13: return mfma_bcast<13>(a, x, c);
-        case 14: return mfma_bcast<14>(a, x, c);
-        default: return mfma_bcast<15>(a, x, c);
-    }
-}
-
-// The mixed-precision multiply-adds with a vector operand in place of the scalar one.
-__device__ __forceinline__ float mixv_mul(bool HI, unsigned w, float s)
-{
-    float d;
-    if (HI) asm volatile("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(s));
-    else asm volatile("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(s));
-    return d;
-}
-// (Its result feeds a matrix instruction.  The compiler does not look inside an asm statement, so
-// it cannot know that a vector instruction wrote the register and leaves out the two wait states
-// that a matrix instruction reading it needs.  The caller keeps the two apart instead: all
-// sixteen results of a batch pass through one more (empty) statement before the first matrix
-// instruction may read any of them, so that at least eight instructions lie between a result
-// and its use.)
-template <bool MINUS>
-__device__ __forceinline__ float mixv_fma(bool HI, unsigned w, float s, float c)
-{
-    float d;
-    if (HI && MINUS) asm volatile("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(s), "v"(c));
-    else if (HI) asm volatile("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(s), "v"(c));
-    else if (MINUS) asm volatile("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(s), "v"(c));
-    else asm volatile("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(s), "v"(c));
-    return d;
-}
-
-// Phase V of the grouped-query kernel for formats whose value codebook fits LDS next to the scores
-// (16 or 32 groups per head), on the matrix cores: the codebook takes the key centroids' place,
-// and for every 64-token tile
-//     O^T[channel][column] += V^T[channel][token] P[token][column]     (v_mfma_f32_16x16x32_f16)
-// with the values gathered and transposed by one LDS instruction and the probabilities of the four
-// heads as three fp16 numbers each (33 bits), one to a column: columns 0..3 the high parts of heads
-// 0..3, 4..7 the middle, 8..11 the low ones.  One pass serves all four heads; it replaces a scan
-// for the maximum, one for the sum, a clear of the bins, a pass over the value tiles for every two
-// heads and a bins x centroids epilogue per head.  A tile costs a wavefront 32 gathers, 16 matrix
-// products and about 150 vector instructions.  Measured: the fused step of CQ-8c8b, 32 / 8 heads,
-// batch 32 x 16384: 196 -> 164 us (key phase about 95 of them).
-// LDS: the codebook, the kernel's scratch (probabilities of wavefronts 0..4), the scores, the new
-// token's keys, the probabilities of wavefronts 5..7.
-constexpr unsigned kProbBytes = 12 * 32 * 2;        // one wavefront's half tile: 12 columns x 32 tokens
-constexpr int kProbInScratch = (int)(kScrBytes / kProbBytes);
-static_assert(kProbInScratch == 5, "places of the probabilities");
-constexpr unsigned kGqaKeyBytes(int gh) { return (unsigned)(kKeyFloats(gh) * 4 + 15) & ~15u; }
-constexpr unsigned kGqaOutBytes = kRopeThreads / 64 * 4 * 128 * 4;     // every wavefront's output rows, where the scores were
-template <int GH, int C, int NT>
-__device__ __forceinline__ void gqa_values(const DecodeArgs& a, float* smem, const float (&top)[4], const TileWalk<GH, 8>& vwalk, int n,
-                                           int hkv, int hq0, int heads, int split, int split_tokens, int tile0, int my_tiles, bool has_new,
-                                           bool writer, bool meets_new, int tile_new, int u_new)
-{
-    constexpr int QH = 4, NW = NT / 64, D = GH * C, K = 256, PL = GH / 16;
-    constexpr unsigned SC_BASE = kTabBytes + kScrBytes;
-    typedef __attribute__((address_space(3))) u32x4 lds_q;
-    typedef __attribute__((address_space(3))) _Float16 lds_h;
-    typedef __attribute__((address_space(3))) float4_t lds_f4;
-    float* scr = smem + kTabBytes / 4;
-    const float* sc = smem + SC_BASE / 4;
-    const unsigned keys_at = SC_BASE + (unsigned)(QH * split_tokens) * 4;
-    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem + keys_at / 4);
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 15, blk = lane >> 4;
-
-    // ---- the value codebook on its way to LDS; the heads' maxima over the split
-    u32x4 book[8];
-    {
-        const u32x4* src = reinterpret_cast<const u32x4*>(a.v_centroids + (size_t)hkv * GH * K * C);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) book[i] = src[i * NT + tid];
-    }
-    // this lane's tokens of a tile: 32 t + 8 blk + 4 r + col / 4 for t, r = 0, 1; its channels: 4 (col % 4) ..
-    // of 16 (C = 8: half of group (col % 4) / 2, then every second group; C = 4: group col % 4, then every fourth)
-    const int g0 = C == 8 ? (col & 3) >> 1 : (col & 3);
-    const int u0 = 8 * blk + (col >> 2);
-    const CodePick<GH, C == 8 ? 2 : 4> pick0(g0, u0), pick1(g0, u0 + 4);
-    const unsigned vbase = C == 8 ? (unsigned)g0 * 4096 + (unsigned)(col & 1) * 8 : (unsigned)g0 * 2048;
-    u32x4 rec[2][2][PL];
-    auto request = [&](int k) {
-        const uint8_t* p = vwalk.at(k < my_tiles ? k : my_tiles - 1);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-#pragma unroll
-                for (int pl = 0; pl < PL; ++pl)
-                    rec[t][r][pl] = *reinterpret_cast<const u32x4*>(p + pl * 1024 + (32 * t + 4 * r + u0) * 16);
-    };
-    if (my_tiles > 0) request(0);
-#pragma unroll
-    for (int h = 0; h < QH; ++h) {
-        const float w = wave_max(top[h]);
-        if (lane == 0) scr[h * NW + wave] = w;
-    }
-    lds_barrier();                                  // all key centroid reads are done, scores and maxima written
-#pragma unroll
-    for (int i = 0; i < 8; ++i) *(lds_q*)((unsigned)(i * NT + tid) * 16) = book[i];
-    float m[QH], l[QH];
-#pragma unroll
-    for (int h = 0; h < QH; ++h) {
-        m[h] = scr[h * NW];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) m[h] = fmaxf(m[h], scr[h * NW + w]);
-        l[h] = 0.f;
-    }
-    lds_barrier();                                  // the codebook is in place, the maxima are read
-    NewTokenCodes<GH, 8> new_codes;
-    if (has_new) {
-        // the new value row against the codebook: ascending index per thread, 64-bit (distance, index) minimum
-        constexpr int TPG = NT / GH;
-        const int g = tid / TPG;
-        float xv[C];
-        load_row_slice<C>(a.xv_new + (size_t)n * a.x_new_stride + (size_t)hkv * GH * C + g * C, xv);
-        Nearest near;
-        for (int j = tid % TPG; j < K; j += TPG) {
-            const CenVec<C> cen = lds_centroid<C>((unsigned)(g * K + j) * (C * 2));
-            near.offer(centroid_distance<C>(xv, cen.w), j);
-        }
-        lds_min_u64(&keys[GH + g], near.key());
-        lds_barrier();
-        if (writer)
-            store_new_codes<GH, 8>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * Fmt<GH, 8>::TILE_BYTES, keys + GH,
-                                   u_new, tid);
-        if (meets_new) new_codes.build(keys + GH, u_new, lane);
-    }
-
-    // ---- the walk: one pass for the four heads
-    const unsigned probs = wave < kProbInScratch ? kTabBytes + (unsigned)wave * kProbBytes
-                                                 : keys_at + kGqaKeyBytes(GH) + (unsigned)(wave - kProbInScratch) * kProbBytes;
-    const unsigned prob_in = probs + (unsigned)(lane & 31) * 2;                                 // token of the half tile
-    const unsigned prob_out = probs + (unsigned)(col < 12 ? col : 0) * 64 + (unsigned)blk * 16;    // column, eight tokens
-    float4_t o[8];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
-    // (the columns of heads beyond NH hold anything, and are not read out)
-    auto walk = [&](auto n_heads) {
-        constexpr int NH = decltype(n_heads)::value;
-#pragma unroll 1
-        for (int k = 0; k < my_tiles; ++k) {
-            const int lt = wave + k * NW;
-            if (meets_new && tile0 + lt == tile_new) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int r = 0; r < 2; ++r) {
-                        const bool mine = 32 * t + 4 * r + u0 == u_new;
-#pragma unroll
-                        for (int pl = 0; pl < PL; ++pl)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) rec[t][r][pl][i] = mine ? new_codes.lo[4 * pl + i] : rec[t][r][pl][i];
-                    }
-            }
-            unsigned z[2][2][2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                pick0(rec[t][0], 0, z[t][0]);
-                pick1(rec[t][1], 0, z[t][1]);
-            }
-            request(k + 1);
-            half8_t av[2][8];
-            auto gather = [&](int t) {
-                unsigned at[2][8];
-#pragma unroll
-                for (int r = 0; r < 2; ++r)
-#pragma unroll
-                    for (int cb = 0; cb < 8; ++cb) at[r][cb] = entry<C>(z[t][r][cb >> 2], cb & 3, vbase);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int cb = 0; cb < 8; ++cb) {
-                    const half4_t v0 = lds_transposed(at[0][cb] + (unsigned)cb * 8192), v1 = lds_transposed(at[1][cb] + (unsigned)cb * 8192);
-                    av[t][cb] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            float s[NH];
-#pragma unroll
-            for (int h = 0; h < NH; ++h) s[h] = sc[h * split_tokens + lt * kTileTokens + lane];
-            gather(0);
-            // lane = token: p 2^12 of each head as the sum of three fp16 numbers
-            _Float16 part[3][NH];
-#pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const float p = __builtin_amdgcn_exp2f(s[h] - m[h]) * 4096.f;      // (12 in the exponent would be lost in a large m)
-                l[h] += p;
-                part[0][h] = (_Float16)p;
-                const float r1 = p - (float)part[0][h];
-                part[1][h] = (_Float16)r1;
-                part[2][h] = (_Float16)(r1 - (float)part[1][h]);
-            }
-            half8_t pb[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                // (a wavefront's LDS operations keep their order: the half tiles share the room)
-                if ((lane >> 5) == t) {
-#pragma unroll
-                    for (int e = 0; e < 3; ++e)
-#pragma unroll
-                        for (int h = 0; h < NH; ++h) *(lds_h*)(prob_in + (unsigned)(e * QH + h) * 64) = part[e][h];
-                }
-                // (the lanes read what other lanes wrote: without these statements the compiler takes a lane's
-                // second read for a repetition of its first)
-                asm volatile("" ::: "memory");
-                const half8_t v = *(__attribute__((address_space(3))) half8_t*)(prob_out);
-                pb[t] = col < 12 ? v : half8_t(0.f16);
-                asm volatile("" ::: "memory");
-            }
-            gather(1);
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int cb = 0; cb < 8; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], pb[t], o[cb], 0, 0, 0);
-        }
-    };
-    if (heads <= 2) walk(std::integral_constant<int, 2>{});
-    else walk(std::integral_constant<int, 4>{});
-
-    // ---- the parts of a head are columns h, h + 4, h + 8; then the wavefronts, all relative to the same maximum
-    lds_barrier();                                  // scores and probabilities are read
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-        float4_t v = o[cb];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));    // row_ror:8
-            v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x124, 0xf, 0xf, false));    // row_ror:4
-        }
-        if (col < QH) *(lds_f4*)(SC_BASE + (unsigned)((wave * QH + col) * D + 16 * cb + 4 * blk) * 4) = v;
-    }
-#pragma unroll
-    for (int h = 0; h < QH; ++h) {
-        const float w = wave_sum(l[h]);
-        if (lane == 0) scr[h * NW + wave] = w;
-    }
-    lds_barrier();
-    static_assert(NT == QH * D, "one output per thread");
-    const int h = tid / D, ch = tid % D;
-    if (h >= heads) return;
-    float sum = 0.f, ll = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        sum += smem[SC_BASE / 4 + (w * QH + h) * D + ch];
-        ll += scr[h * NW + w];
-    }
-    if (a.n_split == 1) {
-        a.out[(size_t)n * a.out_batch_stride + (size_t)(hq0 + h) * D + ch] = __builtin_bit_cast(uint16_t, (_Float16)(sum / ll));
-    } else {
-        float* dst = a.partials + ((size_t)(n * a.n_q_heads + hq0 + h) * a.n_split + split) * (D + kPartialHeader);
-        if (ch == 0) {
-            dst[0] = h == 0 ? m[0] : (h == 1 ? m[1] : (h == 2 ? m[2] : m[3]));
-            dst[1] = ll * 0x1p-12f;
-        }
-        dst[kPartialHeader + ch] = sum * 0x1p-12f;
-    }
-}
-
 // Grouped queries: the (up to) four query heads of a KV head that one workgroup serves share
 // every key rotation.  The roles of the two halves of the angle are swapped against the kernel
 // above: the KEY is rotated by the lane's part (cos / sin(u th_i): 128 registers per lane, from
@@ -881,9 +541,9 @@ __device__ __forceinline__ void gqa_values(const DecodeArgs& a, float* smem, con
 // block of four lanes that holds pair i to all 16 blocks, the B operand (1 x 4 tokens per
 // block) the rotated key itself; lane = token also in the result, heads in its four registers.
 // Per pair: 4 vector instructions and 2 matrix instructions for four heads, against 6 vector
-// instructions per head.  Phase V takes the split's scores of all four heads from LDS in one pass
-// (gqa_values); CQ-2c8b, whose 4-byte centroids the transposing read cannot gather, bins one head
-// after the other (the value tiles of the later heads come from L2).
+// instructions per head.  Phase V bins one head after the other (the value tiles of the later heads
+// come from L2).  CQ-2c8b only: the formats whose value centroids the transposing LDS read can gather
+// (CQ-8c8b, CQ-4c8b) have the kernel of cq_decode_quad.hip, with the same key phase.
 template <int GH, int C, int NT, bool STEP>
 __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const float2* tile_tab, const float2* lane_tab)
 {
@@ -1042,7 +702,6 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
     unrot.dwords = ((unsigned)(GH - lane) & (unsigned)(GH - 1)) >> 2;
     constexpr int kBatch = 8;                       // channel pairs per batch of centroids
     constexpr int GPB = kBatch / C;                 // groups (of each half of the head) per batch
-    float top[QH] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};      // this lane's largest score of each head
     stk.run(kwalk, my_tiles, lane, [&](const Tile<GH, B>& w_in, int k) {
         const int lt = wave + k * NW;
         Tile<GH, B> w = w_in;
@@ -1113,164 +772,158 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
         for (int h = 0; h < QH; ++h) {
             const float s = live ? (acc0[h] + acc1[h]) + (acc2[h] + acc3[h]) : -INFINITY;
             sc[h * split_tokens + lt * kTileTokens + lane] = s;
-            top[h] = fmaxf(top[h], s);
         }
     }, [] {});
-    if constexpr (GH <= 32) {
-        gqa_values<GH, C, NT>(a, smem, top, vwalk, n, hkv, hq0, heads, split, split_tokens, tile0, my_tiles, has_new, writer, meets_new,
-                              tile_new, u_new);
-    } else {
-        lds_barrier();                                  // all centroid reads done, all scores written
+    lds_barrier();                                  // all centroid reads done, all scores written
 
-        // ---- 3. per head: softmax reference, phase V, epilogue ----------------------------------
-        constexpr int RW = F::RW;
-        static_assert(F::R == 1 && NCH == 4, "CQ-2c8b");
-        Columns<GH, B> col;
-        Streamer<GH, B, 1> st;
-        col.init(lane);
-        // (the four lanes of a group are neighbours and read four neighbouring 16-byte pieces of its
-        // value codebook: 64 contiguous bytes, four cache lines per 16 lanes instead of sixteen)
-        const int gl16 = (tid >> 2) & 15;
-        auto piece = [&](int k) { return (((tid + k * NT) >> 6) << 2) + (tid & 3); };
-        const int n_tok = (tile1 - tile0) * kTileTokens;
-        unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
-        if (has_new) {
-            // the new value row against the value codebook (global memory): the walk of the epilogue,
-            // ascending index per thread, 64-bit minimum over the threads of a group
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const size_t xrow = (size_t)n * a.x_new_stride + (size_t)hkv * GH * C;
-                float xv[C];
-                load_row_slice<C>(a.xv_new + xrow + (ch * 16 + gl16) * C, xv);
-                const uint16_t* cvg = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
-                Nearest vnear;
-                Cent16 rawb[IPT];
-#pragma unroll
-                for (int k = 0; k < IPT; ++k) rawb[k] = load_cent16(cvg + (size_t)piece(k) * 8);
-#pragma unroll
-                for (int k = 0; k < IPT; ++k) {
-                    const int j0 = piece(k) * JPL;
-#pragma unroll
-                    for (int jj = 0; jj < JPL; ++jj) vnear.offer(centroid_distance<C>(xv, &rawb[k].w[jj * (C / 2)]), j0 + jj);
-                }
-                const unsigned long long vkey = group_lanes_min<4>(vnear.key());
-                if ((lane & 3) == 0) lds_min_u64(&keys[GH + ch * 16 + gl16], vkey);
-            }
-            lds_barrier();
-            if (writer)
-                store_new_codes<GH, B>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * F::TILE_BYTES, keys + GH, u_new, tid);
-        }
-        // One head per pass: 64 groups fill the bins' rows.  The value centroids of the epilogue are the same
-        // for every head and stay in registers.
-        Cent16 rawv[NCH][IPT];
+    // ---- 3. per head: softmax reference, phase V, epilogue ----------------------------------
+    constexpr int RW = F::RW;
+    static_assert(F::R == 1 && NCH == 4, "CQ-2c8b");
+    Columns<GH, B> col;
+    Streamer<GH, B, 1> st;
+    col.init(lane);
+    // (the four lanes of a group are neighbours and read four neighbouring 16-byte pieces of its
+    // value codebook: 64 contiguous bytes, four cache lines per 16 lanes instead of sixteen)
+    const int gl16 = (tid >> 2) & 15;
+    auto piece = [&](int k) { return (((tid + k * NT) >> 6) << 2) + (tid & 3); };
+    const int n_tok = (tile1 - tile0) * kTileTokens;
+    unsigned* pf_new = reinterpret_cast<unsigned*>(keys + 2 * GH);
+    if (has_new) {
+        // the new value row against the value codebook (global memory): the walk of the epilogue,
+        // ascending index per thread, 64-bit minimum over the threads of a group
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
-            const uint16_t* cv = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
+            const size_t xrow = (size_t)n * a.x_new_stride + (size_t)hkv * GH * C;
+            float xv[C];
+            load_row_slice<C>(a.xv_new + xrow + (ch * 16 + gl16) * C, xv);
+            const uint16_t* cvg = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
+            Nearest vnear;
+            Cent16 rawb[IPT];
 #pragma unroll
-            for (int k = 0; k < IPT; ++k) rawv[ch][k] = load_cent16(cv + (size_t)piece(k) * 8);
+            for (int k = 0; k < IPT; ++k) rawb[k] = load_cent16(cvg + (size_t)piece(k) * 8);
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) {
+                const int j0 = piece(k) * JPL;
+#pragma unroll
+                for (int jj = 0; jj < JPL; ++jj) vnear.offer(centroid_distance<C>(xv, &rawb[k].w[jj * (C / 2)]), j0 + jj);
+            }
+            const unsigned long long vkey = group_lanes_min<4>(vnear.key());
+            if ((lane & 3) == 0) lds_min_u64(&keys[GH + ch * 16 + gl16], vkey);
         }
-        for (int h = 0; h < heads; ++h) {
-            // scr: [0..8) sums, [8..16) maxima, [16..24) estimates of l of the 8 wavefronts
-            const float* sch = sc + h * split_tokens;
-            float lane_max = -INFINITY;
-            for (int i = tid; i < n_tok; i += NT) lane_max = fmaxf(lane_max, sch[i]);
-            lane_max = wave_max(lane_max);
-            if (lane == 0) scr[NW + wave] = lane_max;
-            st.begin(vwalk, my_tiles, lane);
-            lds_barrier();
-            float m = scr[NW];
+        lds_barrier();
+        if (writer)
+            store_new_codes<GH, B>(const_cast<uint8_t*>(a.v_codes) + a.map.tile_index(n, hkv, tile_new) * F::TILE_BYTES, keys + GH, u_new, tid);
+    }
+    // One head per pass: 64 groups fill the bins' rows.  The value centroids of the epilogue are the same
+    // for every head and stay in registers.
+    Cent16 rawv[NCH][IPT];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) m = fmaxf(m, scr[NW + w]);
-            float l_est = 0.f;
-            for (int i = tid; i < n_tok; i += NT) l_est += __builtin_amdgcn_exp2f(sch[i] - m);
-            l_est = wave_sum(l_est);
-            if (lane == 0) scr[2 * NW + wave] = l_est;
-            {
-                float4* t4 = reinterpret_cast<float4*>(tab);
+    for (int ch = 0; ch < NCH; ++ch) {
+        const uint16_t* cv = a.v_centroids + (size_t)(hkv * GH + ch * 16 + gl16) * K * C;
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) rawv[ch][k] = load_cent16(cv + (size_t)piece(k) * 8);
+    }
+    for (int h = 0; h < heads; ++h) {
+        // scr: [0..8) sums, [8..16) maxima, [16..24) estimates of l of the 8 wavefronts
+        const float* sch = sc + h * split_tokens;
+        float lane_max = -INFINITY;
+        for (int i = tid; i < n_tok; i += NT) lane_max = fmaxf(lane_max, sch[i]);
+        lane_max = wave_max(lane_max);
+        if (lane == 0) scr[NW + wave] = lane_max;
+        st.begin(vwalk, my_tiles, lane);
+        lds_barrier();
+        float m = scr[NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, scr[NW + w]);
+        float l_est = 0.f;
+        for (int i = tid; i < n_tok; i += NT) l_est += __builtin_amdgcn_exp2f(sch[i] - m);
+        l_est = wave_sum(l_est);
+        if (lane == 0) scr[2 * NW + wave] = l_est;
+        {
+            float4* t4 = reinterpret_cast<float4*>(tab);
 #pragma unroll 4
-                for (int i = tid; i < F::TAB_FLOATS / 4; i += NT) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int i = tid; i < F::TAB_FLOATS / 4; i += NT) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        lds_barrier();
+        l_est = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l_est += scr[2 * NW + w];
+        const int fx = fixed_point_exponent(l_est);
+        const float fx_scale = ldexpf(1.f, fx), fx_inv = ldexpf(1.f, -fx);
+
+        unsigned lane_sum = 0;
+        st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
+            const int lt = wave + k * NW;
+            const float p = __builtin_amdgcn_exp2f(sch[lt * kTileTokens + lane] - m);
+            unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
+            lane_sum += pf;
+            if (has_new && tile0 + lt == tile_new && lane == u_new) {
+                *pf_new = pf;
+                pf = 0;
+            }
+#pragma unroll
+            for (int s = 0; s < GH; ++s) lds_add(slot_addr<GH, B, false>(w, col, s), pf);
+        }, [] {});
+        lane_sum = wave_sum_u32(lane_sum);
+        lds_barrier();
+        if (lane == 0) scr[wave] = __uint_as_float(lane_sum);
+        if (has_new) {
+            if (tid < GH) {
+                const unsigned code = (unsigned)(keys[GH + tid] & 0xffffffffu);
+                lds_add((code * RW + tid) * 4u, *pf_new);
             }
             lds_barrier();
-            l_est = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) l_est += scr[2 * NW + w];
-            const int fx = fixed_point_exponent(l_est);
-            const float fx_scale = ldexpf(1.f, fx), fx_inv = ldexpf(1.f, -fx);
+        }
 
-            unsigned lane_sum = 0;
-            st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
-                const int lt = wave + k * NW;
-                const float p = __builtin_amdgcn_exp2f(sch[lt * kTileTokens + lane] - m);
-                unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
-                lane_sum += pf;
-                if (has_new && tile0 + lt == tile_new && lane == u_new) {
-                    *pf_new = pf;
-                    pf = 0;
-                }
+        float acc[NCH][C];
 #pragma unroll
-                for (int s = 0; s < GH; ++s) lds_add(slot_addr<GH, B, false>(w, col, s), pf);
-            }, [] {});
-            lane_sum = wave_sum_u32(lane_sum);
-            lds_barrier();
-            if (lane == 0) scr[wave] = __uint_as_float(lane_sum);
-            if (has_new) {
-                if (tid < GH) {
-                    const unsigned code = (unsigned)(keys[GH + tid] & 0xffffffffu);
-                    lds_add((code * RW + tid) * 4u, *pf_new);
-                }
-                lds_barrier();
-            }
-
-            float acc[NCH][C];
+        for (int ch = 0; ch < NCH; ++ch) {
 #pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
+            for (int i = 0; i < C; ++i) acc[ch][i] = 0.f;
 #pragma unroll
-                for (int i = 0; i < C; ++i) acc[ch][i] = 0.f;
+            for (int k = 0; k < IPT; ++k) {
+                const int j0 = piece(k) * JPL;
 #pragma unroll
-                for (int k = 0; k < IPT; ++k) {
-                    const int j0 = piece(k) * JPL;
+                for (int jj = 0; jj < JPL; ++jj) {
+                    const float bin = (float)*reinterpret_cast<const unsigned*>(tab + (j0 + jj) * RW + ch * 16 + gl16) * fx_inv;
 #pragma unroll
-                    for (int jj = 0; jj < JPL; ++jj) {
-                        const float bin = (float)*reinterpret_cast<const unsigned*>(tab + (j0 + jj) * RW + ch * 16 + gl16) * fx_inv;
-#pragma unroll
-                        for (int i = 0; i < C / 2; ++i) {
-                            const half2_t hv = __builtin_bit_cast(half2_t, rawv[ch][k].w[jj * (C / 2) + i]);
-                            acc[ch][2 * i] = __builtin_fmaf(bin, (float)hv.x, acc[ch][2 * i]);
-                            acc[ch][2 * i + 1] = __builtin_fmaf(bin, (float)hv.y, acc[ch][2 * i + 1]);
-                        }
+                    for (int i = 0; i < C / 2; ++i) {
+                        const half2_t hv = __builtin_bit_cast(half2_t, rawv[ch][k].w[jj * (C / 2) + i]);
+                        acc[ch][2 * i] = __builtin_fmaf(bin, (float)hv.x, acc[ch][2 * i]);
+                        acc[ch][2 * i + 1] = __builtin_fmaf(bin, (float)hv.y, acc[ch][2 * i + 1]);
                     }
                 }
-#pragma unroll
-                for (int i = 0; i < C; ++i) {
-                    acc[ch][i] = lanes_sum<2>(acc[ch][i]);
-                }
             }
-            if ((lane & 3) == 0) {
 #pragma unroll
-                for (int ch = 0; ch < NCH; ++ch)
-#pragma unroll
-                    for (int i = 0; i < C; ++i) scr[64 + wave * D + (ch * 16 + gl16) * C + i] = acc[ch][i];
+            for (int i = 0; i < C; ++i) {
+                acc[ch][i] = lanes_sum<2>(acc[ch][i]);
             }
-            lds_barrier();
-            unsigned l_fix = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) l_fix += __float_as_uint(scr[w]);
-            const float l = (float)l_fix * fx_inv;
-            const int hq = hq0 + h;
-            float* part = a.partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
-            if (tid == 0 && !direct) {
-                part[0] = m;
-                part[1] = l;
-            }
-            for (int chn = tid; chn < D; chn += NT) {
-                float o = 0.f;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) o += scr[64 + w * D + chn];
-                if (direct) a.out[(size_t)n * a.out_batch_stride + (size_t)hq * D + chn] = __builtin_bit_cast(uint16_t, (_Float16)(o / l));
-                else part[kPartialHeader + chn] = o;
-            }
-            lds_barrier();                          // the next head reuses the scratch, the next pass the bins
         }
+        if ((lane & 3) == 0) {
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+                for (int i = 0; i < C; ++i) scr[64 + wave * D + (ch * 16 + gl16) * C + i] = acc[ch][i];
+        }
+        lds_barrier();
+        unsigned l_fix = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l_fix += __float_as_uint(scr[w]);
+        const float l = (float)l_fix * fx_inv;
+        const int hq = hq0 + h;
+        float* part = a.partials + ((size_t)(n * a.n_q_heads + hq) * a.n_split + split) * (D + kPartialHeader);
+        if (tid == 0 && !direct) {
+            part[0] = m;
+            part[1] = l;
+        }
+        for (int chn = tid; chn < D; chn += NT) {
+            float o = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) o += scr[64 + w * D + chn];
+            if (direct) a.out[(size_t)n * a.out_batch_stride + (size_t)hq * D + chn] = __builtin_bit_cast(uint16_t, (_Float16)(o / l));
+            else part[kPartialHeader + chn] = o;
+        }
+        lds_barrier();                          // the next head reuses the scratch, the next pass the bins
     }
 }
 
@@ -1296,12 +949,7 @@ cq_status launch_rope_gqa_variant(const DecodeArgs& a, const float2* tile_tab, c
     static LdsKernelSetup setup;
     if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
     size_t smem = kTabBytes + kScrBytes + (size_t)4 * a.tiles_per_split * kTileTokens * 4;
-    if (GH <= 32) {
-        smem += kGqaKeyBytes(GH) + (NT / 64 - kProbInScratch) * kProbBytes;
-        smem = smem > kTabBytes + kScrBytes + kGqaOutBytes ? smem : kTabBytes + kScrBytes + kGqaOutBytes;
-    } else if (STEP) {
-        smem += kKeyFloats(GH) * 4;
-    }
+    if (STEP) smem += kKeyFloats(GH) * 4;
     if (smem > 160 * 1024) return CQ_ERR_INVALID_ARG;
     const int qper = a.n_q_heads / a.f.n_kv_heads;
     const unsigned grid = (unsigned)(a.batch * a.f.n_kv_heads * ((qper + 3) / 4) * a.n_split);
@@ -1319,8 +967,6 @@ int decode_rope_max_tiles_per_split() { return 256; }
 constexpr int kGqaTiles = 88;
 int decode_rope_shared_max_tiles_per_split() { return kGqaTiles; }
 static_assert(kTabBytes + kScrBytes + 4 * kGqaTiles * kTileTokens * 4 + kKeyFloats(64) * 4 <= 160 * 1024, "LDS of the grouped-query kernel");
-static_assert(kTabBytes + kScrBytes + 4 * kGqaTiles * kTileTokens * 4 + kGqaKeyBytes(32) + (kRopeThreads / 64 - kProbInScratch) * kProbBytes <= 160 * 1024,
-              "LDS of the grouped-query kernel");
 
 size_t rope_table_floats(int t_cap) { return ((size_t)(t_cap / kTileTokens) * kPairs + (size_t)kPairs * 64) * 2; }
 
@@ -1340,13 +986,10 @@ cq_status launch_decode_rope(const DecodeArgs& a, const float* tables, int t_cap
     const float2* lane_tab = tile_tab + (size_t)(t_cap / kTileTokens) * kPairs;
     cq_status st = CQ_ERR_UNSUPPORTED;
     const bool shared = a.f.b == 8 && a.f.head_dim == 128 && a.n_q_heads >= 2 * a.f.n_kv_heads && a.tiles_per_split <= kGqaTiles;
+    if (shared && a.f.c >= 4) return launch_decode_quad(a, tile_tab, lane_tab, stream);
     if (shared) {
         const bool step = a.xk_new != nullptr;
-        if (a.f.gh == 16 && a.f.c == 8)
-            st = step ? launch_rope_gqa_variant<16, 8, true>(a, tile_tab, lane_tab, stream) : launch_rope_gqa_variant<16, 8, false>(a, tile_tab, lane_tab, stream);
-        else if (a.f.gh == 32 && a.f.c == 4)
-            st = step ? launch_rope_gqa_variant<32, 4, true>(a, tile_tab, lane_tab, stream) : launch_rope_gqa_variant<32, 4, false>(a, tile_tab, lane_tab, stream);
-        else if (a.f.gh == 64 && a.f.c == 2)
+        if (a.f.gh == 64 && a.f.c == 2)
             st = step ? launch_rope_gqa_variant<64, 2, true>(a, tile_tab, lane_tab, stream) : launch_rope_gqa_variant<64, 2, false>(a, tile_tab, lane_tab, stream);
     } else if (a.f.b == 8 && a.f.head_dim == 128) {
         const bool step = a.xk_new != nullptr;
@@ -1362,7 +1005,7 @@ cq_status launch_decode_rope(const DecodeArgs& a, const float* tables, int t_cap
                       : launch_rope_variant<16, 8, false, 10>(a, tile_tab, lane_tab, stream);
     if (st != CQ_OK) return st;
     if (a.n_split > 1)
-        return launch_decode_merge(a.partials, a.out, a.batch * a.n_q_heads, a.n_q_heads, a.out_batch_stride, a.n_split, a.f.head_dim, stream);
+        return launch_decode_merge(a, stream);
     return CQ_OK;
 }
 

@@ -213,12 +213,17 @@ struct DecodePlan {
 };
 DecodePlan decode_plan(const DecodeArgs& a);
 cq_status launch_decode_pair(const DecodeArgs& a, hipStream_t stream);
+// grouped queries, up to four query heads per workgroup, both codebooks in LDS (cq_decode_quad.hip)
+bool decode_takes_quads(const DecodeArgs& a);
+// arrival counters for the rows of a launch on `stream`; null: none (under capture, beyond their number)
+unsigned* decode_merge_counters(hipStream_t stream, int rows);
+cq_status launch_decode_quad(const DecodeArgs& a, const float2* tile_tab, const float2* lane_tab, hipStream_t stream);    // (tables: keys cached before RoPE)
 // centroids fp16 [G][2^b][c] of a sub-byte format -> fp16 [G / fuse][256][c fuse] of its fused format
 cq_status launch_expand_codebook(const uint16_t* centroids, const Derived& f, uint16_t* fused, hipStream_t stream);
 // writes `count` records of a layer table (device memory) from values passed with the launch
 cq_status launch_layer_table_write(const LayerChunk& chunk, int count, LayerPtrs* dst, hipStream_t stream);
-// merges the partials of `rows` (sequence, query head) pairs, n_split each, into fp16 rows
-// (row r goes to out + (r / n_q_heads) * out_batch_stride + (r % n_q_heads) * head_dim)
+// merges the partials of all rows (and layers) of a call into its fp16 rows
+cq_status launch_decode_merge(const DecodeArgs& a, hipStream_t stream);
 cq_status launch_decode_merge(const float* partials, uint16_t* out, int rows, int n_q_heads, int64_t out_batch_stride,
                               int n_split, int head_dim, hipStream_t stream);
 
