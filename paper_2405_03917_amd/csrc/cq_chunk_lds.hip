@@ -21,7 +21,7 @@
 // 12.3 clocks (16 lanes at a time on 16 bank groups: the fullest holds 3.1), a transposing one
 // 6.2, i.e. 394 clocks per tile and CU at CQ-8c8b; the kernel takes 535 (LDS active 73-75 %).
 // Measured: CQ-4c8b, batch 16, 32 heads, 5 tokens over 4096: 136 us token by token, 264 us in the
-// many-row kernel, 53 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 280 us in two pieces (given as
+// many-row kernel, 50 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 280 us in two pieces (given as
 // tokens_per_split: the default's workspace holds one, and such a call goes token by token).  The first form
 // waited for every gather by itself (5800 clocks per tile and wavefront, 61 us); values gathered
 // ahead of the softmax in one batch of 64 registers spilled at CQ-4c8b and gained nothing.
@@ -29,6 +29,10 @@
 // A workgroup of 8 wavefronts (one per CU) serves RB = 1, 2 or 4 blocks of 16 rows; the 8 / RB wavefronts of
 // a block take every (8 / RB)-th tile and are merged through LDS at the end.  Workgroups walk
 // several (sequence, split) items of one KV head, so the codebooks are staged once per workgroup.
+// (Both codebooks requested together and ahead of the first codes, the rows of up to eight merged in one pass, all keys of
+// a tile gathered at once, priorities: 5 tokens of 16 x 4096, CQ-8c8b 39.9 -> 38.3 us, of 1 x 6000, 8 tokens 13.3 -> 12.5, 40 tokens
+// of 4 x 5000 47.9 -> 45.8; where the LDS is busy throughout, nothing.)
+#include "cq_key_gather.hpp"
 #include "cq_lds_gather.hpp"
 
 namespace cq {
@@ -156,22 +160,25 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         request(it, it.tile0 + slice);
         return it;
     };
-    Item it = open_item();
-
-    // ---- both codebooks of the head to LDS as they are ([group][code] entries)
+    // ---- both codebooks of the head to LDS as they are ([group][code] entries); requested ahead of the first codes, which
+    // come from further away (loads return in order)
+    typedef __attribute__((address_space(3))) u32x4 lds_q;
+    u32x4 book[2][8];
     {
         const u32x4* src[2] = {reinterpret_cast<const u32x4*>(a.k_centroids + (size_t)hkv * GH * 256 * C),
                                reinterpret_cast<const u32x4*>(a.v_centroids + (size_t)hkv * GH * 256 * C)};
-        typedef __attribute__((address_space(3))) u32x4 lds_q;
 #pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            u32x4 v[8];
+        for (int w = 0; w < 2; ++w)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = src[w][i * (kWaves * 64) + tid];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) *(lds_q*)(w * kBookBytes + (unsigned)(i * (kWaves * 64) + tid) * 16) = v[i];
-        }
+            for (int i = 0; i < 8; ++i) book[w][i] = src[w][i * (kWaves * 64) + tid];
     }
+    __builtin_amdgcn_sched_barrier(0);
+    Item it = open_item();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *(lds_q*)(w * kBookBytes + (unsigned)(i * (kWaves * 64) + tid) * 16) = book[w][i];
 
     lds_barrier();
 
@@ -196,12 +203,16 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         unpack();
         request(it, tile + cs);
         const float mult = large ? 1.f : scale, early = large ? scale : 1.f;
+        bool turn = wave < kWaves / 2;                  // (priorities as in cq_decode_quad.hip)
 #pragma unroll 1
         for (; tile < it.tile1; tile += cs) {
             // The gathers are issued in batches that the products behind them work off, one batch ahead
             // (the scheduling fences pin that order: left alone, the compiler waits for every gather by itself,
             // 130 clocks each).
             // ---- scores: acc[i][e] is token 16 i + 4 blk + e, query col
+            turn = !turn;
+            if (turn) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
             float4_t acc[4];
             half8_t kv[4][4];
             auto gather_keys = [&](int i) {
@@ -236,6 +247,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             };
             gather_keys(0);
             gather_keys(1);
+            gather_keys(2);
+            gather_keys(3);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -243,12 +256,12 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
 #pragma unroll
                 for (int s = 0; s < 4; ++s) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv[i][s], qreg[s], acc[i], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (i < 2) gather_keys(i + 2);
-                __builtin_amdgcn_sched_barrier(0);
             }
             gather_values(0);
             __builtin_amdgcn_sched_barrier(0);
             // ---- online softmax of the lane's query column
+            if (turn) __builtin_amdgcn_s_setprio(3);
+            else __builtin_amdgcn_s_setprio(2);
             if (large || tile * kTileTokens + kTileTokens - 1 > it.pos_first) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -350,6 +363,36 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             dst[1] = ll;
         }
         lds_barrier();                                      // the pairs are read: their room is the rows'
+        if constexpr (HALF) {
+            // (8 rows, one row block: all 128 channels of every wavefront at once; the parts of a row's probabilities, columns
+            // q and q + 8, are added here)
+            const int q = tid >> 6;
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) {
+                float4_t v = o[cb];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)             // (lane l + 8 mod 16 of the row)
+                    v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));
+                // (the pieces of row q change places by 4 q: the 32 lanes that write fill 512 bytes)
+                if (col < 8) *(lds_f4*)(kMergeBase + (unsigned)(wave * 8 + col) * 512 + (unsigned)((4 * cb + blk) ^ (4 * col)) * 16) = v * weight;
+            }
+            lds_barrier();
+            float2_t sum = {0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                sum += *(lds_f2*)(kMergeBase + (unsigned)(w * 8 + q) * 512 + (unsigned)((lane >> 1) ^ (4 * q)) * 16 + (lane & 1) * 8);
+            if (q < rows_total) {
+                const int j = row_token(q);
+                const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (q - j * qper);
+                if (a.n_split == 1)
+                    *reinterpret_cast<half2_t*>(a.out + out_row * D + 2 * lane) = __builtin_convertvector(sum, half2_t);
+                else
+                    *reinterpret_cast<float2_t*>(a.partials + (out_row * a.n_split + done.split) * (D + kPartialHeader) + kPartialHeader + 2 * lane) = sum;
+            }
+            if (!more) break;
+            lds_barrier();
+            continue;
+        }
         int tid_o = tid, lane_o = lane;                     // (opaque, as above; all of it only where registers are short)
         if constexpr (C == 4) asm volatile("" : "+v"(tid_o), "+v"(lane_o));
         int q = tid_o >> 5;                                 // this thread's row and pair of channels
@@ -359,12 +402,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         for (int part = 0; part < 2; ++part) {
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
-                float4_t v = o[4 * part + h];
-                if constexpr (HALF) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)         // (lane l + 8 mod 16 of the row)
-                        v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));
-                }
+                const float4_t v = o[4 * part + h];
                 // (16-byte pieces of a row change places by the row's number: 16 rows, 16 different banks)
                 *(lds_f4*)(kMergeBase + (unsigned)(wave * kRows + (lane_o & 15)) * kORow + (unsigned)((4 * h + (lane_o >> 4)) ^ (lane_o & 15)) * 16) = v * weight;
             }
@@ -392,17 +430,321 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
     }
 }
 
-template <int C, bool HALF>
-cq_status launch(const ChunkArgs& a, hipStream_t stream)
+// At most 4 rows: lane = token, as in the decode kernel for four query heads (cq_decode_quad.hip, which says how): a token's
+// scores of the four rows in the registers of its lane, by v_mfma_f32_4x4x4_16B_f16 with the queries broadcast; every
+// wavefront a tile of the item by itself; probabilities relative to a running reference that moves when a score
+// exceeds it by 3, as three fp16 numbers each (33 bits; twelve columns) to a [token][column] array in LDS and back transposed.
+// The kernel above computes sixteen columns of softmax whatever the rows, and is bound by the vector ALU as much as by the
+// LDS then: CQ-4c8b 408 instructions per tile (here 290) next to 454 clocks of LDS, 656 clocks taken, 520 here.  Measured, above
+// -> here: CQ-4c8b, 32 heads, 3 tokens of 16 x 4096 50.5 -> 43.1 us, of 64 x 1000 71.7 -> 58.5; CQ-8c8b, 4 tokens of 16 x 4096 37.8 ->
+// 33.8, of 64 x 1000 55.3 -> 49.9; of 4 x 30000 130 / 130 and 77 / 78.  (The same for eight rows, two fp16 numbers each and
+// twice the matrix instructions, 0.94 to 1.01 times as fast as above: there the columns are no waste.)
+constexpr unsigned kFewWaveBytes = 2048;                // of a wavefront: 64 tokens x 16 columns; at the end of an item four output rows
+constexpr unsigned kFewPairs = kMergeBase + kWaves * kFewWaveBytes;
+constexpr unsigned kFewLds = kFewPairs + kWaves * 4 * 8;
+static_assert(kTileTokens * 32 == kFewWaveBytes && 4 * 128 * 4 == kFewWaveBytes, "a wavefront's room");
+constexpr float kNoScore = -3.0e38f;                    // the reference of a row that has seen no token: finite, and below every score
+
+template <int C>
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves * 64) void chunk_few_kernel(ChunkArgs a, int per_head, int items)
 {
-    auto kernel = chunk_lds_kernel<C, HALF>;
-    static LdsKernelSetup setup;
+    constexpr int D = 128, GH = D / C, K = 256, PL = GH / 16, NT = kWaves * 64, ROWS = 4, PARTS = 3;
+    constexpr int TILE_BYTES = kTileTokens * GH;
+    typedef __attribute__((address_space(3))) u32x4 lds_q;
+    typedef __attribute__((address_space(3))) float lds_f;
+    typedef __attribute__((address_space(3))) float2_t lds_f2;
+    typedef __attribute__((address_space(3))) float4_t lds_f4;
+    extern __shared__ float smem[];
+    (void)smem;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, blk = lane >> 4;
+    const int hkv = blockIdx.x % a.f.n_kv_heads;
+    int item = blockIdx.x / a.f.n_kv_heads;
+    const int qper = a.n_q_heads / a.f.n_kv_heads;
+    const int rows_total = a.m * qper;
+    const float inv_qper = 1.f / (float)qper;
+    const auto row_token = [&](int row) { return (int)(((float)row + 0.5f) * inv_qper); };     // row / qper (few rows: exact)
+
+    // ---- both codebooks of the head on their way to LDS, ahead of the first codes, which come from further away
+    u32x4 book[2][8];
+    {
+        const u32x4* src[2] = {reinterpret_cast<const u32x4*>(a.k_centroids + (size_t)hkv * GH * K * C),
+                               reinterpret_cast<const u32x4*>(a.v_centroids + (size_t)hkv * GH * K * C)};
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) book[w][i] = src[w][i * NT + tid];
+    }
+
+    // ---- this lane's places: keys, token `lane`; values, tokens 32 t + 8 blk + 4 r + col / 4, channels 4 (col % 4) .. of 16
+    // (C = 8: half of group (col % 4) / 2, then every second group; C = 4: group col % 4, then every fourth)
+    Unrotate unrot;
+    unrot.bytes = (unsigned)(GH - lane) & 3u;
+    unrot.dwords = ((unsigned)(GH - lane) & (unsigned)(GH - 1)) >> 2;
+    const int vg0 = C == 8 ? (col & 3) >> 1 : (col & 3);
+    const int u0 = 8 * blk + (col >> 2);
+    const CodePick<GH, C == 8 ? 2 : 4> pick0(vg0, u0), pick1(vg0, u0 + 4);
+    const unsigned vbase = kBookBytes + (C == 8 ? (unsigned)vg0 * 4096 + (unsigned)(col & 1) * 8 : (unsigned)vg0 * 2048);
+    // (a token's 32 bytes of probabilities: halves exchanged for every second run of eight tokens, for the banks)
+    const unsigned work = kMergeBase + (unsigned)wave * kFewWaveBytes;
+    const unsigned prob_in = work + (unsigned)lane * 32, prob_swap = (unsigned)((lane >> 3) & 1) * 16;
+    const unsigned prob_out = work + (unsigned)u0 * 32 + (((unsigned)(col & 3) * 8) ^ (unsigned)(blk & 1) * 16);
+
+    struct Item {
+        int n, split, t_n, tile0, tile1, n_tiles;
+    };
+    half4_t qreg[2];                                    // channels 4 (16 r + lane / 4) .. of row lane % 4
+    Tile<GH, 8> krec;
+    u32x4 vrec[2][2][PL];
+    auto request = [&](const Item& it, int tile) {
+        const size_t at = a.map.tile_index(it.n, hkv, min(tile, it.n_tiles - 1)) * TILE_BYTES;
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) krec.lo[pl] = *reinterpret_cast<const u32x4*>(a.k_codes + at + pl * 1024 + lane * 16);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl)
+                    vrec[t][rr][pl] = *reinterpret_cast<const u32x4*>(a.v_codes + at + pl * 1024 + (32 * t + 4 * rr + u0) * 16);
+    };
+    auto open_item = [&](int at) {
+        Item it;
+        it.split = at % a.n_split;
+        it.n = at / a.n_split;
+        it.t_n = a.t;
+        if (a.seq_lens) it.t_n = min(max(a.seq_lens[it.n], a.m), a.t);
+        it.n_tiles = (it.t_n + kTileTokens - 1) / kTileTokens;
+        it.tile0 = it.split * a.tiles_per_split;
+        it.tile1 = min(it.tile0 + a.tiles_per_split, it.n_tiles);
+        const int row = min(lane & 3, rows_total - 1), j = row_token(row);
+        const uint16_t* qrow = a.q + (((size_t)it.n * a.m + j) * a.n_q_heads + hkv * qper + (row - j * qper)) * D;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) qreg[i] = *reinterpret_cast<const half4_t*>(qrow + 64 * i + 4 * (lane >> 2));
+        request(it, it.tile0 + wave);
+        return it;
+    };
+    Item it = open_item(item);
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *(lds_q*)(w * kBookBytes + (unsigned)(i * NT + tid) * 16) = book[w][i];
+    lds_barrier();
+
+#pragma unroll 1
+    for (;;) {
+        float4_t o[8];
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
+        float ref[ROWS], l[ROWS];                           // (l: this lane's tokens)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            ref[r] = kNoScore;
+            l[r] = 0.f;
+        }
+        unsigned d[GH / 4], z[2][2][2];                     // codes of the tile to come: keys in group order, values as picked
+        auto unpack = [&]() {
+            group_order<GH, 8>(krec, unrot, d);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                pick0(vrec[t][0], 0, z[t][0]);
+                pick1(vrec[t][1], 0, z[t][1]);
+            }
+        };
+        const int pos0 = it.t_n - a.m;                      // position of query token 0
+        int tile = it.tile0 + wave;
+        bool turn = wave < kWaves / 2;                      // (priorities as in cq_decode_quad.hip)
+        unpack();
+        request(it, tile + kWaves);
+#pragma unroll 1
+        for (; tile < it.tile1; tile += kWaves) {
+            turn = !turn;
+            if (turn) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+            // ---- scores of the lane's token
+            float4_t acc[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+            {
+                unsigned at[GH];
+#pragma unroll
+                for (int g = 0; g < GH; ++g) at[g] = entry<C>(d[g >> 2], g & 3, 0u);
+                __builtin_amdgcn_sched_barrier(0);          // (addresses first: a gather right behind its own would wait for it)
+                CenVec<C> kv[GH];
+#pragma unroll
+                for (int g = 0; g < GH; ++g) kv[g] = lds_centroid<C>(at[g] + (unsigned)g * (K * C * 2));
+                __builtin_amdgcn_sched_barrier(0);
+                typedef unsigned u2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                for (int g = 0; g < GH; ++g)
+#pragma unroll
+                    for (int p = 0; p < C / 4; ++p) {
+                        const int i = g * (C / 4) + p;
+                        acc[i & 3] = mfma_quad(qreg, __builtin_bit_cast(half4_t, u2{kv[g].w[2 * p], kv[g].w[2 * p + 1]}), acc[i & 3], i);
+                    }
+            }
+            // ---- the values of tokens 0-31 on their way
+            half8_t av[2][8];
+            auto gather = [&](int t) {
+                unsigned at[2][8];
+#pragma unroll
+                for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+                    for (int cb = 0; cb < 8; ++cb) at[rr][cb] = entry<C>(z[t][rr][cb >> 2], cb & 3, vbase);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) {
+                    const half4_t v0 = lds_transposed(at[0][cb] + (unsigned)cb * 8192), v1 = lds_transposed(at[1][cb] + (unsigned)cb * 8192);
+                    av[t][cb] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if (turn) __builtin_amdgcn_s_setprio(3);
+            else __builtin_amdgcn_s_setprio(2);
+            gather(0);
+            // ---- softmax
+            float s[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) s[r] = ((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r])) * a.scale_log2e;
+            if (tile * kTileTokens + kTileTokens - 1 > pos0) {      // (some row does not see all of this tile)
+                const int tok = tile * kTileTokens + lane;
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) s[r] = tok <= pos0 + row_token(min(r, rows_total - 1)) ? s[r] : -INFINITY;
+            }
+            float over = s[0] - ref[0];
+#pragma unroll
+            for (int r = 1; r < ROWS; ++r) over = fmaxf(over, s[r] - ref[r]);
+            if (__builtin_amdgcn_ballot_w64(over > 3.f) != 0) {
+                float mine = 1.f;
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                    const float top = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(fmaxf(ref[r], wave_max(s[r])))));
+                    const float alpha = __builtin_amdgcn_exp2f(ref[r] - top);
+                    l[r] *= alpha;
+                    ref[r] = top;
+                    mine = (lane & (ROWS - 1)) == r ? alpha : mine;
+                }
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) o[cb] *= mine;
+            }
+            // p 2^12 as the sum of three fp16 numbers (what is left over each time is exact)
+            unsigned part[PARTS][ROWS / 2];
+#pragma unroll
+            for (int r = 0; r < ROWS; r += 2) {
+                float2_t p;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    p[e] = __builtin_amdgcn_exp2f(s[r + e] - ref[r + e]) * 4096.f;     // (12 in the exponent would be lost in a large reference)
+                    l[r + e] += p[e];
+                }
+#pragma unroll
+                for (int k = 0; k < PARTS; ++k) {
+                    const half2_t v = __builtin_convertvector(p, half2_t);
+                    part[k][r >> 1] = __builtin_bit_cast(unsigned, v);
+                    if (k + 1 < PARTS) p = float2_t{__builtin_fmaf((float)v.x, -1.f, p[0]), __builtin_fmaf((float)v.y, -1.f, p[1])};
+                }
+            }
+            // (a wavefront's LDS operations keep their order; the statements keep the compiler from moving the reads, which
+            // are of what other lanes wrote)
+            *(lds_q*)(prob_in + prob_swap) = u32x4{part[0][0], part[0][1], part[1][0], part[1][1]};
+            *(lds_q*)(prob_in + (prob_swap ^ 16u)) = u32x4{part[2][0], part[2][1], 0u, 0u};
+            asm volatile("" ::: "memory");
+            half8_t pb[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const half4_t v0 = lds_transposed(prob_out + (unsigned)t * 1024), v1 = lds_transposed(prob_out + (unsigned)t * 1024 + 128);
+                pb[t] = half8_t{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            }
+            asm volatile("" ::: "memory");
+            gather(1);
+            // ---- O^T += V^T P
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[t][cb], pb[t], o[cb], 0, 0, 0);
+            // the next tile's codes, and the request for the tile after it
+            unpack();
+            request(it, tile + 2 * kWaves);
+        }
+
+        // ---- the next item's requests go out, then the wavefronts are merged
+        const Item done = it;
+        item += per_head;
+        const bool more = item < items;
+        if (more) it = open_item(item);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const float sum = wave_sum(l[r]);
+            if (lane == 0) *(lds_f2*)(kFewPairs + (unsigned)(wave * ROWS + r) * 8) = float2_t{ref[r], sum};
+        }
+        // (the parts of a row are columns r, r + 4, r + 8)
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) {
+            float4_t v = o[cb];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x128, 0xf, 0xf, false));    // row_ror:8
+                v[e] += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v[e]), 0x124, 0xf, 0xf, false));    // row_ror:4
+            }
+            if (col < ROWS) *(lds_f4*)(work + (unsigned)(col * D + 16 * cb + 4 * blk) * 4) = v;
+        }
+        lds_barrier();
+        static_assert(NT == ROWS * D, "one output per thread");
+        const int r = tid / D, ch = tid % D;
+        float2_t ml[kWaves];
+        float m = kNoScore;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            ml[w] = *(lds_f2*)(kFewPairs + (unsigned)(w * ROWS + r) * 8);
+            m = fmaxf(m, ml[w][0]);
+        }
+        float sum = 0.f, ll = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float weight = __builtin_amdgcn_exp2f(ml[w][0] - m);
+            sum = __builtin_fmaf(*(lds_f*)(kMergeBase + (unsigned)(w * ROWS * D + tid) * 4), weight, sum);
+            ll = __builtin_fmaf(ml[w][1], weight, ll);
+        }
+        if (r < rows_total) {
+            const int j = row_token(r);
+            const size_t out_row = ((size_t)done.n * a.m + j) * a.n_q_heads + hkv * qper + (r - j * qper);
+            if (a.n_split == 1) {
+                a.out[out_row * D + ch] = __builtin_bit_cast(uint16_t, (_Float16)(sum / ll));
+            } else {                                    // (a row that sees no token of the split: no weight)
+                float* dst = a.partials + (out_row * a.n_split + done.split) * (D + kPartialHeader);
+                if (ch == 0) {
+                    dst[0] = m;
+                    dst[1] = ll * 0x1p-12f;
+                }
+                dst[kPartialHeader + ch] = sum * 0x1p-12f;
+            }
+        }
+        if (!more) break;
+        lds_barrier();                                  // the rows and pairs are read: their room is the next item's
+    }
+}
+
+template <class Kernel>
+cq_status launch(Kernel kernel, LdsKernelSetup& setup, unsigned lds, const ChunkArgs& a, hipStream_t stream, bool few)
+{
     if (setup.ensure(reinterpret_cast<const void*>(kernel)) != hipSuccess) return CQ_ERR_HIP;
     const ChunkLdsPlan p = chunk_lds_plan(a.f, a.n_q_heads, a.m);
     const int items = a.batch * a.n_split;
     const int per_head = items < p.wgs_per_head ? items : p.wgs_per_head;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_head * a.f.n_kv_heads)), dim3(kWaves * 64), kLdsBytes, stream, a, p.rb_log2, items);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_head * a.f.n_kv_heads)), dim3(kWaves * 64), lds, stream, a, few ? per_head : p.rb_log2, items);
     return hipGetLastError() == hipSuccess ? CQ_OK : CQ_ERR_HIP;
+}
+
+template <int C>
+cq_status launch_rows(const ChunkArgs& a, int rows, hipStream_t stream)
+{
+    static LdsKernelSetup setup[3];
+    if (rows <= 4) return launch(chunk_few_kernel<C>, setup[0], kFewLds, a, stream, true);
+    if (rows <= kRows / 2) return launch(chunk_lds_kernel<C, true>, setup[1], kLdsBytes, a, stream, false);
+    return launch(chunk_lds_kernel<C, false>, setup[2], kLdsBytes, a, stream, false);
 }
 
 }  // namespace
@@ -421,9 +763,8 @@ cq_status launch_chunk_lds(const ChunkArgs& a, hipStream_t stream)
     // (row / qper is formed in floating point: exact for far more rows than are served here)
     const int64_t rows = (int64_t)a.m * (a.n_q_heads / a.f.n_kv_heads);
     if (a.f.b != 8 || a.f.head_dim != 128 || rows > kChunkLdsRows) return CQ_ERR_UNSUPPORTED;
-    const bool half = rows <= kRows / 2;
-    if (a.f.c == 8) return half ? launch<8, true>(a, stream) : launch<8, false>(a, stream);
-    if (a.f.c == 4) return half ? launch<4, true>(a, stream) : launch<4, false>(a, stream);
+    if (a.f.c == 8) return launch_rows<8>(a, (int)rows, stream);
+    if (a.f.c == 4) return launch_rows<4>(a, (int)rows, stream);
     return CQ_ERR_UNSUPPORTED;
 }
 

@@ -79,35 +79,6 @@ __device__ __forceinline__ unsigned long long lanes_min_u64(unsigned long long v
     return v;
 }
 
-template <int ABID>
-__device__ __forceinline__ float4_t mfma_heads(half4_t q, half4_t k, float4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_4x4x4f16(q, k, c, 4, ABID, 0);
-}
-// c += (channels 4 i .. 4 i + 3 of the four queries, from block i % 16 of register i / 16) x (those of the lane's key)
-__device__ __forceinline__ float4_t mfma_quad(const half4_t (&q)[2], half4_t k, float4_t c, int i)
-{
-    const half4_t a = q[i >> 4];
-    switch (i & 15) {
-        case 0: return mfma_heads<0>(a, k, c);
-        case 1: return mfma_heads<1>(a, k, c);
-        case 2: return mfma_heads<2>(a, k, c);
-        case 3: return mfma_heads<3>(a, k, c);
-        case 4: return mfma_heads<4>(a, k, c);
-        case 5: return mfma_heads<5>(a, k, c);
-        case 6: return mfma_heads<6>(a, k, c);
-        case 7: return mfma_heads<7>(a, k, c);
-        case 8: return mfma_heads<8>(a, k, c);
-        case 9: return mfma_heads<9>(a, k, c);
-        case 10: return mfma_heads<10>(a, k, c);
-        case 11: return mfma_heads<11>(a, k, c);
-        case 12: return mfma_heads<12>(a, k, c);
-        case 13: return mfma_heads<13>(a, k, c);
-        case 14: return mfma_heads<14>(a, k, c);
-        default: return mfma_heads<15>(a, k, c);
-    }
-}
-
 template <int GH, int C, bool ROPE, bool STEP, bool LAYERS>
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThreads) void decode_quad_kernel(
     DecodeArgs a, const float2* tile_tab, const float2* lane_tab, int items, int per_head)
