@@ -42,6 +42,17 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The wavefronts of a SIMD (numbers equal modulo 4) take turns in priority from tile to tile.  Left alone the oldest goes first
+// whenever two are ready: it ends its share of the tiles early and the workgroup waits for the others, which then have
+// the SIMD to themselves and do not fill it.  Pairs of query heads 1.00 to 1.06 times as fast (CQ-8c10b, 32 / 16 heads, 32 x 6000,
+// 48.0 -> 45.1 us), keys cached before RoPE 1.00 to 1.03 (CQ-8c8b, 32 heads, 4 x 20000, 62.8 -> 60.9); the kernel for one query
+// head, which has two workgroups of eight wavefronts on a CU, 0.94 to 1.01: it does without.
+__device__ __forceinline__ void take_turns(int wave, int tile)
+{
+    if (((tile ^ (wave >> 2)) & 1) != 0) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
 // Reductions across lanes in the vector ALU (DPP inside a row of 16 lanes, lane swaps between rows): every lane gets
 // the result of its neighbourhood of 2^STEPS lanes.  (As shuffles, i.e. LDS round trips, a wavefront's maximum and sum
 // took about 1200 clocks per chunk of the decode kernels.)

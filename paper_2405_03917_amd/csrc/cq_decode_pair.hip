@@ -394,6 +394,7 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
     Scores sreg[NS];
     auto score_tile = [&](const Tile<GH, B>& w_in, int k) {
         Scores score;
+        take_turns(wave, k);
         const int tile = tile0 + wave + k * NW;
         Tile<GH, B> w = w_in;
         if (meets_new && tile == tile_new) new_codes.patch(w, u_new, lane);
@@ -446,6 +447,7 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
                 pf[h] = 0;
             }
         }
+        take_turns(wave, k);
         // (no bin reaches 2^32: nothing is carried from one head's half to the other's)
         const unsigned long long both = pf[0] | ((unsigned long long)pf[1] << 32);
 #pragma unroll
