@@ -1,6 +1,6 @@
 // Value codebooks in LDS as operands of matrix products: which codes of a 64-token tile a lane needs,
 // where their entries are, and the read that gathers and transposes them.  Shared by the kernels
-// that keep a KV head's value codebook on chip (cq_chunk_lds.hip, cq_decode_rope.hip).
+// that keep a KV head's codebooks on chip (cq_chunk_lds.hip, cq_decode_quad.hip).
 #pragma once
 
 #include "cq_decode_common.hpp"
