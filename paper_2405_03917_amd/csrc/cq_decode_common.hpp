@@ -44,9 +44,11 @@ __device__ __forceinline__ void lds_barrier()
 
 // The wavefronts of a SIMD (numbers equal modulo 4) take turns in priority from tile to tile.  Left alone the oldest goes first
 // whenever two are ready: it ends its share of the tiles early and the workgroup waits for the others, which then have
-// the SIMD to themselves and do not fill it.  Pairs of query heads 1.00 to 1.06 times as fast (CQ-8c10b, 32 / 16 heads, 32 x 6000,
-// 48.0 -> 45.1 us), keys cached before RoPE 1.00 to 1.03 (CQ-8c8b, 32 heads, 4 x 20000, 62.8 -> 60.9); the kernel for one query
-// head, which has two workgroups of eight wavefronts on a CU, 0.94 to 1.01: it does without.
+// the SIMD to themselves and do not fill it.  For the key passes: pairs of query heads 1.00 to 1.02 times as fast (CQ-8c10b, 32 / 8
+// heads, 64 x 8192, 96.9 -> 95.5 us), keys cached before RoPE 1.00 to 1.035 (CQ-8c8b, 32 heads, 8 x 4939, 39.2 -> 37.9).  Value
+// passes do without (bins: 0.98 at 32 x 1500 in pairs, 0.995 over pre-RoPE keys), and so do four heads over
+// pre-RoPE keys of CQ-2c8b (0.97 at 8 x 4939) and the kernel for one query head, which has two workgroups of eight wavefronts
+// on a CU (0.94 to 1.01).
 __device__ __forceinline__ void take_turns(int wave, int tile)
 {
     if (((tile ^ (wave >> 2)) & 1) != 0) __builtin_amdgcn_s_setprio(1);

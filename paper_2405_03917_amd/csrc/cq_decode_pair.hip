@@ -447,7 +447,6 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
                 pf[h] = 0;
             }
         }
-        take_turns(wave, k);
         // (no bin reaches 2^32: nothing is carried from one head's half to the other's)
         const unsigned long long both = pf[0] | ((unsigned long long)pf[1] << 32);
 #pragma unroll

@@ -398,7 +398,6 @@ __global__ __launch_bounds__(NT) void decode_rope_kernel(DecodeArgs a, const flo
     Cent16 rawv[EARLY ? NCH : 1][KB];
     unsigned lane_sum = 0;
     st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
-        take_turns(wave, k);
         const int lt = wave + k * NW;
         const float p = __builtin_amdgcn_exp2f(sc[lt * kTileTokens + lane] - m);
         unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
@@ -705,7 +704,6 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
     constexpr int kBatch = 8;                       // channel pairs per batch of centroids
     constexpr int GPB = kBatch / C;                 // groups (of each half of the head) per batch
     stk.run(kwalk, my_tiles, lane, [&](const Tile<GH, B>& w_in, int k) {
-        take_turns(wave, k);
         const int lt = wave + k * NW;
         Tile<GH, B> w = w_in;
         if (meets_new && tile0 + lt == tile_new) new_codes.patch(w, u_new, lane);
@@ -856,7 +854,6 @@ __global__ __launch_bounds__(NT) void decode_rope_gqa_kernel(DecodeArgs a, const
 
         unsigned lane_sum = 0;
         st.run(vwalk, my_tiles, lane, [&](const Tile<GH, B>& w, int k) {
-            take_turns(wave, k);
             const int lt = wave + k * NW;
             const float p = __builtin_amdgcn_exp2f(sch[lt * kTileTokens + lane] - m);
             unsigned pf = (unsigned)__builtin_fmaf(p, fx_scale, 0.5f);
