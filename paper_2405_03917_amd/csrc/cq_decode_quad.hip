@@ -79,6 +79,23 @@ __device__ __forceinline__ unsigned long long lanes_min_u64(unsigned long long v
     return v;
 }
 
+// This lane's and thread's number for what is done once per item (`turn`) at a place (SITE) of the kernel.  ROPE forms them anew:
+// kept through the tiles, they and what is derived from them would be spilled, and a spilled register comes back behind
+// every load under way.  (The fused step of CQ-8c8b spilled 60, and its first codes were requested when the codebooks had
+// arrived: 32 / 8 heads, 8 x 4939 27.5 -> 22.2 us without, 32 x 16384 117.6 -> 112.3.)
+struct Place {
+    int lane, tid;
+};
+template <bool ROPE, int SITE>
+__device__ __forceinline__ Place place(int turn, int wave)
+{
+    if constexpr (!ROPE) return Place{(int)threadIdx.x & 63, (int)threadIdx.x};
+    unsigned zero;
+    asm("v_mov_b32 %0, 0 ; %1 %2" : "=v"(zero) : "s"(turn), "n"(SITE));
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+    return Place{lane, 64 * wave + lane};
+}
+
 template <int GH, int C, bool ROPE, bool STEP, bool LAYERS>
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThreads) void decode_quad_kernel(
     DecodeArgs a, const float2* tile_tab, const float2* lane_tab, int items, int per_head)
@@ -166,11 +183,13 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         int n, split, t_n, tile0, tile1, n_tiles;
     };
     half4_t qreg[2];                                    // channels 4 (16 r + lane / 4) .. of head lane % 4
-    unsigned qpair[4];                                  // ROPE: both channels of pairs lane / 4 + 16 m of head lane % 4
+    uint16_t qrope[2][4];                               // ROPE: both channels of pairs lane / 4 + 16 m of head lane % 4
     Tile<GH, 8> krec, vtok;                             // vtok, cs_next: ROPE
     u32x4 vrec[2][2][PL];
     float2 cs_next[4];
-    unsigned xrow[2][C / 2];
+    // STEP: the new token's rows: the group that this thread searches; ROPE, for want of registers: a dword of the wavefront's
+    // 16 channels (of the groups that it searches), keys in lanes 0-7 of 16, values in lanes 8-15
+    unsigned xrow[2][ROPE ? 1 : C / 2];
     auto request = [&](const Item& it, int tile) {
         const size_t at = a.map.tile_index(it.n, hkv, min(tile, it.n_tiles - 1)) * TILE_BYTES;
 #pragma unroll
@@ -192,6 +211,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         }
     };
     auto open_item = [&](int at) {
+        const auto [lane, tid] = place<ROPE, 0>(at, wave);
         Item it;
         it.split = at % a.n_split;
         it.n = at / a.n_split;
@@ -204,19 +224,25 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         if constexpr (ROPE) {
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                qpair[m] = qrow[16 * m + (lane >> 2)] | (unsigned)qrow[16 * m + (lane >> 2) + kPairs] << 16;
+                qrope[0][m] = qrow[16 * m + (lane >> 2)];
+                qrope[1][m] = qrow[16 * m + (lane >> 2) + kPairs];
             }
         } else {
 #pragma unroll
             for (int i = 0; i < 2; ++i) qreg[i] = *reinterpret_cast<const half4_t*>(qrow + 64 * i + 4 * (lane >> 2));
         }
         if constexpr (STEP) {
-            const int g = tid / (NT / GH);
-            const size_t at_row = (size_t)it.n * a.x_new_stride + (size_t)hkv * D + g * C;
+            const size_t at_head = (size_t)it.n * a.x_new_stride + (size_t)hkv * D;
+            if constexpr (ROPE) {
+                const uint16_t* row = (lane & 8) ? xv_ptr : xk_ptr;
+                xrow[0][0] = *reinterpret_cast<const unsigned*>(row + at_head + 16 * wave + 2 * (lane & 7));
+            } else {
+                const int g = tid / (NT / GH);
 #pragma unroll
-            for (int i = 0; i < C / 2; ++i) {
-                xrow[0][i] = reinterpret_cast<const unsigned*>(xk_ptr + at_row)[i];
-                xrow[1][i] = reinterpret_cast<const unsigned*>(xv_ptr + at_row)[i];
+                for (int i = 0; i < C / 2; ++i) {
+                    xrow[0][i] = reinterpret_cast<const unsigned*>(xk_ptr + at_head + g * C)[i];
+                    xrow[1][i] = reinterpret_cast<const unsigned*>(xv_ptr + at_head + g * C)[i];
+                }
             }
         }
         request(it, it.tile0 + wave);
@@ -233,10 +259,12 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
             cu[i] = t.x;
             su[i] = t.y;
         }
-        for (int i = tid; i < kTrigPairs * 64; i += NT) {
-            const float2 t = lane_tab[kHeld * 64 + i];
-            *(lds_f2*)(kQuadTrig(GH) + (unsigned)i * 8) = float2_t{t.x, t.y};
-        }
+        static_assert(kTrigPairs * 64 % NT == 0, "whole rounds");
+        float2 t[kTrigPairs * 64 / NT];
+#pragma unroll
+        for (int i = 0; i < kTrigPairs * 64 / NT; ++i) t[i] = lane_tab[kHeld * 64 + i * NT + tid];
+#pragma unroll
+        for (int i = 0; i < kTrigPairs * 64 / NT; ++i) *(lds_f2*)(kQuadTrig(GH) + (unsigned)(i * NT + tid) * 8) = float2_t{t[i].x, t[i].y};
     }
 #pragma unroll
     for (int w = 0; w < 2; ++w)
@@ -252,6 +280,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         const bool has_new = STEP && tile_new >= it.tile0 && tile_new < it.tile1;
         if (has_new) {
             constexpr int TPG = NT / GH;
+            const auto [lane, tid] = place<ROPE, 1>(item, wave);
             const int g = tid / TPG;
             // (TPG neighbouring lanes search a group, each every TPG-th centroid in ascending order)
 #pragma unroll
@@ -259,7 +288,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
                 float x[C];
 #pragma unroll
                 for (int i = 0; i < C / 2; ++i) {
-                    const half2_t h = __builtin_bit_cast(half2_t, xrow[w][i]);
+                    unsigned word;
+                    if constexpr (ROPE) word = (unsigned)__builtin_amdgcn_ds_bpermute((8 * w + lane / TPG * (C / 2) + i) * 4, (int)xrow[0][0]);
+                    else word = xrow[w][i];
+                    const half2_t h = __builtin_bit_cast(half2_t, word);
                     x[2 * i] = (float)h.x;
                     x[2 * i + 1] = (float)h.y;
                 }
@@ -280,6 +312,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
             }
         }
 
+        unsigned qpair[4];                                  // ROPE: both channels in a register (here, where the codes are long under way)
+        if constexpr (ROPE) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) qpair[m] = qrope[0][m] | (unsigned)qrope[1][m] << 16;
+        }
         float4_t o[8];
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) o[cb] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -293,6 +330,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         float qa[4], qb[4];                                 // ROPE: the queries rotated to the tile's base position
         auto unpack = [&](int tile) {
             if (has_new && tile == tile_new) {
+                const int lane = place<ROPE, 2>(tile, wave).lane;
                 NewTokenCodes<GH, 8> c;
                 c.build(keys, u_new, lane);
                 c.patch(krec, u_new, lane);
@@ -536,6 +574,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         item += per_head;
         const bool more = item < items;
         if (more) it = open_item(item);
+        const auto [lane, tid] = place<ROPE, 3>(item, wave);
+        const int col = lane & 15, blk = lane >> 4;
 #pragma unroll
         for (int h = 0; h < QH; ++h) {
             const float sum = wave_sum(l[h]);
