@@ -542,6 +542,7 @@ cq_status decode_common(const void* q, const void* x_k_new, const void* x_v_new,
     a.x_new_stride = x_row_stride;
     a.tiles_per_split = tiles;
     a.n_split = n_split;
+    a.split_given = tokens_per_split != 0;
     a.partials = static_cast<float*>(workspace);
     a.out = static_cast<uint16_t*>(out);
     a.q_batch_stride = view ? view->q_batch_stride : (int64_t)n_q_heads * f.head_dim;
@@ -810,6 +811,7 @@ cq_status chunk_common(const void* q, const void* k_codes, const void* v_codes,
             a.x_new_stride = 0;
             a.tiles_per_split = c.tiles;
             a.n_split = c.n_split;
+            a.split_given = false;
             a.partials = static_cast<float*>(workspace);
             a.f = f;
             if ((st = launch_decode(a, static_cast<hipStream_t>(stream))) != CQ_OK) return st;

@@ -702,7 +702,9 @@ bool decode_takes_quads(const DecodeArgs& a)
 
 cq_status launch_decode_quad(const DecodeArgs& a_in, const float2* tile_tab, const float2* lane_tab, hipStream_t stream)
 {
-    DecodeArgs a = joined_splits(a_in);
+    // (over pre-RoPE keys every call of grouped queries comes here, and a given split fixes its bits in any batch: joining,
+    // which follows the batch, is for the library's own split there)
+    const DecodeArgs a = tile_tab && a_in.split_given ? a_in : joined_splits(a_in);
     const bool step = a.xk_new != nullptr;
     const cq_status st = tile_tab   ? (step ? launch_format<true, true, false>(a, tile_tab, lane_tab, stream)
                                             : launch_format<true, false, false>(a, tile_tab, lane_tab, stream))

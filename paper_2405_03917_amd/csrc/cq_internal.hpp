@@ -110,6 +110,7 @@ struct DecodeArgs {
     const uint16_t* xv_new;
     int64_t x_new_stride;
     int tiles_per_split, n_split;
+    bool split_given;         // by the caller (tokens_per_split), not the library's choice
     float* partials;          // [batch][n_q_heads][n_split][2 + head_dim]
     uint16_t* out;
     // q and out are [batch][n_q_heads][head_dim] with these batch strides (elements); sequence n

@@ -132,3 +132,26 @@ def test_rotated_keys_for_up_to_four_heads_equal_single_heads(c, qper, B, t, spl
     _close(out, cq.cq_decode_attention_rope(*a, seq_lens=lens, tokens_per_split=89 * 64))
     rows = out[::distinct]
     assert torch.equal(rows, rows[:1].expand_as(rows))
+
+
+@pytest.mark.parametrize("c", [8, 4])
+@pytest.mark.parametrize("qper,t,split", [(3, 300, 128), (4, 1500, 128), (2, 700, 64)])
+def test_a_given_split_fixes_the_bits_over_rotated_keys_in_every_batch(c, qper, t, split):
+    """Workgroups walk several splits of a large batch one after the other: each stays a partial of its own, as alone."""
+    B, distinct = 700, 3
+    fmt, ck, cv, q, kc, vc = _problem(t + c, c, 8, qper, 1, distinct, t)
+    t_cap = (t + 63) // 64 * 64
+    rope = cq.RopeTable(10000.0, t_cap)
+    k1, v1 = (codes_to_cache(x, fmt, t_cap).view(distinct, -1) for x in (kc, vc))
+    lens = torch.tensor([t, t // 3, 1], dtype=torch.int32, device="cuda")
+    ckd, cvd, qd = dev(ck), dev(cv), dev(q)
+
+    def run(at, sl):
+        return cq.cq_decode_attention_rope(qd[at].contiguous(), k1[at].flatten(), v1[at].flatten(), ckd, cvd, SCALE, fmt, t, t_cap, rope,
+                                           seq_lens=None if sl is None else sl[at].contiguous(), tokens_per_split=split)
+    at = torch.arange(B, device="cuda") % distinct
+    for sl in (None, lens):
+        out = run(at, sl)
+        for n in range(distinct):
+            rows = out[n::distinct]
+            assert torch.equal(rows.view(torch.int16), run(at[n:n + 1], sl).expand_as(rows).contiguous().view(torch.int16))
