@@ -686,8 +686,10 @@ cq_status launch_format(const DecodeArgs& a, const float2* tile_tab, const float
 //   CQ-8c8b  20 x 1100 13.0 -> 10.3, 40 x 1100 19.3 -> 16.6, 64 x 1100 35.1 -> 16.7, 20 x 4200 21.9 -> 19.4, 28 x 4200 27.5 -> 19.4,
 //            34 x 4200 33.8 -> 34.3, 20 x 16000 50.5 -> 54.0, 48 x 16000 92.5 -> 104.4, 28 x 16000 62.0 -> 55.0, 64 x 16000 122.7 -> 107.5;
 //            16 x 2000 11.0 -> 12.6
-// A tile of CQ-8c8b costs 434 clocks of the LDS here and 258 with tables, so long splits have to fill their rounds; one of
-// CQ-4c8b 476 and 515.  (CQ-4c8b gains below 66 tiles too; there calls stay with the kernels, and the bits, they had.)
+// A tile of CQ-8c8b costs 434 clocks of the LDS here and 258 with tables, so long splits, as they are walked here (joined), have
+// to fill their rounds: of 250 tiles 18 / 20 / 24 x 16000 50.7 / 51.7 / 51.7 -> 53.6 / 53.3 / 53.1, 28 x 16000 61.8 -> 54.1; of 125 tiles 18 x
+// 8000 30.3 -> 30.1, 12 x 16000 33.0 -> 33.0; in two rounds 34 x 8000 46.3 -> 56.7, 34 x 4200 33.6 -> 34.7, 34 x 2000 21.8 -> 20.8.  One of
+// CQ-4c8b costs 476 and 515.  (CQ-4c8b gains below 66 tiles too; there calls stay with the kernels, and the bits, they had.)
 bool decode_takes_quads(const DecodeArgs& a)
 {
     const int qper = a.n_q_heads / a.f.n_kv_heads;
@@ -697,7 +699,7 @@ bool decode_takes_quads(const DecodeArgs& a)
     if (items < 140) return false;
     if (a.f.c == 4) return a.tiles_per_split > 65;
     if (a.tiles_per_split < 16) return false;
-    return items * 100 >= rounds * 256 * 78 || a.tiles_per_split <= (rounds == 1 ? 128 : 64);
+    return items * 100 >= rounds * 256 * 78 || j.tiles_per_split <= (rounds == 1 ? 128 : 64);
 }
 
 cq_status launch_decode_quad(const DecodeArgs& a_in, const float2* tile_tab, const float2* lane_tab, hipStream_t stream)

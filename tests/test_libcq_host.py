@@ -383,6 +383,14 @@ def test_decode_plan_names_the_kernel_of_a_call():
     assert cq.load().cq_probe_decode_plan(ctypes.byref(f), 1, 32, 100, 0, 0, None, None) == cq.CQ_ERR_INVALID_ARG
 
 
+def test_long_splits_of_8c8b_go_in_fours_only_where_they_fill_the_chip():
+    # (of the split as it is walked: neighbouring ones joined: 250 tiles at 18 x 16000)
+    plan = lambda *a: cq.cq_probe_decode_plan(cq.CQFormat(8, 8, 128, 8), *a)[0]
+    assert [plan(b, 32, 16000) for b in (18, 19, 20, 24, 28, 32)] == [1, 1, 1, 1, 4, 4]
+    assert [plan(b, 32, 8000) for b in (18, 20, 28, 34)] == [4, 4, 4, 1] and plan(12, 32, 16000) == 4
+    assert [plan(34, 32, t) for t in (2000, 4200)] == [4, 1]
+
+
 def test_subbyte_formats_sizes_and_argument_checks_without_launching():
     lib = cq.load()
     for (c, b), (cf, bytes_th) in {(1, 2): (4, 32), (2, 2): (8, 16), (1, 4): (2, 64), (2, 4): (4, 32), (4, 4): (8, 16)}.items():
