@@ -990,19 +990,19 @@ int decode_max_tiles_per_split(const Derived& f)
     return 1 << 20;
 }
 
-unsigned* decode_merge_counters(hipStream_t stream, int rows) { return g_merge_counters.for_stream(stream, rows); }
-
 DecodePlan decode_plan(const DecodeArgs& a)
 {
-    if (decode_takes_quads(a)) return DecodePlan{4, 1};
+    DecodeArgs joined;
+    if (decode_takes_quads(a, &joined)) return DecodePlan{4, 1};
     return decode_takes_pairs(a) ? DecodePlan{2, decode_pair_chunk_tiles(a)} : DecodePlan{1, chunk_tiles(a)};
 }
 
 cq_status launch_decode(const DecodeArgs& a_in, hipStream_t stream)
 {
-    if (decode_takes_quads(a_in)) return launch_decode_quad(a_in, nullptr, nullptr, stream);
-    DecodeArgs a = a_in;
-    a.merge_counters = a.n_split > 1 ? decode_merge_counters(stream, a.batch * a.n_q_heads * (a.layers ? a.n_layers : 1)) : nullptr;
+    DecodeArgs a;
+    if (decode_takes_quads(a_in, &a)) return launch_decode_quad(a, stream);
+    a = a_in;
+    a.merge_counters = a.n_split > 1 ? g_merge_counters.for_stream(stream, a.batch * a.n_q_heads * (a.layers ? a.n_layers : 1)) : nullptr;
     // (a layer-batched launch is always a fused step: its table holds the new rows)
     const cq_status st = decode_takes_pairs(a) ? launch_decode_pair(a, stream)
                          : a.layers ? launch_format<true, true>(a, stream) : a.xk_new ? launch_format<true, false>(a, stream) : launch_format<false, false>(a, stream);

@@ -630,7 +630,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
 
 // Neighbouring splits of a call join where that fills the CUs as well: a workgroup walks its items one after the other,
 // and every item costs the merge of its wavefronts (about kItemTiles tiles).  Never more partials than the call's split
-// has, and decided by sizes alone.
+// has, and decided by sizes alone.  (By ceil(n_split / n), the splits to an item, of which there are about 2 sqrt(n_split): with all n
+// a call over 131072 tokens in splits of 64 took 11 us on the host.)
 constexpr int kItemTiles = 6;
 DecodeArgs joined_splits(const DecodeArgs& a)
 {
@@ -639,8 +640,9 @@ DecodeArgs joined_splits(const DecodeArgs& a)
     const int n_tiles = (a.t + kTileTokens - 1) / kTileTokens;
     DecodeArgs best = a;
     int64_t best_cost = -1;
-    for (int n = a.n_split; n >= 1; --n) {
-        const int tiles = (a.n_split + n - 1) / n * a.tiles_per_split, split = (n_tiles + tiles - 1) / tiles;
+    for (int n = a.n_split; n >= 1;) {
+        const int joined = (a.n_split + n - 1) / n, tiles = joined * a.tiles_per_split, split = (n_tiles + tiles - 1) / tiles;
+        n = (a.n_split + joined - 1) / joined - 1;
         const int64_t rounds = ((int64_t)a.batch * split + resident - 1) / resident, cost = rounds * (tiles + kItemTiles);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
@@ -690,29 +692,35 @@ cq_status launch_format(const DecodeArgs& a, const float2* tile_tab, const float
 // to fill their rounds: of 250 tiles 18 / 20 / 24 x 16000 50.7 / 51.7 / 51.7 -> 53.6 / 53.3 / 53.1, 28 x 16000 61.8 -> 54.1; of 125 tiles 18 x
 // 8000 30.3 -> 30.1, 12 x 16000 33.0 -> 33.0; in two rounds 34 x 8000 46.3 -> 56.7, 34 x 4200 33.6 -> 34.7, 34 x 2000 21.8 -> 20.8.  One of
 // CQ-4c8b costs 476 and 515.  (CQ-4c8b gains below 66 tiles too; there calls stay with the kernels, and the bits, they had.)
-bool decode_takes_quads(const DecodeArgs& a)
+bool decode_takes_quads(const DecodeArgs& a, DecodeArgs* joined)
 {
     const int qper = a.n_q_heads / a.f.n_kv_heads;
     if (a.f.b != 8 || a.f.c < 4 || a.f.head_dim != 128 || qper % kQuadHeads != 0) return false;
+    const int64_t items_per_split = (int64_t)a.batch * (a.n_q_heads / kQuadHeads);
+    if (items_per_split * a.n_split < 140 || a.tiles_per_split < (a.f.c == 4 ? 66 : 16)) return false;
     const DecodeArgs j = joined_splits(a);
-    const int64_t items = (int64_t)j.batch * (j.n_q_heads / kQuadHeads) * j.n_split, rounds = (items + 255) / 256;
+    const int64_t items = items_per_split * j.n_split, rounds = (items + 255) / 256;
     if (items < 140) return false;
-    if (a.f.c == 4) return a.tiles_per_split > 65;
-    if (a.tiles_per_split < 16) return false;
+    *joined = j;
+    if (a.f.c == 4) return true;
     return items * 100 >= rounds * 256 * 78 || j.tiles_per_split <= (rounds == 1 ? 128 : 64);
 }
 
-cq_status launch_decode_quad(const DecodeArgs& a_in, const float2* tile_tab, const float2* lane_tab, hipStream_t stream)
+cq_status launch_decode_quad(const DecodeArgs& a, hipStream_t stream)
 {
-    // (over pre-RoPE keys every call of grouped queries comes here, and a given split fixes its bits in any batch: joining,
-    // which follows the batch, is for the library's own split there)
-    const DecodeArgs a = tile_tab && a_in.split_given ? a_in : joined_splits(a_in);
-    const bool step = a.xk_new != nullptr;
-    const cq_status st = tile_tab   ? (step ? launch_format<true, true, false>(a, tile_tab, lane_tab, stream)
-                                            : launch_format<true, false, false>(a, tile_tab, lane_tab, stream))
-                         : a.layers ? launch_format<false, true, true>(a, nullptr, nullptr, stream)
-                         : step     ? launch_format<false, true, false>(a, nullptr, nullptr, stream)
+    const cq_status st = a.layers   ? launch_format<false, true, true>(a, nullptr, nullptr, stream)
+                         : a.xk_new ? launch_format<false, true, false>(a, nullptr, nullptr, stream)
                                     : launch_format<false, false, false>(a, nullptr, nullptr, stream);
+    if (st != CQ_OK || a.n_split == 1) return st;
+    return launch_decode_merge(a, stream);
+}
+
+cq_status launch_decode_quad_rope(const DecodeArgs& a_in, const float2* tile_tab, const float2* lane_tab, hipStream_t stream)
+{
+    // (every call of grouped queries comes here, and a given split fixes its bits in any batch: joining, which follows the
+    // batch, is for the library's own split)
+    const DecodeArgs a = a_in.split_given ? a_in : joined_splits(a_in);
+    const cq_status st = a.xk_new ? launch_format<true, true, false>(a, tile_tab, lane_tab, stream) : launch_format<true, false, false>(a, tile_tab, lane_tab, stream);
     if (st != CQ_OK || a.n_split == 1) return st;
     return launch_decode_merge(a, stream);
 }

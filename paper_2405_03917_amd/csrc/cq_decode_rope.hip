@@ -987,7 +987,7 @@ cq_status launch_decode_rope(const DecodeArgs& a, const float* tables, int t_cap
     const float2* lane_tab = tile_tab + (size_t)(t_cap / kTileTokens) * kPairs;
     cq_status st = CQ_ERR_UNSUPPORTED;
     const bool shared = a.f.b == 8 && a.f.head_dim == 128 && a.n_q_heads >= 2 * a.f.n_kv_heads && a.tiles_per_split <= kGqaTiles;
-    if (shared && a.f.c >= 4) return launch_decode_quad(a, tile_tab, lane_tab, stream);
+    if (shared && a.f.c >= 4) return launch_decode_quad_rope(a, tile_tab, lane_tab, stream);
     if (shared) {
         const bool step = a.xk_new != nullptr;
         if (a.f.gh == 64 && a.f.c == 2)

@@ -214,11 +214,11 @@ struct DecodePlan {
 };
 DecodePlan decode_plan(const DecodeArgs& a);
 cq_status launch_decode_pair(const DecodeArgs& a, hipStream_t stream);
-// grouped queries, up to four query heads per workgroup, both codebooks in LDS (cq_decode_quad.hip)
-bool decode_takes_quads(const DecodeArgs& a);
-// arrival counters for the rows of a launch on `stream`; null: none (under capture, beyond their number)
-unsigned* decode_merge_counters(hipStream_t stream, int rows);
-cq_status launch_decode_quad(const DecodeArgs& a, const float2* tile_tab, const float2* lane_tab, hipStream_t stream);    // (tables: keys cached before RoPE)
+// grouped queries, up to four query heads per workgroup, both codebooks in LDS (cq_decode_quad.hip): whether a call goes
+// there, and its arguments with neighbouring splits joined; the launch of those; that of keys cached before RoPE
+bool decode_takes_quads(const DecodeArgs& a, DecodeArgs* joined);
+cq_status launch_decode_quad(const DecodeArgs& joined, hipStream_t stream);
+cq_status launch_decode_quad_rope(const DecodeArgs& a, const float2* tile_tab, const float2* lane_tab, hipStream_t stream);
 // centroids fp16 [G][2^b][c] of a sub-byte format -> fp16 [G / fuse][256][c fuse] of its fused format
 cq_status launch_expand_codebook(const uint16_t* centroids, const Derived& f, uint16_t* fused, hipStream_t stream);
 // writes `count` records of a layer table (device memory) from values passed with the launch
