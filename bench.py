@@ -441,7 +441,7 @@ def extra_measurements(cq, synth, torch):
         ck_ = torch.randn((fmt_g.groups, 256, 8), device="cuda", generator=gen).half()
         cv_ = torch.randn((fmt_g.groups, 256, 8), device="cuda", generator=gen).half()
         keep.append((kc_, vc_, ck_, cv_))
-        shared_calls.append(cq.prepare_decode_attention_rope(qg, kc_, vc_, ck_, cv_, 0.088, fmt_g, Tg, Tg, rope_g, tokens_per_split=split_g)[0])
+        shared_calls.append(cq.prepare_decode_attention_rope(qg, kc_, vc_, ck_, cv_, 0.088, fmt_g, Tg, Tg, rope_g)[0])
         per_head_calls.append(cq.prepare_decode_attention_rope(qg, kc_, vc_, ck_, cv_, 0.088, fmt_g, Tg, Tg, rope_g, tokens_per_split=Tg)[0])
     ms_sh, ms_ph = (time_rotating(torch, c, 3) for c in (shared_calls, per_head_calls))
     out["decode_gqa_pre_rope_keys_cq8c8b_batch32_ctx16384"] = {

@@ -424,7 +424,8 @@ CQ_API cq_status cq_chunk_attention_paged(const void *q, const void *k_pool, con
  * cq_decode_attention_rope, bit for bit.
  * Formats: head_dim 128.  For b = 8 (CQ-8c8b, CQ-4c8b, CQ-2c8b) the kernel keeps a head's key
  * centroids (64 KiB) on chip; CQ-8c10b (256 KiB per head) reads them from global memory.
- * Workspace size: cq_decode_workspace_bytes with the tokens_per_split actually used.
+ * Workspace size: cq_decode_workspace_bytes with the tokens_per_split given, or (0) with that default.  With 0 and grouped
+ * queries the library may take several of its splits together, which a given split, also of that length, forbids.
  * Errors: as cq_decode_attention; CQ_ERR_INVALID_ARG also for a missing or too short table.
  */
 CQ_API size_t cq_rope_table_bytes(int32_t head_dim, int32_t positions);

@@ -695,14 +695,13 @@ def prepare_decode_attention_rope(q, k_codes, v_codes, k_centroids, v_centroids,
     """Check and marshal the arguments of cq_decode_attention_rope once.  Returns (call, out)."""
     if not isinstance(rope, RopeTable):
         raise TypeError("rope must be a RopeTable")
-    if tokens_per_split == 0:
-        tokens_per_split = cq_decode_rope_default_split(fmt, int(q.shape[0]), int(q.shape[1]), t)
-        if tokens_per_split == 0:
-            raise CQError(CQ_ERR_UNSUPPORTED, "cq_decode_rope_default_split")
+    split = tokens_per_split or cq_decode_rope_default_split(fmt, int(q.shape[0]), int(q.shape[1]), t)
+    if split == 0:
+        raise CQError(CQ_ERR_UNSUPPORTED, "cq_decode_rope_default_split")
     call, out = prepare_decode_attention(q, k_codes, v_codes, k_centroids, v_centroids, scale, fmt, t, t_cap,
-                                         seq_lens, tokens_per_split, out, workspace)
+                                         seq_lens, split, out, workspace)
     a = call._args
-    args = a[:13] + (rope.table.data_ptr(), rope.positions) + a[13:]
+    args = a[:12] + (tokens_per_split, rope.table.data_ptr(), rope.positions) + a[13:]
     return PreparedCall(load().cq_decode_attention_rope, args, call._keep + (rope,), "cq_decode_attention_rope"), out
 
 
@@ -723,14 +722,13 @@ def prepare_decode_step_rope(q, x_k_new, x_v_new, k_codes, v_codes, k_centroids,
     """Check and marshal the arguments of cq_decode_step_rope once.  Returns (call, out)."""
     if not isinstance(rope, RopeTable):
         raise TypeError("rope must be a RopeTable")
-    if tokens_per_split == 0:
-        tokens_per_split = cq_decode_rope_default_split(fmt, int(q.shape[0]), int(q.shape[1]), t)
-        if tokens_per_split == 0:
-            raise CQError(CQ_ERR_UNSUPPORTED, "cq_decode_rope_default_split")
+    split = tokens_per_split or cq_decode_rope_default_split(fmt, int(q.shape[0]), int(q.shape[1]), t)
+    if split == 0:
+        raise CQError(CQ_ERR_UNSUPPORTED, "cq_decode_rope_default_split")
     call, out = prepare_decode_step(q, x_k_new, x_v_new, k_codes, v_codes, k_centroids, v_centroids, scale, fmt, t,
-                                    t_cap, seq_lens, tokens_per_split, out, workspace)
+                                    t_cap, seq_lens, split, out, workspace)
     a = call._args
-    args = a[:16] + (rope.table.data_ptr(), rope.positions) + a[16:]
+    args = a[:15] + (tokens_per_split, rope.table.data_ptr(), rope.positions) + a[16:]
     return PreparedCall(load().cq_decode_step_rope, args, call._keep + (rope,), "cq_decode_step_rope"), out
 
 
@@ -894,7 +892,10 @@ def _paged_decode(fn_name, q, x_k_new, x_v_new, k_pool, v_pool, k_centroids, v_c
     if out is None:
         out = torch.empty((batch, n_q_heads, fmt.head_dim), dtype=torch.float16, device=q.device)
     if workspace is None:
-        workspace = torch.empty(max(16, cq_decode_workspace_bytes(fmt, batch, n_q_heads, t, tokens_per_split)),
+        split = tokens_per_split
+        if rope is not None and split == 0:
+            split = cq_decode_rope_default_split(fmt, batch, n_q_heads, t)
+        workspace = torch.empty(max(16, cq_decode_workspace_bytes(fmt, batch, n_q_heads, t, split)),
                                 dtype=torch.uint8, device=q.device)
     common = (k_pool.data_ptr(), v_pool.data_ptr(), k_centroids.data_ptr(), v_centroids.data_ptr(), float(scale),
               ctypes.byref(fmt._c()), batch, n_q_heads, t, ctypes.byref(pages._c), sl_ptr, tokens_per_split,
@@ -933,8 +934,6 @@ def cq_decode_attention_rope_paged(q, k_pool, v_pool, k_centroids, v_centroids, 
                                    pages: PageTable, rope: RopeTable, seq_lens=None, tokens_per_split: int = 0,
                                    out=None, workspace=None, stream=None):
     """cq_decode_attention_rope over paged pools."""
-    if tokens_per_split == 0:
-        tokens_per_split = cq_decode_rope_default_split(fmt, int(q.shape[0]), int(q.shape[1]), t)
     return _paged_decode("cq_decode_attention_rope_paged", q, None, None, k_pool, v_pool, k_centroids, v_centroids,
                          scale, fmt, t, pages, seq_lens, tokens_per_split, out, workspace, stream, rope=rope)
 
@@ -943,8 +942,6 @@ def cq_decode_step_rope_paged(q, x_k_new, x_v_new, k_pool, v_pool, k_centroids, 
                               fmt: CQFormat, t: int, pages: PageTable, rope: RopeTable, seq_lens=None,
                               tokens_per_split: int = 0, out=None, workspace=None, stream=None):
     """cq_decode_step_rope over paged pools."""
-    if tokens_per_split == 0:
-        tokens_per_split = cq_decode_rope_default_split(fmt, int(q.shape[0]), int(q.shape[1]), t)
     return _paged_decode("cq_decode_step_rope_paged", q, x_k_new, x_v_new, k_pool, v_pool, k_centroids, v_centroids,
                          scale, fmt, t, pages, seq_lens, tokens_per_split, out, workspace, stream, rope=rope)
 
