@@ -443,7 +443,6 @@ constexpr unsigned kFewWaveBytes = 2048;                // of a wavefront: 64 to
 constexpr unsigned kFewPairs = kMergeBase + kWaves * kFewWaveBytes;
 constexpr unsigned kFewLds = kFewPairs + kWaves * 4 * 8;
 static_assert(kTileTokens * 32 == kFewWaveBytes && 4 * 128 * 4 == kFewWaveBytes, "a wavefront's room");
-constexpr float kNoScore = -3.0e38f;                    // the reference of a row that has seen no token: finite, and below every score
 
 template <int C>
 __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves * 64) void chunk_few_kernel(ChunkArgs a, int per_head, int items)

@@ -323,7 +323,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         float ref[QH], l[QH];                               // per head; l: this lane's tokens
 #pragma unroll
         for (int h = 0; h < QH; ++h) {
-            ref[h] = -INFINITY;
+            ref[h] = kNoScore;
             l[h] = 0.f;
         }
         unsigned d[GH / 4], z[2][2][2];                     // codes of the tile to come: keys in group order, values as picked
@@ -596,17 +596,16 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kQuadThr
         static_assert(NT == QH * D, "one output per thread");
         const int h = tid / D, ch = tid % D;
         float2_t ml[NW];
-        float m = -INFINITY;
+        float m = kNoScore;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             ml[w] = *(lds_f2*)(kQuadPairs + (unsigned)(w * QH + h) * 8);
             m = fmaxf(m, ml[w][0]);
         }
-        const float mz = m == -INFINITY ? 0.f : m;          // (a split beyond its sequence's end: weights 0)
-        float sum = 0.f, ll = 0.f;
+        float sum = 0.f, ll = 0.f;                          // (a split beyond its sequence's end: m = kNoScore, both 0)
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float weight = __builtin_amdgcn_exp2f(ml[w][0] - mz);
+            const float weight = __builtin_amdgcn_exp2f(ml[w][0] - m);
             sum = __builtin_fmaf(*(lds_f*)(kQuadWork + (unsigned)(w * QH * D + tid) * 4), weight, sum);
             ll = __builtin_fmaf(ml[w][1], weight, ll);
         }

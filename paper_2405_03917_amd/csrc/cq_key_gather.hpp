@@ -9,6 +9,9 @@ namespace cq {
 namespace {
 
 constexpr int kPairs = 64;                        // head_dim / 2
+// The softmax reference of a head or row that has seen no token.  Finite: tokens that score -inf (masked, or beyond the
+// range of fp32) then have weight 2^-inf = 0, where a reference of -inf gives 2^(-inf + inf).
+constexpr float kNoScore = -3.0e38f;
 
 template <int C>
 struct CenVec {

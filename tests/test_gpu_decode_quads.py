@@ -6,7 +6,7 @@ import torch
 
 import paper_2405_03917_amd as cq
 
-from gpu_util import codes_to_cache, dev
+from gpu_util import check_attention, codes_to_cache, dev
 from test_gpu_decode_pairs import SCALE, _attend, _close, _pools, _problem
 from test_gpu_large_scores import _case, _check, _reference, _scale
 
@@ -155,3 +155,30 @@ def test_a_given_split_fixes_the_bits_over_rotated_keys_in_every_batch(c, qper, 
         for n in range(distinct):
             rows = out[n::distinct]
             assert torch.equal(rows.view(torch.int16), run(at[n:n + 1], sl).expand_as(rows).contiguous().view(torch.int16))
+
+
+@pytest.mark.parametrize("c,t", [(8, 1000), (4, 4200)])
+@pytest.mark.parametrize("rotated", [False, True])
+def test_tokens_beyond_the_range_of_fp32_have_no_weight(c, t, rotated):
+    """A tile whose every token scores -inf for some heads (finite operands, a scale that overflows) and the others score 0."""
+    hq, hkv, B = 8, 2, 70
+    fmt, ck, cv, q, kc, vc = _problem(c, c, 8, hq, hkv, 1, t)
+    g = 64 // c - 1                           # (its last channel: the pair that turns slowest, not past a right angle here)
+    ck[:], q[:], kc[:] = 0, 0, 0
+    ck[g::fmt.groups // hkv, 1, c - 1] = -60000.0
+    q[:, ::2, 63] = 1.0                       # (the odd heads score 0 everywhere)
+    kc[:, :64] = 1
+    t_cap = (t + 63) // 64 * 64
+    at = torch.zeros(B, dtype=torch.long, device="cuda")
+    k, v = (codes_to_cache(x, fmt, t_cap).view(1, -1)[at].flatten() for x in (kc, vc))
+    a = (dev(q)[at].contiguous(), k, v, dev(ck), dev(cv), 1e34, fmt, t, t_cap)
+    if rotated:
+        out = cq.cq_decode_attention_rope(*a, cq.RopeTable(10000.0, t_cap))
+    else:
+        assert cq.cq_probe_decode_plan(fmt, B, hq, t)[0] == 4
+        out = cq.cq_decode_attention(*a)
+    vals = cv.astype(np.float64)[np.arange(fmt.groups), vc[0]].reshape(t, hkv, 128)
+    want = np.empty((hq, 128))
+    for h in range(hq):
+        want[h] = vals[64 if h % 2 == 0 else 0:, h // (hq // hkv)].mean(0)
+    check_attention(out.cpu().numpy(), np.broadcast_to(want, (B, hq, 128)))
