@@ -44,9 +44,17 @@ __device__ __forceinline__ void lds_barrier()
 
 // The wavefronts of a SIMD (numbers equal modulo 4) take turns in priority from tile to tile.  Left alone the oldest goes first
 // whenever two are ready: it ends its share of the tiles early and the workgroup waits for the others, which then have
-// the SIMD to themselves and do not fill it.  For the key passes: pairs of query heads 1.00 to 1.02 times as fast (CQ-8c10b, 32 / 8
-// heads, 64 x 8192, 96.9 -> 95.5 us), keys cached before RoPE 1.00 to 1.035 (CQ-8c8b, 32 heads, 8 x 4939, 39.2 -> 37.9).  Value
-// passes do without (bins: 0.98 at 32 x 1500 in pairs, 0.995 over pre-RoPE keys), and so do four heads over
+// the SIMD to themselves and do not fill it.  For key passes, and where a wavefront has several tiles (with one it is a
+// lasting preference).  Without -> with, us, on the same buffers:
+//   Pairs of query heads, chunks in which every wavefront has all its tiles, not CQ-4c8b: CQ-8c10b, 32 / 8 heads, 64 x 8192 95.2 -> 93.8, 32 x
+//   16384 73.9 -> 72.7; 16 / 8 heads, CQ-8c8b 64 x 8192 38.6 -> 38.0 (chunks of 8 tiles; of 4: 26.4 -> 26.6), CQ-2c8b 64 x 8192 107.5 ->
+//   106.3.  In every chunk: CQ-8c10b 64 x 300 44.8 -> 45.7, CQ-8c8b 64 x 1000 17.9 -> 18.3, CQ-2c8b 64 x 2500 44.4 -> 45.4, CQ-4c8b 32 x 16384
+//   51.2 -> 54.6.  The bins and the merge follow at equal priority.
+//   One head over pre-RoPE keys (32 heads): CQ-8c8b 8 x 4939 37.6 -> 36.4, 8 x 16384 89.4 -> 85.1, CQ-4c8b 105.7 -> 101.2, CQ-2c8b 8 x 4939 56.2 ->
+//   55.2; below two tiles to a wavefront 1.00 to 1.01 times the time, CQ-2c8b excepted, which does without there (32 x 300 72.5, with them
+//   73.1) and ends the key pass at equal priority.  CQ-8c8b and 4c8b go on at the priority of their last key tile: setting it back made no
+//   difference above 0.5 %.
+// Value passes have none of it (bins: 0.98 at 32 x 1500 in pairs, 0.995 over pre-RoPE keys), nor have four heads over
 // pre-RoPE keys of CQ-2c8b (0.97 at 8 x 4939) and the kernel for one query head, which has two workgroups of eight wavefronts
 // on a CU (0.94 to 1.01).
 __device__ __forceinline__ void take_turns(int wave, int tile)

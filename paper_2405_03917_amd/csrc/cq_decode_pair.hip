@@ -392,9 +392,9 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
         float s[H];
     };
     Scores sreg[NS];
-    auto score_tile = [&](const Tile<GH, B>& w_in, int k) {
+    auto score_tile = [&](const Tile<GH, B>& w_in, int k, bool turns) {
         Scores score;
-        take_turns(wave, k);
+        if (turns) take_turns(wave, k);
         const int tile = tile0 + wave + k * NW;
         Tile<GH, B> w = w_in;
         if (meets_new && tile == tile_new) new_codes.patch(w, u_new, lane);
@@ -489,12 +489,13 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
         Scores none;
 #pragma unroll
         for (int h = 0; h < H; ++h) none.s[h] = -INFINITY;
+        constexpr bool kTurns = B == 10 || GH == 64 || (GH == 16 && NS == 8);      // (of a FULL chunk; see take_turns)
         if constexpr (FULL) {
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
                 // (the tile exists; the test keeps each tile's arithmetic in a block of its own, which the
                 // compiler schedules with far fewer registers than the chunk as one block)
-                sreg[i] = tile_exists(c, i) ? score_tile(buf[i % PF], c * NS + i) : none;
+                sreg[i] = tile_exists(c, i) ? score_tile(buf[i % PF], c * NS + i, kTurns) : none;
                 // the request PF tiles ahead: a key tile of this chunk, then its first value tiles
                 buf[i % PF] = i + PF < NS ? request(kbase, c, i + PF, pages) : request(vbase, c, i + PF - NS, pages);
                 __builtin_amdgcn_sched_barrier(0);
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
 #pragma unroll
                     for (int ii = 0; ii < PF; ++ii) {
                         const int i = ib * PF + ii;
-                        sreg[i] = tile_exists(c, i) ? score_tile(buf[ii], c * NS + i) : none;
+                        sreg[i] = tile_exists(c, i) ? score_tile(buf[ii], c * NS + i, false) : none;
                         if (i + PF < NS) buf[ii] = request(kbase, c, i + PF, pages);
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -521,6 +522,7 @@ __global__ __launch_bounds__(kPairThreads, 4) void decode_pair_kernel(DecodeArgs
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if constexpr (FULL && kTurns) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             const float wave_m = wave_max(lane_m[h]);

@@ -276,8 +276,9 @@ __global__ __launch_bounds__(NT) void decode_rope_kernel(DecodeArgs a, const flo
 #pragma unroll
         for (int e = 0; e < kBatch; ++e) { cur[e].c = first[e].c; cur[e].s = first[e].s; }
     }
+    const bool turns = C != 2 || tile1 - tile0 >= 2 * NW;
     stk.run(kwalk, my_tiles, lane, [&](const Tile<GH, B>& w_in, int k) {
-        take_turns(wave, k);
+        if (turns) take_turns(wave, k);
         const int lt = wave + k * NW;
         Tile<GH, B> w = w_in;
         if (meets_new && tile0 + lt == tile_new) new_codes.patch(w, u_new, lane);
@@ -364,6 +365,7 @@ __global__ __launch_bounds__(NT) void decode_rope_kernel(DecodeArgs a, const flo
         sc[lt * kTileTokens + lane] = sv;
         lane_max = fmaxf(lane_max, sv);
     }, [] {});
+    if constexpr (C == 2) __builtin_amdgcn_s_setprio(0);
     st.begin(vwalk, my_tiles, lane);
 
     lane_max = wave_max(lane_max);
