@@ -680,23 +680,24 @@ cq_status launch_format(const DecodeArgs& a, const float2* tile_tab, const float
 }  // namespace
 
 // Whether a call over keys as stored goes here rather than to the kernels with tables and bins (cq_decode.hip, cq_decode_pair.hip):
-// query heads in fours, enough items for the CUs (one workgroup each, 256), and splits long enough; 32 / 8 heads, tables ->
-// here, us per cq_decode_attention call:
-//   CQ-4c8b  18 x 1100 17.3 -> 11.1, 34 x 1100 26.1 -> 18.2, 64 x 1100 40.4 -> 18.5, 20 x 4200 31.0 -> 21.3, 34 x 4200 49.1 -> 38.1,
-//            20 x 16000 80.2 -> 60.1, 48 x 16000 135.0 -> 115.5, 64 x 16000 176.7 -> 133.4; 16 x 2000 (128 items) 13.1 -> 14.1
-//   CQ-8c8b  20 x 1100 13.0 -> 10.3, 40 x 1100 19.3 -> 16.6, 64 x 1100 35.1 -> 16.7, 20 x 4200 21.9 -> 19.4, 28 x 4200 27.5 -> 19.4,
-//            34 x 4200 33.8 -> 34.3, 20 x 16000 50.5 -> 54.0, 48 x 16000 92.5 -> 104.4, 28 x 16000 62.0 -> 55.0, 64 x 16000 122.7 -> 107.5;
-//            16 x 2000 11.0 -> 12.6
+// query heads in fours, enough items for the CUs (one workgroup each, 256), and, of CQ-8c8b, splits that are short or
+// fill their rounds; 32 / 8 heads, tables -> here, us per cq_decode_attention call:
+//   CQ-4c8b  18 x 64 11.6 -> 7.0, 64 x 64 31.4 -> 9.7, 64 x 300 32.6 -> 11.9, 18 x 1100 17.1 -> 10.5, 64 x 1100 41.3 -> 18.6, 20 x 2000 20.9 -> 13.4,
+//            12 x 8000 (two splits) 31.4 -> 22.9, 34 x 4200 49.0 -> 38.1, 48 x 16000 131 -> 116, 64 x 16000 189 -> 131; with 128 items (16
+//            sequences, which fill the CUs in pairs) 300 9.1 -> 7.7, 2000 13.2 -> 13.4, 4200 18.0 -> 20.7, 16000 46.9 -> 58.7
+//   CQ-8c8b  18 x 64 10.5 -> 7.1, 64 x 64 31.3 -> 8.7, 64 x 300 31.8 -> 10.9, 18 x 1100 13.0 -> 10.1, 64 x 1100 36.0 -> 17.1, 20 x 4200 22.2 -> 19.3,
+//            28 x 4200 27.4 -> 19.5, 64 x 16000 123 -> 105; 128 items: 300 9.0 -> 7.2, 2000 10.9 -> 12.1
+// (the fused step, with its search here, alike: 18 x 64 17.4 -> 9.6 and 15.4 -> 8.8, 34 x 2000 39.6 -> 27.9 and 29.8 -> 25.4).
 // A tile of CQ-8c8b costs 434 clocks of the LDS here and 258 with tables, so long splits, as they are walked here (joined), have
 // to fill their rounds: of 250 tiles 18 / 20 / 24 x 16000 50.7 / 51.7 / 51.7 -> 53.6 / 53.3 / 53.1, 28 x 16000 61.8 -> 54.1; of 125 tiles 18 x
 // 8000 30.3 -> 30.1, 12 x 16000 33.0 -> 33.0; in two rounds 34 x 8000 46.3 -> 56.7, 34 x 4200 33.6 -> 34.7, 34 x 2000 21.8 -> 20.8.  One of
-// CQ-4c8b costs 476 and 515.  (CQ-4c8b gains below 66 tiles too; there calls stay with the kernels, and the bits, they had.)
+// CQ-4c8b costs 476 and 515.
 bool decode_takes_quads(const DecodeArgs& a, DecodeArgs* joined)
 {
     const int qper = a.n_q_heads / a.f.n_kv_heads;
     if (a.f.b != 8 || a.f.c < 4 || a.f.head_dim != 128 || qper % kQuadHeads != 0) return false;
     const int64_t items_per_split = (int64_t)a.batch * (a.n_q_heads / kQuadHeads);
-    if (items_per_split * a.n_split < 140 || a.tiles_per_split < (a.f.c == 4 ? 66 : 16)) return false;
+    if (items_per_split * a.n_split < 140) return false;
     const DecodeArgs j = joined_splits(a);
     const int64_t items = items_per_split * j.n_split, rounds = (items + 255) / 256;
     if (items < 140) return false;

@@ -128,7 +128,7 @@ def _pools(fmt, k1, v1, B, tiles, seed):
 
 # (16 wavefronts of at most 8 tiles, of 16 with 10-bit codes, make a chunk: 8192 or 16384 tokens)
 PAGED = [(4, 1, 128, 8900, 8960, "growing"), (4, 1, 128, 8900, 8960, "opposed"), (4, 2, 64, 3000, 768, "plain"),
-         (8, 2, 64, 130, 0, "plain"), (4, 1, 250, 700, 0, "plain"), (32, 8, 8, 2100, 1088, "plain")]
+         (8, 2, 64, 130, 0, "plain"), (2, 1, 500, 700, 0, "plain"), (32, 8, 8, 2100, 1088, "plain")]
 
 
 @pytest.mark.parametrize("c,b", [(8, 8), (4, 8), (2, 8), (8, 10)])

@@ -14,9 +14,11 @@ pytestmark = pytest.mark.gpu
 
 # (query heads, KV heads, batch, t, split): the shortest contexts and the fewest items that go here, odd ends, two quads
 # per KV head, more items than CUs (a workgroup walks several), splits that join and splits that do not
-SHAPES = {8: [(4, 1, 140, 961, 0, "plain"), (8, 1, 70, 1024, 0, "plain"), (32, 8, 18, 1025, 0, "plain"), (4, 1, 300, 1000, 0, "plain"),
-              (4, 1, 150, 2049, 1088, "plain"), (8, 2, 20, 4100, 1024, "growing"), (8, 2, 20, 4100, 1024, "opposed"), (4, 1, 140, 3000, 3008, "shrinking")],
-          4: [(4, 1, 140, 4161, 0, "plain"), (8, 2, 70, 4224, 0, "plain"), (4, 1, 150, 8500, 4288, "growing"), (4, 1, 36, 16800, 4224, "opposed")]}
+SHAPES = {8: [(4, 1, 140, 1, 0, "plain"), (8, 2, 70, 65, 0, "plain"), (4, 1, 140, 961, 0, "plain"), (8, 1, 70, 1024, 0, "plain"), (32, 8, 18, 1025, 0, "plain"),
+              (4, 1, 300, 1000, 0, "plain"), (4, 1, 150, 2049, 1088, "plain"), (8, 2, 20, 4100, 1024, "growing"), (8, 2, 20, 4100, 1024, "opposed"),
+              (4, 1, 140, 3000, 3008, "shrinking")],
+          4: [(4, 1, 140, 1, 0, "plain"), (4, 1, 300, 65, 0, "plain"), (32, 8, 18, 1500, 0, "plain"), (4, 1, 140, 4161, 0, "plain"), (8, 2, 70, 4224, 0, "plain"),
+              (4, 1, 150, 8500, 4288, "growing"), (4, 1, 36, 16800, 4224, "opposed")]}
 LENS = lambda t: torch.tensor([t, max(1, t - 1), max(1, t // 2), 1, max(1, t - 64)], dtype=torch.int32, device="cuda")
 
 

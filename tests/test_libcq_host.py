@@ -364,12 +364,15 @@ def test_chunk_attention_sizes_and_argument_checks_without_launching():
 
 
 def test_decode_plan_names_the_kernel_of_a_call():
-    plan, gqa, mha = cq.cq_probe_decode_plan, cq.CQFormat(4, 8, 128, 8), cq.CQFormat(4, 8, 128, 32)
+    plan, gqa, mha, twos = cq.cq_probe_decode_plan, cq.CQFormat(4, 8, 128, 8), cq.CQFormat(4, 8, 128, 32), cq.CQFormat(4, 8, 128, 16)
     assert plan(mha, 16, 32, 4096) == (1, 8) and plan(mha, 16, 32, 16384) == (1, 16)           # one query head per KV head
     # grouped queries: from 256 workgroups of two heads on, byte codes with a last round at least 0.85 full
-    assert [plan(gqa, b, 32, 2000)[0] for b in (15, 16, 20, 27, 28, 32)] == [1, 2, 1, 1, 2, 2]
+    assert [plan(twos, b, 32, 2000)[0] for b in (15, 16, 20, 27, 28, 32)] == [1, 2, 1, 1, 2, 2]
+    # heads in fours: from 140 workgroups of four heads on, at any length
+    assert [plan(gqa, b, 32, 2000)[0] for b in (15, 16, 18, 20, 32)] == [1, 2, 4, 4, 4]
+    assert [plan(cq.CQFormat(c, 8, 128, 8), b, 32, t)[0] for c in (4, 8) for b in (17, 18) for t in (1, 1000)] == [1, 1, 4, 4] * 2
     assert [plan(cq.CQFormat(8, 10, 128, 8), b, 32, 2000) for b in (15, 16, 20)] == [(1, 16), (2, 8), (2, 8)]
-    assert plan(gqa, 32, 32, 4096) == (2, 4) and plan(gqa, 32, 32, 4097) == (2, 8)
+    assert plan(twos, 32, 32, 4096) == (2, 4) and plan(gqa, 16, 32, 4097) == (2, 8)
     assert plan(gqa, 8, 32, 4096)[0] == 1 and plan(gqa, 8, 32, 4096, 2048)[0] == 2             # two splits
     assert plan(cq.CQFormat(4, 8, 128, 8), 64, 24, 2000)[0] == 1                               # three heads per KV head
     # the shortest splits of CQ-8c8b have a form of their own, not in layer-batched launches
