@@ -232,6 +232,9 @@ def test_chunk_attention_sweep(case):
 
 @pytest.mark.parametrize("c", [8, 4])
 @pytest.mark.parametrize("m,hq,hkv,B,T,scale", [
+    (3, 2, 2, 2, 250, -0.09),          # 3 and 4 rows (three or four tokens, one query head): lane = token
+    (4, 3, 3, 2, 300, -0.09),
+    (4, 2, 2, 2, 330, 0.0),
     (8, 2, 2, 2, 250, 0.09),           # 8 rows: both halves of the probabilities in one product
     (3, 6, 2, 3, 640, 0.09),           # 9 rows
     (4, 8, 2, 2, 229, -0.09),          # one block of 16, scores falling with the product

@@ -184,3 +184,74 @@ def test_tokens_beyond_the_range_of_fp32_have_no_weight(c, t, rotated):
     for h in range(hq):
         want[h] = vals[64 if h % 2 == 0 else 0:, h // (hq // hkv)].mean(0)
     check_attention(out.cpu().numpy(), np.broadcast_to(want, (B, hq, 128)))
+
+
+@pytest.mark.parametrize("c", [8, 4])
+@pytest.mark.parametrize("rotated,qper,hkv,B,t,split", [(True, 4, 1, 300, 700, 0), (True, 3, 1, 270, 700, 128), (True, 4, 2, 140, 130, 64), (True, 2, 1, 300, 1, 0),
+                                                        (False, 4, 1, 300, 1000, 0), (False, 8, 2, 70, 700, 384)])
+def test_the_fused_step_of_workgroups_with_several_items(c, rotated, qper, hkv, B, t, split):
+    """Every item brings its own new rows (rows of a wider array) and its own search: cq_encode_kv, sequence by sequence, then
+    the attention, bit for bit, with the same codes in the caches; also over pages."""
+    distinct, hq = 7, qper * hkv
+    fmt, ck, cv, q, kc, vc = _problem(t + c, c, 8, hq, hkv, distinct, t)
+    tiles = (t + 63) // 64
+    t_cap = tiles * 64
+    k1, v1 = (codes_to_cache(x, fmt, t_cap).view(distinct, -1) for x in (kc, vc))
+    at = torch.arange(B, device="cuda") % distinct
+    lens1 = torch.tensor([t, max(1, t - 1), max(1, t // 2), 1, max(1, t - 64), max(1, t // 3), min(t, 65)], dtype=torch.int32, device="cuda")
+    lens = lens1[at].contiguous()
+    ckd, cvd, qd = dev(ck), dev(cv), dev(q)[at].contiguous()
+    rng = np.random.default_rng(t)
+    wide = dev(rng.standard_normal((distinct, 2 * fmt.channels + 8)).astype(np.float16))
+    xk, xv = wide[:, :fmt.channels], wide[:, fmt.channels:2 * fmt.channels]
+    k2, v2 = k1.clone(), v1.clone()
+    for n in range(distinct):
+        cq.cq_encode_kv(xk[n:n + 1, None], xv[n:n + 1, None], ckd, cvd, fmt, k2[n], v2[n], int(lens1[n]) - 1, t_cap)
+    wide_b = wide[at].contiguous()
+    xkb, xvb = wide_b[:, :fmt.channels], wide_b[:, fmt.channels:2 * fmt.channels]
+    rope = (cq.RopeTable(10000.0, t_cap),) if rotated else ()
+    attention, step, step_paged = ((cq.cq_decode_attention_rope, cq.cq_decode_step_rope, cq.cq_decode_step_rope_paged) if rotated
+                                   else (cq.cq_decode_attention, cq.cq_decode_step, cq.cq_decode_step_paged))
+    assert rotated or cq.cq_probe_decode_plan(fmt, B, hq, t, split)[0] == 4
+    want = attention(qd, k2[at].flatten(), v2[at].flatten(), ckd, cvd, SCALE, fmt, t, t_cap, *rope, seq_lens=lens, tokens_per_split=split)
+    assert torch.isfinite(want.float()).all()
+    k3, v3 = k1[at].flatten(), v1[at].flatten()
+    got = step(qd, xkb, xvb, k3, v3, ckd, cvd, SCALE, fmt, t, t_cap, *rope, seq_lens=lens, tokens_per_split=split)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(k3, k2[at].flatten()) and torch.equal(v3, v2[at].flatten())
+    (kp, vp), pages, unused = _pools(fmt, k1, v1, B, tiles, t)
+    got = step_paged(qd, xkb, xvb, kp.view(-1), vp.view(-1), ckd, cvd, SCALE, fmt, t, pages, *rope, seq_lens=lens, tokens_per_split=split)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    (k4, v4), _, _ = _pools(fmt, k2, v2, B, tiles, t)
+    assert torch.equal(kp, k4) and torch.equal(vp, v4)
+
+
+@pytest.mark.parametrize("c,T", [(8, 1500), (4, 700)])
+def test_a_chunk_of_two_tokens_goes_to_quads_token_by_token(c, T):
+    """Query rows two tokens apart, contexts shortened by a token: the bits of the single-token calls."""
+    hq, hkv, B, m = 8, 2, 72, 2
+    fmt, ck, cv, _, kc, vc = _problem(c, c, 8, hq, hkv, 4, T)
+    t_cap = (T + 63) // 64 * 64
+    assert all(cq.cq_probe_decode_plan(fmt, B, hq, t)[0] == 4 for t in (T, T - 1))
+    at = torch.arange(B, device="cuda") % 4
+    k, v = (codes_to_cache(x, fmt, t_cap).view(4, -1)[at].flatten() for x in (kc, vc))
+    q = dev(np.random.default_rng(c).standard_normal((B, m, hq, 128)).astype(np.float16))
+    lens = torch.tensor([T, 2, T // 2, 65], dtype=torch.int32, device="cuda")[at].contiguous()
+    a = (k, v, dev(ck), dev(cv), SCALE, fmt)
+    for sl in (None, lens):
+        out = cq.cq_chunk_attention(q, *a, T, t_cap, seq_lens=sl)
+        for j in range(m):
+            back = m - 1 - j
+            one = cq.cq_decode_attention(q[:, j].contiguous(), *a, T - back, t_cap, seq_lens=None if sl is None else sl - back)
+            assert torch.equal(out[:, j].contiguous().view(torch.int16), one.view(torch.int16))
+
+
+@pytest.mark.parametrize("seed", range(10))
+def test_quads_of_drawn_sizes(seed):
+    rng = np.random.default_rng(1000 + seed)
+    c, hkv = (8, 4)[seed % 2], int(rng.choice([1, 2, 3, 8]))
+    hq = 4 * hkv * int(rng.choice([1, 1, 2, 3]))
+    B = int(rng.integers(-(-140 * 4 // hq), -(-140 * 4 // hq) + 40))
+    t = int(rng.choice([int(rng.integers(1, 300)), int(rng.integers(300, 2500))]))
+    split = int(rng.choice([0, 64 * int(rng.integers(1, 20))]))
+    test_quads_equal_single_heads_over_pages_and_in_the_fused_step(c, hq, hkv, B, t, split, "plain")

@@ -77,7 +77,7 @@ def test_grouped_decode_over_rotated_keys(c, hq, magnitude):
 
 
 @pytest.mark.parametrize("magnitude,sign", [(x, 1.0) for x in MAGNITUDES] + [(2.0 ** 30, -1.0)])
-@pytest.mark.parametrize("c,m,hq", [(8, 5, 2), (8, 6, 8), (4, 5, 2), (4, 16, 4)])
+@pytest.mark.parametrize("c,m,hq", [(8, 5, 2), (8, 6, 8), (4, 5, 2), (4, 16, 4), (8, 3, 2), (8, 4, 2), (4, 3, 2), (4, 4, 2)])
 def test_chunks_of_few_rows(c, m, hq, magnitude, sign):
     hkv, B, T = 2, 2, 500
     fmt, q, kc, vc, ck, cv = _case(10 + c + m, c, 8, hq, hkv, B, m, T, 40)
