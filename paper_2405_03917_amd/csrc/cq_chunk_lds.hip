@@ -21,7 +21,7 @@
 // 12.3 clocks (16 lanes at a time on 16 bank groups: the fullest holds 3.1), a transposing one
 // 6.2, i.e. 394 clocks per tile and CU at CQ-8c8b; the kernel takes 535 (LDS active 73-75 %).
 // Measured: CQ-4c8b, batch 16, 32 heads, 5 tokens over 4096: 136 us token by token, 264 us in the
-// many-row kernel, 50 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 280 us in two pieces (given as
+// many-row kernel, 43 to 49 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 280 us in two pieces (given as
 // tokens_per_split: the default's workspace holds one, and such a call goes token by token).  The first form
 // waited for every gather by itself (5800 clocks per tile and wavefront, 61 us); values gathered
 // ahead of the softmax in one batch of 64 registers spilled at CQ-4c8b and gained nothing.
@@ -29,9 +29,11 @@
 // A workgroup of 8 wavefronts (one per CU) serves RB = 1, 2 or 4 blocks of 16 rows; the 8 / RB wavefronts of
 // a block take every (8 / RB)-th tile and are merged through LDS at the end.  Workgroups walk
 // several (sequence, split) items of one KV head, so the codebooks are staged once per workgroup.
-// (Both codebooks requested together and ahead of the first codes, the rows of up to eight merged in one pass, all keys of
-// a tile gathered at once, priorities: 5 tokens of 16 x 4096, CQ-8c8b 39.9 -> 38.3 us, of 1 x 6000, 8 tokens 13.3 -> 12.5, 40 tokens
-// of 4 x 5000 47.9 -> 45.8; where the LDS is busy throughout, nothing.)
+// Parts, each taken out by itself (32 heads): all keys of a tile gathered at once and not two of four batches ahead, CQ-8c8b, 40 tokens, 64 x 1000
+// 143.4 -> 140.3 us, 16 tokens 62.8 -> 61.5; CQ-4c8b, 5 tokens of 16 x 4096, 43.3 -> 42.9.  Priorities: CQ-8c8b, 40 tokens
+// of 64 x 1000, 145.4 -> 140.3, CQ-4c8b, 5 tokens of 16 x 4096, 44.2 -> 42.9, of 64 x 300 44.8 -> 45.8; up to eight rows of CQ-8c8b do without
+// (5 tokens of 64 x 1000 52.6, with them 55.7; 8 of 16 x 16384 119.0 and 123.8).  Codebooks ahead of the first codes and eight rows merged in one
+// pass: the rest of CQ-8c8b, 5 tokens of 64 x 1000, 57.9 -> 52.6, 16 x 4096 39.2 -> 36.9.
 #include "cq_key_gather.hpp"
 #include "cq_lds_gather.hpp"
 
@@ -204,15 +206,18 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
         request(it, tile + cs);
         const float mult = large ? 1.f : scale, early = large ? scale : 1.f;
         bool turn = wave < kWaves / 2;                  // (priorities as in cq_decode_quad.hip)
+        constexpr bool kPriorities = !(HALF && C == 8);
 #pragma unroll 1
         for (; tile < it.tile1; tile += cs) {
-            // The gathers are issued in batches that the products behind them work off, one batch ahead
-            // (the scheduling fences pin that order: left alone, the compiler waits for every gather by itself,
+            // All keys of the tile are gathered at once, the values in batches that the products behind them work off, one batch
+            // ahead (the scheduling fences pin that order: left alone, the compiler waits for every gather by itself,
             // 130 clocks each).
             // ---- scores: acc[i][e] is token 16 i + 4 blk + e, query col
-            turn = !turn;
-            if (turn) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
+            if constexpr (kPriorities) {
+                turn = !turn;
+                if (turn) __builtin_amdgcn_s_setprio(1);
+                else __builtin_amdgcn_s_setprio(0);
+            }
             float4_t acc[4];
             half8_t kv[4][4];
             auto gather_keys = [&](int i) {
@@ -260,8 +265,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(kWaves *
             gather_values(0);
             __builtin_amdgcn_sched_barrier(0);
             // ---- online softmax of the lane's query column
-            if (turn) __builtin_amdgcn_s_setprio(3);
-            else __builtin_amdgcn_s_setprio(2);
+            if constexpr (kPriorities) {
+                if (turn) __builtin_amdgcn_s_setprio(3);
+                else __builtin_amdgcn_s_setprio(2);
+            }
             if (large || tile * kTileTokens + kTileTokens - 1 > it.pos_first) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
