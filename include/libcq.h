@@ -151,24 +151,27 @@ CQ_API size_t cq_decode_workspace_bytes(const cq_format *fmt, int32_t batch, int
  *   seq_lens          device int32 [batch] or NULL; if given, sequence n attends positions
  *                     0 .. seq_lens[n]-1; values must lie in [1, t] (not checked on the host;
  *                     the kernels clamp them into that range)
- *   tokens_per_split  0 = library default; otherwise a multiple of 64: each workgroup handles
- *                     that many tokens of one (sequence, query head) and a second kernel merges
- *                     the partial softmax results (exact rescaling by the running maximum);
- *                     CQ-8c8b / 4c8b: any length (a workgroup walks its split in chunks of
- *                     8192 tokens with one score table); CQ-2c8b: at most 8192 tokens,
- *                     CQ-8c10b: at most 16384 (one chunk, whose scores stay in registers)
+ *   tokens_per_split  0 = library default; otherwise a multiple of 64: a workgroup handles that
+ *                     many tokens of a sequence for one query head, or for two or four of a KV
+ *                     head, and the partial softmax results of the splits are merged (exact
+ *                     rescaling by the running maximum).  Where four heads share a workgroup, it
+ *                     takes neighbouring splits together, given ones too, if the GPU is filled as
+ *                     well that way: fewer partials, never more than the workspace is sized for;
+ *                     CQ-8c8b / 4c8b: any length; CQ-2c8b: at most 8192 tokens, CQ-8c10b: at most
+ *                     16384 (one chunk, whose scores stay in registers)
  *   out               device, fp16 [batch][n_q_heads][head_dim]
  *   workspace         device scratch of at least cq_decode_workspace_bytes(...) bytes; contents
  *                     need not be initialised and are overwritten
- *   Arithmetic: fp32 lookup tables, scores, softmax and accumulation; the result is rounded to
- *   fp16 once (round to nearest even).
+ *   Arithmetic: exact products of fp16 numbers or fp32 lookup tables of them, fp32 scores and softmax, weights of 30
+ *   bits (bins) or 33 (three fp16 parts), fp32 accumulation; the result is rounded to fp16 once (to nearest even).
  *   Equal sizes give equal bits: which kernel a call takes, and how it cuts the context, depend on the
  *   format and the sizes alone (batch, heads, t, tokens_per_split), not on contents, lengths, pages or the workspace.
  *   Another batch can give a sequence other bits.  With tokens_per_split = 0 the split follows the batch.  With an
  *   even number of query heads per KV head so does the kernel, also where tokens_per_split is given: from 256
  *   workgroups of two query heads on, calls may take the kernel that serves two heads per workgroup, and with a multiple
  *   of four, from 140 workgroups of four on, the one that serves four (cq_probe_decode_plan tells); these form the same
- *   sums in fp32 in another order, and the results agree to a unit in the last place of fp16.  With an odd number (one among them) a given tokens_per_split fixes the bits.
+ *   sums in fp32 in another order, and the results agree to a unit in the last place of fp16.  With an odd number (one
+ *   among them) a given tokens_per_split fixes the bits.
  * Errors: as cq_encode, plus CQ_ERR_INVALID_ARG when n_q_heads is not a multiple of
  * n_kv_heads or tokens_per_split is not a positive multiple of 64 (or too large for the
  * kernel's on-chip score buffer), and CQ_ERR_WORKSPACE_TOO_SMALL.
