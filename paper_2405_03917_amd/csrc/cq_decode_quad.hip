@@ -26,8 +26,8 @@
 // new token's codes 3, 22 for the 94 tiles of the longest row (LDS busy throughout), merge 1.
 // ROPE: issue of vector and matrix instructions, 576 and 144 per tile, which hardly overlap: 2304 + 1280 of 3800 clocks per
 // tile and SIMD.  The fused step of CQ-8c8b, 32 / 8 heads, 32 x 16384: 161.4 us with the phases one after the other in a
-// workgroup (scores of a split to LDS, the value codebook in the key codebook's place) -> 119.9.  On the way: splits
-// that one workgroup walks joined 143 -> 121; priorities 121 -> 116.
+// workgroup (scores of a split to LDS, the value codebook in the key codebook's place) -> 112.  On the way: splits
+// that one workgroup walks joined 143 -> 121; priorities 121 -> 116; nothing spilled ahead of the first requests 118 -> 112.
 // Priorities: the two wavefronts of a SIMD should be in different phases, and neither may fall behind (an item ends
 // with its slowest wavefront).  A wavefront's priority is high in its latency-bound half of a tile (softmax, values), and
 // within both halves the wavefronts take turns from tile to tile: with none, wavefront 0 waited 26 of 130 us for the
