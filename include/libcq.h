@@ -427,7 +427,8 @@ CQ_API cq_status cq_chunk_attention_paged(const void *q, const void *k_pool, con
  * cq_decode_attention_rope, bit for bit.
  * Formats: head_dim 128.  For b = 8 (CQ-8c8b, CQ-4c8b, CQ-2c8b) the kernel keeps a head's key
  * centroids (64 KiB) on chip; CQ-8c10b (256 KiB per head) reads them from global memory.
- * Workspace size: cq_decode_workspace_bytes with the tokens_per_split given, or (0) with that default.  With 0 and grouped
+ * Workspace size: cq_decode_workspace_bytes with the tokens_per_split given, or (0) with that default; CQ-2c8b in splits of
+ * more than 8192 tokens, which that function refuses: cq_chunk_rope_workspace_bytes with m = 1.  With 0 and grouped
  * queries the library may take several of its splits together, which a given split, also of that length, forbids.
  * Errors: as cq_decode_attention; CQ_ERR_INVALID_ARG also for a missing or too short table.
  */
