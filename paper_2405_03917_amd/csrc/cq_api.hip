@@ -705,7 +705,7 @@ size_t chunk_workspace(const Derived& f, int batch, int n_q_heads, int m, int t,
 // library reports for a chunk are those of the other two paths, and the split has to fit the reported workspace:
 // a function of format and sizes alone, so that a call gives the same bits with any workspace it accepts.  Where
 // that leaves a quarter of the CUs or more without an item and the chunk can go token by token, it does: 5 tokens
-// of batch 4 x 131072, 32 KV heads, CQ-8c8b: 440 us token by token, about 560 in one piece (280 us with two,
+// of batch 4 x 131072, 32 KV heads, CQ-8c8b: 440 us token by token, about 560 in one piece (271 us with two,
 // which that workspace does not hold).
 int chunk_lds_tiles(const Derived& f, int batch, int n_q_heads, int m, int t, bool by_token)
 {

@@ -19,9 +19,9 @@
 // rows) and about 260 / 330 vector instructions, nothing is shared between wavefronts inside the
 // loop and there is no barrier.  Bound: the LDS.  A gather of 64 random 16-byte entries takes
 // 12.3 clocks (16 lanes at a time on 16 bank groups: the fullest holds 3.1), a transposing one
-// 6.2, i.e. 394 clocks per tile and CU at CQ-8c8b; the kernel takes 535 (LDS active 73-75 %).
+// 6.2, i.e. 394 clocks per tile and CU at CQ-8c8b; the kernel takes 488 (LDS active 79 %; up to eight rows).
 // Measured: CQ-4c8b, batch 16, 32 heads, 5 tokens over 4096: 136 us token by token, 264 us in the
-// many-row kernel, 43 to 49 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 280 us in two pieces (given as
+// many-row kernel, 43 to 49 us here; CQ-8c8b, batch 4 x 131072, 5 tokens: 441 -> 271 us in two pieces (given as
 // tokens_per_split: the default's workspace holds one, and such a call goes token by token).  The first form
 // waited for every gather by itself (5800 clocks per tile and wavefront, 61 us); values gathered
 // ahead of the softmax in one batch of 64 registers spilled at CQ-4c8b and gained nothing.

@@ -830,8 +830,9 @@ cq_status launch_format(const DecodeArgs& a, hipStream_t stream)
 // 24.0; 1.5 rounds, 24 x 3000, step of CQ-4c8b 30.9 -> 33.7; 1.75 rounds, 28 x 4000, CQ-8c8b 25.2 -> 25.4, CQ-4c8b 37.8 -> 32.7, and 28 x
 // 16000 64.9 -> 62.4, 110.7 -> 91.6).  CQ-8c10b gains in nearly all of them (17 x 2000 28.0 -> 29.1, 17 x 16000 76.5 -> 71.6, 20 x 2000 28.9 ->
 // 29.4, 20 x 16000 78.2 -> 72.0, 24 x 2000 30.3 -> 29.7, 36 x 2000 45.4 -> 43.5): of its codebooks, 256 KB each, a workgroup reads
-// half as much per head.  (Of a layer-batched launch the layer decides, so that
-// its results are those of the layers' own calls.)
+// half as much per head.  (Calls of CQ-8c8b and CQ-4c8b with heads in fours are offered to cq_decode_quad.hip first, which takes those
+// byte-code sizes above; the rule is for two or six heads per KV head as it was for four.  Of a layer-batched launch the layer
+// decides, so that its results are those of the layers' own calls.)
 bool decode_takes_pairs(const DecodeArgs& a)
 {
     const int qper = a.n_q_heads / a.f.n_kv_heads;
